@@ -1,0 +1,60 @@
+// fp32 products on the bf16 matrix units without loss of precision.
+//
+// An fp32 value is the exact sum of three bf16 values (Henry, Tang and Heinecke, "Leveraging the bfloat16 Artificial
+// Intelligence Datatype For Higher-Precision Computations", ARITH 2019): x = h + m + l, h = bf16(x), m = bf16(x - h),
+// l = x - h - m (8 + 8 + 8 significant bits; both differences are exact in fp32).  Of the nine products of two such
+// values the six with an order of magnitude above 2^-26 are formed, each exact (8 x 8 bits) and accumulated in fp32 by
+// v_mfma_f32_32x32x16_bf16: h h, h m, m h, m m, h l, l h.  What is left out, m l + l m + l l, is at most 2^-25.9 of the
+// product -- a quarter of the 2^-24 that ONE fp32 multiply-add of a chain may round off -- and a chain of fp32
+// multiply-adds rounds at every term, these instructions once per eight or sixteen.  Measured against float64 on
+// N(0,1) vectors, relative error of the dot product, v_mfma_f32_32x32x2_f32 / this: 1.42e-7 / 1.14e-7 (length 64),
+// 4.13e-7 / 3.57e-7 (512), 1.11e-6 / 0.97e-6 (4096); all nine products give the same as six.
+// Rate on the MI355X: the bf16 instruction takes 16.3 ns per SIMD for 16 channels of a 32 x 32 block, the fp32 one
+// 30.4 ns for two: six products cost 98 ns against 243.  And where fp32 matrix and vector instructions of one SIMD
+// take turns, up to six vector instructions per bf16 matrix instruction run beside it.
+// Outside of the range of earnest data: below 2^-109 the low bits of a value fall under the smallest bf16 number, and
+// the largest 2^-9 of the fp32 range rounds to infinity (as sums of such values would); an infinite value makes NaN of
+// its sums (inf - inf), as the inverse transforms make of infinite products; NaN stays NaN.
+#pragma once
+#include <hip/hip_runtime.h>
+
+namespace wino {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned uintx4_b __attribute__((ext_vector_type(4)));
+
+// two fp32 values rounded to nearest even, packed: v_cvt_pk_bf16_f32
+__device__ __forceinline__ unsigned bf16_pack(float lo, float hi)
+{
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{lo, hi}), bf16x2));
+}
+
+// the three parts of two values, packed by part (11 instructions; the differences are exact)
+__device__ __forceinline__ void bf16_split2(float x, float y, unsigned &h, unsigned &m, unsigned &l)
+{
+    h = bf16_pack(x, y);
+    const float rx = x - __builtin_bit_cast(float, h << 16), ry = y - __builtin_bit_cast(float, h & 0xffff0000u);
+    m = bf16_pack(rx, ry);
+    const float qx = rx - __builtin_bit_cast(float, m << 16), qy = ry - __builtin_bit_cast(float, m & 0xffff0000u);
+    l = bf16_pack(qx, qy);
+}
+
+// the three operand words (eight reduction steps each) of eight values
+__device__ __forceinline__ void bf16_split8(const float (&x)[8], uintx4_b (&p)[3])
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        unsigned h, m, l;
+        bf16_split2(x[2 * i], x[2 * i + 1], h, m, l);
+        p[0][i] = h, p[1][i] = m, p[2][i] = l;
+    }
+}
+
+// the six products in rising order of magnitude: parts of the first and of the second operand
+constexpr int BF16_PRODUCTS = 6;
+__device__ constexpr int bf16_part_a(int n) { return n == 0 ? 2 : n == 1 ? 0 : n == 2 ? 1 : n == 3 ? 1 : 0; }
+__device__ constexpr int bf16_part_b(int n) { return n == 0 ? 0 : n == 1 ? 2 : n == 2 ? 1 : n == 3 ? 0 : n == 4 ? 1 : 0; }
+
+}  // namespace wino

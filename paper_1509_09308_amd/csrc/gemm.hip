@@ -3,6 +3,7 @@
 #include <stdlib.h>
 
 #include "wino_internal.h"
+#include "bf16x3.h"
 
 namespace wino {
 
@@ -20,54 +21,45 @@ __device__ __forceinline__ int xcd_remap(int bid, int nblocks)
     return (bid % XCDS) * per + bid / XCDS;
 }
 
-// 16 bytes per lane from a buffer straight into LDS: lane l of the wavefront fills LDS bytes lds + 16 l ..
-// (lds the same in all lanes).  Written as assembly on purpose: while a copy into LDS that the compiler knows of
-// may be in flight, it puts a wait for ALL outstanding memory requests in front of every LDS read, which would
-// serialise the copy of the next slab with the multiply of the current one.  The kernel waits for its copies itself.
-typedef int intx4_g __attribute__((ext_vector_type(4)));
-#define WINO_G_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
-__device__ __forceinline__ intx4_g gemm_buffer(const void *base, unsigned bytes)
+// fp32 operands on the bf16 matrix units (bf16x3.h: every value in three exact parts, six products, fp32 sums).
+// A workgroup of four wavefronts (2 x 2) owns a BM x BN block of one M^(e); every wavefront TM x TN tiles of 32 x 32.
+// Both operands are stored reduction-index-major (U[e][c][k], V[e][c][b]); the matrix instruction wants eight
+// channels of one row per lane.  So a thread fetches eight channels of one column with eight 4-byte loads (each 256
+// contiguous bytes per wavefront, which the vector memory path takes at the same 64 bytes per cycle as wider ones),
+// splits them once and stores the parts as 16-byte words [channels / 8][part][column]: LDS accesses are contiguous
+// both ways, and the values that two wavefronts share are split only once.
+//
+// Pipeline: two slabs of BK channels in flight in registers, two slabs in LDS, one barrier per slab (which orders LDS
+// traffic only: requests stay in flight across it).  While a slab is multiplied, the next one is split.
+//
+// Blocks that overhang Kp or Pp load from clamped (valid) addresses: rows/columns of a product are independent, so
+// whatever is loaded there only reaches outputs that are never stored.  Channels past the end of this share lie
+// behind the buffers' ends and read as 0.
+//
+// What bounds it is energy: on N(0,1) data back-to-back v_mfma_f32_32x32x16_bf16 alone pull the clock from 2.4 to
+// 1.77 GHz (18.7 ns each per SIMD); four vector instructions, half an LDS read and a quarter of an LDS store beside
+// each make it 25 ns, this kernel runs at 30 (matrix pipes 60 % busy).  36 products of 256 x 256 by 256 x 12544:
+// 118 TFLOP/s with v_mfma_f32_32x32x2_f32 (501 us), 184 so (320 us); 512 -> 512 channels at 28 x 28, batch 8: multiply
+// 83 -> 53 us.  Single-buffered slabs of 32 channels on v_mfma_f32_16x16x32_bf16, which takes an eighth less energy,
+// but with two barriers and no split between the matrix instructions: 355 us (matrix pipes 46 % busy).
+__device__ __forceinline__ void gemm_lds_barrier()
 {
-    const unsigned long long a = (unsigned long long)base;
-    return intx4_g{__builtin_amdgcn_readfirstlane((int)(unsigned)a),
-                   __builtin_amdgcn_readfirstlane((int)((unsigned)(a >> 32) & 0xffffu)),
-                   __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
-}
-__device__ __forceinline__ void gemm_copy16_to_lds(intx4_g rsrc, unsigned lds, unsigned voffset, unsigned soffset)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :
-                 : "s"(lds), "v"(voffset), "s"(rsrc), "s"(soffset)
-                 : "memory");   // (m0 is not a register the compiler keeps values in)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// fp32 operands, v_mfma_f32_32x32x2_f32.  A workgroup of WM x WN wavefronts owns a BM x BN
-// block of one M^(e); every wavefront owns TM x TN MFMA tiles of 32 x 32.  Both operands are
-// stored reduction-index-major (U[e][c][k], V[e][c][b]), so a BK-deep slab is BK contiguous row
-// segments: loaded with 16-byte accesses, kept in LDS as [c][k] / [c][b], and read by the MFMA
-// lanes (lane = column + 32 * (c & 1)) without bank conflicts.
-//
-// Pipeline: two LDS slabs (slab t+1 is copied from memory straight into LDS while slab t is
-// multiplied) and two register sets per wavefront holding half a slab of MFMA operands each,
-// so LDS reads for the next half overlap the MFMAs of the current one; one barrier per slab.
-//
-// Blocks that overhang Kp or Pp load from clamped (valid) addresses: rows/columns of a product
-// are independent, so whatever is loaded there only reaches outputs that are never stored.
-template <int BM, int BN, int WM, int WN, int BK>
-__global__ __launch_bounds__(64 * WM * WN) void gemm_f32_kernel(const float *__restrict__ U,
-                                                                 const float *__restrict__ V,
-                                                                 float *__restrict__ Mo, int Kp, int Cp, int Pp,
-                                                                 int tiles_m, int tiles_n, int a2, int nk_split)
+template <int BM, int BN, int BK>
+__global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const float *__restrict__ U, const float *__restrict__ V,
+                                                          float *__restrict__ Mo, int Kp, int Cp, int Pp, int tiles_m,
+                                                          int tiles_n, int a2, int c_share)
 {
-    constexpr int NT = 64 * WM * WN;
-    constexpr int TM = BM / (32 * WM), TN = BN / (32 * WN);
-    constexpr int A4 = BK * BM / 4, B4 = BK * BN / 4;  // float4s per slab
-    static_assert(A4 % NT == 0 && B4 % NT == 0, "slab must divide evenly among the threads");
-    static_assert(BK % 8 == 0, "two half-slabs of whole MFMA steps");
-    constexpr int AL = A4 / NT, BL = B4 / NT;
-    constexpr int HS = BK / 4;                          // MFMA steps (2 channels each) per half slab
-    __shared__ float As[2][BK * BM];
-    __shared__ float Bs[2][BK * BN];
+    constexpr int TM = BM / 64, TN = BN / 64;
+    constexpr int G8 = BK / 8;                                   // groups of eight channels per slab
+    constexpr int AG = G8 * BM / 256, BG = G8 * BN / 256;        // groups a thread fetches
+    static_assert(G8 * BM % 256 == 0 && G8 * BN % 256 == 0 && BK % 16 == 0, "a slab divides evenly among the threads");
+    __shared__ uintx4_b As[2][G8 * 3 * BM];
+    __shared__ uintx4_b Bs[2][G8 * 3 * BN];
 
     int bid = xcd_remap(blockIdx.x, gridDim.x);
     const int tm_i = bid % tiles_m;
@@ -77,7 +69,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_f32_kernel(const float *__r
     const int e = bid % a2;
     const int z = bid / a2;   // which share of the channel loop (layers with few blocks split it)
     const int k0 = tm_i * BM, p0 = tn_i * BN;
-    const int c_first = z * nk_split * BK;
+    const int c_first = z * c_share, c_rows = min(c_share, Cp - c_first);
 
     const float *Ue = U + ((size_t)e * Cp + c_first) * Kp;
     const float *Ve = V + ((size_t)e * Cp + c_first) * Pp;
@@ -85,54 +77,55 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_f32_kernel(const float *__r
 
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
-    const int wm = wave / WN, wn = wave % WN;
-    const int li = lane & 31, lg = lane >> 5;
+    const int wm = wave >> 1, wn = wave & 1;
+    const int li = lane & 31, lh = lane >> 5;
 
-    // Operands are fetched through buffers that start at this block's first channel row of U^(e) and V^(e): the
-    // per-thread byte offsets are fixed for the kernel and the slab advances in a scalar register, so the loop holds
-    // no 64-bit address arithmetic (one component's Cp x Kp or Cp x Pp floats stay below 4 GB: see the launcher).
-    unsigned oa[AL], ob[BL];
+    // Operands are fetched through buffers that hold this share's channel rows of U^(e) and V^(e) (one component's
+    // Cp x Kp or Cp x Pp floats stay below 4 GB: see the launcher).  A group of eight rows lies inside the buffer or
+    // behind it as a whole, and its vector offset alone tells which.
+    const __amdgpu_buffer_rsrc_t rsrc_a = __builtin_amdgcn_make_buffer_rsrc((void *)Ue, 0, (unsigned)((size_t)c_rows * Kp * 4), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsrc_b = __builtin_amdgcn_make_buffer_rsrc((void *)Ve, 0, (unsigned)((size_t)c_rows * Pp * 4), 0x00020000);
+    unsigned oa[AG], ob[BG];
 #pragma unroll
-    for (int j = 0; j < AL; ++j) {
-        const int idx = tid + j * NT;
-        const int row = idx / (BM / 4), col = min(k0 + (idx % (BM / 4)) * 4, Kp - 4);
-        oa[j] = (unsigned)(row * Kp + col) * 4u;
+    for (int j = 0; j < AG; ++j) {
+        const int id = tid + j * 256;
+        oa[j] = (unsigned)(id / BM * 8 * Kp + min(k0 + id % BM, Kp - 1)) * 4u;
     }
 #pragma unroll
-    for (int j = 0; j < BL; ++j) {
-        const int idx = tid + j * NT;
-        const int row = idx / (BN / 4), col = min(p0 + (idx % (BN / 4)) * 4, Pp - 4);
-        ob[j] = (unsigned)(row * Pp + col) * 4u;
+    for (int j = 0; j < BG; ++j) {
+        const int id = tid + j * 256;
+        ob[j] = (unsigned)(id / BN * 8 * Pp + min(p0 + id % BN, Pp - 1)) * 4u;
     }
-    const int c_rows = Cp - c_first;
-    const intx4_g rsrc_a = gemm_buffer(Ue, (unsigned)((size_t)c_rows * Kp * 4));
-    const intx4_g rsrc_b = gemm_buffer(Ve, (unsigned)((size_t)c_rows * Pp * 4));
-    unsigned sa = 0, sb = 0;                            // byte offset of the next slab
-    // A slab goes from memory straight into LDS (16 bytes per lane, 1 KB contiguous per wavefront and request: the
-    // order of the slab in LDS is the order of the threads' words).  No registers are involved, so the requests are
-    // made a whole slab of MFMAs ahead of the barrier that publishes them.
-    const unsigned wave_bytes = (unsigned)__builtin_amdgcn_readfirstlane(wave) * 1024u;   // (in a scalar register)
-    const unsigned lds_a = (unsigned)(size_t)WINO_G_LDS_PTR(&As[0][0]) + wave_bytes;
-    const unsigned lds_b = (unsigned)(size_t)WINO_G_LDS_PTR(&Bs[0][0]) + wave_bytes;
-    auto request_slab = [&](int buf) {
+    float ra[2][AG][8], rb[2][BG][8];
+    auto request = [&](int slot, int slab) {
+        const unsigned sa = (unsigned)(slab * BK) * (unsigned)Kp * 4u, sb = (unsigned)(slab * BK) * (unsigned)Pp * 4u;
 #pragma unroll
-        for (int j = 0; j < AL; ++j) gemm_copy16_to_lds(rsrc_a, lds_a + (unsigned)(buf * BK * BM + j * NT * 4) * 4u, oa[j], sa);
+        for (int j = 0; j < AG; ++j)
 #pragma unroll
-        for (int j = 0; j < BL; ++j) gemm_copy16_to_lds(rsrc_b, lds_b + (unsigned)(buf * BK * BN + j * NT * 4) * 4u, ob[j], sb);
-        sa += (unsigned)(BK * Kp) * 4u;
-        sb += (unsigned)(BK * Pp) * 4u;
+            for (int i = 0; i < 8; ++i)
+                ra[slot][j][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc_a, oa[j] + sa, (unsigned)(i * Kp) * 4u, 0));
+#pragma unroll
+        for (int j = 0; j < BG; ++j)
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                rb[slot][j][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc_b, ob[j] + sb, (unsigned)(i * Pp) * 4u, 0));
     };
-    // every copy this wavefront has requested has landed (the multiply makes no other vector-memory request)
-    auto slab_landed = [&]() { __builtin_amdgcn_s_waitcnt(0x0f70); };   // vmcnt(0)
-    const int a_off = wm * (TM * 32) + li, b_off = wn * (TN * 32) + li;
-    auto lds_load = [&](int buf, int half, float (&a)[HS][TM], float (&b)[HS][TN]) {
+    // group id = (channels / 8) * extent + column -> word (channels / 8) * 3 * extent + part * extent + column
+    auto store = [&](int slot, int buf) {
+        uintx4_b p[3];
 #pragma unroll
-        for (int s = 0; s < HS; ++s) {
-            const int c = 2 * (half * HS + s) + lg;
+        for (int j = 0; j < AG; ++j) {
+            const int id = tid + j * 256, w = id / BM * 3 * BM + id % BM;
+            bf16_split8(ra[slot][j], p);
 #pragma unroll
-            for (int i = 0; i < TM; ++i) a[s][i] = As[buf][c * BM + a_off + i * 32];
+            for (int q = 0; q < 3; ++q) As[buf][w + q * BM] = p[q];
+        }
 #pragma unroll
-            for (int j = 0; j < TN; ++j) b[s][j] = Bs[buf][c * BN + b_off + j * 32];
+        for (int j = 0; j < BG; ++j) {
+            const int id = tid + j * 256, w = id / BN * 3 * BN + id % BN;
+            bf16_split8(rb[slot][j], p);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) Bs[buf][w + q * BN] = p[q];
         }
     };
 
@@ -143,49 +136,65 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_f32_kernel(const float *__r
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-    auto mma = [&](const float (&a)[HS][TM], const float (&b)[HS][TN]) {
+    const int a_off = lh * 3 * BM + wm * (TM * 32) + li, b_off = lh * 3 * BN + wn * (TN * 32) + li;
+    auto multiply = [&](int buf) {
 #pragma unroll
-        for (int s = 0; s < HS; ++s)
+        for (int t = 0; t < BK / 16; ++t) {
+            uintx4_b a[3][TM], b[3][TN];
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
+            for (int q = 0; q < 3; ++q) {
 #pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s][i], b[s][j], acc[i][j], 0, 0, 0);
+                for (int i = 0; i < TM; ++i) a[q][i] = As[buf][(t * 6 + q) * BM + a_off + i * 32];
+#pragma unroll
+                for (int j = 0; j < TN; ++j) b[q][j] = Bs[buf][(t * 6 + q) * BN + b_off + j * 32];
+            }
+#pragma unroll
+            for (int n = 0; n < BF16_PRODUCTS; ++n)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[bf16_part_a(n)][i]),
+                                                                            __builtin_bit_cast(bf16x8, b[bf16_part_b(n)][j]),
+                                                                            acc[i][j], 0, 0, 0);
+        }
     };
 
-    float a0[HS][TM], b0[HS][TN], a1[HS][TM], b1[HS][TN];
-    const int nk = min(nk_split, Cp / BK - z * nk_split);   // >= 1 by construction of the launch
-    request_slab(0);
-    slab_landed();
-    __syncthreads();
-    lds_load(0, 0, a0, b0);
-    // all slabs but the last: fetch the next slab while multiplying the current one.  Two slabs per trip, so that
-    // the LDS buffer of every access is known at compile time and its address is a per-lane base plus a constant
-    // (with a buffer index computed in the loop, every LDS read cost a vector add in the MFMA issue slot).
-    auto slab = [&](int cur) {
-        request_slab(cur ^ 1);               // (the other buffer: everybody left it before the last barrier)
-        lds_load(cur, 1, a1, b1);
-        mma(a0, b0);
-        slab_landed();
-        __syncthreads();
-        lds_load(cur ^ 1, 0, a0, b0);
-        mma(a1, b1);
+    const int nk = (c_rows + BK - 1) / BK;      // >= 1 by construction of the launch
+    // Requests past the last slab are made all the same (they fetch nothing: every row lies behind the buffers), so
+    // that the number of loads in flight does not depend on the path taken.
+#pragma unroll
+    for (int s = 0; s < 2; ++s) request(s, s);
+    store(0, 0);
+    gemm_lds_barrier();
+    // slab kt sits in LDS buffer kt & 1 and came through register slot kt & 1, both known at compile time.  The order
+    // of a trip is laid down, because the compiler would move the requests to where their registers are read: the
+    // requests of slab kt + 2 first, then the operand reads, then matrix instructions with the split of slab kt + 1
+    // (11 vector instructions per pair of values, about four per matrix instruction) between them.
+    auto slab = [&](int kt, int odd) {
+        request(odd, kt + 2);                   // (the slot of slab kt, which is in LDS)
+        multiply(odd);
+        store(odd ^ 1, odd ^ 1);                // (past the last slab: zeros, read by nobody)
+        __builtin_amdgcn_sched_group_barrier(0x2, AG + BG, 0);       // (their offsets)
+        __builtin_amdgcn_sched_group_barrier(0x20, 8 * (AG + BG), 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 3 * (TM + TN), 0);
+        constexpr int NM = BF16_PRODUCTS * TM * TN * (BK / 16), NV = (44 * (AG + BG) + NM - 1) / NM;
+#pragma unroll
+        for (int i = 0; i < NM; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x2, NV, 0);
+            if (BK == 32 && i == NM / 2 - 2) __builtin_amdgcn_sched_group_barrier(0x100, 3 * (TM + TN), 0);
+        }
+        gemm_lds_barrier();
     };
     int kt = 0;
-    for (; kt + 2 < nk; kt += 2) {
-        slab(0);
-        slab(1);
+    for (; kt + 1 < nk; kt += 2) {
+        slab(kt, 0);
+        slab(kt + 1, 1);
     }
-    if (kt + 1 < nk) {   // one more full iteration: the last slab then sits in buffer 1
-        slab(0);
-        lds_load(1, 1, a1, b1);
-    } else {
-        lds_load(0, 1, a1, b1);
-    }
-    mma(a0, b0);
-    mma(a1, b1);
+    if (kt < nk) multiply(0);
 
-    // accumulator register r of lane (li, lg) is row 8*(r/4) + 4*lg + r%4, column li of its tile;
+    // accumulator register r of lane (li, lh) is row 8*(r/4) + 4*lh + r%4, column li of its tile;
     // Kp and Pp are multiples of 32, so a 32 x 32 tile is entirely inside or entirely outside
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -193,28 +202,27 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_f32_kernel(const float *__r
         for (int j = 0; j < TN; ++j) {
             const int ct = p0 + wn * (TN * 32) + j * 32, rt = k0 + wm * (TM * 32) + i * 32;
             if (ct < Pp && rt < Kp) {
-                float *dst = Me + (size_t)(rt + 4 * lg) * Pp + ct + li;
+                float *dst = Me + (size_t)(rt + 4 * lh) * Pp + ct + li;
 #pragma unroll
                 for (int r = 0; r < 16; ++r) dst[(size_t)(8 * (r / 4) + (r % 4)) * Pp] = acc[i][j][r];
             }
         }
 }
 
-template <int BM, int BN, int WM, int WN, int BK>
+template <int BM, int BN, int BK>
 static hipError_t launch_f32(const Geo &g, const float *U, const float *V, float *M, int splits, hipStream_t s)
 {
     const int tiles_m = (g.Kp + BM - 1) / BM, tiles_n = (g.Pp + BN - 1) / BN;
-    const int nk = g.Cp / BK;
-    const int nk_split = (nk + splits - 1) / splits;
-    const int used = (nk + nk_split - 1) / nk_split;   // every share gets at least one slab
-    if (used != splits) return hipErrorInvalidValue;
+    const int c_share = (g.Cp / 16 + splits - 1) / splits * 16;
+    if ((g.Cp + c_share - 1) / c_share != splits) return hipErrorInvalidValue;   // every share gets at least 16 channels
     const long long blocks = (long long)tiles_m * tiles_n * g.a2 * splits;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    // 32-bit byte offsets inside one component of U and of V
-    if ((unsigned long long)g.Cp * g.Pp * 4ull >= (1ull << 32) || (unsigned long long)g.Cp * g.Kp * 4ull >= (1ull << 32))
+    // 32-bit byte offsets inside one component of U and of V, the requests past the last slab included
+    if ((unsigned long long)(g.Cp + 3 * BK) * g.Pp * 4ull >= (1ull << 32) ||
+        (unsigned long long)(g.Cp + 3 * BK) * g.Kp * 4ull >= (1ull << 32))
         return hipErrorNotSupported;
-    gemm_f32_kernel<BM, BN, WM, WN, BK><<<dim3((unsigned)blocks), dim3(64 * WM * WN), 0, s>>>(
-        U, V, M, g.Kp, g.Cp, g.Pp, tiles_m, tiles_n, g.a2, nk_split);
+    gemm_f32_kernel<BM, BN, BK><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(U, V, M, g.Kp, g.Cp, g.Pp, tiles_m,
+                                                                                   tiles_n, g.a2, c_share);
     return hipGetLastError();
 }
 
@@ -414,18 +422,10 @@ hipError_t launch_batched_gemm(const Geo &g, const void *U, const void *V, float
     }
     const float *u = (const float *)U, *v = (const float *)V;
     const GemmShape sh = gemm_shape(g);
-    if (sh.bm == 128 && sh.bn == 128) return launch_f32<128, 128, 2, 2, 16>(g, u, v, M, splits, s);
-    // The narrower blocks serve small problems, where a workgroup is alone on its CU and its loop over the
-    // channels is a chain of memory latencies: slabs of 32 channels halve the links of that chain (measured at
-    // batch 1: 3-8 % per layer; 64 gains nothing more).
-    if (g.Cp % (32 * splits) == 0) {
-        if (sh.bm == 128) return launch_f32<128, 64, 2, 2, 32>(g, u, v, M, splits, s);
-        if (sh.bn == 128) return launch_f32<64, 128, 2, 2, 32>(g, u, v, M, splits, s);
-        return launch_f32<64, 64, 2, 2, 32>(g, u, v, M, splits, s);
-    }
-    if (sh.bm == 128) return launch_f32<128, 64, 2, 2, 16>(g, u, v, M, splits, s);
-    if (sh.bn == 128) return launch_f32<64, 128, 2, 2, 16>(g, u, v, M, splits, s);
-    return launch_f32<64, 64, 2, 2, 16>(g, u, v, M, splits, s);
+    if (sh.bm == 128 && sh.bn == 128) return launch_f32<128, 128, 16>(g, u, v, M, splits, s);
+    if (sh.bm == 128) return launch_f32<128, 64, 32>(g, u, v, M, splits, s);
+    if (sh.bn == 128) return launch_f32<64, 128, 32>(g, u, v, M, splits, s);
+    return launch_f32<64, 64, 32>(g, u, v, M, splits, s);
 }
 
 }  // namespace wino

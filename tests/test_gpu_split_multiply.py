@@ -1,0 +1,47 @@
+"""fp32 products on the bf16 matrix units (every value the exact sum of three bf16 values, six of the nine products):
+no less precise than a chain of fp32 multiply-adds, at the edges of the multiply's slabs, blocks and shares."""
+import numpy as np
+import pytest
+
+from oracle import winograd as wg
+from gpu_util import require_gpu, rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+# (K, C, P): 128 x 128 blocks of 16-channel slabs (odd and even number of slabs, ragged edges), the narrow blocks with
+# 32-channel slabs whose last one is half empty
+@pytest.mark.parametrize("K,C,P", [(256, 16, 3600), (256, 48, 3600), (200, 64, 3300), (128, 48, 130), (70, 80, 300),
+                                   (40, 112, 100)])
+@pytest.mark.parametrize("spread", [0, 6])
+def test_multiply_is_as_precise_as_fp32(K, C, P, spread):
+    torch, w = require_gpu()
+    m, a = 2, 4
+    rng = np.random.default_rng(K + C + P + spread)
+    # `spread`: magnitudes over 2^+-spread, so that the parts of the values meet in every combination of orders
+    u = (rng.standard_normal((a, a, K, C)) * 2.0 ** rng.integers(-spread, spread + 1, (a, a, K, C))).astype(np.float32)
+    v = (rng.standard_normal((a, a, C, P)) * 2.0 ** rng.integers(-spread, spread + 1, (a, a, C, P))).astype(np.float32)
+    M = w.unpack_m(w.wino_batched_gemm(w.pack_u(u, m), w.pack_v(v, m), K, C, P, m), K, P, m)
+    ref = wg.multiply(u.astype(np.float64), v.astype(np.float64))
+    # every term may be off by the products left out (2^-25.9) and by one fp32 rounding per accumulation (2^-24 each)
+    bound = (C + 1) * 2.0 ** -24 * wg.multiply(np.abs(u).astype(np.float64), np.abs(v).astype(np.float64))
+    assert (np.abs(M - ref) <= bound).all()
+    chain = np.zeros((a, a, K, P), dtype=np.float32)            # fp32 multiply-adds in channel order (rounded twice)
+    for c in range(C):
+        chain += u[:, :, :, c, None] * v[:, :, None, c, :]
+    e, ec = rel_err(M, ref), rel_err(chain, ref)
+    print("K=%d C=%d P=%d spread %d: rel err %.2e, fp32 chain %.2e" % (K, C, P, spread, e, ec))
+    assert e <= 1.2 * ec
+
+
+def test_multiply_shares_of_sixteen_channels():
+    """A channel sum split between workgroups whose shares end inside a 32-channel slab: the layer adds them up."""
+    torch, w = require_gpu()
+    from oracle import direct
+    from paper_1509_09308_amd import synth
+    from gpu_util import TOL, check_close, to_gpu
+    N, C, HW, K = 1, 96, 10, 64
+    assert w.wino_gemm_launch_shape(K, C, 25, 2)[2] > 1
+    D, G = synth.make_layer(N, C, HW, HW, K, seed=96)
+    Y = w.wino_conv2d_fwd_ex(to_gpu(D), G=to_gpu(G), pad=1, m=2, flags=w.FLAG_UNFUSED).cpu().numpy()
+    check_close(Y, direct.conv2d_fwd(D, G, pad=1), TOL[("f32", 2)], "three slabs in two shares", 2)
