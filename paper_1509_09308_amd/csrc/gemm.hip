@@ -49,8 +49,11 @@ __device__ __forceinline__ void gemm_lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-template <int BM, int BN, int BK>
-__global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const float *__restrict__ U, const float *__restrict__ V,
+// ONE: the share is one slab.  Then there is nothing to overlap within a workgroup and what bounds the launch is writing
+// M: no second slab, half the LDS, twice the workgroups per CU, and no matrix instructions for the empty half of a
+// slab (64 products of 32 x 16 by 16 x 3600: layer 32.8 -> 30.3 us).
+template <int BM, int BN, int BK, bool ONE>
+__global__ __launch_bounds__(256, ONE && BM * BN < 128 * 128 ? 4 : 2) void gemm_f32_kernel(const float *__restrict__ U, const float *__restrict__ V,
                                                           float *__restrict__ Mo, int Kp, int Cp, int Pp, int tiles_m,
                                                           int tiles_n, int a2, int c_share)
 {
@@ -58,8 +61,8 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const float *__restric
     constexpr int G8 = BK / 8;                                   // groups of eight channels per slab
     constexpr int AG = G8 * BM / 256, BG = G8 * BN / 256;        // groups a thread fetches
     static_assert(G8 * BM % 256 == 0 && G8 * BN % 256 == 0 && BK % 16 == 0, "a slab divides evenly among the threads");
-    __shared__ uintx4_b As[2][G8 * 3 * BM];
-    __shared__ uintx4_b Bs[2][G8 * 3 * BN];
+    __shared__ uintx4_b As[ONE ? 1 : 2][G8 * 3 * BM];
+    __shared__ uintx4_b Bs[ONE ? 1 : 2][G8 * 3 * BN];
 
     int bid = xcd_remap(blockIdx.x, gridDim.x);
     const int tm_i = bid % tiles_m;
@@ -137,9 +140,10 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const float *__restric
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
     const int a_off = lh * 3 * BM + wm * (TM * 32) + li, b_off = lh * 3 * BN + wn * (TN * 32) + li;
-    auto multiply = [&](int buf) {
+    auto multiply = [&](int buf, int depth = BK / 16) {      // (depth in units of 16 channels, the rest of the slab is zeros)
 #pragma unroll
         for (int t = 0; t < BK / 16; ++t) {
+            if (t >= depth) break;
             uintx4_b a[3][TM], b[3][TN];
 #pragma unroll
             for (int q = 0; q < 3; ++q) {
@@ -161,6 +165,12 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const float *__restric
     };
 
     const int nk = (c_rows + BK - 1) / BK;      // >= 1 by construction of the launch
+    if constexpr (ONE) {
+        request(0, 0);
+        store(0, 0);
+        gemm_lds_barrier();
+        multiply(0, c_rows <= 16 ? 1 : BK / 16);
+    } else {
     // Requests past the last slab are made all the same (they fetch nothing: every row lies behind the buffers), so
     // that the number of loads in flight does not depend on the path taken.
 #pragma unroll
@@ -193,6 +203,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const float *__restric
         slab(kt + 1, 1);
     }
     if (kt < nk) multiply(0);
+    }
 
     // accumulator register r of lane (li, lh) is row 8*(r/4) + 4*lh + r%4, column li of its tile;
     // Kp and Pp are multiples of 32, so a 32 x 32 tile is entirely inside or entirely outside
@@ -221,8 +232,12 @@ static hipError_t launch_f32(const Geo &g, const float *U, const float *V, float
     if ((unsigned long long)(g.Cp + 3 * BK) * g.Pp * 4ull >= (1ull << 32) ||
         (unsigned long long)(g.Cp + 3 * BK) * g.Kp * 4ull >= (1ull << 32))
         return hipErrorNotSupported;
-    gemm_f32_kernel<BM, BN, BK><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(U, V, M, g.Kp, g.Cp, g.Pp, tiles_m,
-                                                                                   tiles_n, g.a2, c_share);
+    if (c_share <= BK)
+        gemm_f32_kernel<BM, BN, BK, true><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(U, V, M, g.Kp, g.Cp, g.Pp, tiles_m,
+                                                                                       tiles_n, g.a2, c_share);
+    else
+        gemm_f32_kernel<BM, BN, BK, false><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(U, V, M, g.Kp, g.Cp, g.Pp, tiles_m,
+                                                                                        tiles_n, g.a2, c_share);
     return hipGetLastError();
 }
 
