@@ -397,47 +397,41 @@ bool fused_eligible(const Geo &g)
     return bytes < (1ull << 31) - 65536;
 }
 
-// Where the one-kernel path beats the four-stage path (measured on MI355X at N = 64).  The one-kernel path
-// repeats the data transform for every 32 filters, the four-stage path writes and re-reads V (C rows per tile) and
-// M (K rows per tile): the first wins while K C / (K + C) is small -- 43 to 85 for the VGG layers with 64 to 128
-// channels (1.15x to 2x faster), a tie at 128 (256 -> 256 channels), a loss from 170 up (256 -> 512) -- and there
-// are enough workgroups to fill the 256 CUs.
+// Where the one-kernel path beats the four-stage path (measured on MI355X).  The one-kernel path repeats the data
+// transform for every block of filters, the four-stage path writes and re-reads V (C rows per tile) and M (K rows per
+// tile): the first wins while K C / (K + C) is small and there are enough workgroups to fill the 256 CUs.
 bool fused_preferred(const Geo &g)
 {
     if (!fused_eligible(g)) return false;
     const long long blocks = (long long)((g.P + FP - 1) / FP) * ((g.K + FK - 1) / FK);
     if (g.dt == WINO_F16)   // same crossover as in fp32 (N = 32: 128 -> 256 channels 0.139 vs 0.155 ms, 256 -> 256 0.249 vs 0.197)
         return (long long)g.K * g.C <= 100LL * (g.K + g.C) && (long long)((g.P + 31) / 32) * ((g.K + 63) / 64) >= 256;
+    if (fused_split_eligible(g)) {
+        // One kernel on the bf16 matrix units (fused_split.hip) against the four stages: their multiply reaches 184
+        // TFLOP/s and what passes through memory -- input and output once, V and M twice -- about 6.2 TB/s (36 products
+        // of 512 -> 512 channels at 28 x 28: N = 16 124 us, estimate 129; N = 64 506, estimate 507; F(2x2,3x3), 14 x 14,
+        // N = 64: 217, estimate 221).  Below 160 items three CUs of eight have nothing to do and the two are within a few
+        // per cent of each other for 64 and 128 channels, the four stages ahead for more (F(2x2,3x3), 512 -> 512 at
+        // 14 x 14, N = 24, 152 items: 105 against 89 us).
+        const double flops = 2.0 * g.a2 * g.Kp * g.Cp * g.Pp;
+        const double bytes = 4.0 * ((double)g.N * g.C * g.H * g.W + (double)g.N * g.K * g.Ho * g.Wo +
+                                    2.0 * g.a2 * ((double)g.Cp + g.Kp) * g.Pp);
+        return fused_split_items(g) >= 160 && fused_split_us(g) <= 3.0 + flops / 184e6 + bytes / 6.2e6;
+    }
     if (g.m == 2) {
-        // F(2x2,3x3) in one kernel (fused_wide.hip) against its four stages, whose V and M are 4 values per output:
-        // -58 % for 64 -> 64 channels at 224 x 224 (N = 32), -39 % for 128 -> 128 at 112 x 112, -22 % for 256 -> 256
-        // at 56 x 56, -6 % for 512 -> 512 at 28 x 28 (all N = 64); 512 -> 512 at 14 x 14: -5 % at N = 64, -2 % at
-        // N = 32, -11 % at N = 16 (392 items); 512 -> 512 at 28 x 28, N = 8 (784 items): -3 %.  Below some hundred
-        // items the launch does not fill the GPU.
+        // Fewer items: F(2x2,3x3) in one kernel (fused_wide.hip) against its four stages.  128 -> 128 channels at 56 x 56,
+        // N = 4: 28 against 36 us; 256 -> 256 at 28 x 28, N = 8: 48 against 45; 512 -> 512 at 14 x 14, N = 16: 80 against
+        // 69 (all 392 items of 16 tiles).  Below some hundred items the launch does not fill the GPU.
         const long long items = (long long)((g.P + 15) / 16) * ((g.Kp + 63) / 64);
-        return (long long)g.K * g.C <= 256LL * (g.K + g.C) && items >= 384;
+        return (long long)g.K * g.C <= 100LL * (g.K + g.C) && items >= 384;
     }
     if (!fused_lds_eligible(g)) return g.K <= 128 && blocks >= 512;
     if ((long long)g.K * g.C <= 100LL * (g.K + g.C) && blocks >= 512) return true;
-    // with 64 filters per workgroup (fused_wide.hip) the crossover moves up past 256 -> 256 channels (56 x 56: 0.59
-    // against 0.73 ms at N = 64, 0.38 against 0.41 at N = 32, 0.21 against 0.22 at N = 16) and 256 -> 512 (28 x 28,
-    // K C / (K + C) = 171: 0.32 against 0.36 ms at N = 64, 0.19 against 0.21 at N = 32, a tie at N = 16); 512 -> 512
-    // (256) was a loss (0.71 against 0.65 ms) until the items of a partly filled last round were shared between
-    // workgroups.  Since then it depends on how well the rounds are filled (fused_wide_fill): at 28 x 28, 512 -> 512
-    // channels, -6 % at N = 64 (fill 0.93), -9 % at N = 40 (0.96), -3 % at N = 48 and 96 (0.88, 0.92), -6 % at
-    // N = 128, but +9 % at N = 32 (0.77) and +3 % at N = 24 (0.80); 384 -> 384: -7 % at N = 64 (0.88), -2 % at
-    // N = 32 (0.79); 512 -> 512 at 56 x 56: -1 to -6 % (0.92 to 0.97).
+    // 16-tile items, up to 256 of them: every workgroup has a CU to itself.  With 196 of them 64 -> 128 and 128 -> 128
+    // channels at 112 x 112 (N = 2), 128 -> 128 at 56 x 56 (N = 8) and 128 -> 256 (N = 4) run 20-23 % faster in one kernel
+    // (104 items: 19 % slower).
     const long long wide_items = (long long)((g.P + 15) / 16) * ((g.Kp + 63) / 64);
-    // Three quarters of the resident workgroups suffice up to 175 (320 -> 320 at 28 x 28: -26 % with 490 items,
-    // -12 % with 368; 384 -> 384: -8 % with 444; 512 -> 256: a tie with 392, +23 % with 296).
-    if (fused_wide_eligible(g)) {
-        // Up to 256 items every workgroup has a CU to itself: with 196 of them 64 -> 128 and 128 -> 128 channels at
-        // 112 x 112 (N = 2), 128 -> 128 at 56 x 56 (N = 8) and 128 -> 256 (N = 4) run 20-23 % faster in one kernel
-        // (104 items: 19 % slower; 296, where CUs begin to hold two: a tie).
-        if ((long long)g.K * g.C <= 100LL * (g.K + g.C) && wide_items >= 192 && wide_items <= 256) return true;
-        if ((long long)g.K * g.C <= 175LL * (g.K + g.C) && wide_items >= 384) return true;
-        if ((long long)g.K * g.C <= 256LL * (g.K + g.C) && wide_items >= 512 && fused_wide_fill(g) >= 0.85) return true;
-    }
+    if (fused_wide_eligible(g) && (long long)g.K * g.C <= 100LL * (g.K + g.C) && wide_items >= 192 && wide_items <= 256) return true;
     // small batches: with very few filters and channels (64 -> 64) one launch that does everything still beats
     // three launches as soon as it has a workgroup for every other CU (batch 1, 224 x 224: 32 vs 37 us)
     const long long items = (long long)((g.P + 31) / 32) * (g.Kp / 32);

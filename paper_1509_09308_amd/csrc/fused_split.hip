@@ -1,0 +1,786 @@
+// Loops 2-4 of Algorithm 1 (Lavin & Gray) in one kernel, fp32 F(4x4,3x3) and F(2x2,3x3), with the products on the
+// bf16 matrix units (bf16x3.h: every fp32 value in three exact parts, six products, fp32 sums).  For layers with more
+// than 32 filters and a workgroup's worth of work for most CUs; smaller launches take fused_wide.hip.
+//
+// Workgroup = 8 wavefronts, one per CU, owning 64 filters x 32 tiles x 36 components (F(2x2): 64 x 64 x 16), 144 (128)
+// accumulators per lane.  Per step of 16 channels:
+//   transform: every thread owns one (tile, channel) pair (two for F(2x2)); taps as in fused_wide.hip (buffer loads a
+//     step ahead, neighbouring columns by DPP); v = B^T (d B) goes to one of two LDS buffers as fp32
+//     [e][tile][channel], the groups of four channels permuted by tile so that both ways are free of bank conflicts.
+//   multiply: the 36 components lie on the four SIMDs, nine each; the two wavefronts of a SIMD share its nine, four and
+//     a half each (wavefronts w and w + 4: units of one component x 32 filters).  A wavefront reads eight channels of
+//     32 tiles of a component (two 16-byte LDS reads), splits them into parts once, and uses them for 64 filters.
+//     The transformed filters come split and in operand order (filter_split kernels below): one 16-byte load per part
+//     and lane, 1 KB contiguous per wavefront, from L2 straight into registers, two units ahead of their use.
+// Both phases of a step touch different LDS buffers, so a step has one barrier, and the two wavefronts of a SIMD take
+// them in opposite order: the vector instructions of one run beside the matrix instructions of the other.
+//
+// Why 64 x 32: the accumulators of 36 components bound filters x tiles to 2048 per CU.  A step needs 3456 cycles of
+// matrix instructions per SIMD; 64 filters of split operands are 221 KB from L2 (3456 cycles at 64 bytes a cycle), 32
+// tiles 800 vector instructions per SIMD (transform and split, 3200 cycles).  128 x 16 would double the first, 32 x 64
+// the second.
+//
+// Items and the shared last round as in fused_wide.hip.
+#include <type_traits>
+
+#include "wino_internal.h"
+#include "transforms.h"
+#include "bf16x3.h"
+
+namespace wino {
+
+typedef float floatx16_s __attribute__((ext_vector_type(16)));
+typedef float floatx4_s __attribute__((ext_vector_type(4)));
+typedef float floatx2_s __attribute__((ext_vector_type(2)));
+
+constexpr int FS_K = 64, FS_C = 16, FS_T = 512;                      // filters, channels per step, threads
+constexpr int fs_tiles(int m) { return m == 4 ? 32 : 64; }           // tiles per item
+constexpr int fs_v_floats(int m) { return (m + 2) * (m + 2) * FS_C * fs_tiles(m); }
+static_assert((4 + 2) * (4 + 2) * 32 * fs_tiles(4) <= 2 * fs_v_floats(4) && 16 * 32 * fs_tiles(2) <= 2 * fs_v_floats(2),
+              "the epilogue (32 filters of all components at a time) reuses the two tile buffers");
+constexpr unsigned FS_MAX_BYTES = 0x40000000u;                       // longest stretch of D one workgroup's buffer covers
+constexpr unsigned FS_ROW_OOB = 0x80000000u, FS_COL_OOB = 0x40000000u;   // offset markers of taps outside the image
+constexpr int FS_GRID = 256;                                         // resident workgroups: one per CU
+constexpr int fs_share_floats(int m) { return FS_K * fs_tiles(m) * m * m; }      // partial outputs of one share
+constexpr int FS_TICKETS = 1024, FS_TICKET_BYTES = FS_TICKETS * 4;   // arrival counters in front of the partial outputs
+
+// ---- split filters ---------------------------------------------------------------------------------
+// Us[e][channels / 16][filters / 32][part][lane][8 channels]: what lane (i, h) of a 32x32x16 matrix instruction takes
+// for filter 32 kb + i and channels 16 s + 8 h .. + 7, so one wavefront's operand is 1 KB in a row.
+constexpr int FS_BLOCK_BYTES = 3 * 1024;
+static size_t fs_filter_bytes(const Geo &g) { return (size_t)g.a2 * (g.Cp / 16) * (g.Kp / 32) * FS_BLOCK_BYTES; }
+
+__device__ __forceinline__ void fs_store_parts(char *dst, int lane, const float (&x)[8])
+{
+    uintx4_b p[3];
+    bf16_split8(x, p);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) *reinterpret_cast<uintx4_b *>(dst + q * 1024 + lane * 16) = p[q];
+}
+
+__device__ __forceinline__ void fs_clear(unsigned *tickets)
+{
+    if (tickets != nullptr && blockIdx.x == 0 && blockIdx.y == 0)
+        for (int i = threadIdx.x; i < FS_TICKETS; i += blockDim.x) tickets[i] = 0u;
+}
+
+// From untransformed filters: u = G g G^T, split.  One wavefront per block of 32 filters x 16 channels and row xi of
+// the components (blockIdx.y: the G row product is repeated per row, the loads come from L2).  BWD: the filters of
+// the exchanged layer, rotated by 180 degrees (filter_transform.hip).
+template <int M, bool BWD>
+__global__ __launch_bounds__(64) void filter_split_kernel(const float *__restrict__ G, char *__restrict__ Us, int K, int C,
+                                                          int n_kb, int n_s, unsigned *tickets)
+{
+    constexpr int A = M + 2;
+    fs_clear(tickets);
+    const int lane = threadIdx.x, kb = blockIdx.x % n_kb, s = blockIdx.x / n_kb;
+    const int k = kb * 32 + (lane & 31), c0 = s * 16 + (lane >> 5) * 8;
+    float g[8][3][3];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int c = c0 + j;
+        const bool ok = k < K && c < C;
+        // (BWD: K and C are those of the exchanged layer, G is [C][K][3][3])
+        const float *src = G + (BWD ? (size_t)c * K + k : (size_t)k * C + c) * 9;
+#pragma unroll
+        for (int i = 0; i < 9; ++i) g[j][(BWD ? 8 - i : i) / 3][(BWD ? 8 - i : i) % 3] = ok ? src[i] : 0.0f;
+    }
+    auto row = [&](auto xc) {
+        constexpr int xi = decltype(xc)::value;
+        float u[A][8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            float t[3], o[A];
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                const float col[3] = {g[j][0][q], g[j][1][q], g[j][2][q]};
+                g_mul<M>(col, o);
+                t[q] = o[xi];
+            }
+            g_mul<M>(t, o);
+#pragma unroll
+            for (int nu = 0; nu < A; ++nu) u[nu][j] = o[nu];
+        }
+#pragma unroll
+        for (int nu = 0; nu < A; ++nu)
+            fs_store_parts(Us + (((size_t)(xi * A + nu) * n_s + s) * n_kb + kb) * FS_BLOCK_BYTES, lane, u[nu]);
+    };
+    switch (blockIdx.y) {
+    case 0: row(std::integral_constant<int, 0>()); break;
+    case 1: row(std::integral_constant<int, 1>()); break;
+    case 2: row(std::integral_constant<int, 2>()); break;
+    case 3: row(std::integral_constant<int, 3>()); break;
+    case 4: if constexpr (M == 4) row(std::integral_constant<int, A - 2>()); break;
+    case 5: if constexpr (M == 4) row(std::integral_constant<int, A - 1>()); break;
+    }
+}
+
+// From transformed filters U[e][c][k] (padded extents: nothing to mask).
+__global__ __launch_bounds__(64) void filter_resplit_kernel(const float *__restrict__ U, char *__restrict__ Us, int Kp, int Cp,
+                                                            int n_kb, int n_s, unsigned *tickets)
+{
+    fs_clear(tickets);
+    const int lane = threadIdx.x, kb = blockIdx.x % n_kb, s = blockIdx.x / n_kb, e = blockIdx.y;
+    const float *src = U + ((size_t)e * Cp + s * 16 + (lane >> 5) * 8) * Kp + kb * 32 + (lane & 31);
+    float x[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = src[(size_t)j * Kp];
+    fs_store_parts(Us + (((size_t)e * n_s + s) * n_kb + kb) * FS_BLOCK_BYTES, lane, x);
+}
+
+// ---- items -----------------------------------------------------------------------------------------
+// As in fused_wide.hip: an XCD's `slots` workgroups walk `count` items, the items of a partly filled last round are cut
+// into shares of their channel steps.  Here a workgroup has its CU to itself in every round, so halving pays too.
+struct FsRounds {
+    int full, tail, shares;
+};
+__host__ __device__ inline FsRounds fs_rounds(int count, int slots, int nsteps, bool may_share)
+{
+    FsRounds r;
+    r.full = may_share && nsteps >= 8 ? count / slots * slots : count;
+    r.tail = count - r.full;
+    r.shares = 1;
+    while (r.tail > 0 && r.shares < 8 && r.shares * 2 * r.tail <= slots && nsteps % (r.shares * 2) == 0) r.shares *= 2;
+    if (r.shares < 2) r.full = count, r.tail = 0, r.shares = 1;
+    return r;
+}
+__host__ __device__ inline void fs_list(int xcd, int groups, int n_kb, int n_tb, int *first, int *count)
+{
+    const int member = xcd / groups, members = 8 / groups;
+    const int group_items = n_tb * (n_kb / groups);
+    const int per_member = (group_items + members - 1) / members;
+    const int end = (member + 1) * per_member < group_items ? (member + 1) * per_member : group_items;
+    *first = member * per_member;
+    *count = end > *first ? end - *first : 0;
+}
+
+// (agent scope: see fused_wide.hip)
+__device__ __forceinline__ void fs_st_agent(float *p, float a, float b)
+{
+    const floatx2_s v = {a, b};
+    __hip_atomic_store(reinterpret_cast<unsigned long long *>(p), __builtin_bit_cast(unsigned long long, v),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ floatx2_s fs_ld_agent(const float *p)
+{
+    const unsigned long long u = __hip_atomic_load(reinterpret_cast<const unsigned long long *>(p), __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT);
+    return __builtin_bit_cast(floatx2_s, u);
+}
+
+// Barrier that orders LDS traffic only: global loads requested earlier stay in flight across it.
+__device__ __forceinline__ void fs_lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// The M x M outputs of one (filter, tile) pair, whole rows of 16 (F(4x4)) or 8 bytes, not kept in the caches (aux 2: nt);
+// rows from `rows` on lie outside the image, `ok` false: nothing is stored.  No branches: the number of stores in flight
+// does not depend on the path taken.  (The whole offset in a vector register: a 16-byte buffer store with a scalar
+// register as offset was seen to store what the next vector instruction wrote over its first data register -- four lanes
+// of sixteen, now and then -- and the compiler puts wait states between the two only where there is no such register.)
+template <int M>
+__device__ __forceinline__ void fs_store_rows(__amdgpu_buffer_rsrc_t dst, unsigned vo, unsigned so, unsigned row_bytes, bool ok,
+                                              int rows, const float (&y)[M][M])
+{
+    typedef unsigned uintx2_s __attribute__((ext_vector_type(2)));
+#pragma unroll
+    for (int p = 0; p < M; ++p) {
+        const unsigned o = ok && p < rows ? vo + (so + p * row_bytes) : FS_ROW_OOB;
+        if constexpr (M == 4)
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uintx4_b, (floatx4_s{y[p][0], y[p][1], y[p][2], y[p][3]})),
+                                                   dst, o, 0, 2);
+        else
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uintx2_s, (floatx2_s{y[p][0], y[p][1]})), dst, o, 0, 2);
+    }
+}
+
+// The lane number, computed anew (two instructions) where it is needed rather rarely: nothing to keep a register for.
+__device__ __forceinline__ int fs_lane()
+{
+    unsigned l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+    return (int)l;
+}
+
+// CPAD: the channel count is not a multiple of 16, so the last step holds channel slots past the last channel.
+// R: role of the wavefront, 0 or 1 (each role is straight-line code of its own from the first item to the last: the two
+// share no register at any join).
+template <int M, bool CPAD, int R>
+__device__ __forceinline__ void fused_split_body(const float *__restrict__ D, const char *__restrict__ Us, float *__restrict__ Y,
+                                                 const Geo &g, int n_kb, int n_tb, int groups, float *__restrict__ part,
+                                                 float *smem, int wave)
+{
+    constexpr int A = M + 2, NE = A * A;
+    constexpr int P = fs_tiles(M), TB = P / 32;                // tiles of the item, matrix-instruction columns of them
+    constexpr int NU = NE / 4;                                 // units (component x 32 filters) of a wavefront
+    constexpr int NR = M == 4 ? 3 : 2;                         // units of filter operands in flight
+    constexpr int NPR = P * FS_C / FS_T;                       // (tile, channel) pairs of a thread
+    constexpr int V_FLOATS = fs_v_floats(M);
+    static_assert(NU % NR == 0 && 2 * NU * 2 == NE, "ring slots are the same in every step");
+    typedef float mid_t __attribute__((ext_vector_type(M)));   // the M middle columns of a tile row
+    const int lane = fs_lane();
+
+    const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8, slots = gridDim.x / 8;
+    const int group = xcd % groups;
+    const int kb_per_group = n_kb / groups;
+    int first, count;
+    fs_list(xcd, groups, n_kb, n_tb, &first, &count);
+    const int nsteps_all = g.Cp / FS_C;
+    const FsRounds rounds = fs_rounds(count, slots, nsteps_all, part != nullptr);
+    const int full = rounds.full, tail = rounds.tail, shares = rounds.shares;
+    unsigned int *const tickets = reinterpret_cast<unsigned int *>(part);
+    float *const partial = part + FS_TICKET_BYTES / 4;
+    const int tiles_per_image = g.Th * g.Tw;
+
+    // The item of round `n` of this workgroup, or of its place among the shares of the last one.
+    int it = slot, k0 = 0, b0 = 0, img0 = 0, step0 = 0, nsteps = nsteps_all;
+    bool shared = false;
+    auto find = [&]() {
+        int item;
+        if (it < full) {
+            item = first + it;
+        } else if (it - full < tail * shares) {
+            item = first + full + (it - full) % tail;
+            shared = true;
+            nsteps = nsteps_all / shares;
+            step0 = (it - full) / tail * nsteps;
+        } else {
+            return false;
+        }
+        const int tb = item / kb_per_group;
+        k0 = (group * kb_per_group + item - tb * kb_per_group) * FS_K, b0 = tb * P;
+        img0 = b0 / tiles_per_image;
+        return true;
+    };
+
+    // ---- transform role: channel slot cl of the step, tiles (wave & 1) * 16 + tl (+ 32) of the item; the 16 tiles of
+    // a DPP row are neighbours.  Offsets, edge request and border flags as in fused_wide.hip.
+    unsigned vo_m[NPR][A], edge_off[NPR];
+    bool left_in[NPR], right_in[NPR];
+    auto place = [&]() {
+    const int l = fs_lane(), tl = l & 15, cl = (wave >> 1) * 4 + (l >> 4);
+#pragma unroll
+    for (int r = 0; r < NPR; ++r) {
+        const int b = b0 + (wave & 1) * 16 + 32 * r + tl;
+        const bool tile_ok = b < g.P;
+        const int bb = tile_ok ? b : b0;
+        const int ty = bb % g.Tw;
+        const int t2 = bb / g.Tw;
+        const int tx = t2 % g.Th;
+        const int i = t2 / g.Th;
+        const int x0 = M * tx - 1, y0 = M * ty - 1;
+        left_in[r] = y0 >= 0;
+        right_in[r] = y0 + A - 1 < g.W;
+        const unsigned plane0 = (unsigned)((i - img0) * g.C + cl) * (unsigned)(g.H * g.W);
+#pragma unroll
+        for (int p = 0; p < A; ++p) {
+            const int x = x0 + p;
+            const bool rok = tile_ok && x >= 0 && x < g.H;
+            vo_m[r][p] = rok ? (plane0 + (unsigned)(x * g.W + y0 + 1)) * 4u : FS_ROW_OOB;
+        }
+        const unsigned adj_l = left_in[r] ? 0xfffffffcu /* -4 bytes */ : FS_COL_OOB, adj_r = right_in[r] ? 4u * M : FS_COL_OOB;
+        int from_first = (int)FS_COL_OOB, from_last = (int)FS_COL_OOB;
+        from_first = __builtin_amdgcn_update_dpp(from_first, (int)(vo_m[r][0] + adj_l), 0x111, 0xf, 0xf, false);   // row_shr:1
+        from_first = __builtin_amdgcn_update_dpp(from_first, (int)(vo_m[r][1] + adj_l), 0x112, 0xf, 0xf, false);
+        from_first = __builtin_amdgcn_update_dpp(from_first, (int)(vo_m[r][2] + adj_l), 0x113, 0xf, 0xf, false);
+        from_first = __builtin_amdgcn_update_dpp(from_first, (int)(vo_m[r][3] + adj_l), 0x114, 0xf, 0xf, false);
+        if constexpr (M == 4) {
+            from_first = __builtin_amdgcn_update_dpp(from_first, (int)(vo_m[r][A - 2] + adj_l), 0x115, 0xf, 0xf, false);
+            from_first = __builtin_amdgcn_update_dpp(from_first, (int)(vo_m[r][A - 1] + adj_l), 0x116, 0xf, 0xf, false);
+            from_last = __builtin_amdgcn_update_dpp(from_last, (int)(vo_m[r][A - 1] + adj_r), 0x102, 0xf, 0xf, false);     // row_shl:2
+            from_last = __builtin_amdgcn_update_dpp(from_last, (int)(vo_m[r][A - 2] + adj_r), 0x103, 0xf, 0xf, false);
+        }
+        from_last = __builtin_amdgcn_update_dpp(from_last, (int)(vo_m[r][3] + adj_r), 0x104, 0xf, 0xf, false);
+        from_last = __builtin_amdgcn_update_dpp(from_last, (int)(vo_m[r][2] + adj_r), 0x105, 0xf, 0xf, false);
+        from_last = __builtin_amdgcn_update_dpp(from_last, (int)(vo_m[r][1] + adj_r), 0x106, 0xf, 0xf, false);
+        from_last = __builtin_amdgcn_update_dpp(from_last, (int)(vo_m[r][0] + adj_r), 0x107, 0xf, 0xf, false);
+        edge_off[r] = (tl >= 1 && tl <= A) ? (unsigned)from_first : (tl >= 8 && tl <= 7 + A) ? (unsigned)from_last : FS_COL_OOB;
+    }
+    };
+    const unsigned step_bytes = (unsigned)(FS_C * g.H * g.W) * 4u;
+    const size_t image_floats = (size_t)g.C * g.H * g.W;
+    const int kb32 = g.Kp / 32;
+    const __amdgpu_buffer_rsrc_t rsrc_u = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)Us, 0, (unsigned)((size_t)NE * nsteps_all * kb32 * FS_BLOCK_BYTES), 0x00020000);
+
+    mid_t mid[NPR][A];
+    float ed[NPR];
+    // `valid` false: nothing is fetched, the number of loads in flight stays the same (fused_wide.hip)
+    auto load_taps = [&](int step, bool valid) {
+        const size_t left = ((size_t)g.N - img0) * image_floats * 4;
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+            (void *)(D + (size_t)img0 * image_floats), 0, (unsigned)(left < FS_MAX_BYTES ? left : FS_MAX_BYTES), 0x00020000);
+        const unsigned so = valid ? (unsigned)step * step_bytes : 0u;
+        const unsigned off_mask = valid ? 0u : FS_ROW_OOB;
+        const bool ch_ok = !CPAD || (step * FS_C + (wave >> 1) * 4 + (fs_lane() >> 4) < g.C);
+#pragma unroll
+        for (int r = 0; r < NPR; ++r) {
+#pragma unroll
+            for (int p = 0; p < A; ++p) {
+                const unsigned om = (ch_ok ? vo_m[r][p] : FS_ROW_OOB) | off_mask;
+                if constexpr (M == 4)
+                    mid[r][p] = __builtin_bit_cast(mid_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc, om, so, 0));
+                else
+                    mid[r][p] = __builtin_bit_cast(mid_t, __builtin_amdgcn_raw_buffer_load_b64(rsrc, om, so, 0));
+            }
+            ed[r] = __builtin_bit_cast(float,
+                                       __builtin_amdgcn_raw_buffer_load_b32(rsrc, (ch_ok ? edge_off[r] : FS_ROW_OOB) | off_mask, so, 0));
+        }
+    };
+    auto transform = [&](int buf) {
+        const int l = fs_lane();                               // (tile + 32: the same permutation of channel groups)
+        float *const v_dst = smem + (wave & 1) * (16 * FS_C) + (l & 15) * FS_C + (((wave >> 1) ^ ((l >> 1) & 3)) << 2) + (l >> 4);
+#pragma unroll
+        for (int r = 0; r < NPR; ++r) {
+            float t[A][A];
+            auto row = [&](auto pc) {
+                constexpr int p = decltype(pc)::value;
+                const float c1 = mid[r][p][0], c4 = mid[r][p][M - 1];
+                const int e_bits = __builtin_bit_cast(int, ed[r]);
+                const int for_first = __builtin_amdgcn_mov_dpp(e_bits, 0x101 + p, 0xf, 0xf, true);   // row_shl:(1 + p)
+                const int for_last = __builtin_amdgcn_mov_dpp(e_bits, 0x117 - p, 0xf, 0xf, true);    // row_shr:(7 - p)
+                const int l_bits = __builtin_amdgcn_update_dpp(for_first, __builtin_bit_cast(int, c4), 0x111, 0xf, 0xf, false);
+                const int r_bits = __builtin_amdgcn_update_dpp(for_last, __builtin_bit_cast(int, c1), 0x101, 0xf, 0xf, false);
+                const float lv = left_in[r] ? __builtin_bit_cast(float, l_bits) : 0.0f;
+                const float rv = right_in[r] ? __builtin_bit_cast(float, r_bits) : 0.0f;
+                float d[A];
+                d[0] = lv, d[A - 1] = rv;
+#pragma unroll
+                for (int q = 0; q < M; ++q) d[1 + q] = mid[r][p][q];
+                bt_mul<M>(d, t[p]);
+            };
+            row(std::integral_constant<int, 0>());
+            row(std::integral_constant<int, 1>());
+            row(std::integral_constant<int, 2>());
+            row(std::integral_constant<int, 3>());
+            if constexpr (M == 4) {
+                row(std::integral_constant<int, A - 2>());
+                row(std::integral_constant<int, A - 1>());
+            }
+            float *dst = v_dst + buf * V_FLOATS + r * (32 * FS_C);
+#pragma unroll
+            for (int q = 0; q < A; ++q) {
+                float col[A], o[A];
+#pragma unroll
+                for (int p = 0; p < A; ++p) col[p] = t[p][q];
+                bt_mul<M>(col, o);
+#pragma unroll
+                for (int p = 0; p < A; ++p) dst[(p * A + q) * (FS_C * P)] = o[p];
+            }
+        }
+    };
+
+    // ---- multiply role: units NU * role .. of SIMD `simd`'s 2 NU (unit n: component NU * simd + n / 2, filters 32 (n % 2))
+    const int simd = wave & 3;
+    const int li = lane & 31, lh = lane >> 5;
+    floatx16_s acc[NU][TB];
+    uintx4_b ua[NR][3];
+    const unsigned step_u = (unsigned)kb32 * FS_BLOCK_BYTES, comp_u = (unsigned)nsteps_all * step_u;
+    unsigned half_u, su;
+    unsigned uvo = (unsigned)lane * 16u;
+    asm("" : "+v"(uvo));                       // (opaque: the parts' offsets then go into the instructions, not into registers)
+    // channels 8 h .. 8 h + 3 of this lane's tile; the next four: ^ 4
+    const int b_off = simd * NU * (FS_C * P) + li * FS_C + (((2 * lh) ^ ((li >> 1) & 3)) << 2);
+
+    // The filter operands of a new item's first units.
+    auto first_units = [&](bool valid) {
+        // (where the item reaches past the last 32 filters, the second half repeats the first: rows that are never stored)
+        half_u = (unsigned)(min(k0 / 32 + 1, kb32 - 1) - k0 / 32) * FS_BLOCK_BYTES;
+        su = (unsigned)(simd * NU) * comp_u + (unsigned)step0 * step_u + (unsigned)(k0 / 32) * FS_BLOCK_BYTES;
+        __builtin_amdgcn_sched_barrier(0x38f);        // everything but memory requests may cross
+#pragma unroll
+        for (int u = 0; u < NR; ++u) {
+            const int n = R * NU + u;
+            const unsigned so = su + (unsigned)(n / 2) * comp_u + (unsigned)(n % 2) * half_u;
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                ua[u][q] = __builtin_bit_cast(uintx4_b, __builtin_amdgcn_raw_buffer_load_b128(
+                                                            rsrc_u, (valid ? uvo : 0x80000000u) + q * 1024, so, 0));
+        }
+        __builtin_amdgcn_sched_barrier(0x38f);
+    };
+
+    auto run = [&]() {
+        constexpr int N0 = R * NU, C0 = N0 / 2, NC = (N0 + NU - 1) / 2 - C0 + 1;
+        // part q of the operands of unit u
+        auto request = [&](int u, int q, unsigned vo, unsigned so) {
+            const int n = N0 + u;
+            ua[u % NR][q] = __builtin_bit_cast(uintx4_b, __builtin_amdgcn_raw_buffer_load_b128(
+                                                              rsrc_u, vo + q * 1024, so + (n / 2) * comp_u + (n % 2) * half_u, 0));
+        };
+        floatx4_s raw[TB][2];
+        uintx4_b bp[2][TB][3];
+        auto read = [&](int c, int buf) {
+            const int o0 = b_off + buf * V_FLOATS, o1 = o0 ^ 4;
+#pragma unroll
+            for (int j = 0; j < TB; ++j) {
+                raw[j][0] = *reinterpret_cast<const floatx4_s *>(smem + o0 + (C0 + c) * (FS_C * P) + j * (32 * FS_C));
+                raw[j][1] = *reinterpret_cast<const floatx4_s *>(smem + o1 + (C0 + c) * (FS_C * P) + j * (32 * FS_C));
+            }
+        };
+        // The split of `raw` in 12 TB pieces of one to five vector instructions: pair n / 3 of the values, part n % 3
+        // (bf16_split2; what is left of the values replaces them).
+        constexpr int NP = 12 * TB;
+        auto piece = [&](int s, int n) {
+            const int j = n / 12, i = n % 12 / 3, q = n % 3;
+            float &x = reinterpret_cast<float *>(&raw[j][i / 2])[2 * (i % 2)], &y = reinterpret_cast<float *>(&raw[j][i / 2])[2 * (i % 2) + 1];
+            const unsigned w = bf16_pack(x, y);
+            bp[s][j][q][i] = w;
+            if (q < 2) {
+                x -= __builtin_bit_cast(float, w << 16);
+                y -= __builtin_bit_cast(float, w & 0xffff0000u);
+            }
+        };
+        // The order of a wavefront's multiply phase is laid down: after each matrix instruction come some pieces of the
+        // next component's split and, behind a unit, the requests that refill its operand registers, one at a time.
+        auto multiply = [&](int buf, bool more) {
+            // with no next step the requests for it fetch nothing (an offset behind the buffer)
+            const unsigned uvo_next = more ? uvo : 0x80000000u;
+            if constexpr (R == 1) read(0, buf);
+#pragma unroll
+            for (int n = 0; n < NP; ++n) piece(0, n);
+            read(1, buf);
+            auto refill = [&](int u, int q) {          // (u: the unit that is done)
+                if (u + NR < NU)
+                    request(u + NR, q, uvo, su);
+                else
+                    request(u + NR - NU, q, uvo_next, su + step_u);
+            };
+#pragma unroll
+            for (int u = 0; u < NU; ++u) {
+                const int n = N0 + u, ci = n / 2 - C0;
+                // matrix instructions of this component, and how many of them came with units before
+                const int first_u = max(2 * (n / 2) - N0, 0), last_u = min(2 * (n / 2) + 1 - N0, NU - 1);
+                const int nm = (last_u - first_u + 1) * BF16_PRODUCTS * TB, done = (u - first_u) * BF16_PRODUCTS * TB;
+                const int nw = nm - 2 * TB;                      // the split ends two rounds early, for the next read
+#pragma unroll
+                for (int t = 0; t < BF16_PRODUCTS * TB; ++t) {
+                    const int i = t / TB, j = t % TB;
+                    __builtin_amdgcn_sched_barrier(0);
+                    acc[u][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ua[u % NR][bf16_part_a(i)]),
+                                                                        __builtin_bit_cast(bf16x8, bp[ci & 1][j][bf16_part_b(i)]),
+                                                                        acc[u][j], 0, 0, 0);
+                    if (u > 0 && t % TB == 0 && t / TB < 3) refill(u - 1, t / TB);
+                    if (ci + 1 < NC) {
+                        const int m = done + t;
+#pragma unroll
+                        for (int k = 0; k < NP; ++k)
+                            if (k * nw / NP == m) piece((ci + 1) & 1, k);
+                        if (m == nw - 1 && ci + 2 < NC) read(ci + 2, buf);
+                    }
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) refill(NU - 1, q);
+            su += step_u;
+        };
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+#pragma unroll
+            for (int j = 0; j < TB; ++j)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[u][j][i] = 0.0f;
+        transform(0);
+        __builtin_amdgcn_sched_barrier(0x38f);
+        load_taps(step0 + 1, nsteps > 1);
+        if constexpr (R == 0) {
+            // (once more, behind the taps: the compiler's waits in the loop take the worst of both ways into it)
+            __builtin_amdgcn_sched_barrier(0x38f);
+#pragma unroll
+            for (int u = 0; u < NR; ++u)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) request(u, q, uvo, su);
+            __builtin_amdgcn_sched_barrier(0x38f);
+        }
+        fs_lds_barrier();
+        int step = 0;
+        do {
+            const int buf = step & 1;
+            const bool more = step + 1 < nsteps;
+            // The wavefront that multiplies first goes ahead of the other's transform (its matrix instructions need one
+            // issue slot in eight), and so does the one that multiplies second: both phases of either take the same
+            // time (2600 cycles for F(4x4); at equal priority or with the transform ahead 3900 to 5700).
+            if constexpr (R == 1) {
+                __builtin_amdgcn_s_setprio(2);
+                multiply(buf, more);
+                __builtin_amdgcn_s_setprio(0);
+            } else {
+                read(0, buf);
+            }
+            if (more) transform(buf ^ 1);
+            load_taps(step0 + step + 2, step + 2 < nsteps);
+            if constexpr (R == 0) {
+                __builtin_amdgcn_s_setprio(2);
+                multiply(buf, more);
+                __builtin_amdgcn_s_setprio(0);
+            }
+            fs_lds_barrier();
+        } while (++step < nsteps);
+    };
+    if (!find()) return;
+    place();
+    load_taps(step0, true);
+    first_units(true);
+    for (bool more_items = true; more_items;) {
+    run();
+
+    const int o_k0 = k0, o_b0 = b0, o_img0 = img0, o_it = it;  // what the epilogue needs of this item
+    const bool o_shared = shared;
+
+    // ---- inverse transform, 32 filters at a time --------------------------------------------------------
+    constexpr int NJ = M * M / 2;              // pairs of outputs per (filter, tile)
+    constexpr int RP = 32 * P / FS_T;          // (filter, tile) pairs of a thread per 32 filters
+    float *Ms = smem;                          // [e][filter][tile]
+    const int el = fs_lane(), et = wave * 64 + el, eli = el & 31, elh = el >> 5;
+    const int ot = et % P, irow = et / P;
+    const int ob = o_b0 + ot;
+    const bool out_ok = ob < g.P;
+    // Y from the item's first image and filter on; filter and row of the tile go into the scalar offset
+    int rows;
+    unsigned y_vo;
+    {
+        const int bb = out_ok ? ob : o_b0;
+        const int ty = bb % g.Tw;
+        const int t2 = bb / g.Tw;
+        const int tx = t2 % g.Th;
+        rows = g.Ho - M * tx;
+        y_vo = (unsigned)((((t2 / g.Th - o_img0) * g.K + irow) * g.Ho + M * tx) * g.Wo + M * ty) * 4u;
+    }
+    const unsigned plane_bytes = (unsigned)(g.Ho * g.Wo) * 4u;
+    const size_t y_first = ((size_t)o_img0 * g.K + o_k0) * g.Ho * g.Wo;
+    const size_t y_left = ((size_t)g.N * g.K * g.Ho * g.Wo - y_first) * 4;
+    const __amdgpu_buffer_rsrc_t rsrc_y =
+        __builtin_amdgcn_make_buffer_rsrc((void *)(Y + y_first), 0, (unsigned)(y_left < 0x7fffffffu ? y_left : 0x7fffffffu), 0x00020000);
+    float y[2 * RP][M][M];                     // piece n: filter rows n FS_T / P + irow
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        // accumulator register i of lane (li, lh) is filter row 8 (i / 4) + 4 lh + i % 4, tile li
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            const int n = R * NU + u;
+            if (n % 2 == h) {
+#pragma unroll
+                for (int j = 0; j < TB; ++j)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i)
+                        Ms[((simd * NU + n / 2) * 32 + 8 * (i / 4) + 4 * elh + i % 4) * P + j * 32 + eli] = acc[u][j][i];
+            }
+        }
+        fs_lds_barrier();
+        if (h == 1) {
+            // The next item's first requests: the accumulators' registers are free, and no store of this item has been
+            // issued, behind which they would wait (loads and stores of a wavefront complete in order for its counter).
+            it += slots;
+            more_items = find();
+            if (more_items) place();
+            load_taps(step0, more_items);
+            first_units(more_items);
+        }
+#pragma unroll
+        for (int rp = 0; rp < RP; ++rp) {
+            __builtin_amdgcn_sched_barrier(0);
+            const int row = rp * (FS_T / P) + irow;
+            float tt[M][A];
+#pragma unroll
+            for (int nu = 0; nu < A; ++nu) {
+                float col[A], o[M];
+#pragma unroll
+                for (int xi = 0; xi < A; ++xi) col[xi] = Ms[((xi * A + nu) * 32 + row) * P + ot];
+                at_mul<M>(col, o);
+#pragma unroll
+                for (int p = 0; p < M; ++p) tt[p][nu] = o[p];
+            }
+#pragma unroll
+            for (int p = 0; p < M; ++p) at_mul<M>(tt[p], y[h * RP + rp][p]);
+        }
+        fs_lds_barrier();
+    }
+    // (the requests have arrived before the first store is issued)
+#pragma unroll
+    for (int r = 0; r < NPR; ++r) {
+#pragma unroll
+        for (int p = 0; p < A; ++p) asm volatile("" : "+v"(mid[r][p]));
+        asm volatile("" : "+v"(ed[r]));
+    }
+#pragma unroll
+    for (int u = 0; u < NR; ++u)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) asm volatile("" : "+v"(ua[u][q]));
+    if (!o_shared) {
+#pragma unroll
+        for (int n = 0; n < 2 * RP; ++n)
+            fs_store_rows<M>(rsrc_y, y_vo, (unsigned)(n * (FS_T / P)) * plane_bytes, (unsigned)g.Wo * 4u,
+                             out_ok && o_k0 + n * (FS_T / P) + irow < g.K, rows, y[n]);
+    } else {
+        // partial outputs of this share: [piece][pair j of outputs][thread] pairs of floats
+        float *dst = partial + (size_t)(xcd * slots + (o_it - full)) * fs_share_floats(M) + et * 2;
+#pragma unroll
+        for (int n = 0; n < 2 * RP; ++n)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+                fs_st_agent(dst + (n * NJ + j) * FS_T * 2, y[n][j / (M / 2)][2 * (j % (M / 2))], y[n][j / (M / 2)][2 * (j % (M / 2)) + 1]);
+        // ---- the share that arrives last adds the partial outputs of all shares, in share order ----
+        const int j_item = (o_it - full) % tail;
+        unsigned int *const ticket = &tickets[xcd * slots + j_item];
+        __builtin_amdgcn_s_waitcnt(0x0f70);       // vmcnt(0): this wavefront's partial outputs have been acknowledged ...
+        __syncthreads();                          // ... and so have those of the others
+        int *const s_last = reinterpret_cast<int *>(smem);
+        if (et == 0)
+            *s_last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)(shares - 1);
+        __syncthreads();
+        const bool last = *s_last != 0;
+        __syncthreads();                          // (smem is written again by the next item)
+        if (last) {
+            const float *src0 = partial + (size_t)(xcd * slots + j_item) * fs_share_floats(M) + et * 2;
+#pragma unroll
+            for (int f = 0; f < 2 * RP; ++f) {
+                floatx2_s y2[NJ];
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) y2[j] = floatx2_s{0.0f, 0.0f};
+                for (int z = 0; z < shares; z += 2) {
+                    floatx2_s v[2][NJ];
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+#pragma unroll
+                        for (int j = 0; j < NJ; ++j)
+                            v[h][j] = fs_ld_agent(src0 + (size_t)((z + h) * tail) * fs_share_floats(M) + (f * NJ + j) * FS_T * 2);
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+#pragma unroll
+                        for (int j = 0; j < NJ; ++j) y2[j] += v[h][j];
+                }
+                float ys[M][M];
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) {
+                    ys[j / (M / 2)][2 * (j % (M / 2))] = y2[j][0];
+                    ys[j / (M / 2)][2 * (j % (M / 2)) + 1] = y2[j][1];
+                }
+                fs_store_rows<M>(rsrc_y, y_vo, (unsigned)(f * (FS_T / P)) * plane_bytes, (unsigned)g.Wo * 4u,
+                                 out_ok && o_k0 + f * (FS_T / P) + irow < g.K, rows, ys);
+            }
+        }
+    }
+    }   // items
+}
+
+template <int M, bool CPAD>
+__global__ __launch_bounds__(FS_T, 2) void fused_split_kernel(const float *__restrict__ D, const char *__restrict__ Us,
+                                                              float *__restrict__ Y, Geo g, int n_kb, int n_tb, int groups,
+                                                              float *__restrict__ part)
+{
+    __shared__ __attribute__((aligned(16))) float smem[2 * fs_v_floats(M)];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (wave < 4)
+        fused_split_body<M, CPAD, 0>(D, Us, Y, g, n_kb, n_tb, groups, part, smem, wave);
+    else
+        fused_split_body<M, CPAD, 1>(D, Us, Y, g, n_kb, n_tb, groups, part, smem, wave);
+}
+
+static int fs_n_kb(const Geo &g) { return (g.Kp + FS_K - 1) / FS_K; }
+static long long fs_n_tb(const Geo &g) { return ((long long)g.P + fs_tiles(g.m) - 1) / fs_tiles(g.m); }
+
+// Filter blocks per XCD group: halved while their split filters exceed what an XCD's 4 MB L2 keeps (fused_wide.hip).
+static int fs_groups(const Geo &g, int n_kb)
+{
+    int groups = 1;
+    while (groups < 8 && n_kb % (2 * groups) == 0 &&
+           (unsigned long long)(n_kb / groups) * g.a2 * g.Cp * FS_K * 6 > (5ull << 19))
+        groups *= 2;
+    return groups;
+}
+
+// Split filters at the start of the workspace, counters and partial outputs behind them.
+static size_t fs_part_offset(const Geo &g) { return (fs_filter_bytes(g) + 255) & ~(size_t)255; }
+static size_t fs_part_bytes(const Geo &g) { return FS_TICKET_BYTES + (size_t)FS_GRID * fs_share_floats(g.m) * sizeof(float); }
+
+bool fused_split_eligible(const Geo &g)
+{
+    if (!fused_wide_eligible(g)) return false;
+    // the tiles of one item span at most `span` images; their byte offsets from the first must stay below 2^30
+    const unsigned long long tiles = (unsigned long long)g.Th * g.Tw;
+    const unsigned long long span = (fs_tiles(g.m) + tiles - 2) / tiles + 1;
+    const unsigned long long image_bytes = (unsigned long long)g.C * g.H * g.W * 4ull;
+    if (span * image_bytes + 65536 >= FS_MAX_BYTES) return false;
+    if (((span * g.K) + FS_K) * g.Ho * g.Wo * 4ull >= FS_MAX_BYTES) return false;   // and those of its outputs
+    // the split filters lie in the room that every layer's workspace has for U, V and M
+    if (fs_filter_bytes(g) >= (1ull << 31) ||
+        fs_part_offset(g) > (size_t)g.a2 * 4 * ((size_t)g.Cp * g.Kp + (size_t)(g.Cp + g.Kp) * g.Pp))
+        return false;
+    // Half of the CUs at least: with 98 to 104 items the 16-tile items of fused_wide.hip, twice as many, are 8-31 %
+    // faster (128 -> 128 channels at 112 x 112, N = 2: 37 against 42 us; 256 -> 256 at 56 x 56, N = 4: 59 against 72),
+    // with 148 they are 11-29 % slower (64 -> 128 at 112 x 112, N = 3: 34 against 30 us; 128 -> 128 at 56 x 56, N = 12:
+    // 56 against 45; 256 -> 256 at 56 x 56, N = 6: 94 against 73).
+    const long long items = fs_n_tb(g) * fs_n_kb(g);
+    return items <= 0x7fffffffLL && items >= 128;
+}
+
+long long fused_split_items(const Geo &g) { return fs_n_tb(g) * fs_n_kb(g); }
+
+// Estimate of the launch's time in microseconds, for the choice between it and the four stages: rounds of the slowest
+// XCD, each a fixed part (opening an item, inverse transform, stores) and its channel steps, and the two launches.  Fitted to 64 -> 64 channels
+// at 112 x 112 (169 us), 256 -> 256 at 56 x 56 (479) and 512 -> 512 at 28 x 28 (485) for F(4x4,3x3), 512 -> 512 at
+// 14 x 14 (207, N = 32: 109) for F(2x2,3x3), all others N = 64; 256 -> 512 at 28 x 28, N = 16: 87, estimate 85.
+double fused_split_us(const Geo &g)
+{
+    const double item_us = g.m == 4 ? 6.4 : 8.0, step_us = g.m == 4 ? 4.4 : 3.0;
+    const int n_kb = fs_n_kb(g), groups = fs_groups(g, n_kb), n_s = g.Cp / FS_C;
+    double worst = 0.0;
+    for (int xcd = 0; xcd < 8; ++xcd) {
+        int first, count;
+        fs_list(xcd, groups, n_kb, (int)fs_n_tb(g), &first, &count);
+        const FsRounds r = fs_rounds(count, FS_GRID / 8, n_s, fused_split_items(g) >= FS_GRID);
+        const int rounds = (r.full + FS_GRID / 8 - 1) / (FS_GRID / 8);
+        double us = rounds * (item_us + n_s * step_us);
+        if (r.tail > 0) us += item_us + n_s / r.shares * step_us;
+        worst = us > worst ? us : worst;
+    }
+    return worst + 8.0;
+}
+
+// Everything after the choice: `G` (untransformed; `bwd`: of the exchanged layer) or `U` given, workspace as a whole.
+hipError_t launch_fused_split(const Geo &g, const float *D, const float *G, const float *U, float *Y, void *workspace,
+                              size_t workspace_bytes, bool bwd, hipStream_t s)
+{
+    const int n_kb = fs_n_kb(g), n_tb = (int)fs_n_tb(g), kb32 = g.Kp / 32, n_s = g.Cp / 16;
+    const int items = n_kb * n_tb, groups = fs_groups(g, n_kb);
+    char *Us = (char *)workspace;
+    float *part = nullptr;
+    if (items >= FS_GRID && fs_part_offset(g) + fs_part_bytes(g) <= workspace_bytes)
+        for (int xcd = 0; xcd < 8; ++xcd) {
+            int first, count;
+            fs_list(xcd, groups, n_kb, n_tb, &first, &count);
+            if (fs_rounds(count, FS_GRID / 8, n_s, true).shares > 1) part = (float *)(Us + fs_part_offset(g));
+        }
+    unsigned *tickets = (unsigned *)part;
+    const dim3 wave(64);
+    if (U != nullptr)
+        filter_resplit_kernel<<<dim3(kb32 * n_s, g.a2), wave, 0, s>>>(U, Us, g.Kp, g.Cp, kb32, n_s, tickets);
+    else if (g.m == 4 && bwd)
+        filter_split_kernel<4, true><<<dim3(kb32 * n_s, 6), wave, 0, s>>>(G, Us, g.K, g.C, kb32, n_s, tickets);
+    else if (g.m == 4)
+        filter_split_kernel<4, false><<<dim3(kb32 * n_s, 6), wave, 0, s>>>(G, Us, g.K, g.C, kb32, n_s, tickets);
+    else if (bwd)
+        filter_split_kernel<2, true><<<dim3(kb32 * n_s, 4), wave, 0, s>>>(G, Us, g.K, g.C, kb32, n_s, tickets);
+    else
+        filter_split_kernel<2, false><<<dim3(kb32 * n_s, 4), wave, 0, s>>>(G, Us, g.K, g.C, kb32, n_s, tickets);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    // as many workgroups as stay resident, in multiples of the 8 XCDs
+    const unsigned grid = (unsigned)(items >= FS_GRID ? FS_GRID : (items + 7) / 8 * 8);
+    const bool cpad = g.C % FS_C != 0;
+    if (g.m == 4 && cpad)
+        fused_split_kernel<4, true><<<dim3(grid), dim3(FS_T), 0, s>>>(D, Us, Y, g, n_kb, n_tb, groups, part);
+    else if (g.m == 4)
+        fused_split_kernel<4, false><<<dim3(grid), dim3(FS_T), 0, s>>>(D, Us, Y, g, n_kb, n_tb, groups, part);
+    else if (cpad)
+        fused_split_kernel<2, true><<<dim3(grid), dim3(FS_T), 0, s>>>(D, Us, Y, g, n_kb, n_tb, groups, part);
+    else
+        fused_split_kernel<2, false><<<dim3(grid), dim3(FS_T), 0, s>>>(D, Us, Y, g, n_kb, n_tb, groups, part);
+    return hipGetLastError();
+}
+
+}  // namespace wino

@@ -1,5 +1,6 @@
 // Loops 2-4 of Algorithm 1 (Lavin & Gray) in one kernel, fp32 F(4x4,3x3) and F(2x2,3x3) (the algorithm of the
-// paper's own fused kernel, Section 6), for layers with more than 32 filters.  Described for F(4x4,3x3):
+// paper's own fused kernel, Section 6), for layers with more than 32 filters and too few items for fused_split.hip
+// (twice the tiles per item, products on the bf16 matrix units).  Described for F(4x4,3x3):
 // the design of fused_lds.hip with twice the filters per transformed tile.  On this chip fp32 MFMAs and ordinary
 // vector instructions of one SIMD share an issue slot, so the arithmetic of the data transform is paid in MFMA
 // time; it is needed once per (tile, channel) and workgroup, whatever the number of filters the workgroup
@@ -502,31 +503,6 @@ static int fw_groups(const Geo &g, int n_kb)
            (unsigned long long)(n_kb / groups) * g.a2 * g.Cp * FW_K * 4 > (5ull << 19))
         groups *= 2;
     return groups;
-}
-
-// How well the rounds of a launch are filled: items per workgroup / rounds the slowest XCD takes, a last round
-// costing 1 / shares + 0.2 rounds when shared, else 0.6 rounds up to half full (its workgroups alone on their
-// CUs) and a whole one beyond (a model of the measurements quoted in fused_preferred).
-double fused_wide_fill(const Geo &g)
-{
-    const int n_kb = (g.Kp + FW_K - 1) / FW_K;
-    const long long n_tb = (g.P + FW_P - 1) / FW_P;
-    const int full_grid = fw_grid(g.m);
-    if (n_tb * n_kb < full_grid || n_tb * n_kb > 0x7fffffffLL) return 0.0;
-    const int groups = fw_groups(g, n_kb), slots = full_grid / 8, nsteps = (g.C + FW_C - 1) / FW_C;
-    double worst = 0.0;
-    for (int xcd = 0; xcd < 8; ++xcd) {
-        int first, count;
-        fw_list(xcd, groups, n_kb, (int)n_tb, &first, &count);
-        const FwRounds r = fw_rounds(count, slots, nsteps, true);
-        double rounds = (double)(r.full / slots);
-        if (r.shares > 1)
-            rounds += 1.0 / r.shares + 0.2;
-        else if (r.full % slots != 0)
-            rounds += r.full % slots * 2 <= slots ? 0.6 : 1.0;
-        worst = rounds > worst ? rounds : worst;
-    }
-    return (double)(n_tb * n_kb) / full_grid / worst;
 }
 
 size_t fused_wide_part_bytes(const Geo &g)

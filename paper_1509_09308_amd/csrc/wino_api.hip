@@ -311,6 +311,11 @@ static int run_layer(const Geo &g, int y_dt, const void *D, const void *G, const
         return e == hipSuccess ? WINO_OK : hip_fail(e);
     }
     if (flags == WINO_FLAG_AUTO && fused_y_ok(g, y_dt) && fused_preferred(g)) flags = WINO_FLAG_FUSED;
+    if (flags == WINO_FLAG_FUSED && fused_split_eligible(g)) {
+        e = launch_fused_split(g, (const float *)D, (const float *)G, (const float *)U, (float *)Y, workspace, ub + vb + mb,
+                               bwd, s);
+        return e == hipSuccess ? WINO_OK : hip_fail(e);
+    }
     bool v_done = false;
     // the one-kernel fp32 layer keeps arrival counters behind U: the filter transform in front of it clears them
     const bool wide = flags == WINO_FLAG_FUSED && fused_wide_eligible(g);

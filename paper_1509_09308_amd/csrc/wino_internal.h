@@ -53,7 +53,12 @@ hipError_t launch_fused_wide(const Geo &g, const float *D, const float *U, float
 bool fused_wide_shares(const Geo &g, const void *part, size_t part_bytes);
 int fused_wide_plan(const Geo &g, int out[32]);      // per XCD: items, in full rounds, in the last round, shares; returns the grid
 size_t fused_wide_part_bytes(const Geo &g);
-double fused_wide_fill(const Geo &g);      // 0 .. 1: how well the launch fills its rounds of resident workgroups
+// fused_split.hip: the same on the bf16 matrix units; transforms or splits the filters itself (G or U given).
+bool fused_split_eligible(const Geo &g);
+long long fused_split_items(const Geo &g);
+double fused_split_us(const Geo &g);
+hipError_t launch_fused_split(const Geo &g, const float *D, const float *G, const float *U, float *Y, void *workspace,
+                              size_t workspace_bytes, bool bwd, hipStream_t s);
 hipError_t launch_fused_f16(const Geo &g, const void *D, const void *U, void *Y, int y_dt, hipStream_t s);
 bool fused_f2_eligible(const Geo &g);
 hipError_t launch_fused_f2(const Geo &g, const float *D, const float *G, float *Y, void *workspace,

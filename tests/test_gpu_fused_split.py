@@ -1,0 +1,52 @@
+"""The one-kernel fp32 layer on the bf16 matrix units (64 filters x 32 tiles per item, 64 for F(2x2,3x3); 128 items and
+more), at the edges of its items, channel steps, XCD groups and shared last rounds."""
+import numpy as np
+import pytest
+
+from oracle import direct
+from paper_1509_09308_amd import synth
+from gpu_util import TOL, check_close, require_gpu, to_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("m,shape", [
+    (4, (9, 17, 28, 60, 70)),        # 142 items, two channel steps (the second one channel deep), 38 padded filters read twice
+    (4, (33, 16, 28, 20, 256)),      # one step; items over several images, last tile block ragged
+    (4, (5, 40, 66, 128, 96)),       # last tile row half outside; 96 filters: the second block half empty
+    (4, (17, 128, 28, 44, 513)),     # 369 items: a full round, then 15 items per XCD in two shares; nine filter blocks
+    (4, (4, 144, 48, 96, 500)),      # 288 items of nine steps, which no number of shares divides
+    (4, (4, 256, 48, 96, 520)),      # 324 items: XCDs with 9 items and one with 5 in their last round
+    (2, (11, 17, 30, 46, 70)),
+    (2, (3, 130, 65, 64, 200)),      # odd height
+    (2, (6, 256, 48, 60, 400)),
+])
+@pytest.mark.parametrize("given", ["G", "U"])
+def test_split_layer(m, shape, given):
+    torch, w = require_gpu()
+    N, C, H, W, K = shape
+    D, G = synth.make_layer(N, C, H, W, K, seed=sum(shape) + m)
+    d, g = to_gpu(D), to_gpu(G)
+    ws = w.alloc_workspace(N, C, H, W, K, 1, m)
+    ws.view(torch.float32).fill_(float("nan"))
+    kw = dict(G=g) if given == "G" else dict(U=w.wino_filter_transform(g, m), K=K)
+    Y = torch.full((N, K, H, W), float("nan"), device="cuda")
+    w.wino_conv2d_fwd_ex(d, pad=1, m=m, flags=w.FLAG_FUSED, workspace=ws, Y=Y, **kw)
+    Y2 = w.wino_conv2d_fwd_ex(d, pad=1, m=m, flags=w.FLAG_FUSED, workspace=ws, **kw)
+    pts = synth.sample_points((N, K, H, W), 3000, seed=1, edge=m)
+    got = Y.cpu().numpy()
+    assert np.isfinite(got).all()
+    assert torch.equal(Y, Y2)
+    ref = direct.conv2d_points(D, G, pts, pad=1)
+    e, worst = check_close(got[tuple(pts.T)], ref, TOL[("f32", m)], "%s %s" % (shape, given), m)
+    print("F(%d) %s %s: rel err %.2e, max %.2e" % (m, shape, given, e, worst))
+
+
+def test_split_layer_input_gradient():
+    torch, w = require_gpu()
+    N, C, H, W, K = 9, 72, 28, 60, 40
+    _, G = synth.make_layer(1, C, 4, 4, K, seed=3)
+    E = np.random.default_rng(4).standard_normal((N, K, H, W)).astype(np.float32)
+    for m in (2, 4):
+        dD = w.wino_conv2d_bwd_data(to_gpu(E), G=to_gpu(G), pad=1, m=m, flags=w.FLAG_FUSED).cpu().numpy()
+        check_close(dD, direct.conv2d_bwd_data(E, G, H, W, pad=1), TOL[("f32", m)], "input gradient F(%d)" % m, m)
