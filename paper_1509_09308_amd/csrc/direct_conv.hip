@@ -2,6 +2,7 @@
 // over channels), for layers the fast algorithm does not cover: other filter sizes, strides,
 // and layers with very few channels such as the 3-channel first layer of Table 3.
 #include "wino_internal.h"
+#include "bf16x3.h"
 
 namespace wino {
 
@@ -12,7 +13,8 @@ template <typename T> __device__ __forceinline__ void st_d(T *p, float v);
 template <> __device__ __forceinline__ void st_d<float>(float *p, float v) { *p = v; }
 template <> __device__ __forceinline__ void st_d<__half>(__half *p, float v) { *p = __float2half_rn(v); }
 
-// One thread per output pixel, KB filters at a time held in registers.  The filter block is
+// The general form, for the little that the matrix units do not take (see the launcher): one thread per output pixel, KB
+// filters at a time held in registers.  The filter block is
 // staged in LDS as [c][u][v][k] so a thread fetches 4 filters per LDS read (all lanes read the
 // same address: broadcast).  Loads of D and stores of Y are contiguous across a wavefront.
 constexpr int DC_KB = 16;
@@ -74,11 +76,6 @@ __global__ __launch_bounds__(256) void direct_conv_kernel(const T *__restrict__ 
     }
 }
 
-// 3 x 3, stride 1 specialisation (the 3-channel first layer of Table 3 is its main use): one
-// thread computes 4 neighbouring outputs of a row for DC_KB filters.  Per channel it holds the
-// 3 x 6 input window in registers (one aligned 16-byte load and two single loads per row), and
-// every 16-byte broadcast LDS read of 4 filter taps feeds 16 FMAs.  Stores are 16 bytes per
-// filter and contiguous across a wavefront.
 typedef float floatx4_dc __attribute__((ext_vector_type(4)));
 
 // four consecutive elements from an address aligned to four elements, widened to fp32
@@ -93,110 +90,6 @@ template <> __device__ __forceinline__ floatx4_dc ld4_d<__half>(const __half *p)
     const __half2 a = *reinterpret_cast<const __half2 *>(&raw.x), b = *reinterpret_cast<const __half2 *>(&raw.y);
     return floatx4_dc{__low2float(a), __high2float(a), __low2float(b), __high2float(b)};
 }
-template <typename T> __device__ __forceinline__ void st4_d(T *p, floatx4_dc v);
-template <> __device__ __forceinline__ void st4_d<float>(float *p, floatx4_dc v)
-{
-    *reinterpret_cast<floatx4_dc *>(p) = v;
-}
-template <> __device__ __forceinline__ void st4_d<__half>(__half *p, floatx4_dc v)
-{
-    const __half2 a = __floats2half2_rn(v[0], v[1]), b = __floats2half2_rn(v[2], v[3]);
-    uint2 raw;
-    raw.x = *reinterpret_cast<const unsigned *>(&a);
-    raw.y = *reinterpret_cast<const unsigned *>(&b);
-    *reinterpret_cast<uint2 *>(p) = raw;
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void direct_conv3x3_kernel(const T *__restrict__ D, const T *__restrict__ G,
-                                                             T *__restrict__ Y, int C, int H, int W, int K, int pad,
-                                                             int Ho, int Wo, int Wq, int CC)
-{
-    __shared__ float gs[DC_LDS_FLOATS];
-    const int item = blockIdx.x * 256 + threadIdx.x;   // (output row, group of 4 columns)
-    const int k0 = blockIdx.y * DC_KB;
-    const int i = blockIdx.z;
-    const bool live = item < Ho * Wq;
-    const int ox = live ? item / Wq : 0, oy = live ? (item % Wq) * 4 : 0;
-    const int y0 = oy - pad;                            // first input column of the window
-    const bool vec_in = (W % 4 == 0) && (pad == 1);     // columns y0+1..y0+4 are then one aligned float4
-    float acc[4][DC_KB];
-#pragma unroll
-    for (int p = 0; p < 4; ++p)
-#pragma unroll
-        for (int kk = 0; kk < DC_KB; ++kk) acc[p][kk] = 0.0f;
-    const T *Di = D + (size_t)i * C * H * W;
-    for (int c0 = 0; c0 < C; c0 += CC) {
-        const int cn = min(CC, C - c0);
-        __syncthreads();
-        for (int idx = threadIdx.x; idx < cn * 9 * DC_KB; idx += 256) {
-            const int kk = idx % DC_KB, j = idx / DC_KB;
-            const int k = k0 + kk;
-            gs[idx] = (k < K) ? ld_d<T>(G + ((size_t)k * C + c0) * 9 + j) : 0.0f;
-        }
-        __syncthreads();
-        if (!live) continue;
-        for (int cc = 0; cc < cn; ++cc) {
-            const T *Dc = Di + (size_t)(c0 + cc) * H * W;
-            float win[3][6];
-#pragma unroll
-            for (int u = 0; u < 3; ++u) {
-                const int x = ox + u - pad;
-                const bool rok = x >= 0 && x < H;
-                const T *row = Dc + (size_t)(rok ? x : 0) * W;
-                if (vec_in) {
-                    const floatx4_dc mid = rok ? ld4_d<T>(row + y0 + 1) : floatx4_dc{0.f, 0.f, 0.f, 0.f};
-                    win[u][0] = (rok && y0 >= 0) ? ld_d<T>(row + y0) : 0.0f;
-                    win[u][1] = mid[0];
-                    win[u][2] = mid[1];
-                    win[u][3] = mid[2];
-                    win[u][4] = mid[3];
-                    win[u][5] = (rok && y0 + 5 < W) ? ld_d<T>(row + y0 + 5) : 0.0f;
-                } else {
-#pragma unroll
-                    for (int q = 0; q < 6; ++q) {
-                        const int y = y0 + q;
-                        win[u][q] = (rok && y >= 0 && y < W) ? ld_d<T>(row + y) : 0.0f;
-                    }
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < 3; ++u)
-#pragma unroll
-                for (int v = 0; v < 3; ++v) {
-                    const floatx4_dc *wv = reinterpret_cast<const floatx4_dc *>(&gs[((cc * 3 + u) * 3 + v) * DC_KB]);
-#pragma unroll
-                    for (int q4 = 0; q4 < DC_KB / 4; ++q4) {
-                        const floatx4_dc f = wv[q4];
-#pragma unroll
-                        for (int p = 0; p < 4; ++p) {
-                            const float d = win[u][p + v];
-                            acc[p][4 * q4 + 0] = fmaf(d, f[0], acc[p][4 * q4 + 0]);
-                            acc[p][4 * q4 + 1] = fmaf(d, f[1], acc[p][4 * q4 + 1]);
-                            acc[p][4 * q4 + 2] = fmaf(d, f[2], acc[p][4 * q4 + 2]);
-                            acc[p][4 * q4 + 3] = fmaf(d, f[3], acc[p][4 * q4 + 3]);
-                        }
-                    }
-                }
-        }
-    }
-    if (!live) return;
-    const bool vec_out = (Wo % 4 == 0);
-#pragma unroll
-    for (int kk = 0; kk < DC_KB; ++kk) {
-        if (k0 + kk < K) {
-            T *dst = Y + (((size_t)i * K + k0 + kk) * Ho + ox) * Wo + oy;
-            if (vec_out) {
-                st4_d<T>(dst, floatx4_dc{acc[0][kk], acc[1][kk], acc[2][kk], acc[3][kk]});
-            } else {
-#pragma unroll
-                for (int p = 0; p < 4; ++p)
-                    if (oy + p < Wo) st_d<T>(dst + p, acc[p][kk]);
-            }
-        }
-    }
-}
-
 // store that does not keep the line in the caches (an output plane is written once and is far larger than they are)
 template <typename T> __device__ __forceinline__ void st_nt_d(T *p, float v);
 template <> __device__ __forceinline__ void st_nt_d<float>(float *p, float v) { __builtin_nontemporal_store(v, p); }
@@ -326,6 +219,284 @@ static bool direct_mfma_ok(int C, int H, int W, int K, int R, int S, int pad, in
     return (Ho + DM_RB - 1) / DM_RB <= 0x7fffffff && (K + 63) / 64 <= 65535 && N <= 65535;
 }
 
+// Any filter, stride and padding as a matrix product on the matrix units: Y[k][pixel] = sum over taps j = (c, u, v) of
+// G[k][j] D[pixel's window][j], the K x CRS matrix of filters as it lies in memory times the CRS x N Ho Wo matrix of
+// windows, which is never built: a thread fetches its elements from D with one bounds check each (the tap is the same for
+// a whole wavefront, so its row, column and offset are scalars).  fp32 goes through the bf16 units in three exact parts
+// (bf16x3.h), fp16 directly; sums are fp32.
+// A workgroup of four wavefronts owns BM filters x BN pixels.  Per step of 16 taps every thread fetches quads of four
+// taps of one filter or pixel, splits them and stores the parts to LDS as 8-byte halves of the 16-byte words (eight taps
+// of one row) that the matrix instruction takes; two steps are in flight in registers, two in LDS, one barrier per step.
+// A step is a chain of fetch, split, barrier, LDS reads and six dependent matrix instructions, about 1 500 cycles for a
+// workgroup alone on its CU, so KS groups of four wavefronts take every KS-th step of the same block and add their sums in
+// LDS at the end: four groups where there are no more blocks than CUs, two up to twice as many.  64 x 128 blocks spare a
+// third of the fetches per product where there are 512 of them.  (Fetching a filter's taps with lanes along the filters:
+// 64 cache lines per request, 50 us for the first of these.)  Against one thread per pixel and 16 filters on the vector
+// ALUs: 64 -> 128 channels at 56 x 56, stride 2, N = 16: 151 -> 34 us in fp32, 127 -> 28 in fp16 (N = 1: 115 -> 17); 512 ->
+// 512 at 14 x 14, stride 2, N = 1: 807 -> 98; 1 x 1, 256 -> 512 at 28 x 28, stride 2, N = 8: 120 -> 15; 7 x 7, 3 -> 64 at
+// 224 x 224, stride 2, N = 8: 84 -> 36; 5 x 5, 48 -> 128 at 27 x 27, N = 4: 210 -> 31.  Error against float64: 25-60 % less.
+constexpr int DG_STEP = 16;
+typedef _Float16 halfx8_dc __attribute__((ext_vector_type(8)));
+
+// Barrier that orders LDS traffic only: global loads requested earlier stay in flight across it.
+__device__ __forceinline__ void dg_lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+struct DgGeo {
+    int C, H, W, K, R, S, pad, stride, Ho, Wo;
+    int J, P;                    // taps, pixels of all images
+    int dv, du, dc;              // KS steps ahead in (c, u, v)
+    int tiles_m;
+};
+
+template <typename T, int BM, int BN, int KS>
+__global__ __launch_bounds__(256 * KS) void direct_gemm_kernel(const T *__restrict__ D, const T *__restrict__ G, T *__restrict__ Y,
+                                                             DgGeo g, unsigned g_bytes, size_t d_elems)
+{
+    constexpr bool F32 = sizeof(T) == 4;
+    constexpr int NP = F32 ? 3 : 1;                            // parts
+    constexpr int WM = BM / 32, WN = 4 / WM, TN = BN / 32 / WN; // wavefronts along filters and pixels, pixel tiles of one
+    constexpr int BQ = BN * 4 / 256;                           // quads of pixels a thread fetches (of filters: one, or none)
+    static_assert(WM == 1 || WM == 2, "32 or 64 filters");
+    constexpr int GROUP_WORDS = 2 * 2 * NP * (BM + BN);        // LDS of a group: two slabs of both operands
+    constexpr int SUM_WORDS = (KS - 1) * BM * BN / 4;          // or the sums of all groups but one
+    __shared__ uintx4_b lds[KS * GROUP_WORDS > SUM_WORDS ? KS * GROUP_WORDS : SUM_WORDS];
+    const int tid = threadIdx.x & 255, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ks = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+    uintx4_b *const As = lds + ks * GROUP_WORDS, *const Bs = As + 2 * 2 * NP * BM;
+    const int bid = blockIdx.x;
+    const int k0 = bid % g.tiles_m * BM, p0 = bid / g.tiles_m * BN;
+    const int plane = g.Ho * g.Wo, image = g.C * g.H * g.W;
+    const int n0 = p0 / plane;
+
+    // D from the block's first image on, and (pad rows and columns) in front of it, so that offsets are not negative;
+    // only taps inside an image are fetched
+    const int lead = g.pad * g.W + g.pad;
+    const size_t left = (d_elems - (size_t)n0 * image + lead) * sizeof(T);
+    const __amdgpu_buffer_rsrc_t rsrc_d = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(D + (size_t)n0 * image - lead), 0, (unsigned)(left < 0x7fffffffu ? left : 0x7fffffffu), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsrc_g = __builtin_amdgcn_make_buffer_rsrc((void *)G, 0, g_bytes, 0x00020000);
+    constexpr unsigned OOB = 0x80000000u;
+
+    // quad j of this thread: taps 4 qb[j] .. + 3 of a step, pixel (filter) column; the quad is the wavefront's
+    int x0[BQ], y0[BQ], cb[BQ], ub[BQ], vb[BQ];
+    unsigned vo[BQ];
+#pragma unroll
+    for (int j = 0; j < BQ; ++j) {
+        const int col = (tid + j * 256) % BN, q = (wave * 64 + j * 256) / BN;
+        const int p = min(p0 + col, g.P - 1);                  // (pixels past the last are never stored)
+        const int n = p / plane, r = p - n * plane;
+        const int ox = r / g.Wo, oy = r - ox * g.Wo;
+        x0[j] = ox * g.stride - g.pad, y0[j] = oy * g.stride - g.pad;
+        vo[j] = (unsigned)((n - n0) * image + ox * g.stride * g.W + oy * g.stride) * (unsigned)sizeof(T);
+        const int first = DG_STEP * ks + 4 * q;
+        vb[j] = first % g.S, ub[j] = first / g.S % g.R, cb[j] = first / g.S / g.R;
+    }
+    // filters: four threads fetch the 16 taps of a step of one filter, which lie side by side
+    const int arow = tid >> 2, a_quad = tid & 3;
+    const bool a_role = BM == 64 || arow < BM;
+    const unsigned ao = a_role ? ((unsigned)min(k0 + arow, g.K - 1) * (unsigned)g.J + 4u * a_quad) * (unsigned)sizeof(T) : OOB;
+    // (a 16-byte request needs four-byte alignment, an 8-byte one of fp16 taps too)
+    const bool a_wide = F32 || g.J % 2 == 0;
+
+    T rb[2][BQ][4], ra[2][4];
+    int j_next = DG_STEP * ks;                                 // first tap of the step requested next
+    auto request = [&](int slot) {
+#pragma unroll
+        for (int j = 0; j < BQ; ++j) {
+            const int q = (wave * 64 + j * 256) / BN;
+            int c = cb[j], u = ub[j], v = vb[j];
+            // (scalars throughout; masks from signs, because choices between scalars become branches or vector code)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int tap = (j_next + 4 * q + i - g.J) >> 31;          // all ones up to the last tap
+                const bool ok = (unsigned)(x0[j] + u) < (unsigned)(g.H & tap) && (unsigned)(y0[j] + v) < (unsigned)g.W;
+                const unsigned so = (unsigned)((((c * g.H + u) * g.W + v) & tap) * (int)sizeof(T));
+                if constexpr (F32)
+                    rb[slot][j][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc_d, ok ? vo[j] : OOB, so, 0));
+                else
+                    rb[slot][j][i] = __builtin_bit_cast(__half, __builtin_amdgcn_raw_buffer_load_b16(rsrc_d, ok ? vo[j] : OOB, so, 0));
+                const int in_v = (v + 1 - g.S) >> 31;                      // all ones while the next tap is in the same row
+                v = (v + 1) & in_v;
+                const int u1 = u + 1 + in_v, in_u = (u1 - g.R) >> 31;
+                u = u1 & in_u, c += 1 + in_u;
+            }
+            const int v2 = vb[j] + g.dv - g.S, v_low = v2 >> 31;           // ... a step ahead
+            vb[j] = v2 + (g.S & v_low);
+            const int u2 = ub[j] + g.du + 1 + v_low - g.R, u_low = u2 >> 31;
+            ub[j] = u2 + (g.R & u_low), cb[j] += g.dc + 1 + u_low;
+        }
+        const unsigned o = ao + (unsigned)j_next * (unsigned)sizeof(T);
+        if (a_wide && j_next + DG_STEP <= g.J) {
+            if constexpr (F32) {
+                const floatx4_dc w = __builtin_bit_cast(floatx4_dc, __builtin_amdgcn_raw_buffer_load_b128(rsrc_g, o, 0, 0));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) ra[slot][i] = w[i];
+            } else {
+                typedef _Float16 halfx4_dc __attribute__((ext_vector_type(4)));
+                const halfx4_dc w = __builtin_bit_cast(halfx4_dc, __builtin_amdgcn_raw_buffer_load_b64(rsrc_g, o, 0, 0));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) ra[slot][i] = __builtin_bit_cast(__half, (_Float16)w[i]);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const unsigned oi = a_role && j_next + 4 * a_quad + i < g.J ? o + i * (unsigned)sizeof(T) : OOB;
+                if constexpr (F32)
+                    ra[slot][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc_g, oi, 0, 0));
+                else
+                    ra[slot][i] = __builtin_bit_cast(__half, __builtin_amdgcn_raw_buffer_load_b16(rsrc_g, oi, 0, 0));
+            }
+        }
+        j_next += DG_STEP * KS;
+    };
+    typedef unsigned uintx2_d __attribute__((ext_vector_type(2)));
+    // quad q of column col: half q % 2 of words [q / 2][part][col]
+    auto put = [&](uintx4_b *dst, int cols, int col, int q, const T (&x)[4]) {
+        uintx2_d *w = reinterpret_cast<uintx2_d *>(dst + (q / 2) * NP * cols + col) + q % 2;
+        if constexpr (F32) {
+            unsigned h0, m0, l0, h1, m1, l1;
+            bf16_split2(x[0], x[1], h0, m0, l0);
+            bf16_split2(x[2], x[3], h1, m1, l1);
+            w[0] = uintx2_d{h0, h1}, w[2 * cols] = uintx2_d{m0, m1}, w[4 * cols] = uintx2_d{l0, l1};
+        } else {
+            const unsigned short *h = reinterpret_cast<const unsigned short *>(x);
+            w[0] = uintx2_d{h[0] | (unsigned)h[1] << 16, h[2] | (unsigned)h[3] << 16};
+        }
+    };
+    auto store = [&](int slot, int buf) {
+#pragma unroll
+        for (int j = 0; j < BQ; ++j) put(Bs + buf * (2 * NP * BN), BN, (tid + j * 256) % BN, (wave * 64 + j * 256) / BN, rb[slot][j]);
+        if (a_role) put(As + buf * (2 * NP * BM), BM, arow, a_quad, ra[slot]);
+    };
+
+    const int wm = wave % WM, wn = wave / WM, li = lane & 31, lh = lane >> 5;
+    floatx16_dc acc[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[j][r] = 0.0f;
+    auto multiply = [&](int buf) {
+        uintx4_b a[NP], b[NP][TN];
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            a[q] = As[(buf * 2 * NP + lh * NP + q) * BM + wm * 32 + li];
+#pragma unroll
+            for (int j = 0; j < TN; ++j) b[q][j] = Bs[(buf * 2 * NP + lh * NP + q) * BN + (wn * TN + j) * 32 + li];
+        }
+        if constexpr (F32) {
+#pragma unroll
+            for (int n = 0; n < BF16_PRODUCTS; ++n)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[bf16_part_a(n)]),
+                                                                     __builtin_bit_cast(bf16x8, b[bf16_part_b(n)][j]), acc[j], 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8_dc, a[0]),
+                                                                __builtin_bit_cast(halfx8_dc, b[0][j]), acc[j], 0, 0, 0);
+        }
+    };
+    const int steps = (g.J + DG_STEP * KS - 1) / (DG_STEP * KS);     // (the same for every group: a step past the last tap is zeros)
+    // (requests past the last step fetch nothing; the number of loads in flight does not depend on the path taken)
+    request(0);
+    request(1);
+    store(0, 0);
+    __syncthreads();
+    int t = 0;
+    auto step = [&](int odd) {
+        request(odd);
+        multiply(odd);
+        store(odd ^ 1, odd ^ 1);
+        dg_lds_barrier();
+    };
+    for (; t + 1 < steps; t += 2) {
+        step(0);
+        step(1);
+    }
+    if (t < steps) multiply(0);
+    if constexpr (KS > 1) {
+        // the groups' sums, added in order by the first: [group - 1][register][thread]
+        float *sums = reinterpret_cast<float *>(lds);
+        __syncthreads();
+        if (ks > 0) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) sums[(((ks - 1) * TN + j) * 16 + r) * 256 + tid] = acc[j][r];
+        }
+        __syncthreads();
+        if (ks > 0) return;
+#pragma unroll
+        for (int z = 0; z < KS - 1; ++z)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[j][r] += sums[((z * TN + j) * 16 + r) * 256 + tid];
+    }
+
+    // accumulator register r of lane (li, lh) is filter row 8 (r / 4) + 4 lh + r % 4, pixel li of its tile
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const int p = p0 + (wn * TN + j) * 32 + li;
+        if (p < g.P) {
+            const int n = p / plane;
+            T *dst = Y + ((size_t)n * g.K + k0 + wm * 32 + 4 * lh) * plane + (p - n * plane);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int kk = 8 * (r / 4) + r % 4;
+                if (k0 + wm * 32 + 4 * lh + kk < g.K) st_d<T>(dst + (size_t)kk * plane, acc[j][r]);
+            }
+        }
+    }
+}
+
+// What the product form takes: the images one block of pixels touches within 31-bit byte offsets, filters likewise,
+// pixels and blocks within 32 bits.  Everything else goes to the general form above.
+static bool direct_gemm_ok(int N, int C, int H, int W, int K, int R, int S, int pad, int Ho, int Wo, int size)
+{
+    const unsigned long long plane = (unsigned long long)Ho * Wo, P = plane * N;
+    const unsigned long long span = (128 + plane - 2) / plane + 1;
+    const unsigned long long image = (unsigned long long)C * H * W + (unsigned long long)pad * W + pad;
+    const unsigned long long limit = 1ull << 31;
+    return P < limit - 256 && (unsigned long long)C * R * S < limit / 8 && span * image * size < limit - 65536 &&
+           (unsigned long long)K * C * R * S * size < limit && (P / 64 + 1) * ((K + 31) / 32) < limit;
+}
+
+template <typename T, int BM, int BN, int KS>
+static hipError_t launch_direct_gemm(DgGeo g, int N, const void *D, const void *G, void *Y, hipStream_t s)
+{
+    g.tiles_m = (g.K + BM - 1) / BM;
+    g.dv = DG_STEP * KS % g.S, g.du = DG_STEP * KS / g.S % g.R, g.dc = DG_STEP * KS / g.S / g.R;
+    const long long blocks = (long long)g.tiles_m * ((g.P + BN - 1) / BN);
+    direct_gemm_kernel<T, BM, BN, KS><<<dim3((unsigned)blocks), dim3(256 * KS), 0, s>>>(
+        (const T *)D, (const T *)G, (T *)Y, g, (unsigned)((size_t)g.K * g.J * sizeof(T)), (size_t)N * g.C * g.H * g.W);
+    return hipGetLastError();
+}
+
+template <typename T>
+static hipError_t launch_direct_gemm(const DgGeo &g, int N, const void *D, const void *G, void *Y, hipStream_t s)
+{
+    const int steps = (g.J + DG_STEP - 1) / DG_STEP;
+    if (g.K <= 32) {
+        const long long blocks = (g.P + 127) / 128;
+        if (blocks <= 256 && steps >= 8) return launch_direct_gemm<T, 32, 128, 4>(g, N, D, G, Y, s);
+        if (blocks <= 512 && steps >= 4) return launch_direct_gemm<T, 32, 128, 2>(g, N, D, G, Y, s);
+        return launch_direct_gemm<T, 32, 128, 1>(g, N, D, G, Y, s);
+    }
+    if ((long long)((g.K + 63) / 64) * ((g.P + 127) / 128) >= 512) return launch_direct_gemm<T, 64, 128, 1>(g, N, D, G, Y, s);
+    const long long blocks = (long long)((g.K + 63) / 64) * ((g.P + 63) / 64);
+    if (blocks <= 256 && steps >= 8) return launch_direct_gemm<T, 64, 64, 4>(g, N, D, G, Y, s);
+    if (blocks <= 512 && steps >= 4) return launch_direct_gemm<T, 64, 64, 2>(g, N, D, G, Y, s);
+    return launch_direct_gemm<T, 64, 64, 1>(g, N, D, G, Y, s);
+}
+
 hipError_t launch_direct_conv(int N, int C, int H, int W, int K, int R, int S, int pad, int stride, int dt,
                               const void *D, const void *G, void *Y, hipStream_t s)
 {
@@ -349,16 +520,14 @@ hipError_t launch_direct_conv(int N, int C, int H, int W, int K, int R, int S, i
                             : launch_direct_mfma<__half, 4>(N, H, W, K, pad, Ho, Wo, D, G, Y, s);
         }
     }
-    if (R == 3 && S == 3 && stride == 1) {
-        const int Wq = (Wo + 3) / 4;
-        dim3 grid3((Ho * Wq + 255) / 256, grid.y, N);
-        if (dt == WINO_F32)
-            direct_conv3x3_kernel<float><<<grid3, block, 0, s>>>((const float *)D, (const float *)G, (float *)Y, C, H, W,
-                                                                 K, pad, Ho, Wo, Wq, CC);
-        else
-            direct_conv3x3_kernel<__half><<<grid3, block, 0, s>>>((const __half *)D, (const __half *)G, (__half *)Y, C,
-                                                                  H, W, K, pad, Ho, Wo, Wq, CC);
-        return hipGetLastError();
+    // (up to four taps the layer is bound by writing Y, in 256-pixel runs by the general form: 1 x 1, 3 -> 300 channels, stride
+    // 2 at 32 x 32, N = 64: 9.0 us against 10.0)
+    if (C * R * S > 4 && direct_gemm_ok(N, C, H, W, K, R, S, pad, Ho, Wo, dt == WINO_F32 ? 4 : 2)) {
+        DgGeo g;
+        g.C = C, g.H = H, g.W = W, g.K = K, g.R = R, g.S = S, g.pad = pad, g.stride = stride, g.Ho = Ho, g.Wo = Wo;
+        g.J = C * R * S, g.P = N * Ho * Wo, g.tiles_m = 0;
+        g.dv = g.du = g.dc = 0;
+        return dt == WINO_F32 ? launch_direct_gemm<float>(g, N, D, G, Y, s) : launch_direct_gemm<__half>(g, N, D, G, Y, s);
     }
     if (dt == WINO_F32)
         direct_conv_kernel<float><<<grid, block, 0, s>>>((const float *)D, (const float *)G, (float *)Y, N, C, H, W, K,

@@ -1,0 +1,39 @@
+"""Direct layers as a product on the matrix units, at the edges of its steps (16 taps), quads, blocks and groups."""
+import numpy as np
+import pytest
+
+from oracle import direct
+from gpu_util import check_close, require_gpu, to_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+@pytest.mark.parametrize("N,C,H,W,K,R,S,pad,stride", [
+    (3, 5, 9, 11, 33, 1, 1, 0, 1),          # fewer taps than a step, blocks over several images
+    (2, 16, 13, 10, 32, 1, 1, 0, 2),        # one whole step, 32 filters
+    (1, 7, 12, 9, 65, 3, 3, 1, 2),          # 63 taps
+    (2, 3, 17, 20, 40, 5, 3, 2, 3),         # 45 taps (odd), filters higher than wide
+    (1, 6, 8, 31, 17, 2, 7, 3, 1),          # rows of taps longer than a quad, padding wider than the filter is high
+    (70, 9, 3, 3, 70, 3, 3, 1, 1),          # whole images of nine pixels
+    (1, 40, 14, 14, 64, 3, 3, 1, 1),        # few blocks: four groups
+    (4, 24, 56, 52, 96, 3, 3, 0, 2),        # two groups
+    (6, 12, 112, 100, 72, 3, 3, 1, 1),      # wide blocks
+    (1, 1, 40, 520, 16, 1, 512, 4, 1),      # the longest row of taps
+])
+def test_direct_product(N, C, H, W, K, R, S, pad, stride, dtype):
+    torch, w = require_gpu()
+    rng = np.random.default_rng(N + C + H + W + K + R + S)
+    D = rng.standard_normal((N, C, H, W)).astype(np.float32)
+    G = (rng.standard_normal((K, C, R, S)) * np.sqrt(2.0 / (C * R * S))).astype(np.float32)
+    if dtype == "f16":
+        D, G = D.astype(np.float16), G.astype(np.float16)
+    # the tensors end where NaNs begin, and begin where NaNs end: nothing outside them may be used
+    def guarded(a):
+        buf = torch.full((a.size + 4096,), float("nan"), dtype=torch.from_numpy(a).dtype, device="cuda")
+        buf[2048:2048 + a.size] = to_gpu(a).reshape(-1)
+        return buf[2048:2048 + a.size].view(a.shape)
+    Y = w.direct_conv2d_fwd(guarded(D), guarded(G), pad=pad, stride=stride).cpu().numpy()
+    ref = direct.conv2d_fwd(D.astype(np.float32), G.astype(np.float32), pad=pad, stride=stride)
+    # fp32: a rounding per tap at most (2^-24 each, random: under 1e-6 in norm); fp16: one rounding of Y, 2^-11 at most
+    check_close(Y, ref, 1e-6 if dtype == "f32" else 4.9e-4, "direct %s" % dtype)
