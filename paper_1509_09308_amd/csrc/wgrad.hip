@@ -10,6 +10,7 @@
 #include <stdlib.h>
 
 #include "wino_internal.h"
+#include "bf16x3.h"
 
 namespace wino {
 
@@ -245,58 +246,47 @@ __global__ __launch_bounds__(256) void wgrad_gemm_kernel(const float *__restrict
         }
 }
 
-// The same products with both transforms inside the multiply: W and V never reach memory.  For
-// layers with few filters and channels the stand-alone transforms and the multiply above are all
-// bound by the 4x expansion of E and D into W and V; here a workgroup of 8 wavefronts owns a
-// 64 x 64 block of all 16 M^(e) and walks its share of the error blocks 16 at a time:
-//   1. every thread transforms two horizontally adjacent 2 x 2 error blocks (filter r) and the two
-//      4 x 4 input tiles around them (channel r) from registers loaded during the previous step
-//      -- per row one aligned 16-byte load plus the two outer columns -- and writes the results
-//      to LDS as [e][r][b] (b contiguous, row stride 18: conflict-free 8-byte accesses);
-//   2. after a barrier the raw data of the next 16 blocks is requested, then each wavefront
-//      multiplies: 8 of the 16 components x one 32 x 32 quarter of the block, 64 MFMAs, operands
-//      read as in wgrad_gemm_kernel (one 8-byte read feeds two MFMAs), the 8 accumulators
-//      interleaved so that consecutive MFMAs are independent.
-// Transform and multiply phases alternate rather than overlap; on this chip MFMA and ordinary
-// vector instructions do not overlap anyway, and the global loads (about 3 us of latency for this
-// access pattern: 64 planes x 128 bytes per step) are in flight during phase 2.  Loads are
-// unconditional from clamped (valid) addresses; what falls outside the image, past the last block
-// or past K / C is zeroed afterwards, so the loop has no branches and no divisions.
-// Needs W % 4 == 0 (block pairs never straddle a row; 16-byte loads) and tensors of fewer than
-// 2^31 elements (32-bit offsets).  Partial M per share as above.
-constexpr int WF_BK = 16, WF_LS = WF_BK + 2;
+// The same products with both transforms inside the multiply, on the bf16 matrix units (bf16x3.h): W and V never reach
+// memory.  A workgroup of 8 wavefronts, one per CU, owns a 64 x 64 block of all 16 M^(e) -- two components per wavefront,
+// 128 accumulators per lane -- and walks its share of the error blocks 8 at a time.  Per step
+//   transform: wavefronts 0 - 3 take two horizontally adjacent 2 x 2 error blocks of one filter per lane, wavefronts 4 - 7
+//     the two 4 x 4 input tiles around them of one channel, from registers requested a step ahead -- per row one aligned
+//     16-byte load plus, for tiles, one of four bytes -- and write the results to LDS as fp32 [e][row][b];
+//   multiply: a lane reads four blocks of a row (16 bytes), splits them into three parts once and uses them for 64 rows of
+//     the other operand.  A 32x32x16 instruction has two places per block for them: (l, h) with (h, l), (h, m) with
+//     (m, h), (h, m) with (h, m) are the six products, three instructions per tile and step.
+// Both phases use different LDS buffers (one barrier per step), and the two wavefronts of a SIMD take them in opposite
+// order (fused_split.hip).  The halves of a row of 8 blocks change places every four rows: reads of 16 bytes and writes of
+// 8 are free of bank conflicts.
+// Bound by vector instructions: split 350, transform 190 per SIMD and step, 2 400 cycles with the matrix instructions'
+// issue slots, where those need 1 536.  256 -> 256 channels at 56 x 56, N = 64: 1 264 us with fp32 matrix instructions,
+// 835 so (700 of them without the loads); 512 -> 512 at 28 x 28: 1 073 in separate stages, 804 so.
+// Loads are unconditional from clamped (valid) addresses; what falls outside the image, past the last block or past K / C
+// is zeroed afterwards, so the loop has no branches and no divisions.  Needs W % 4 == 0 (block pairs never straddle a
+// row; 16-byte loads) and tensors of fewer than 2^31 elements (32-bit offsets).  Partial M per share as above.
+constexpr int WF_BK = 8, WF_T = 512;
+constexpr int WF_OP = 16 * 64 * WF_BK;                       // floats of one operand of a step
+typedef unsigned uintx8_w __attribute__((ext_vector_type(8)));
 
-__global__ __launch_bounds__(512) void wgrad_fused_kernel(const float *__restrict__ D, const float *__restrict__ E,
-                                                          float *__restrict__ Mo, WgradGeo g, int tiles_k, int tiles_c,
-                                                          int slabs_per_share)
+__device__ __forceinline__ void wf_lds_barrier()             // orders LDS traffic only: loads stay in flight across it
 {
-    __shared__ float Ws[16 * 64 * WF_LS];
-    __shared__ float Vs[16 * 64 * WF_LS];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
 
-    int bid = blockIdx.x;
-    const int kt = bid % tiles_k;
-    bid /= tiles_k;
-    const int ct = bid % tiles_c;
-    const int z = bid / tiles_c;
-    const int tid = threadIdx.x;
-    const int r = tid >> 3, pl = tid & 7;        // row of the block (filter / channel), pair of blocks
-    const int k = kt * 64 + r, c = ct * 64 + r;
+// ERR: wavefronts 0 - 3 (error blocks, transform first), else 4 - 7 (input tiles, multiply first)
+template <bool ERR>
+__device__ __forceinline__ void wgrad_fused_body(const float *__restrict__ X, float *__restrict__ Mo, const WgradGeo &g, int kt,
+                                                 int ct, int z, int slabs_per_share, float *smem, int wave)
+{
+    const int tid = threadIdx.x & 255;
+    const int r = tid >> 2, pl = tid & 3;                    // row of the block (filter / channel), pair of blocks
+    const int rows = ERR ? g.K : g.C, row = (ERR ? kt : ct) * 64 + r, rowc = min(row, rows - 1);
     const int slab_lo = z * slabs_per_share;
     const int slab_hi = min(slab_lo + slabs_per_share, (g.Pb + WF_BK - 1) / WF_BK);
 
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int st = wave & 3, ch = wave >> 2;
-    const int wm = st >> 1, wn = st & 1;
-    const int li = lane & 31, lh = lane >> 5;
-
-    floatx16_w acc[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-#pragma unroll
-        for (int q = 0; q < 16; ++q) acc[e][q] = 0.0f;
-
     // position of this thread's pair of blocks (b, b + 1; b even, so is by)
-    const int kc = min(k, g.K - 1), cc = min(c, g.C - 1);
     int b_cur = slab_lo * WF_BK + 2 * pl;
     int by, bx, im;
     {
@@ -306,29 +296,35 @@ __global__ __launch_bounds__(512) void wgrad_fused_kernel(const float *__restric
         bx = t2 % g.Bh;
         im = t2 / g.Bh;
     }
-    floatx4_w er[2], dm[4];    // error rows 2bx, 2bx+1 and input rows 2bx-1 .. 2bx+2, columns 2by .. 2by+3
-    float dl[4], dr[4];        // input columns 2by-1 and 2by+4
-    bool okb, ok1, okl, okr, okx[4];
+    // Every other share sums the products of the negated error and stores the negative of what it gets.  Adding a small
+    // product to a large sum, the instruction rounds down rather than to nearest: on average 3e-8 of a sum over 1 568
+    // blocks, little by itself, but the same way in every share and component (64 -> 64 channels at 224 x 224, N = 64, 512
+    // shares: error against float64 5.6e-6 without this, with it 1.0e-6; fp32 matrix instructions 1.2e-6).
+    const float sign = z % 2 ? -1.0f : 1.0f;
+    constexpr int NR = ERR ? 2 : 4;
+    floatx4_w xm[NR];          // error rows 2bx, 2bx+1 or input rows 2bx-1 .. 2bx+2, columns 2by .. 2by+3
+    // The outer input columns 2by-1 and 2by+4 are the neighbouring pairs' (DPP); of the four lanes that share a row the first
+    // lacks its left and the last its right neighbour and fetch those (the others something harmless).
+    float xe[NR];
+    unsigned okx;              // row p is inside the image, and so is the block
+    bool okl, okr;
     auto load_raw = [&]() {
-        okb = b_cur < g.Pb;
-        ok1 = 2 * bx + 1 < g.H;
+        const bool okb = b_cur < g.Pb && row < rows;
+        okx = 0;
         okl = by > 0;
         okr = by + 2 < g.Bw;
-        const unsigned eo = (((unsigned)im * g.K + kc) * g.H + 2 * bx) * g.W + 2 * by;
-        er[0] = *reinterpret_cast<const floatx4_w *>(E + eo);
-        er[1] = *reinterpret_cast<const floatx4_w *>(E + eo + (ok1 ? g.W : 0));
-        const unsigned dbase = ((unsigned)im * g.C + cc) * g.H * g.W + 2 * by;
+        const unsigned base = ((unsigned)im * rows + rowc) * g.H * g.W + 2 * by;
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            const int x = 2 * bx - 1 + p;
-            okx[p] = x >= 0 && x < g.H;
-            const float *row = D + dbase + (unsigned)min(max(x, 0), g.H - 1) * g.W;
-            dm[p] = *reinterpret_cast<const floatx4_w *>(row);
-            dl[p] = *(row - (okl ? 1 : 0));
-            dr[p] = *(row + (okr ? 4 : 3));
+        for (int p = 0; p < NR; ++p) {
+            const int x = 2 * bx + p - (ERR ? 0 : 1);
+            okx |= okb && x >= 0 && x < g.H ? 1u << p : 0u;
+            const float *src = X + base + (unsigned)min(max(x, 0), g.H - 1) * g.W;
+            xm[p] = *reinterpret_cast<const floatx4_w *>(src);
+            if constexpr (!ERR) {
+                xe[p] = *(src + (pl == 0 ? (okl ? -1 : 0) : (okr ? 4 : 3)));
+            }
         }
-    };
-    auto advance = [&]() {
+        // the pair of the next step
         b_cur += WF_BK;
         if (b_cur < g.Pb) {          // past the end the position stays on the last valid pair
             by += WF_BK;
@@ -341,94 +337,179 @@ __global__ __launch_bounds__(512) void wgrad_fused_kernel(const float *__restric
             }
         }
     };
-    auto transform_to_lds = [&]() {
-        const bool ke = okb && k < g.K, kd = okb && c < g.C;
+    float *const t_dst = smem + (ERR ? 0 : WF_OP) + r * WF_BK + (((pl >> 1) ^ ((r >> 2) & 1)) << 2) + 2 * (pl & 1);
+    auto transform = [&](int buf) {
         float t[4][4], o[4], wa[16], wb[16];
-        // w = G e G^T of the two error blocks
+        if constexpr (ERR) {
+            // w = G e G^T of the two error blocks
 #pragma unroll
-        for (int blk = 0; blk < 2; ++blk) {
-            float *dst = blk ? wb : wa;
+            for (int blk = 0; blk < 2; ++blk) {
+                float *dst = blk ? wb : wa;
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const float col[2] = {ke ? er[0][2 * blk + q] : 0.0f, (ke && ok1) ? er[1][2 * blk + q] : 0.0f};
-                g32_mul(col, o);
+                for (int q = 0; q < 2; ++q) {
+                    const float col[2] = {okx & 1u ? sign * xm[0][2 * blk + q] : 0.0f, okx & 2u ? sign * xm[1][2 * blk + q] : 0.0f};
+                    g32_mul(col, o);
 #pragma unroll
-                for (int p = 0; p < 4; ++p) t[p][q] = o[p];
+                    for (int p = 0; p < 4; ++p) t[p][q] = o[p];
+                }
+#pragma unroll
+                for (int p = 0; p < 4; ++p) g32_mul(t[p], dst + 4 * p);
+            }
+        } else {
+            // v = B^T d B of the two input tiles: columns 2by-1 .. 2by+2 and 2by+1 .. 2by+4
+            float d[4][6];
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                const bool v = okx & (1u << p);
+                const int pp = p < NR ? p : 0;
+                const float x0 = xm[pp][0], x3 = xm[pp][3];
+                const float from_l = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x3), 0x111, 0xf, 0xf, true));
+                const float from_r = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x0), 0x101, 0xf, 0xf, true));
+                d[p][0] = v && okl ? (pl == 0 ? xe[pp] : from_l) : 0.0f;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) d[p][1 + q] = v ? xm[pp][q] : 0.0f;
+                d[p][5] = v && okr ? (pl == 3 ? xe[pp] : from_r) : 0.0f;
+            }
+            // (the first pass serves both tiles: they share two columns)
+            float c6[6][4];
+#pragma unroll
+            for (int q = 0; q < 6; ++q) {
+                const float col[4] = {d[0][q], d[1][q], d[2][q], d[3][q]};
+                bt32_mul(col, c6[q]);
             }
 #pragma unroll
-            for (int p = 0; p < 4; ++p) g32_mul(t[p], dst + 4 * p);
+            for (int p = 0; p < 4; ++p) {
+                const float ta[4] = {c6[0][p], c6[1][p], c6[2][p], c6[3][p]}, tb[4] = {c6[2][p], c6[3][p], c6[4][p], c6[5][p]};
+                bt32_mul(ta, wa + 4 * p);
+                bt32_mul(tb, wb + 4 * p);
+            }
         }
 #pragma unroll
         for (int e = 0; e < 16; ++e)
-            *reinterpret_cast<floatx2_w *>(&Ws[(e * 64 + r) * WF_LS + 2 * pl]) = floatx2_w{wa[e], wb[e]};
-        // v = B^T d B of the two input tiles: columns 2by-1 .. 2by+2 and 2by+1 .. 2by+4
-        float d[4][6];
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            const bool v = kd && okx[p];
-            d[p][0] = (v && okl) ? dl[p] : 0.0f;
-            d[p][1] = v ? dm[p][0] : 0.0f;
-            d[p][2] = v ? dm[p][1] : 0.0f;
-            d[p][3] = v ? dm[p][2] : 0.0f;
-            d[p][4] = v ? dm[p][3] : 0.0f;
-            d[p][5] = (v && okr) ? dr[p] : 0.0f;
-        }
-#pragma unroll
-        for (int blk = 0; blk < 2; ++blk) {
-            float *dst = blk ? wb : wa;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float col[4] = {d[0][2 * blk + q], d[1][2 * blk + q], d[2][2 * blk + q], d[3][2 * blk + q]};
-                bt32_mul(col, o);
-#pragma unroll
-                for (int p = 0; p < 4; ++p) t[p][q] = o[p];
-            }
-#pragma unroll
-            for (int p = 0; p < 4; ++p) bt32_mul(t[p], dst + 4 * p);
-        }
-#pragma unroll
-        for (int e = 0; e < 16; ++e)
-            *reinterpret_cast<floatx2_w *>(&Vs[(e * 64 + r) * WF_LS + 2 * pl]) = floatx2_w{wa[e], wb[e]};
-    };
-    const int a_off = (wm * 32 + li) * WF_LS + 2 * lh, b_off = (wn * 32 + li) * WF_LS + 2 * lh;
-    auto multiply = [&]() {
-#pragma unroll
-        for (int t = 0; t < WF_BK / 4; ++t) {
-            floatx2_w a[8], b[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int eo = (ch * 8 + e) * 64 * WF_LS;
-                a[e] = *reinterpret_cast<const floatx2_w *>(&Ws[eo + a_off + 4 * t]);
-                b[e] = *reinterpret_cast<const floatx2_w *>(&Vs[eo + b_off + 4 * t]);
-            }
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    acc[e] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e][h], b[e][h], acc[e], 0, 0, 0);
-        }
+            *reinterpret_cast<floatx2_w *>(t_dst + buf * (2 * WF_OP) + e * (64 * WF_BK)) = floatx2_w{wa[e], wb[e]};
     };
 
-    load_raw();
-    for (int slab = slab_lo; slab < slab_hi; ++slab) {
-        transform_to_lds();
-        __syncthreads();
-        advance();
-        load_raw();          // after the last slab this re-reads a valid position and is discarded
-        multiply();
-        __syncthreads();
+    const int lane = tid & 63, li = lane & 31, lh = lane >> 5;
+    floatx16_w acc[2][2][2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int q = 0; q < 16; ++q) acc[e][i][j][q] = 0.0f;
+    // operand o (0, 1: 32 filters each; 2, 3: 32 channels) of component e: four blocks of row li
+    const int m_off = 2 * wave * (64 * WF_BK) + li * WF_BK + ((lh ^ ((li >> 2) & 1)) << 2);
+    floatx4_w raw[4];
+    uintx8_w op[2][4];         // filters: parts l h m; channels: h m h l (two words each)
+    auto read = [&](int e, int buf) {
+#pragma unroll
+        for (int o = 0; o < 4; ++o)
+            raw[o] = *reinterpret_cast<const floatx4_w *>(smem + m_off + buf * (2 * WF_OP) + (o / 2) * WF_OP + e * (64 * WF_BK) +
+                                                          (o % 2) * (32 * WF_BK));
+    };
+    // the split in 24 pieces of one to five vector instructions: operand n / 6, pair n / 3 % 2, part n % 3
+    auto piece = [&](int e, int n) {
+        const int o = n / 6, i = n / 3 % 2, q = n % 3;
+        float x = raw[o][2 * i], y = raw[o][2 * i + 1];
+        const unsigned w = bf16_pack(x, y);
+        if (o < 2) {
+            op[e][o][(q == 0 ? 2 : q == 1 ? 4 : 0) + i] = w;
+        } else {
+            op[e][o][(q == 0 ? 0 : q == 1 ? 2 : 6) + i] = w;
+            if (q == 0) op[e][o][4 + i] = w;
+        }
+        if (q < 2) {
+            raw[o][2 * i] = x - __builtin_bit_cast(float, w << 16);
+            raw[o][2 * i + 1] = y - __builtin_bit_cast(float, w & 0xffff0000u);
+        }
+    };
+    auto mma = [&](int e, int n) {         // instruction n of 12: product n / 4, tile n % 4
+        const int i = n % 4 / 2, j = n % 2, q = n / 4;
+        const uintx8_w a = op[e][i], b = op[e][2 + j];
+        const uintx4_b av = q == 0 ? __builtin_shufflevector(a, a, 0, 1, 2, 3) : __builtin_shufflevector(a, a, 2, 3, 4, 5);
+        const uintx4_b bv = q == 0 ? __builtin_shufflevector(b, b, 4, 5, 6, 7)
+                          : q == 1 ? __builtin_shufflevector(b, b, 2, 3, 4, 5) : __builtin_shufflevector(b, b, 0, 1, 2, 3);
+        acc[e][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av), __builtin_bit_cast(bf16x8, bv),
+                                                               acc[e][i][j], 0, 0, 0);
+    };
+    auto multiply = [&](int buf) {
+        read(0, buf);
+#pragma unroll
+        for (int n = 0; n < 24; ++n) piece(0, n);
+        read(1, buf);
+#pragma unroll
+        for (int n = 0; n < 12; ++n) {
+            __builtin_amdgcn_sched_barrier(0);
+            mma(0, n);
+#pragma unroll
+            for (int k = 0; k < 24; ++k)
+                if (n > 0 && k * 11 / 24 == n - 1) piece(1, k);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int n = 0; n < 12; ++n) mma(1, n);
+    };
+
+    if (slab_lo < slab_hi) {
+        load_raw();
+        transform(0);
+        load_raw();
+        wf_lds_barrier();
+        int slab = slab_lo;
+        do {
+            const int buf = (slab - slab_lo) & 1;
+            const bool more = slab + 1 < slab_hi;
+            if constexpr (!ERR) {
+                __builtin_amdgcn_s_setprio(2);
+                multiply(buf);
+                __builtin_amdgcn_s_setprio(0);
+            }
+            if (more) transform(buf ^ 1);
+            load_raw();                    // (past the share's end: a valid position, read and discarded)
+            if constexpr (ERR) {
+                __builtin_amdgcn_s_setprio(2);
+                multiply(buf);
+                __builtin_amdgcn_s_setprio(0);
+            }
+            wf_lds_barrier();
+        } while (++slab < slab_hi);
     }
 
     // a share past the end of the blocks still writes its (zero) partial M
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const int rt = kt * 64 + wm * 32, ctile = ct * 64 + wn * 32;
-        if (rt < g.Kp && ctile < g.Cq) {
-            float *dst = Mo + (((size_t)z * 16 + ch * 8 + e) * g.Kp + rt + 4 * lh) * g.Cq + ctile + li;
+    for (int e = 0; e < 2; ++e)
 #pragma unroll
-            for (int q = 0; q < 16; ++q) dst[(size_t)(8 * (q / 4) + (q % 4)) * g.Cq] = acc[e][q];
-        }
-    }
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int rt = kt * 64 + i * 32, ctile = ct * 64 + j * 32;
+                if (rt < g.Kp && ctile < g.Cq) {
+                    float *dst = Mo + (((size_t)z * 16 + 2 * wave + e) * g.Kp + rt + 4 * lh) * g.Cq + ctile + li;
+#pragma unroll
+                    for (int q = 0; q < 16; ++q) dst[(size_t)(8 * (q / 4) + (q % 4)) * g.Cq] = sign * acc[e][i][j][q];
+                }
+            }
+}
+
+__global__ __launch_bounds__(WF_T, 2) void wgrad_fused_kernel(const float *__restrict__ D, const float *__restrict__ E,
+                                                              float *__restrict__ Mo, WgradGeo g, int tiles_k, int tiles_c,
+                                                              int slabs_per_share)
+{
+    __shared__ __attribute__((aligned(16))) float smem[2 * 2 * WF_OP];      // [buffer][operand][e][row][b]
+    // workgroups go to the 8 XCDs in turn: the blocks of M of one share, which read the same data, to one XCD's L2
+    const int per = gridDim.x / 8;
+    int bid = blockIdx.x < per * 8 ? (blockIdx.x % 8) * per + blockIdx.x / 8 : blockIdx.x;
+    const int kt = bid % tiles_k;
+    bid /= tiles_k;
+    const int ct = bid % tiles_c;
+    const int z = bid / tiles_c;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (wave < 4)
+        wgrad_fused_body<true>(E, Mo, g, kt, ct, z, slabs_per_share, smem, wave);
+    else
+        wgrad_fused_body<false>(D, Mo, g, kt, ct, z, slabs_per_share, smem, wave);
 }
 
 // First level of the sum over shares when there are many of them: out[zg][i] = sum of in[z][i] over
@@ -618,25 +699,25 @@ static void wgrad_shape(const WgradGeo &g, int *bm, int *bn, int *shares, int *n
     *shares = (nk + *nk_split - 1) / *nk_split;
 }
 
-// The fused kernel is chosen where the stand-alone transforms dominate: few filters and channels
-// (every 64 x 64 block of M repeats both transforms, so their cost grows with K * C).
+// Where the one-kernel form applies: block pairs in 16-byte loads, 32-bit offsets.
 static bool wgrad_fused_ok(const WgradGeo &g)
 {
     if (g.W % 4 != 0) return false;
-    if ((long long)g.N * (g.K > g.C ? g.K : g.C) * g.H * g.W >= (1LL << 31)) return false;   // 32-bit offsets
-    return g.K <= 256 && g.C <= 256;   // measured at N=64: faster up to 256 x 256, slower at 512 x 512
+    return (long long)g.N * (g.K > g.C ? g.K : g.C) * g.H * g.W < (1LL << 31);
 }
 
-static void wgrad_fused_shape(const WgradGeo &g, int *tiles_k, int *tiles_c, int *shares, int *slabs_per_share)
+// `workgroups`: 512, two rounds of one per CU (or 256 where the workspace holds no more partial M)
+static void wgrad_fused_shape(const WgradGeo &g, int workgroups, int *tiles_k, int *tiles_c, int *shares, int *slabs_per_share)
 {
     *tiles_k = (g.Kp + 63) / 64;
     *tiles_c = (g.Cq + 63) / 64;
-    const int slabs = (g.Pb + WF_BK - 1) / WF_BK;
-    int want = 512 / (*tiles_k * *tiles_c);   // one workgroup fits a CU at a time: two rounds of 256
-    if (want > slabs / 4) want = slabs / 4;   // at least 4 slabs per share
+    const int slabs = (g.Pb + 15) / 16;       // (shares are whole numbers of 16 blocks)
+    int want = workgroups / (*tiles_k * *tiles_c);
+    if (want > slabs / 4) want = slabs / 4;   // at least 64 blocks per share
     if (want < 1) want = 1;
-    *slabs_per_share = (slabs + want - 1) / want;
-    *shares = (slabs + *slabs_per_share - 1) / *slabs_per_share;
+    const int per_share = (slabs + want - 1) / want;
+    *shares = (slabs + per_share - 1) / per_share;
+    *slabs_per_share = per_share * (16 / WF_BK);
 }
 
 bool wgrad_supported(long long N, long long C, long long H, long long W, long long K)
@@ -645,21 +726,29 @@ bool wgrad_supported(long long N, long long C, long long H, long long W, long lo
     return Pb < (1LL << 30) && C <= 65000 && K <= 65000;
 }
 
+static size_t wgrad_align(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// Partial M of the one-kernel form and, with many shares, the first level of their sum.
+static size_t wgrad_fused_bytes(const WgradGeo &g, int shares)
+{
+    return wgrad_align((size_t)shares * 16 * g.Kp * g.Cq * 4) + wgrad_pre_reduce_bytes((size_t)16 * g.Kp * g.Cq, shares);
+}
+
+// Room for the one-kernel form up to 256 filters and channels, beyond that for W, V and M of the separate stages, which
+// is more than the one-kernel form takes unless there are few blocks.
 size_t wgrad_workspace_bytes(int N, int C, int H, int W, int K)
 {
     if (wgrad_direct_ok(C, W))
-        return (((size_t)N * WD_RS * K * C * 9 * 4 + 255) & ~(size_t)255) + wgrad_pre_reduce_bytes((size_t)K * C * 9, N * WD_RS);
+        return wgrad_align((size_t)N * WD_RS * K * C * 9 * 4) + wgrad_pre_reduce_bytes((size_t)K * C * 9, N * WD_RS);
     const WgradGeo g = make_wgeo(N, C, H, W, K);
     int bm, bn, shares, nk_split;
-    auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
-    if (wgrad_fused_ok(g)) {
+    if (wgrad_fused_ok(g) && g.K <= 256 && g.C <= 256) {
         int tk, tc, sps;
-        wgrad_fused_shape(g, &tk, &tc, &shares, &sps);
-        return al((size_t)shares * 16 * g.Kp * g.Cq * 4) + wgrad_pre_reduce_bytes((size_t)16 * g.Kp * g.Cq, shares);
+        wgrad_fused_shape(g, 512, &tk, &tc, &shares, &sps);
+        return wgrad_fused_bytes(g, shares);
     }
     wgrad_shape(g, &bm, &bn, &shares, &nk_split);
-    return al((size_t)16 * g.Kp * g.Pbp * 4) + al((size_t)16 * g.Cq * g.Pbp * 4) + al((size_t)shares * 16 * g.Kp * g.Cq * 4) +
-           wgrad_pre_reduce_bytes((size_t)16 * g.Kp * g.Cq, shares);
+    return wgrad_align((size_t)16 * g.Kp * g.Pbp * 4) + wgrad_align((size_t)16 * g.Cq * g.Pbp * 4) + wgrad_fused_bytes(g, shares);
 }
 
 hipError_t launch_wgrad(int N, int C, int H, int W, int K, const float *D, const float *E, float *dG, void *workspace,
@@ -679,19 +768,22 @@ hipError_t launch_wgrad(int N, int C, int H, int W, int K, const float *D, const
         return hipGetLastError();
     }
     const WgradGeo g = make_wgeo(N, C, H, W, K);
-    int bm, bn, shares, nk_split;
-    if (wgrad_fused_ok(g)) {
-        int tk, tc, sps;
-        wgrad_fused_shape(g, &tk, &tc, &shares, &sps);
+    int bm, bn, shares = 0, nk_split, tk = 0, tc = 0, sps = 0;
+    const size_t room = wgrad_workspace_bytes(N, C, H, W, K);
+    for (int workgroups = 512; workgroups >= 256 && shares == 0 && wgrad_fused_ok(g); workgroups /= 2) {
+        wgrad_fused_shape(g, workgroups, &tk, &tc, &shares, &sps);
+        if (wgrad_fused_bytes(g, shares) > room) shares = 0;
+    }
+    if (shares > 0) {
         float *Mw = (float *)workspace;
         float *tmp = (float *)((char *)workspace + (((size_t)shares * 16 * g.Kp * g.Cq * 4 + 255) & ~(size_t)255));
-        wgrad_fused_kernel<<<dim3((unsigned)(tk * tc * shares)), dim3(512), 0, s>>>(D, E, Mw, g, tk, tc, sps);
+        wgrad_fused_kernel<<<dim3((unsigned)(tk * tc * shares)), dim3(WF_T), 0, s>>>(D, E, Mw, g, tk, tc, sps);
         const float *Ms = wgrad_pre_reduce(Mw, tmp, (size_t)16 * g.Kp * g.Cq, &shares, s);
         wgrad_output_kernel<<<dim3((C + 255) / 256, K), dim3(256), 0, s>>>(Ms, dG, g, shares);
         return hipGetLastError();
     }
     wgrad_shape(g, &bm, &bn, &shares, &nk_split);
-    auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
+    auto al = wgrad_align;
     char *ws = (char *)workspace;
     float *Wt = (float *)ws;
     float *Vt = (float *)(ws + al((size_t)16 * g.Kp * g.Pbp * 4));
