@@ -404,8 +404,12 @@ bool fused_preferred(const Geo &g)
 {
     if (!fused_eligible(g)) return false;
     const long long blocks = (long long)((g.P + FP - 1) / FP) * ((g.K + FK - 1) / FK);
-    if (g.dt == WINO_F16)   // same crossover as in fp32 (N = 32: 128 -> 256 channels 0.139 vs 0.155 ms, 256 -> 256 0.249 vs 0.197)
+    if (g.dt == WINO_F16) {
+        // 256 -> 256 channels at 56 x 56: N = 32 (784 items of fused_split.hip) 158 against 195 us, N = 16 (392 items) 88
+        // against 87; 256 -> 512 at 28 x 28, N = 32: 95 against 80
+        if (fused_split_f16_eligible(g) && (long long)g.K * g.C <= 130LL * (g.K + g.C) && fused_split_items(g) >= 512) return true;
         return (long long)g.K * g.C <= 100LL * (g.K + g.C) && (long long)((g.P + 31) / 32) * ((g.K + 63) / 64) >= 256;
+    }
     if (fused_split_eligible(g)) {
         // One kernel on the bf16 matrix units (fused_split.hip) against the four stages: their multiply reaches 184
         // TFLOP/s and what passes through memory -- input and output once, V and M twice -- about 6.2 TB/s (36 products

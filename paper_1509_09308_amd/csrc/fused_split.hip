@@ -1,6 +1,7 @@
-// Loops 2-4 of Algorithm 1 (Lavin & Gray) in one kernel, fp32 F(4x4,3x3) and F(2x2,3x3), with the products on the
-// bf16 matrix units (bf16x3.h: every fp32 value in three exact parts, six products, fp32 sums).  For layers with more
-// than 32 filters and a workgroup's worth of work for most CUs; smaller launches take fused_wide.hip.
+// Loops 2-4 of Algorithm 1 (Lavin & Gray) in one kernel, F(4x4,3x3) and F(2x2,3x3), the products of fp32 values on the
+// bf16 matrix units (bf16x3.h: every value in three exact parts, six products, fp32 sums).  For layers with more than 32
+// filters and a workgroup's worth of work for half of the CUs at least; smaller launches take fused_wide.hip and
+// fused_f16.hip.
 //
 // Workgroup = 8 wavefronts, one per CU, owning 64 filters x 32 tiles x 36 components (F(2x2): 64 x 64 x 16), 144 (128)
 // accumulators per lane.  Per step of 16 channels:
@@ -20,6 +21,15 @@
 // tiles 800 vector instructions per SIMD (transform and split, 3200 cycles).  128 x 16 would double the first, 32 x 64
 // the second.
 //
+// What bounds it: 6 500 cycles per step (multiply and transform of either wavefront 2 500 - 2 700 each), 27 000 per item
+// around them (first taps, inverse transform, the stores of all CUs at once), at a clock that falls to 1.7 GHz under the
+// power of it.  256 -> 256 channels at 56 x 56, N = 64: 590 us in fused_wide.hip, 480 here.
+//
+// fp16 storage (F(4x4,3x3)): the same with one part per value -- U as the filter transform lays it down is in operand
+// order already, a tile's 16 channels are 32 bytes of LDS, a unit is one matrix instruction, and the filters of a whole
+// step are in flight.  The transform and the per-item part bound it: 64 -> 64 channels at 224 x 224, N = 32: 244 us in
+// fused_f16.hip, 195 here; 128 -> 128 at 112 x 112: 228, 168.
+//
 // Items and the shared last round as in fused_wide.hip.
 #include <type_traits>
 
@@ -32,6 +42,8 @@ namespace wino {
 typedef float floatx16_s __attribute__((ext_vector_type(16)));
 typedef float floatx4_s __attribute__((ext_vector_type(4)));
 typedef float floatx2_s __attribute__((ext_vector_type(2)));
+typedef _Float16 halfx4_s __attribute__((ext_vector_type(4)));
+typedef _Float16 halfx8_s __attribute__((ext_vector_type(8)));
 
 constexpr int FS_K = 64, FS_C = 16, FS_T = 512;                      // filters, channels per step, threads
 constexpr int fs_tiles(int m) { return m == 4 ? 32 : 64; }           // tiles per item
@@ -181,7 +193,7 @@ __device__ __forceinline__ void fs_lds_barrier()
 // does not depend on the path taken.  (The whole offset in a vector register: a 16-byte buffer store with a scalar
 // register as offset was seen to store what the next vector instruction wrote over its first data register -- four lanes
 // of sixteen, now and then -- and the compiler puts wait states between the two only where there is no such register.)
-template <int M>
+template <int M, typename TY>
 __device__ __forceinline__ void fs_store_rows(__amdgpu_buffer_rsrc_t dst, unsigned vo, unsigned so, unsigned row_bytes, bool ok,
                                               int rows, const float (&y)[M][M])
 {
@@ -189,9 +201,13 @@ __device__ __forceinline__ void fs_store_rows(__amdgpu_buffer_rsrc_t dst, unsign
 #pragma unroll
     for (int p = 0; p < M; ++p) {
         const unsigned o = ok && p < rows ? vo + (so + p * row_bytes) : FS_ROW_OOB;
-        if constexpr (M == 4)
+        if constexpr (M == 4 && sizeof(TY) == 4)
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uintx4_b, (floatx4_s{y[p][0], y[p][1], y[p][2], y[p][3]})),
                                                    dst, o, 0, 2);
+        else if constexpr (M == 4)
+            __builtin_amdgcn_raw_buffer_store_b64(
+                __builtin_bit_cast(uintx2_s, (halfx4_s{(_Float16)y[p][0], (_Float16)y[p][1], (_Float16)y[p][2], (_Float16)y[p][3]})),
+                dst, o, 0, 2);
         else
             __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uintx2_s, (floatx2_s{y[p][0], y[p][1]})), dst, o, 0, 2);
     }
@@ -208,19 +224,25 @@ __device__ __forceinline__ int fs_lane()
 // CPAD: the channel count is not a multiple of 16, so the last step holds channel slots past the last channel.
 // R: role of the wavefront, 0 or 1 (each role is straight-line code of its own from the first item to the last: the two
 // share no register at any join).
-template <int M, bool CPAD, int R>
-__device__ __forceinline__ void fused_split_body(const float *__restrict__ D, const char *__restrict__ Us, float *__restrict__ Y,
+// T: storage type of D and of the transformed filters and tiles, TY: of Y.
+template <int M, bool CPAD, typename T, typename TY, int R>
+__device__ __forceinline__ void fused_split_body(const T *__restrict__ D, const char *__restrict__ Us, TY *__restrict__ Y,
                                                  const Geo &g, int n_kb, int n_tb, int groups, float *__restrict__ part,
                                                  float *smem, int wave)
 {
     constexpr int A = M + 2, NE = A * A;
     constexpr int P = fs_tiles(M), TB = P / 32;                // tiles of the item, matrix-instruction columns of them
     constexpr int NU = NE / 4;                                 // units (component x 32 filters) of a wavefront
-    constexpr int NR = M == 4 ? 3 : 2;                         // units of filter operands in flight
+    constexpr bool F16 = sizeof(T) == 2;
+    constexpr int NP = F16 ? 1 : 3;                            // parts of a value
+    constexpr int NR = F16 ? NU : M == 4 ? 3 : 2;              // units of filter operands in flight
     constexpr int NPR = P * FS_C / FS_T;                       // (tile, channel) pairs of a thread
     constexpr int V_FLOATS = fs_v_floats(M);
     static_assert(NU % NR == 0 && 2 * NU * 2 == NE, "ring slots are the same in every step");
-    typedef float mid_t __attribute__((ext_vector_type(M)));   // the M middle columns of a tile row
+    static_assert(!F16 || M == 4, "fp16 storage: F(4x4,3x3) only");
+    typedef std::conditional_t<F16, halfx4_s, std::conditional_t<M == 4, floatx4_s, floatx2_s>> mid_t;   // the M middle columns of a tile row
+    constexpr unsigned SZ = sizeof(T);
+    typedef std::conditional_t<F16, _Float16, float> LT;       // a transformed value in LDS
     const int lane = fs_lane();
 
     const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8, slots = gridDim.x / 8;
@@ -228,7 +250,7 @@ __device__ __forceinline__ void fused_split_body(const float *__restrict__ D, co
     const int kb_per_group = n_kb / groups;
     int first, count;
     fs_list(xcd, groups, n_kb, n_tb, &first, &count);
-    const int nsteps_all = g.Cp / FS_C;
+    const int nsteps_all = (g.C + FS_C - 1) / FS_C;
     const FsRounds rounds = fs_rounds(count, slots, nsteps_all, part != nullptr);
     const int full = rounds.full, tail = rounds.tail, shares = rounds.shares;
     unsigned int *const tickets = reinterpret_cast<unsigned int *>(part);
@@ -279,9 +301,9 @@ __device__ __forceinline__ void fused_split_body(const float *__restrict__ D, co
         for (int p = 0; p < A; ++p) {
             const int x = x0 + p;
             const bool rok = tile_ok && x >= 0 && x < g.H;
-            vo_m[r][p] = rok ? (plane0 + (unsigned)(x * g.W + y0 + 1)) * 4u : FS_ROW_OOB;
+            vo_m[r][p] = rok ? (plane0 + (unsigned)(x * g.W + y0 + 1)) * SZ : FS_ROW_OOB;
         }
-        const unsigned adj_l = left_in[r] ? 0xfffffffcu /* -4 bytes */ : FS_COL_OOB, adj_r = right_in[r] ? 4u * M : FS_COL_OOB;
+        const unsigned adj_l = left_in[r] ? 0u - SZ : FS_COL_OOB, adj_r = right_in[r] ? SZ * M : FS_COL_OOB;
         int from_first = (int)FS_COL_OOB, from_last = (int)FS_COL_OOB;
         from_first = __builtin_amdgcn_update_dpp(from_first, (int)(vo_m[r][0] + adj_l), 0x111, 0xf, 0xf, false);   // row_shr:1
         from_first = __builtin_amdgcn_update_dpp(from_first, (int)(vo_m[r][1] + adj_l), 0x112, 0xf, 0xf, false);
@@ -300,17 +322,17 @@ __device__ __forceinline__ void fused_split_body(const float *__restrict__ D, co
         edge_off[r] = (tl >= 1 && tl <= A) ? (unsigned)from_first : (tl >= 8 && tl <= 7 + A) ? (unsigned)from_last : FS_COL_OOB;
     }
     };
-    const unsigned step_bytes = (unsigned)(FS_C * g.H * g.W) * 4u;
+    const unsigned step_bytes = (unsigned)(FS_C * g.H * g.W) * SZ;
     const size_t image_floats = (size_t)g.C * g.H * g.W;
     const int kb32 = g.Kp / 32;
     const __amdgpu_buffer_rsrc_t rsrc_u = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)Us, 0, (unsigned)((size_t)NE * nsteps_all * kb32 * FS_BLOCK_BYTES), 0x00020000);
+        (void *)Us, 0, (unsigned)(F16 ? (size_t)NE * g.Cp * g.Kp * 2 : (size_t)NE * nsteps_all * kb32 * FS_BLOCK_BYTES), 0x00020000);
 
     mid_t mid[NPR][A];
-    float ed[NPR];
+    std::conditional_t<F16, unsigned, float> ed[NPR];          // (fp16: the value in the low half)
     // `valid` false: nothing is fetched, the number of loads in flight stays the same (fused_wide.hip)
     auto load_taps = [&](int step, bool valid) {
-        const size_t left = ((size_t)g.N - img0) * image_floats * 4;
+        const size_t left = ((size_t)g.N - img0) * image_floats * SZ;
         const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
             (void *)(D + (size_t)img0 * image_floats), 0, (unsigned)(left < FS_MAX_BYTES ? left : FS_MAX_BYTES), 0x00020000);
         const unsigned so = valid ? (unsigned)step * step_bytes : 0u;
@@ -321,25 +343,35 @@ __device__ __forceinline__ void fused_split_body(const float *__restrict__ D, co
 #pragma unroll
             for (int p = 0; p < A; ++p) {
                 const unsigned om = (ch_ok ? vo_m[r][p] : FS_ROW_OOB) | off_mask;
-                if constexpr (M == 4)
+                if constexpr (M == 4 && !F16)
                     mid[r][p] = __builtin_bit_cast(mid_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc, om, so, 0));
                 else
                     mid[r][p] = __builtin_bit_cast(mid_t, __builtin_amdgcn_raw_buffer_load_b64(rsrc, om, so, 0));
             }
-            ed[r] = __builtin_bit_cast(float,
-                                       __builtin_amdgcn_raw_buffer_load_b32(rsrc, (ch_ok ? edge_off[r] : FS_ROW_OOB) | off_mask, so, 0));
+            const unsigned oe = (ch_ok ? edge_off[r] : FS_ROW_OOB) | off_mask;
+            if constexpr (F16)
+                ed[r] = __builtin_amdgcn_raw_buffer_load_b16(rsrc, oe, so, 0);
+            else
+                ed[r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, oe, so, 0));
         }
     };
     auto transform = [&](int buf) {
         const int l = fs_lane();                               // (tile + 32: the same permutation of channel groups)
-        float *const v_dst = smem + (wave & 1) * (16 * FS_C) + (l & 15) * FS_C + (((wave >> 1) ^ ((l >> 1) & 3)) << 2) + (l >> 4);
+        // fp32: groups of four channels permuted by tile; fp16: groups of eight
+        const int group = F16 ? ((wave >> 2) ^ ((l >> 2) & 1)) * 8 + (wave >> 1 & 1) * 4 : ((wave >> 1) ^ ((l >> 1) & 3)) << 2;
+        LT *const v_dst = reinterpret_cast<LT *>(smem) + (wave & 1) * (16 * FS_C) + (l & 15) * FS_C + group + (l >> 4);
 #pragma unroll
         for (int r = 0; r < NPR; ++r) {
             float t[A][A];
+            float edge_value;
+            if constexpr (F16)
+                edge_value = (float)__builtin_bit_cast(_Float16, (unsigned short)ed[r]);
+            else
+                edge_value = ed[r];
             auto row = [&](auto pc) {
                 constexpr int p = decltype(pc)::value;
-                const float c1 = mid[r][p][0], c4 = mid[r][p][M - 1];
-                const int e_bits = __builtin_bit_cast(int, ed[r]);
+                const float c1 = (float)mid[r][p][0], c4 = (float)mid[r][p][M - 1];
+                const int e_bits = __builtin_bit_cast(int, edge_value);
                 const int for_first = __builtin_amdgcn_mov_dpp(e_bits, 0x101 + p, 0xf, 0xf, true);   // row_shl:(1 + p)
                 const int for_last = __builtin_amdgcn_mov_dpp(e_bits, 0x117 - p, 0xf, 0xf, true);    // row_shr:(7 - p)
                 const int l_bits = __builtin_amdgcn_update_dpp(for_first, __builtin_bit_cast(int, c4), 0x111, 0xf, 0xf, false);
@@ -349,7 +381,7 @@ __device__ __forceinline__ void fused_split_body(const float *__restrict__ D, co
                 float d[A];
                 d[0] = lv, d[A - 1] = rv;
 #pragma unroll
-                for (int q = 0; q < M; ++q) d[1 + q] = mid[r][p][q];
+                for (int q = 0; q < M; ++q) d[1 + q] = (float)mid[r][p][q];
                 bt_mul<M>(d, t[p]);
             };
             row(std::integral_constant<int, 0>());
@@ -360,7 +392,7 @@ __device__ __forceinline__ void fused_split_body(const float *__restrict__ D, co
                 row(std::integral_constant<int, A - 2>());
                 row(std::integral_constant<int, A - 1>());
             }
-            float *dst = v_dst + buf * V_FLOATS + r * (32 * FS_C);
+            LT *dst = v_dst + buf * V_FLOATS + r * (32 * FS_C);
 #pragma unroll
             for (int q = 0; q < A; ++q) {
                 float col[A], o[A];
@@ -368,7 +400,7 @@ __device__ __forceinline__ void fused_split_body(const float *__restrict__ D, co
                 for (int p = 0; p < A; ++p) col[p] = t[p][q];
                 bt_mul<M>(col, o);
 #pragma unroll
-                for (int p = 0; p < A; ++p) dst[(p * A + q) * (FS_C * P)] = o[p];
+                for (int p = 0; p < A; ++p) dst[(p * A + q) * (FS_C * P)] = (LT)o[p];
             }
         }
     };
@@ -377,26 +409,29 @@ __device__ __forceinline__ void fused_split_body(const float *__restrict__ D, co
     const int simd = wave & 3;
     const int li = lane & 31, lh = lane >> 5;
     floatx16_s acc[NU][TB];
-    uintx4_b ua[NR][3];
-    const unsigned step_u = (unsigned)kb32 * FS_BLOCK_BYTES, comp_u = (unsigned)nsteps_all * step_u;
+    uintx4_b ua[NR][NP];
+    // fp32: blocks as filter_split_kernel lays them down; fp16: U[e][c / 8][k][8 channels], two rows of c / 8 per step
+    constexpr unsigned HALF_BYTES = F16 ? 512 : FS_BLOCK_BYTES;
+    const unsigned step_u = F16 ? (unsigned)g.Kp * 32u : (unsigned)kb32 * FS_BLOCK_BYTES;
+    const unsigned comp_u = F16 ? (unsigned)(g.Cp / 16) * step_u : (unsigned)nsteps_all * step_u;
     unsigned half_u, su;
-    unsigned uvo = (unsigned)lane * 16u;
+    unsigned uvo = F16 ? (unsigned)(lh * g.Kp + li) * 16u : (unsigned)lane * 16u;
     asm("" : "+v"(uvo));                       // (opaque: the parts' offsets then go into the instructions, not into registers)
     // channels 8 h .. 8 h + 3 of this lane's tile; the next four: ^ 4
-    const int b_off = simd * NU * (FS_C * P) + li * FS_C + (((2 * lh) ^ ((li >> 1) & 3)) << 2);
+    const int b_off = simd * NU * (FS_C * P) + li * FS_C + (F16 ? (lh ^ ((li >> 2) & 1)) << 3 : ((2 * lh) ^ ((li >> 1) & 3)) << 2);
 
     // The filter operands of a new item's first units.
     auto first_units = [&](bool valid) {
         // (where the item reaches past the last 32 filters, the second half repeats the first: rows that are never stored)
-        half_u = (unsigned)(min(k0 / 32 + 1, kb32 - 1) - k0 / 32) * FS_BLOCK_BYTES;
-        su = (unsigned)(simd * NU) * comp_u + (unsigned)step0 * step_u + (unsigned)(k0 / 32) * FS_BLOCK_BYTES;
+        half_u = (unsigned)(min(k0 / 32 + 1, kb32 - 1) - k0 / 32) * HALF_BYTES;
+        su = (unsigned)(simd * NU) * comp_u + (unsigned)step0 * step_u + (unsigned)(k0 / 32) * HALF_BYTES;
         __builtin_amdgcn_sched_barrier(0x38f);        // everything but memory requests may cross
 #pragma unroll
         for (int u = 0; u < NR; ++u) {
             const int n = R * NU + u;
             const unsigned so = su + (unsigned)(n / 2) * comp_u + (unsigned)(n % 2) * half_u;
 #pragma unroll
-            for (int q = 0; q < 3; ++q)
+            for (int q = 0; q < NP; ++q)
                 ua[u][q] = __builtin_bit_cast(uintx4_b, __builtin_amdgcn_raw_buffer_load_b128(
                                                             rsrc_u, (valid ? uvo : 0x80000000u) + q * 1024, so, 0));
         }
@@ -436,7 +471,27 @@ __device__ __forceinline__ void fused_split_body(const float *__restrict__ D, co
         };
         // The order of a wavefront's multiply phase is laid down: after each matrix instruction come some pieces of the
         // next component's split and, behind a unit, the requests that refill its operand registers, one at a time.
+        // fp16: an operand is what one 16-byte read gives, and a unit one matrix instruction.
+        auto multiply_f16 = [&](int buf, bool more) {
+            const unsigned uvo_next = more ? uvo : 0x80000000u;
+            const LT *vb = reinterpret_cast<const LT *>(smem) + b_off + buf * V_FLOATS + C0 * (FS_C * P);
+            uintx4_b b[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) b[c] = *reinterpret_cast<const uintx4_b *>(vb + c * (FS_C * P));
+#pragma unroll
+            for (int u = 0; u < NU; ++u) {
+                acc[u][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8_s, ua[u % NR][0]),
+                                                                   __builtin_bit_cast(halfx8_s, b[(N0 + u) / 2 - C0]), acc[u][0], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                request(u, 0, uvo_next, su + step_u);
+            }
+            su += step_u;
+        };
         auto multiply = [&](int buf, bool more) {
+            if constexpr (F16) {
+                multiply_f16(buf, more);
+                return;
+            } else {
             // with no next step the requests for it fetch nothing (an offset behind the buffer)
             const unsigned uvo_next = more ? uvo : 0x80000000u;
             if constexpr (R == 1) read(0, buf);
@@ -475,8 +530,9 @@ __device__ __forceinline__ void fused_split_body(const float *__restrict__ D, co
             }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int q = 0; q < 3; ++q) refill(NU - 1, q);
+            for (int q = 0; q < NP; ++q) refill(NU - 1, q);
             su += step_u;
+            }
         };
 #pragma unroll
         for (int u = 0; u < NU; ++u)
@@ -493,7 +549,7 @@ __device__ __forceinline__ void fused_split_body(const float *__restrict__ D, co
 #pragma unroll
             for (int u = 0; u < NR; ++u)
 #pragma unroll
-                for (int q = 0; q < 3; ++q) request(u, q, uvo, su);
+                for (int q = 0; q < NP; ++q) request(u, q, uvo, su);
             __builtin_amdgcn_sched_barrier(0x38f);
         }
         fs_lds_barrier();
@@ -508,7 +564,7 @@ __device__ __forceinline__ void fused_split_body(const float *__restrict__ D, co
                 __builtin_amdgcn_s_setprio(2);
                 multiply(buf, more);
                 __builtin_amdgcn_s_setprio(0);
-            } else {
+            } else if constexpr (!F16) {
                 read(0, buf);
             }
             if (more) transform(buf ^ 1);
@@ -548,11 +604,11 @@ __device__ __forceinline__ void fused_split_body(const float *__restrict__ D, co
         const int t2 = bb / g.Tw;
         const int tx = t2 % g.Th;
         rows = g.Ho - M * tx;
-        y_vo = (unsigned)((((t2 / g.Th - o_img0) * g.K + irow) * g.Ho + M * tx) * g.Wo + M * ty) * 4u;
+        y_vo = (unsigned)((((t2 / g.Th - o_img0) * g.K + irow) * g.Ho + M * tx) * g.Wo + M * ty) * (unsigned)sizeof(TY);
     }
-    const unsigned plane_bytes = (unsigned)(g.Ho * g.Wo) * 4u;
+    const unsigned plane_bytes = (unsigned)(g.Ho * g.Wo) * (unsigned)sizeof(TY);
     const size_t y_first = ((size_t)o_img0 * g.K + o_k0) * g.Ho * g.Wo;
-    const size_t y_left = ((size_t)g.N * g.K * g.Ho * g.Wo - y_first) * 4;
+    const size_t y_left = ((size_t)g.N * g.K * g.Ho * g.Wo - y_first) * sizeof(TY);
     const __amdgpu_buffer_rsrc_t rsrc_y =
         __builtin_amdgcn_make_buffer_rsrc((void *)(Y + y_first), 0, (unsigned)(y_left < 0x7fffffffu ? y_left : 0x7fffffffu), 0x00020000);
     float y[2 * RP][M][M];                     // piece n: filter rows n FS_T / P + irow
@@ -609,11 +665,11 @@ __device__ __forceinline__ void fused_split_body(const float *__restrict__ D, co
 #pragma unroll
     for (int u = 0; u < NR; ++u)
 #pragma unroll
-        for (int q = 0; q < 3; ++q) asm volatile("" : "+v"(ua[u][q]));
+        for (int q = 0; q < NP; ++q) asm volatile("" : "+v"(ua[u][q]));
     if (!o_shared) {
 #pragma unroll
         for (int n = 0; n < 2 * RP; ++n)
-            fs_store_rows<M>(rsrc_y, y_vo, (unsigned)(n * (FS_T / P)) * plane_bytes, (unsigned)g.Wo * 4u,
+            fs_store_rows<M, TY>(rsrc_y, y_vo, (unsigned)(n * (FS_T / P)) * plane_bytes, (unsigned)g.Wo * (unsigned)sizeof(TY),
                              out_ok && o_k0 + n * (FS_T / P) + irow < g.K, rows, y[n]);
     } else {
         // partial outputs of this share: [piece][pair j of outputs][thread] pairs of floats
@@ -659,7 +715,7 @@ __device__ __forceinline__ void fused_split_body(const float *__restrict__ D, co
                     ys[j / (M / 2)][2 * (j % (M / 2))] = y2[j][0];
                     ys[j / (M / 2)][2 * (j % (M / 2)) + 1] = y2[j][1];
                 }
-                fs_store_rows<M>(rsrc_y, y_vo, (unsigned)(f * (FS_T / P)) * plane_bytes, (unsigned)g.Wo * 4u,
+                fs_store_rows<M, TY>(rsrc_y, y_vo, (unsigned)(f * (FS_T / P)) * plane_bytes, (unsigned)g.Wo * (unsigned)sizeof(TY),
                                  out_ok && o_k0 + f * (FS_T / P) + irow < g.K, rows, ys);
             }
         }
@@ -667,17 +723,17 @@ __device__ __forceinline__ void fused_split_body(const float *__restrict__ D, co
     }   // items
 }
 
-template <int M, bool CPAD>
-__global__ __launch_bounds__(FS_T, 2) void fused_split_kernel(const float *__restrict__ D, const char *__restrict__ Us,
-                                                              float *__restrict__ Y, Geo g, int n_kb, int n_tb, int groups,
+template <int M, bool CPAD, typename T, typename TY>
+__global__ __launch_bounds__(FS_T, 2) void fused_split_kernel(const T *__restrict__ D, const char *__restrict__ Us,
+                                                              TY *__restrict__ Y, Geo g, int n_kb, int n_tb, int groups,
                                                               float *__restrict__ part)
 {
     __shared__ __attribute__((aligned(16))) float smem[2 * fs_v_floats(M)];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (wave < 4)
-        fused_split_body<M, CPAD, 0>(D, Us, Y, g, n_kb, n_tb, groups, part, smem, wave);
+        fused_split_body<M, CPAD, T, TY, 0>(D, Us, Y, g, n_kb, n_tb, groups, part, smem, wave);
     else
-        fused_split_body<M, CPAD, 1>(D, Us, Y, g, n_kb, n_tb, groups, part, smem, wave);
+        fused_split_body<M, CPAD, T, TY, 1>(D, Us, Y, g, n_kb, n_tb, groups, part, smem, wave);
 }
 
 static int fs_n_kb(const Geo &g) { return (g.Kp + FS_K - 1) / FS_K; }
@@ -688,7 +744,7 @@ static int fs_groups(const Geo &g, int n_kb)
 {
     int groups = 1;
     while (groups < 8 && n_kb % (2 * groups) == 0 &&
-           (unsigned long long)(n_kb / groups) * g.a2 * g.Cp * FS_K * 6 > (5ull << 19))
+           (unsigned long long)(n_kb / groups) * g.a2 * g.Cp * FS_K * (g.dt == WINO_F16 ? 2 : 6) > (5ull << 19))
         groups *= 2;
     return groups;
 }
@@ -741,20 +797,49 @@ double fused_split_us(const Geo &g)
     return worst + 8.0;
 }
 
+// Whether some XCD has a last round to share (the full grid: places in the workspace and counters are numbered by it).
+static bool fs_shares(const Geo &g, int groups)
+{
+    if (fused_split_items(g) < FS_GRID) return false;
+    for (int xcd = 0; xcd < 8; ++xcd) {
+        int first, count;
+        fs_list(xcd, groups, fs_n_kb(g), (int)fs_n_tb(g), &first, &count);
+        if (fs_rounds(count, FS_GRID / 8, (g.C + FS_C - 1) / FS_C, true).shares > 1) return true;
+    }
+    return false;
+}
+
+template <typename T, typename TY>
+static hipError_t fs_launch(const Geo &g, const T *D, const char *Us, TY *Y, int n_kb, int n_tb, int groups, float *part, hipStream_t s)
+{
+    // as many workgroups as stay resident, in multiples of the 8 XCDs
+    const int items = n_kb * n_tb;
+    const dim3 grid((unsigned)(items >= FS_GRID ? FS_GRID : (items + 7) / 8 * 8)), block(FS_T);
+    const bool cpad = g.C % FS_C != 0;
+    if constexpr (sizeof(T) == 4) {
+        if (g.m == 2) {
+            if (cpad)
+                fused_split_kernel<2, true, T, TY><<<grid, block, 0, s>>>(D, Us, Y, g, n_kb, n_tb, groups, part);
+            else
+                fused_split_kernel<2, false, T, TY><<<grid, block, 0, s>>>(D, Us, Y, g, n_kb, n_tb, groups, part);
+            return hipGetLastError();
+        }
+    }
+    if (cpad)
+        fused_split_kernel<4, true, T, TY><<<grid, block, 0, s>>>(D, Us, Y, g, n_kb, n_tb, groups, part);
+    else
+        fused_split_kernel<4, false, T, TY><<<grid, block, 0, s>>>(D, Us, Y, g, n_kb, n_tb, groups, part);
+    return hipGetLastError();
+}
+
 // Everything after the choice: `G` (untransformed; `bwd`: of the exchanged layer) or `U` given, workspace as a whole.
 hipError_t launch_fused_split(const Geo &g, const float *D, const float *G, const float *U, float *Y, void *workspace,
                               size_t workspace_bytes, bool bwd, hipStream_t s)
 {
     const int n_kb = fs_n_kb(g), n_tb = (int)fs_n_tb(g), kb32 = g.Kp / 32, n_s = g.Cp / 16;
-    const int items = n_kb * n_tb, groups = fs_groups(g, n_kb);
+    const int groups = fs_groups(g, n_kb);
     char *Us = (char *)workspace;
-    float *part = nullptr;
-    if (items >= FS_GRID && fs_part_offset(g) + fs_part_bytes(g) <= workspace_bytes)
-        for (int xcd = 0; xcd < 8; ++xcd) {
-            int first, count;
-            fs_list(xcd, groups, n_kb, n_tb, &first, &count);
-            if (fs_rounds(count, FS_GRID / 8, n_s, true).shares > 1) part = (float *)(Us + fs_part_offset(g));
-        }
+    float *part = fs_shares(g, groups) && fs_part_offset(g) + fs_part_bytes(g) <= workspace_bytes ? (float *)(Us + fs_part_offset(g)) : nullptr;
     unsigned *tickets = (unsigned *)part;
     const dim3 wave(64);
     if (U != nullptr)
@@ -769,18 +854,33 @@ hipError_t launch_fused_split(const Geo &g, const float *D, const float *G, cons
         filter_split_kernel<2, false><<<dim3(kb32 * n_s, 4), wave, 0, s>>>(G, Us, g.K, g.C, kb32, n_s, tickets);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // as many workgroups as stay resident, in multiples of the 8 XCDs
-    const unsigned grid = (unsigned)(items >= FS_GRID ? FS_GRID : (items + 7) / 8 * 8);
-    const bool cpad = g.C % FS_C != 0;
-    if (g.m == 4 && cpad)
-        fused_split_kernel<4, true><<<dim3(grid), dim3(FS_T), 0, s>>>(D, Us, Y, g, n_kb, n_tb, groups, part);
-    else if (g.m == 4)
-        fused_split_kernel<4, false><<<dim3(grid), dim3(FS_T), 0, s>>>(D, Us, Y, g, n_kb, n_tb, groups, part);
-    else if (cpad)
-        fused_split_kernel<2, true><<<dim3(grid), dim3(FS_T), 0, s>>>(D, Us, Y, g, n_kb, n_tb, groups, part);
-    else
-        fused_split_kernel<2, false><<<dim3(grid), dim3(FS_T), 0, s>>>(D, Us, Y, g, n_kb, n_tb, groups, part);
-    return hipGetLastError();
+    return fs_launch<float, float>(g, D, Us, Y, n_kb, n_tb, groups, part, s);
+}
+
+// ---- fp16 storage, F(4x4,3x3) -----------------------------------------------------------------------
+__global__ void fused_split_clear_kernel(unsigned *tickets) { tickets[threadIdx.x] = 0u; }
+
+bool fused_split_f16_eligible(const Geo &g)
+{
+    if (!fused_f16_eligible(g) || g.Kp < FS_K) return false;
+    const unsigned long long tiles = (unsigned long long)g.Th * g.Tw;
+    const unsigned long long span = (fs_tiles(4) + tiles - 2) / tiles + 1;
+    if (span * g.C * g.H * g.W * 2ull + 65536 >= FS_MAX_BYTES) return false;
+    if (((span * g.K) + FS_K) * g.Ho * g.Wo * 4ull >= FS_MAX_BYTES) return false;
+    if ((size_t)g.a2 * g.Cp * g.Kp * 2 >= (1ull << 31)) return false;
+    const long long items = fused_split_items(g);
+    return items <= 0x7fffffffLL && items >= 128;
+}
+
+// `U` as filter_transform_f16 lays it down; `part`: the workspace behind it.
+hipError_t launch_fused_split_f16(const Geo &g, const void *D, const void *U, void *Y, int y_dt, void *part, size_t part_bytes,
+                                  hipStream_t s)
+{
+    const int n_kb = fs_n_kb(g), n_tb = (int)fs_n_tb(g), groups = fs_groups(g, n_kb);
+    float *const p = fs_shares(g, groups) && fs_part_bytes(g) <= part_bytes ? (float *)part : nullptr;
+    if (p != nullptr) fused_split_clear_kernel<<<dim3(1), dim3(FS_TICKETS), 0, s>>>((unsigned *)p);
+    return y_dt == WINO_F16 ? fs_launch<__half, __half>(g, (const __half *)D, (const char *)U, (__half *)Y, n_kb, n_tb, groups, p, s)
+                            : fs_launch<__half, float>(g, (const __half *)D, (const char *)U, (float *)Y, n_kb, n_tb, groups, p, s);
 }
 
 }  // namespace wino

@@ -334,7 +334,9 @@ static int run_layer(const Geo &g, int y_dt, const void *D, const void *G, const
     if (flags == WINO_FLAG_FUSED) {
         // fp32 with pad 1 and W % 4 == 0: the designs with two workgroups per CU (64 filters per workgroup where
         // there are that many); otherwise the general one
-        if (wide)
+        if (g.dt == WINO_F16 && fused_split_f16_eligible(g))
+            e = launch_fused_split_f16(g, D, U, Y, y_dt, Vw, vb + mb, s);
+        else if (wide)
             e = launch_fused_wide(g, (const float *)D, (const float *)U, (float *)Y, Vw, vb + mb, counters != nullptr, s);
         else
             e = fused_lds_eligible(g) ? launch_fused_lds(g, (const float *)D, (const float *)U, (float *)Y, s)

@@ -59,6 +59,9 @@ long long fused_split_items(const Geo &g);
 double fused_split_us(const Geo &g);
 hipError_t launch_fused_split(const Geo &g, const float *D, const float *G, const float *U, float *Y, void *workspace,
                               size_t workspace_bytes, bool bwd, hipStream_t s);
+bool fused_split_f16_eligible(const Geo &g);
+hipError_t launch_fused_split_f16(const Geo &g, const void *D, const void *U, void *Y, int y_dt, void *part, size_t part_bytes,
+                                  hipStream_t s);
 hipError_t launch_fused_f16(const Geo &g, const void *D, const void *U, void *Y, int y_dt, hipStream_t s);
 bool fused_f2_eligible(const Geo &g);
 hipError_t launch_fused_f2(const Geo &g, const float *D, const float *G, float *Y, void *workspace,

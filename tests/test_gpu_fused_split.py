@@ -50,3 +50,25 @@ def test_split_layer_input_gradient():
     for m in (2, 4):
         dD = w.wino_conv2d_bwd_data(to_gpu(E), G=to_gpu(G), pad=1, m=m, flags=w.FLAG_FUSED).cpu().numpy()
         check_close(dD, direct.conv2d_bwd_data(E, G, H, W, pad=1), TOL[("f32", m)], "input gradient F(%d)" % m, m)
+
+
+@pytest.mark.parametrize("shape", [(9, 17, 28, 60, 70), (33, 16, 28, 20, 256), (5, 40, 66, 128, 96), (17, 128, 28, 44, 513),
+                                   (4, 256, 48, 96, 520)])
+@pytest.mark.parametrize("given", ["G", "U"])
+@pytest.mark.parametrize("y", ["f32", "f16"])
+def test_split_layer_f16(shape, given, y):
+    torch, w = require_gpu()
+    N, C, H, W, K = shape
+    D, G = synth.make_layer(N, C, H, W, K, seed=sum(shape), dtype=np.float16)
+    d, g = to_gpu(D), to_gpu(G)
+    ws = torch.full((w.wino_workspace_bytes(N, C, H, W, K, 1, 4, w.WINO_F16) // 4 + 1,), float("nan"), device="cuda").view(torch.uint8)
+    kw = dict(G=g) if given == "G" else dict(U=w.wino_filter_transform(g, 4), K=K)
+    Y = torch.full((N, K, H, W), float("nan"), device="cuda", dtype=torch.float32 if y == "f32" else torch.float16)
+    w.wino_conv2d_fwd_ex(d, pad=1, m=4, flags=w.FLAG_FUSED, workspace=ws, Y=Y, **kw)
+    Y2 = w.wino_conv2d_fwd_ex(d, pad=1, m=4, flags=w.FLAG_FUSED, workspace=ws, y_dtype=Y.dtype, **kw)
+    assert torch.equal(Y, Y2)
+    pts = synth.sample_points((N, K, H, W), 3000, seed=2, edge=4)
+    got = Y.float().cpu().numpy()
+    assert np.isfinite(got).all()
+    ref = direct.conv2d_points(D.astype(np.float32), G.astype(np.float32), pts, pad=1)
+    check_close(got[tuple(pts.T)], ref, TOL[("f16", 4)], "%s %s" % (shape, given), 4)
