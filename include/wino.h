@@ -184,7 +184,7 @@ int wino_conv2d_bwd_filter(int N, int C, int H, int W, int K, int pad, int dt, c
  * wino_status_t (e.g. -WINO_EUNSUPPORTED) if the call would be rejected. */
 int wino_conv2d_variant(int N, int C, int H, int W, int K, int pad, int m, int dt, int y_dt, unsigned flags);
 /* Host-side query: how the one-kernel fp32 F(4x4,3x3) layer (64 filters x 16 tiles per item, Section 6's
- * fusion of the transforms into the multiply; layers with half a CU's worth of 32-tile items and more run those instead)
+ * fusion of the transforms into the multiply; layers of 128 items of 32 tiles and more -- 64 tiles for m = 2 -- run those)
  * deals its items to the GPU's 8 XCDs when the workspace has room for
  * partial outputs (m = 4 or 2).  out[4 x + 0..3] for XCD x: number of items, how many of them run in rounds that
  * occupy all resident workgroups of the XCD (64 for m = 4, 96 for m = 2), how many are left for the last round,

@@ -76,26 +76,34 @@ __device__ __forceinline__ void fs_clear(unsigned *tickets)
         for (int i = threadIdx.x; i < FS_TICKETS; i += blockDim.x) tickets[i] = 0u;
 }
 
-// From untransformed filters: u = G g G^T, split.  One wavefront per block of 32 filters x 16 channels and row xi of
-// the components (blockIdx.y: the G row product is repeated per row, the loads come from L2).  BWD: the filters of
-// the exchanged layer, rotated by 180 degrees (filter_transform.hip).
+// From untransformed filters: u = G g G^T, split.  A workgroup takes a block of 32 filters x 16 channels, one wavefront per
+// row xi of the components; the block's filters come through LDS in whole lines (each lane fetching its own 72 values
+// from memory, once per row: 17.6 us on average over the layers of a stack, 24 for 512 x 512 F(2x2); so 16.5 and 16.6,
+// bound by writing 6 bytes per value: 57 MB for 512 x 512, F(4x4)).  BWD: the filters of the exchanged layer, rotated by 180 degrees (filter_transform.hip).
 template <int M, bool BWD>
-__global__ __launch_bounds__(64) void filter_split_kernel(const float *__restrict__ G, char *__restrict__ Us, int K, int C,
-                                                          int n_kb, int n_s, unsigned *tickets)
+__global__ __launch_bounds__(64 * (M + 2)) void filter_split_kernel(const float *__restrict__ G, char *__restrict__ Us, int K,
+                                                                    int C, int n_kb, int n_s, unsigned *tickets)
 {
     constexpr int A = M + 2;
+    // forward: [filter][16 channels x 9], BWD (K and C are those of the exchanged layer, G is [C][K][3][3]): [channel][32
+    // filters x 9]; lanes read at an odd stride
+    constexpr int ROWS = BWD ? 16 : 32, LEN = BWD ? 32 * 9 : 16 * 9, STRIDE = BWD ? LEN : LEN + 1;
+    __shared__ float gs[ROWS * STRIDE];
     fs_clear(tickets);
-    const int lane = threadIdx.x, kb = blockIdx.x % n_kb, s = blockIdx.x / n_kb;
-    const int k = kb * 32 + (lane & 31), c0 = s * 16 + (lane >> 5) * 8;
+    const int lane = threadIdx.x & 63, kb = blockIdx.x % n_kb, s = blockIdx.x / n_kb;
+    for (int idx = threadIdx.x; idx < ROWS * LEN; idx += 64 * A) {
+        const int r = idx / LEN, j = idx % LEN;
+        const int k = kb * 32 + (BWD ? j / 9 : r), c = s * 16 + (BWD ? r : j / 9);
+        gs[r * STRIDE + j] = k < K && c < C ? G[(BWD ? (size_t)c * K + kb * 32 : (size_t)k * C + s * 16) * 9 + j] : 0.0f;
+    }
+    __syncthreads();
     float g[8][3][3];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        const int c = c0 + j;
-        const bool ok = k < K && c < C;
-        // (BWD: K and C are those of the exchanged layer, G is [C][K][3][3])
-        const float *src = G + (BWD ? (size_t)c * K + k : (size_t)k * C + c) * 9;
+        const int cj = (lane >> 5) * 8 + j;
+        const float *src = gs + (BWD ? cj * STRIDE + (lane & 31) * 9 : (lane & 31) * STRIDE + cj * 9);
 #pragma unroll
-        for (int i = 0; i < 9; ++i) g[j][(BWD ? 8 - i : i) / 3][(BWD ? 8 - i : i) % 3] = ok ? src[i] : 0.0f;
+        for (int i = 0; i < 9; ++i) g[j][(BWD ? 8 - i : i) / 3][(BWD ? 8 - i : i) % 3] = src[i];
     }
     auto row = [&](auto xc) {
         constexpr int xi = decltype(xc)::value;
@@ -117,7 +125,7 @@ __global__ __launch_bounds__(64) void filter_split_kernel(const float *__restric
         for (int nu = 0; nu < A; ++nu)
             fs_store_parts(Us + (((size_t)(xi * A + nu) * n_s + s) * n_kb + kb) * FS_BLOCK_BYTES, lane, u[nu]);
     };
-    switch (blockIdx.y) {
+    switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
     case 0: row(std::integral_constant<int, 0>()); break;
     case 1: row(std::integral_constant<int, 1>()); break;
     case 2: row(std::integral_constant<int, 2>()); break;
@@ -845,13 +853,13 @@ hipError_t launch_fused_split(const Geo &g, const float *D, const float *G, cons
     if (U != nullptr)
         filter_resplit_kernel<<<dim3(kb32 * n_s, g.a2), wave, 0, s>>>(U, Us, g.Kp, g.Cp, kb32, n_s, tickets);
     else if (g.m == 4 && bwd)
-        filter_split_kernel<4, true><<<dim3(kb32 * n_s, 6), wave, 0, s>>>(G, Us, g.K, g.C, kb32, n_s, tickets);
+        filter_split_kernel<4, true><<<dim3(kb32 * n_s), dim3(64 * 6), 0, s>>>(G, Us, g.K, g.C, kb32, n_s, tickets);
     else if (g.m == 4)
-        filter_split_kernel<4, false><<<dim3(kb32 * n_s, 6), wave, 0, s>>>(G, Us, g.K, g.C, kb32, n_s, tickets);
+        filter_split_kernel<4, false><<<dim3(kb32 * n_s), dim3(64 * 6), 0, s>>>(G, Us, g.K, g.C, kb32, n_s, tickets);
     else if (bwd)
-        filter_split_kernel<2, true><<<dim3(kb32 * n_s, 4), wave, 0, s>>>(G, Us, g.K, g.C, kb32, n_s, tickets);
+        filter_split_kernel<2, true><<<dim3(kb32 * n_s), dim3(64 * 4), 0, s>>>(G, Us, g.K, g.C, kb32, n_s, tickets);
     else
-        filter_split_kernel<2, false><<<dim3(kb32 * n_s, 4), wave, 0, s>>>(G, Us, g.K, g.C, kb32, n_s, tickets);
+        filter_split_kernel<2, false><<<dim3(kb32 * n_s), dim3(64 * 4), 0, s>>>(G, Us, g.K, g.C, kb32, n_s, tickets);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return fs_launch<float, float>(g, D, Us, Y, n_kb, n_tb, groups, part, s);
