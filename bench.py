@@ -36,16 +36,16 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-PEAK = {"hbm_GBs": 8000.0, "mfma_f32_TFs": 157.3, "mfma_f16_TFs": 2500.0}
+# fp32 products run on the bf16 matrix units, every value in three exact parts: six bf16 products each (csrc/bf16x3.h)
+PEAK = {"hbm_GBs": 8000.0, "mfma_f32_TFs": 2500.0 / 6, "mfma_f16_TFs": 2500.0}
 # HBM bytes per launch of a workload's dominant kernel, from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of
 # `bench.py --probe` (summaries under profiles/); keyed by (workload, kernel).  None until measured.
 MEASURED_TRAFFIC = {
-    # profiles/vgg16_n64_fp32_hbm_traffic.md
-    ("vgg16_3x3_conv_stack_N64_f32", "fused_wide_kernel<4, false>"): 1137.0e6,     # 9 launches (algorithmic 544.5 MB)
-    ("vgg16_3x3_conv_stack_N64_f32", "fused_wide_kernel<2, false>"): 303.5e6,      # 3 launches (algorithmic 68.2 MB)
-    # profiles/vgg16_n32_fp16_hbm_traffic.md (algorithmic: 328.7 MB resp. 183.5 MB per launch)
-    ("vgg16_3x3_conv_stack_N32_f16", "fused_f16_kernel<false, 2, float>"): 355.9e6,
-    ("vgg16_3x3_conv_stack_N32_f16", "gemm_f16_kernel<128, 128>"): 187.3e6,
+    # profiles/cases_counters.md
+    ("vgg16_3x3_conv_stack_N64_f32", "fused_split_kernel<4, false, float, float>"): 767.4e6,     # 9 launches (algorithmic 544.5 MB)
+    ("vgg16_3x3_conv_stack_N64_f32", "fused_split_kernel<2, false, float, float>"): 161.9e6,     # 3 launches (algorithmic 68.2 MB)
+    ("vgg16_3x3_conv_stack_N32_f16", "fused_split_kernel<4, false, __half, float>"): 288.3e6,
+    ("vgg16_3x3_conv_stack_N32_f16", "gemm_f16_kernel<128, 128>"): 104.0e6,
 }
 # Titan X (Maxwell) numbers of the paper, F(2x2,3x3), VGG network E (Tables 5 and 6): context only.
 PAPER_TITANX = {"fp32": {1: 7.03, 64: 9.37}, "fp16": {1: 7.06, 64: 10.28}}
@@ -195,7 +195,11 @@ def stage_plan(torch, w, L, ws, sets):
                                                                            flags=w.FLAG_FUSED)))])
         nbytes = {"filter": 9 * L.K * L.C * s + nU, "fused": nD + nU + nY}
         cpad = "false" if L.C % 8 == 0 else "true"
-        if L.dt == w.WINO_F16:
+        tiles = 32 if L.m == 4 else 64               # of an item of fused_split.hip, which takes 128 items and more
+        if L.K > 32 and -(-L.P // tiles) * -(-L.K // 64) >= 128:
+            kernel = "fused_split_kernel<%d, %s, %s, float>" % (L.m, "false" if L.C % 16 == 0 else "true",
+                                                                "__half" if L.dt == w.WINO_F16 else "float")
+        elif L.dt == w.WINO_F16:
             kernel = "fused_f16_kernel<%s, %d, float>" % (cpad, 2 if L.K > 32 else 1)
         elif L.K > 32:           # 64 filters per workgroup, 16 channels per step
             kernel = "fused_wide_kernel<%d, %s>" % (L.m, "false" if L.C % 16 == 0 else "true")
