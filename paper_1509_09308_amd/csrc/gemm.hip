@@ -49,6 +49,12 @@ __device__ __forceinline__ void gemm_lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Byte offset of a float in a buffer of less than 4 GiB; what lies behind 4 GiB stays there (rows past the last channel).
+__device__ __forceinline__ unsigned gemm_offset(unsigned long long floats)
+{
+    return floats < 0x3fffffffull ? (unsigned)floats * 4u : 0xffffffffu;
+}
+
 // ONE: the share is one slab.  Then there is nothing to overlap within a workgroup and what bounds the launch is writing
 // M: no second slab, half the LDS, twice the workgroups per CU, and no matrix instructions for the empty half of a
 // slab (64 products of 32 x 16 by 16 x 3600: layer 32.8 -> 30.3 us).
@@ -73,6 +79,7 @@ __global__ __launch_bounds__(256, ONE && BM * BN < 128 * 128 ? 4 : 2) void gemm_
     const int z = bid / a2;   // which share of the channel loop (layers with few blocks split it)
     const int k0 = tm_i * BM, p0 = tn_i * BN;
     const int c_first = z * c_share, c_rows = min(c_share, Cp - c_first);
+    const int nk = (c_rows + BK - 1) / BK;      // slabs, >= 1 by construction of the launch
 
     const float *Ue = U + ((size_t)e * Cp + c_first) * Kp;
     const float *Ve = V + ((size_t)e * Cp + c_first) * Pp;
@@ -85,33 +92,39 @@ __global__ __launch_bounds__(256, ONE && BM * BN < 128 * 128 ? 4 : 2) void gemm_
 
     // Operands are fetched through buffers that hold this share's channel rows of U^(e) and V^(e) (one component's
     // Cp x Kp or Cp x Pp floats stay below 4 GB: see the launcher).  A group of eight rows lies inside the buffer or
-    // behind it as a whole, and its vector offset alone tells which.
+    // behind it as a whole, and its vector offset alone tells which: sums of offsets saturate, they must not wrap around
+    // into the buffer.
     const __amdgpu_buffer_rsrc_t rsrc_a = __builtin_amdgcn_make_buffer_rsrc((void *)Ue, 0, (unsigned)((size_t)c_rows * Kp * 4), 0x00020000);
     const __amdgpu_buffer_rsrc_t rsrc_b = __builtin_amdgcn_make_buffer_rsrc((void *)Ve, 0, (unsigned)((size_t)c_rows * Pp * 4), 0x00020000);
     unsigned oa[AG], ob[BG];
 #pragma unroll
     for (int j = 0; j < AG; ++j) {
         const int id = tid + j * 256;
-        oa[j] = (unsigned)(id / BM * 8 * Kp + min(k0 + id % BM, Kp - 1)) * 4u;
+        oa[j] = gemm_offset((unsigned long long)(id / BM * 8) * Kp + min(k0 + id % BM, Kp - 1));
     }
 #pragma unroll
     for (int j = 0; j < BG; ++j) {
         const int id = tid + j * 256;
-        ob[j] = (unsigned)(id / BN * 8 * Pp + min(p0 + id % BN, Pp - 1)) * 4u;
+        ob[j] = gemm_offset((unsigned long long)(id / BN * 8) * Pp + min(p0 + id % BN, Pp - 1));
     }
     float ra[2][AG][8], rb[2][BG][8];
     auto request = [&](int slot, int slab) {
-        const unsigned sa = (unsigned)(slab * BK) * (unsigned)Kp * 4u, sb = (unsigned)(slab * BK) * (unsigned)Pp * 4u;
+        const unsigned past = slab < nk ? 0u : 0xffffffffu;
+        const unsigned sa = (unsigned)(slab * BK) * (unsigned)Kp * 4u | past, sb = (unsigned)(slab * BK) * (unsigned)Pp * 4u | past;
 #pragma unroll
         for (int j = 0; j < AG; ++j)
 #pragma unroll
             for (int i = 0; i < 8; ++i)
-                ra[slot][j][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc_a, oa[j] + sa, (unsigned)(i * Kp) * 4u, 0));
+                ra[slot][j][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                                rsrc_a, __builtin_elementwise_add_sat(oa[j], sa),
+                                                                (unsigned)(i * Kp) * 4u, 0));
 #pragma unroll
         for (int j = 0; j < BG; ++j)
 #pragma unroll
             for (int i = 0; i < 8; ++i)
-                rb[slot][j][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc_b, ob[j] + sb, (unsigned)(i * Pp) * 4u, 0));
+                rb[slot][j][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                                rsrc_b, __builtin_elementwise_add_sat(ob[j], sb),
+                                                                (unsigned)(i * Pp) * 4u, 0));
     };
     // group id = (channels / 8) * extent + column -> word (channels / 8) * 3 * extent + part * extent + column
     auto store = [&](int slot, int buf) {
@@ -164,7 +177,6 @@ __global__ __launch_bounds__(256, ONE && BM * BN < 128 * 128 ? 4 : 2) void gemm_
         }
     };
 
-    const int nk = (c_rows + BK - 1) / BK;      // >= 1 by construction of the launch
     if constexpr (ONE) {
         request(0, 0);
         store(0, 0);
@@ -236,9 +248,8 @@ static hipError_t launch_f32(const Geo &g, const float *U, const float *V, float
     if ((g.Cp + c_share - 1) / c_share != splits) return hipErrorInvalidValue;   // every share gets at least 16 channels
     const long long blocks = (long long)tiles_m * tiles_n * g.a2 * splits;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    // 32-bit byte offsets inside one component of U and of V, the requests past the last slab included
-    if ((unsigned long long)(g.Cp + 3 * BK) * g.Pp * 4ull >= (1ull << 32) ||
-        (unsigned long long)(g.Cp + 3 * BK) * g.Kp * 4ull >= (1ull << 32))
+    // 32-bit byte offsets inside one component of U and of V
+    if ((unsigned long long)g.Cp * g.Pp * 4ull >= (1ull << 32) || (unsigned long long)g.Cp * g.Kp * 4ull >= (1ull << 32))
         return hipErrorNotSupported;
     if (c_share <= BK)
         gemm_f32_kernel<BM, BN, BK, true><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(U, V, M, g.Kp, g.Cp, g.Pp, tiles_m,

@@ -45,3 +45,23 @@ def test_multiply_shares_of_sixteen_channels():
     D, G = synth.make_layer(N, C, HW, HW, K, seed=96)
     Y = w.wino_conv2d_fwd_ex(to_gpu(D), G=to_gpu(G), pad=1, m=2, flags=w.FLAG_UNFUSED).cpu().numpy()
     check_close(Y, direct.conv2d_fwd(D, G, pad=1), TOL[("f32", 2)], "three slabs in two shares", 2)
+
+
+@pytest.mark.parametrize("C", [16, 48])
+def test_multiply_of_many_tiles(C):
+    """Components of V up to 4 GiB are taken: a pipeline's requests past the last slab must not count."""
+    torch, w = require_gpu()
+    K, P, m = 32, 14000000, 2               # one component of V is 0.9 GB (C = 16) or 2.7 GB, all of them 14 or 43 GB
+    Kp, Cp, Pp = w.wino_padded_dims(K, C, P, m)
+    assert Cp * Pp * 4 < 2 ** 32 <= (Cp + 64) * Pp * 4
+    U = torch.randint(-3, 4, (16, Cp, Kp), device="cuda").float()
+    V = torch.empty((16, Cp, Pp), device="cuda")
+    b = torch.arange(Pp, device="cuda")
+    for c in range(Cp):
+        row = ((b * (2 * c + 1) + c * c) % 7 - 3).float()
+        for e in range(16):
+            V[e, c] = row if e % 2 else -row
+    M = w.wino_batched_gemm(U.reshape(-1), V.reshape(-1), K, C, P, m).view(16, Kp, Pp)
+    for e in range(16):
+        for p in range(0, P, 3000000):      # whole numbers below 2^24: exact in any order
+            assert torch.equal(M[e, :, p:min(p + 3000000, P)], U[e].t().contiguous() @ V[e, :, p:min(p + 3000000, P)])
