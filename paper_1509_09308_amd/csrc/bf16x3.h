@@ -12,9 +12,13 @@
 // Rate on the MI355X: the bf16 instruction takes 16.3 ns per SIMD for 16 channels of a 32 x 32 block, the fp32 one
 // 30.4 ns for two: six products cost 98 ns against 243.  And where fp32 matrix and vector instructions of one SIMD
 // take turns, up to six vector instructions per bf16 matrix instruction run beside it.
-// Outside of the range of earnest data: below 2^-109 the low bits of a value fall under the smallest bf16 number, and
-// the largest 2^-9 of the fp32 range rounds to infinity (as sums of such values would); an infinite value makes NaN of
-// its sums (inf - inf), as the inverse transforms make of infinite products; NaN stays NaN.
+//
+// The whole range of fp32.  Operands are multiplied by 2^24 before they are split, so that the parts of every value,
+// subnormal ones included, are bf16 numbers (multiples of 2^-125), and sums by 2^-48 (all exact).  In exchange operands
+// from 2^104 and sums from 2^80 on overflow, and an infinite value makes NaN of its sums (its parts are inf, NaN, NaN).
+// Either way the sum is not finite.  So every kernel looks at its sums once they are complete, and forms those that are
+// not finite again with fp32 instructions, from the operands as they are: they become what a chain of fp32 multiply-adds
+// gives (finite, infinite or NaN), and no other sum is touched.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -41,13 +45,15 @@ __device__ __forceinline__ void bf16_split2(float x, float y, unsigned &h, unsig
     l = bf16_pack(qx, qy);
 }
 
+constexpr float BF16_SCALE = 0x1p24f, BF16_UNSCALE = 0x1p-48f;       // of operands and of sums
+
 // the three operand words (eight reduction steps each) of eight values
-__device__ __forceinline__ void bf16_split8(const float (&x)[8], uintx4_b (&p)[3])
+__device__ __forceinline__ void bf16_split8(const float (&x)[8], uintx4_b (&p)[3], float scale = 1.0f)
 {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         unsigned h, m, l;
-        bf16_split2(x[2 * i], x[2 * i + 1], h, m, l);
+        bf16_split2(scale * x[2 * i], scale * x[2 * i + 1], h, m, l);
         p[0][i] = h, p[1][i] = m, p[2][i] = l;
     }
 }
@@ -56,5 +62,12 @@ __device__ __forceinline__ void bf16_split8(const float (&x)[8], uintx4_b (&p)[3
 constexpr int BF16_PRODUCTS = 6;
 __device__ constexpr int bf16_part_a(int n) { return n == 0 ? 2 : n == 1 ? 0 : n == 2 ? 1 : n == 3 ? 1 : 0; }
 __device__ constexpr int bf16_part_b(int n) { return n == 0 ? 0 : n == 1 ? 2 : n == 2 ? 1 : n == 3 ? 0 : n == 4 ? 1 : 0; }
+
+// the largest magnitude so far, infinite or NaN as soon as one of the values is not finite (v_maximum3_f32)
+__device__ __forceinline__ float bf16_look(float x, float y, float t)
+{
+    return __builtin_elementwise_maximum(__builtin_elementwise_maximum(__builtin_fabsf(x), __builtin_fabsf(y)), t);
+}
+__device__ __forceinline__ bool bf16_finite(float x) { return __builtin_fabsf(x) < __builtin_inff(); }
 
 }  // namespace wino

@@ -41,7 +41,8 @@ __device__ __forceinline__ int xcd_remap(int bid, int nblocks)
 // each make it 25 ns, this kernel runs at 30 (matrix pipes 60 % busy).  36 products of 256 x 256 by 256 x 12544:
 // 118 TFLOP/s with v_mfma_f32_32x32x2_f32 (501 us), 184 so (320 us); 512 -> 512 channels at 28 x 28, batch 8: multiply
 // 83 -> 53 us.  Single-buffered slabs of 32 channels on v_mfma_f32_16x16x32_bf16, which takes an eighth less energy,
-// but with two barriers and no split between the matrix instructions: 355 us (matrix pipes 46 % busy).
+// but with two barriers and no split between the matrix instructions: 355 us (matrix pipes 46 % busy).  (Operands were
+// split as they are then; the multiplication by 2^24, for the whole range of fp32, costs 5 %: that layer 84.1 -> 86.7 us.)
 __device__ __forceinline__ void gemm_lds_barrier()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
@@ -132,14 +133,14 @@ __global__ __launch_bounds__(256, ONE && BM * BN < 128 * 128 ? 4 : 2) void gemm_
 #pragma unroll
         for (int j = 0; j < AG; ++j) {
             const int id = tid + j * 256, w = id / BM * 3 * BM + id % BM;
-            bf16_split8(ra[slot][j], p);
+            bf16_split8(ra[slot][j], p, BF16_SCALE);
 #pragma unroll
             for (int q = 0; q < 3; ++q) As[buf][w + q * BM] = p[q];
         }
 #pragma unroll
         for (int j = 0; j < BG; ++j) {
             const int id = tid + j * 256, w = id / BN * 3 * BN + id % BN;
-            bf16_split8(rb[slot][j], p);
+            bf16_split8(rb[slot][j], p, BF16_SCALE);
 #pragma unroll
             for (int q = 0; q < 3; ++q) Bs[buf][w + q * BN] = p[q];
         }
@@ -192,7 +193,7 @@ __global__ __launch_bounds__(256, ONE && BM * BN < 128 * 128 ? 4 : 2) void gemm_
     // slab kt sits in LDS buffer kt & 1 and came through register slot kt & 1, both known at compile time.  The order
     // of a trip is laid down, because the compiler would move the requests to where their registers are read: the
     // requests of slab kt + 2 first, then the operand reads, then matrix instructions with the split of slab kt + 1
-    // (11 vector instructions per pair of values, about four per matrix instruction) between them.
+    // (13 vector instructions per pair of values, four to five per matrix instruction) between them.
     auto slab = [&](int kt, int odd) {
         request(odd, kt + 2);                   // (the slot of slab kt, which is in LDS)
         multiply(odd);
@@ -200,7 +201,7 @@ __global__ __launch_bounds__(256, ONE && BM * BN < 128 * 128 ? 4 : 2) void gemm_
         __builtin_amdgcn_sched_group_barrier(0x2, AG + BG, 0);       // (their offsets)
         __builtin_amdgcn_sched_group_barrier(0x20, 8 * (AG + BG), 0);
         __builtin_amdgcn_sched_group_barrier(0x100, 3 * (TM + TN), 0);
-        constexpr int NM = BF16_PRODUCTS * TM * TN * (BK / 16), NV = (44 * (AG + BG) + NM - 1) / NM;
+        constexpr int NM = BF16_PRODUCTS * TM * TN * (BK / 16), NV = (52 * (AG + BG) + NM - 1) / NM;
 #pragma unroll
         for (int i = 0; i < NM; ++i) {
             __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
@@ -224,6 +225,31 @@ __global__ __launch_bounds__(256, ONE && BM * BN < 128 * 128 ? 4 : 2) void gemm_
         multiply(0, depth);
     }
     }
+
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            float t = 0.0f;
+#pragma unroll
+            for (int r = 0; r < 16; r += 2) {
+                acc[i][j][r] *= BF16_UNSCALE, acc[i][j][r + 1] *= BF16_UNSCALE;
+                t = bf16_look(acc[i][j][r], acc[i][j][r + 1], t);
+            }
+            if (!__any(!bf16_finite(t))) continue;
+            // the sums that are not finite, with fp32 instructions (bf16x3.h)
+            const float *a = Ue + min(k0 + wm * (TM * 32) + i * 32 + li, Kp - 1) + (size_t)lh * Kp;
+            const float *b = Ve + min(p0 + wn * (TN * 32) + j * 32 + li, Pp - 1) + (size_t)lh * Pp;
+            floatx16 exact;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) exact[r] = 0.0f;
+#pragma unroll 8
+            for (int c = 0; c < c_rows; c += 2)
+                exact = __builtin_amdgcn_mfma_f32_32x32x2f32(a[(size_t)c * Kp], b[(size_t)c * Pp], exact, 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if (!bf16_finite(acc[i][j][r])) acc[i][j][r] = exact[r];
+        }
 
     // accumulator register r of lane (li, lh) is row 8*(r/4) + 4*lh + r%4, column li of its tile;
     // Kp and Pp are multiples of 32, so a 32 x 32 tile is entirely inside or entirely outside

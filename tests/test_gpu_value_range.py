@@ -1,0 +1,83 @@
+"""fp32 entry points over the whole range of fp32 values: tiny, huge and infinite ones give what chains of fp32
+multiply-adds give, and the sums that such a value does not enter keep their bits."""
+import numpy as np
+import pytest
+
+from oracle import direct
+from oracle import winograd as wg
+from paper_1509_09308_amd import synth
+from gpu_util import TOL, rel_err, require_gpu, to_gpu
+
+pytestmark = pytest.mark.gpu
+
+FLT_MAX = np.finfo(np.float32).max
+# (scale of the first operand, of the second): the low bits of a tiny operand lie below what a bf16 part of it can hold;
+# products of the huge ones, and sums of those, stay within fp32
+SCALES = {"tiny data": (2.0 ** -118, 2.0 ** 20), "tiny filters": (2.0 ** 20, 2.0 ** -118), "subnormal data": (2.0 ** -132, 2.0 ** 40),
+          "huge data": (2.0 ** 112, 2.0 ** -30), "huge filters": (2.0 ** -30, 2.0 ** 112)}
+
+
+def scaled(a, s):
+    return (a.astype(np.float64) * s).astype(np.float32)
+
+
+def check(got, ref, tol, what):
+    """The same infinities and NaNs, everything else within `tol` in norm."""
+    got, ref = np.asarray(got, dtype=np.float64), np.asarray(ref, dtype=np.float64)
+    assert (np.isnan(got) == np.isnan(ref)).all(), "%s: %d NaNs, expected %d" % (what, np.isnan(got).sum(), np.isnan(ref).sum())
+    inf = np.isinf(ref)
+    assert (np.isinf(got) == inf).all() and (got[inf] == ref[inf]).all(), what
+    ok = np.isfinite(ref)
+    e = rel_err(got[ok], ref[ok])
+    print("%s: rel err %.2e" % (what, e))
+    assert e <= tol, "%s: %.3e > %.1e" % (what, e, tol)
+
+
+def terms(mat, x, axis):
+    """mat x along `axis` as the kernels form it: coefficients of zero stand for no term at all."""
+    x = np.moveaxis(x, axis, 0)
+    out = []
+    for row in np.asarray(mat, dtype=np.float64):
+        out.append(sum(float(c) * x[j] for j, c in enumerate(row) if c != 0))
+    return np.moveaxis(np.stack(out), 0, axis)
+
+
+# ---- the multiply -------------------------------------------------------------------------------
+
+GEMM = [(40, 16, 100), (200, 16, 3300), (70, 80, 300), (256, 48, 3600)]     # one slab, several; 64- and 128-wide blocks
+
+
+def gemm_operands(K, C, P):
+    rng = np.random.default_rng(K + C + P)
+    return rng.standard_normal((4, 4, K, C)).astype(np.float32), rng.standard_normal((4, 4, C, P)).astype(np.float32)
+
+
+def gemm(w, u, v):
+    K, C, P = u.shape[2], u.shape[3], v.shape[3]
+    return w.unpack_m(w.wino_batched_gemm(w.pack_u(u, 2), w.pack_v(v, 2), K, C, P, 2), K, P, 2)
+
+
+@pytest.mark.parametrize("K,C,P", GEMM)
+@pytest.mark.parametrize("scale", list(SCALES))
+def test_multiply_scaled(K, C, P, scale):
+    torch, w = require_gpu()
+    u, v = gemm_operands(K, C, P)
+    u, v = scaled(u, SCALES[scale][1]), scaled(v, SCALES[scale][0])
+    check(gemm(w, u, v), wg.multiply(u.astype(np.float64), v.astype(np.float64)), 1e-6, "multiply %s %s" % ((K, C, P), scale))
+
+
+@pytest.mark.parametrize("K,C,P", GEMM)
+@pytest.mark.parametrize("value", [np.inf, FLT_MAX, -FLT_MAX, np.nan])
+def test_multiply_single_values(K, C, P, value):
+    torch, w = require_gpu()
+    u, v = gemm_operands(K, C, P)
+    u *= 2.0 ** -6
+    plain = gemm(w, u, v)
+    x = v.copy()
+    x[1, 2, C - 1, P - 3] = value
+    x[3, 0, 0, 5] = value
+    got = gemm(w, u, x)
+    check(got, wg.multiply(u.astype(np.float64), x.astype(np.float64)), 1e-6, "multiply %s, %g" % ((K, C, P), value))
+    rest = np.ones_like(got, dtype=bool)
+    rest[1, 2, :, P - 3] = rest[3, 0, :, 5] = False
+    assert (got[rest] == plain[rest]).all()
