@@ -361,8 +361,8 @@ __global__ __launch_bounds__(256 * KS) void direct_gemm_kernel(const T *__restri
         uintx2_d *w = reinterpret_cast<uintx2_d *>(dst + (q / 2) * NP * cols + col) + q % 2;
         if constexpr (F32) {
             unsigned h0, m0, l0, h1, m1, l1;
-            bf16_split2(x[0], x[1], h0, m0, l0);
-            bf16_split2(x[2], x[3], h1, m1, l1);
+            bf16_split2(BF16_SCALE * x[0], BF16_SCALE * x[1], h0, m0, l0);
+            bf16_split2(BF16_SCALE * x[2], BF16_SCALE * x[3], h1, m1, l1);
             w[0] = uintx2_d{h0, h1}, w[2 * cols] = uintx2_d{m0, m1}, w[4 * cols] = uintx2_d{l0, l1};
         } else {
             const unsigned short *h = reinterpret_cast<const unsigned short *>(x);
@@ -439,6 +439,38 @@ __global__ __launch_bounds__(256 * KS) void direct_gemm_kernel(const T *__restri
             for (int j = 0; j < TN; ++j)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[j][r] += sums[((z * TN + j) * 16 + r) * 256 + tid];
+    }
+
+    if constexpr (F32) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            float t = 0.0f;
+#pragma unroll
+            for (int r = 0; r < 16; r += 2) {
+                acc[j][r] *= BF16_UNSCALE, acc[j][r + 1] *= BF16_UNSCALE;
+                t = bf16_look(acc[j][r], acc[j][r + 1], t);
+            }
+            if (!__any(!bf16_finite(t))) continue;
+            // the sums that are not finite, with fp32 instructions (bf16x3.h): lane (li, lh) brings tap 2 i + lh of filter and
+            // pixel li
+            const int p = min(p0 + (wn * TN + j) * 32 + li, g.P - 1);
+            const int n = p / plane, ox = (p - n * plane) / g.Wo, oy = p - n * plane - ox * g.Wo;
+            const T *window = D + (size_t)n * image, *filter = G + (size_t)min(k0 + wm * 32 + li, g.K - 1) * g.J;
+            floatx16_dc exact;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) exact[r] = 0.0f;
+#pragma unroll 4
+            for (int i = 0; i < (g.J + 1) / 2; ++i) {
+                const int tap = 2 * i + lh, c = tap / (g.R * g.S), uv = tap - c * (g.R * g.S);
+                const int x = ox * g.stride - g.pad + uv / g.S, y = oy * g.stride - g.pad + uv % g.S;
+                const bool ok = tap < g.J && x >= 0 && x < g.H && y >= 0 && y < g.W;
+                exact = __builtin_amdgcn_mfma_f32_32x32x2f32(tap < g.J ? filter[tap] : 0.0f,
+                                                             ok ? window[((size_t)c * g.H + x) * g.W + y] : 0.0f, exact, 0, 0, 0);
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if (!bf16_finite(acc[j][r])) acc[j][r] = exact[r];
+        }
     }
 
     // accumulator register r of lane (li, lh) is filter row 8 (r / 4) + 4 lh + r % 4, pixel li of its tile

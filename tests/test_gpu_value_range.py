@@ -42,6 +42,48 @@ def terms(mat, x, axis):
     return np.moveaxis(np.stack(out), 0, axis)
 
 
+# ---- direct layers ------------------------------------------------------------------------------
+
+DIRECT = [(2, 16, 13, 10, 32, 1, 1, 0, 2), (1, 40, 14, 14, 64, 3, 3, 1, 1), (4, 24, 56, 52, 96, 3, 3, 0, 2),
+          (6, 12, 112, 100, 72, 3, 3, 1, 1)]     # one step; four groups of steps, two, one with wide blocks
+
+
+def direct_layer(shape):
+    N, C, H, W, K, R, S, pad, stride = shape
+    rng = np.random.default_rng(sum(shape))
+    return (rng.standard_normal((N, C, H, W)).astype(np.float32),
+            (rng.standard_normal((K, C, R, S)) * np.sqrt(2.0 / (C * R * S))).astype(np.float32), dict(pad=pad, stride=stride))
+
+
+@pytest.mark.parametrize("shape", DIRECT)
+@pytest.mark.parametrize("scale", list(SCALES))
+def test_direct_scaled(shape, scale):
+    torch, w = require_gpu()
+    D, G, kw = direct_layer(shape)
+    D, G = scaled(D, SCALES[scale][0]), scaled(G, SCALES[scale][1])
+    Y = w.direct_conv2d_fwd(to_gpu(D), to_gpu(G), **kw).cpu().numpy()
+    check(Y, direct.conv2d_fwd(D, G, **kw), 1e-6, "direct %s %s" % (shape, scale))
+
+
+@pytest.mark.parametrize("shape", DIRECT)
+@pytest.mark.parametrize("value", [np.inf, -np.inf, FLT_MAX, -FLT_MAX, np.nan])
+def test_direct_single_values(shape, value):
+    torch, w = require_gpu()
+    D, G, kw = direct_layer(shape)
+    G *= 2.0 ** -6
+    g = to_gpu(G)
+    plain = w.direct_conv2d_fwd(to_gpu(D), g, **kw).cpu().numpy()
+    for at in ((0, 0, 0, 0), (-1, -1, 6, 4), (-1, shape[1] // 2, 3, -1)):
+        X = D.copy()
+        X[at] = value
+        Y = w.direct_conv2d_fwd(to_gpu(X), g, **kw).cpu().numpy()
+        ref = direct.conv2d_fwd(X, G, **kw)
+        check(Y, ref, 1e-6, "direct %s, %g at %s" % (shape, value, at))
+        X[at] = np.nan
+        out = ~np.isnan(direct.conv2d_fwd(X, G, **kw))
+        assert (Y[out] == plain[out]).all()
+
+
 # ---- the multiply -------------------------------------------------------------------------------
 
 GEMM = [(40, 16, 100), (200, 16, 3300), (70, 80, 300), (256, 48, 3600)]     # one slab, several; 64- and 128-wide blocks
