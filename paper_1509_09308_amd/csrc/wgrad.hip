@@ -287,15 +287,15 @@ __device__ __forceinline__ void wgrad_fused_body(const float *__restrict__ X, fl
     const int slab_hi = min(slab_lo + slabs_per_share, (g.Pb + WF_BK - 1) / WF_BK);
 
     // position of this thread's pair of blocks (b, b + 1; b even, so is by)
-    int b_cur = slab_lo * WF_BK + 2 * pl;
-    int by, bx, im;
-    {
+    int b_cur, by, bx, im;
+    auto place = [&]() {
+        b_cur = slab_lo * WF_BK + 2 * pl;
         const int b = min(b_cur, g.Pb - 2);
         by = b % g.Bw;
         const int t2 = b / g.Bw;
         bx = t2 % g.Bh;
         im = t2 / g.Bh;
-    }
+    };
     // Every other share sums the products of the negated error and stores the negative of what it gets.  Adding a small
     // product to a large sum, the instruction rounds down rather than to nearest: on average 3e-8 of a sum over 1 568
     // blocks, little by itself, but the same way in every share and component (64 -> 64 channels at 224 x 224, N = 64, 512
@@ -338,8 +338,13 @@ __device__ __forceinline__ void wgrad_fused_body(const float *__restrict__ X, fl
         }
     };
     float *const t_dst = smem + (ERR ? 0 : WF_OP) + r * WF_BK + (((pl >> 1) ^ ((r >> 2) & 1)) << 2) + 2 * (pl & 1);
-    auto transform = [&](int buf) {
+    auto transform = [&](int buf, float scale) {
         float t[4][4], o[4], wa[16], wb[16];
+#pragma unroll
+        for (int p = 0; p < NR; ++p) {
+            xm[p] *= scale;
+            if constexpr (!ERR) xe[p] *= scale;
+        }
         if constexpr (ERR) {
             // w = G e G^T of the two error blocks
 #pragma unroll
@@ -347,7 +352,7 @@ __device__ __forceinline__ void wgrad_fused_body(const float *__restrict__ X, fl
                 float *dst = blk ? wb : wa;
 #pragma unroll
                 for (int q = 0; q < 2; ++q) {
-                    const float col[2] = {okx & 1u ? sign * xm[0][2 * blk + q] : 0.0f, okx & 2u ? sign * xm[1][2 * blk + q] : 0.0f};
+                    const float col[2] = {okx & 1u ? xm[0][2 * blk + q] : 0.0f, okx & 2u ? xm[1][2 * blk + q] : 0.0f};
                     g32_mul(col, o);
 #pragma unroll
                     for (int p = 0; p < 4; ++p) t[p][q] = o[p];
@@ -391,14 +396,16 @@ __device__ __forceinline__ void wgrad_fused_body(const float *__restrict__ X, fl
 
     const int lane = tid & 63, li = lane & 31, lh = lane >> 5;
     floatx16_w acc[2][2][2];
+    auto clear = [&]() {
 #pragma unroll
-    for (int e = 0; e < 2; ++e)
+        for (int e = 0; e < 2; ++e)
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+            for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+                for (int j = 0; j < 2; ++j)
 #pragma unroll
-                for (int q = 0; q < 16; ++q) acc[e][i][j][q] = 0.0f;
+                    for (int q = 0; q < 16; ++q) acc[e][i][j][q] = 0.0f;
+    };
     // operand o (0, 1: 32 filters each; 2, 3: 32 channels) of component e: four blocks of row li
     const int m_off = 2 * wave * (64 * WF_BK) + li * WF_BK + ((lh ^ ((li >> 2) & 1)) << 2);
     floatx4_w raw[4];
@@ -452,9 +459,12 @@ __device__ __forceinline__ void wgrad_fused_body(const float *__restrict__ X, fl
         for (int n = 0; n < 12; ++n) mma(1, n);
     };
 
+    const float scale = ERR ? sign * BF16_SCALE : BF16_SCALE;
+    place();
+    clear();
     if (slab_lo < slab_hi) {
         load_raw();
-        transform(0);
+        transform(0, scale);
         load_raw();
         wf_lds_barrier();
         int slab = slab_lo;
@@ -466,7 +476,7 @@ __device__ __forceinline__ void wgrad_fused_body(const float *__restrict__ X, fl
                 multiply(buf);
                 __builtin_amdgcn_s_setprio(0);
             }
-            if (more) transform(buf ^ 1);
+            if (more) transform(buf ^ 1, scale);
             load_raw();                    // (past the share's end: a valid position, read and discarded)
             if constexpr (ERR) {
                 __builtin_amdgcn_s_setprio(2);
@@ -478,19 +488,60 @@ __device__ __forceinline__ void wgrad_fused_body(const float *__restrict__ X, fl
     }
 
     // a share past the end of the blocks still writes its (zero) partial M
+    float t = 0.0f;
+    auto write = [&](bool again, float factor) {
 #pragma unroll
-    for (int e = 0; e < 2; ++e)
+        for (int e = 0; e < 2; ++e)
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+            for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int rt = kt * 64 + i * 32, ctile = ct * 64 + j * 32;
-                if (rt < g.Kp && ctile < g.Cq) {
-                    float *dst = Mo + (((size_t)z * 16 + 2 * wave + e) * g.Kp + rt + 4 * lh) * g.Cq + ctile + li;
+                for (int j = 0; j < 2; ++j) {
+                    const int rt = kt * 64 + i * 32, ctile = ct * 64 + j * 32;
+                    if (rt < g.Kp && ctile < g.Cq) {
+                        float *dst = Mo + (((size_t)z * 16 + 2 * wave + e) * g.Kp + rt + 4 * lh) * g.Cq + ctile + li;
 #pragma unroll
-                    for (int q = 0; q < 16; ++q) dst[(size_t)(8 * (q / 4) + (q % 4)) * g.Cq] = sign * acc[e][i][j][q];
+                        for (int q = 0; q < 16; ++q) {
+                            float *at = dst + (size_t)(8 * (q / 4) + (q % 4)) * g.Cq;
+                            const float m = factor * acc[e][i][j][q];
+                            if (!again) t = bf16_look(m, m, t);
+                            if (!again || !bf16_finite(*at)) *at = m;
+                        }
+                    }
                 }
+    };
+    write(false, sign * BF16_UNSCALE);
+
+    // Sums that are not finite: the share once more with fp32 instructions (bf16x3.h), one phase after the other, keeping
+    // what is finite.  Every wavefront learns from all others whether there are any.
+    int *const votes = reinterpret_cast<int *>(smem);          // (everybody is done with the last step's buffers)
+    votes[wave] = __any(!bf16_finite(t));
+    __syncthreads();
+    int again = 0;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) again |= votes[w];
+    __syncthreads();
+    if (again) {
+        place();
+        clear();
+        for (int slab = slab_lo; slab < slab_hi; ++slab) {
+            load_raw();
+            transform(0, 1.0f);
+            __syncthreads();
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                read(e, 0);
+#pragma unroll
+                for (int n = 0; n < 4; ++n)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+                            acc[e][i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(raw[i][n], raw[2 + j][n], acc[e][i][j], 0, 0, 0);
             }
+            __syncthreads();
+        }
+        write(true, 1.0f);
+    }
 }
 
 __global__ __launch_bounds__(WF_T, 2) void wgrad_fused_kernel(const float *__restrict__ D, const float *__restrict__ E,

@@ -123,3 +123,62 @@ def test_multiply_single_values(K, C, P, value):
     rest = np.ones_like(got, dtype=bool)
     rest[1, 2, :, P - 3] = rest[3, 0, :, 5] = False
     assert (got[rest] == plain[rest]).all()
+
+
+# ---- filter gradient ----------------------------------------------------------------------------
+
+WGRAD = [(5, 70, 9, 20, 130), (3, 320, 28, 28, 288)]
+
+
+@pytest.mark.parametrize("N,C,H,W,K", WGRAD)
+@pytest.mark.parametrize("scale", list(SCALES))
+def test_filter_gradient_scaled(N, C, H, W, K, scale):
+    torch, w = require_gpu()
+    rng = np.random.default_rng(N + C + H + W + K)
+    D = scaled(rng.standard_normal((N, C, H, W)), SCALES[scale][0])
+    E = scaled(rng.standard_normal((N, K, H, W)), SCALES[scale][1])
+    dG = w.wino_conv2d_bwd_filter(to_gpu(D), to_gpu(E), pad=1).cpu().numpy()
+    check(dG, direct.conv2d_bwd_filter(D, E, pad=1), 1e-5, "filter gradient %s %s" % ((N, C, H, W, K), scale))
+
+
+@pytest.mark.parametrize("value", [np.inf, FLT_MAX, np.nan])
+@pytest.mark.parametrize("which", ["data", "error"])
+def test_filter_gradient_single_values(value, which):
+    torch, w = require_gpu()
+    N, C, H, W, K = 5, 70, 9, 20, 130
+    rng = np.random.default_rng(7)
+    D = rng.standard_normal((N, C, H, W)).astype(np.float32)
+    E = (rng.standard_normal((N, K, H, W)) * 2.0 ** -6).astype(np.float32)
+    if which == "error":
+        D, E = (D * 2.0 ** -6).astype(np.float32), (E * 2.0 ** 6).astype(np.float32)
+    plain = w.wino_conv2d_bwd_filter(to_gpu(D), to_gpu(E), pad=1).cpu().numpy()
+    line = 66
+    (D if which == "data" else E)[3, line, 4, 7] = value
+    dG = w.wino_conv2d_bwd_filter(to_gpu(D), to_gpu(E), pad=1).cpu().numpy()
+    rest = np.ones(dG.shape, dtype=bool)
+    if which == "data":
+        rest[:, line] = False
+    else:
+        rest[line] = False
+    assert (dG[rest] == plain[rest]).all()
+    Bt, Gm, At = (np.array(x, dtype=np.float64) for x in wg.matrices(3, 2))
+    d = np.zeros((N, C, H + 3, W + 2))
+    d[:, :, 1:H + 1, 1:W + 1] = D
+    e = np.zeros((N, K, H + 1, W))
+    e[:, :, :H] = E
+    if which == "data":
+        d = d[:, line:line + 1]
+    else:
+        e = e[:, line:line + 1]
+    bx, by = (H + 1) // 2, W // 2
+    tiles = np.stack([d[:, :, 2 * x:2 * x + 4, 2 * y:2 * y + 4] for x in range(bx) for y in range(by)])
+    blocks = np.stack([e[:, :, 2 * x:2 * x + 2, 2 * y:2 * y + 2] for x in range(bx) for y in range(by)])
+    with np.errstate(invalid="ignore"):
+        v, u = terms(Bt, terms(Bt, tiles, 3), 4), terms(Gm, terms(Gm, blocks, 3), 4)     # [b][n][c or k][4][4]
+        M = np.zeros((u.shape[2], v.shape[2], 4, 4))
+        for b in range(bx * by):
+            for n in range(N):
+                M += u[b, n][:, None] * v[b, n][None]
+        ref = terms(At, terms(At, M, 2), 3)
+    got = dG[:, line:line + 1] if which == "data" else dG[line:line + 1]
+    check(got, ref, 1e-5, "filter gradient, %g in the %s" % (value, which))
