@@ -18,7 +18,8 @@
 // from 2^104 and sums from 2^80 on overflow, and an infinite value makes NaN of its sums (its parts are inf, NaN, NaN).
 // Either way the sum is not finite.  So every kernel looks at its sums once they are complete, and forms those that are
 // not finite again with fp32 instructions, from the operands as they are: they become what a chain of fp32 multiply-adds
-// gives (finite, infinite or NaN), and no other sum is touched.
+// gives (finite, infinite or NaN), and no other sum is touched.  A layer whose data is all NaN takes three to five times as
+// long for it (256 -> 256 channels at 56 x 56, F(4x4,3x3), N = 16: 158 us, all NaN 776).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -48,7 +49,7 @@ __device__ __forceinline__ void bf16_split2(float x, float y, unsigned &h, unsig
 constexpr float BF16_SCALE = 0x1p24f, BF16_UNSCALE = 0x1p-48f;       // of operands and of sums
 
 // the three operand words (eight reduction steps each) of eight values
-__device__ __forceinline__ void bf16_split8(const float (&x)[8], uintx4_b (&p)[3], float scale = 1.0f)
+__device__ __forceinline__ void bf16_split8(const float (&x)[8], uintx4_b (&p)[3], float scale)
 {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {

@@ -23,7 +23,7 @@
 //
 // What bounds it: 6 500 cycles per step (multiply and transform of either wavefront 2 500 - 2 700 each), 27 000 per item
 // around them (first taps, inverse transform, the stores of all CUs at once), at a clock that falls to 1.7 GHz under the
-// power of it.  256 -> 256 channels at 56 x 56, N = 64: 590 us in fused_wide.hip, 480 here.
+// power of it (scaling the data for the whole range of fp32, bf16x3.h, costs 1 - 3 %).  256 -> 256 channels at 56 x 56, N = 64: 590 us in fused_wide.hip, 480 here.
 //
 // fp16 storage (F(4x4,3x3)): the same with one part per value -- U as the filter transform lays it down is in operand
 // order already, a tile's 16 channels are 32 bytes of LDS, a unit is one matrix instruction, and the filters of a whole
@@ -62,10 +62,26 @@ constexpr int FS_TICKETS = 1024, FS_TICKET_BYTES = FS_TICKETS * 4;   // arrival 
 constexpr int FS_BLOCK_BYTES = 3 * 1024;
 static size_t fs_filter_bytes(const Geo &g) { return (size_t)g.a2 * (g.Cp / 16) * (g.Kp / 32) * FS_BLOCK_BYTES; }
 
+// Filters that the scaling takes out of bounds (and infinite ones) are kept whole for fused_split_again: NaN as first
+// part, the value's bits as the other two.
+constexpr float FS_WHOLE = 0x1p103f;
 __device__ __forceinline__ void fs_store_parts(char *dst, int lane, const float (&x)[8])
 {
     uintx4_b p[3];
-    bf16_split8(x, p);
+    bf16_split8(x, p, BF16_SCALE);
+    float t = 0.0f;
+#pragma unroll
+    for (int j = 0; j < 8; j += 2) t = bf16_look(x[j], x[j + 1], t);
+    if (__any(!(t < FS_WHOLE))) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if (!(__builtin_fabsf(x[j]) < FS_WHOLE)) {
+                const unsigned bits = __builtin_bit_cast(unsigned, x[j]), low = 16 * (j % 2), keep = 0xffff0000u >> low;
+                p[0][j / 2] = (p[0][j / 2] & keep) | 0x7fc0u << low;
+                p[1][j / 2] = (p[1][j / 2] & keep) | (bits >> 16) << low;
+                p[2][j / 2] = (p[2][j / 2] & keep) | (bits & 0xffffu) << low;
+            }
+    }
 #pragma unroll
     for (int q = 0; q < 3; ++q) *reinterpret_cast<uintx4_b *>(dst + q * 1024 + lane * 16) = p[q];
 }
@@ -236,7 +252,7 @@ __device__ __forceinline__ int fs_lane()
 template <int M, bool CPAD, typename T, typename TY, int R>
 __device__ __forceinline__ void fused_split_body(const T *__restrict__ D, const char *__restrict__ Us, TY *__restrict__ Y,
                                                  const Geo &g, int n_kb, int n_tb, int groups, float *__restrict__ part,
-                                                 float *smem, int wave)
+                                                 float *smem, int *again, int wave)
 {
     constexpr int A = M + 2, NE = A * A;
     constexpr int P = fs_tiles(M), TB = P / 32;                // tiles of the item, matrix-instruction columns of them
@@ -390,7 +406,10 @@ __device__ __forceinline__ void fused_split_body(const T *__restrict__ D, const 
                 d[0] = lv, d[A - 1] = rv;
 #pragma unroll
                 for (int q = 0; q < M; ++q) d[1 + q] = (float)mid[r][p][q];
-                bt_mul<M>(d, t[p]);
+                if constexpr (F16)
+                    bt_mul<M>(d, t[p]);
+                else
+                    bt_mul_scaled<M>(d, t[p], BF16_SCALE);
             };
             row(std::integral_constant<int, 0>());
             row(std::integral_constant<int, 1>());
@@ -659,10 +678,25 @@ __device__ __forceinline__ void fused_split_body(const T *__restrict__ D, const 
                 for (int p = 0; p < M; ++p) tt[p][nu] = o[p];
             }
 #pragma unroll
-            for (int p = 0; p < M; ++p) at_mul<M>(tt[p], y[h * RP + rp][p]);
+            for (int p = 0; p < M; ++p) {
+                at_mul<M>(tt[p], y[h * RP + rp][p]);
+                if constexpr (!F16) {
+#pragma unroll
+                    for (int q = 0; q < M; ++q) y[h * RP + rp][p][q] *= BF16_UNSCALE;
+                }
+            }
         }
         fs_lds_barrier();
     }
+    // outputs that are not finite are formed again at the end (fused_split_again)
+    auto look = [&](const float (&o)[M][M], int *flag) {
+        float t = 0.0f;
+#pragma unroll
+        for (int p = 0; p < M; ++p)
+#pragma unroll
+            for (int q = 0; q < M; q += 2) t = bf16_look(o[p][q], o[p][q + 1], t);
+        if (!bf16_finite(t)) *flag = 1;
+    };
     // (the requests have arrived before the first store is issued)
 #pragma unroll
     for (int r = 0; r < NPR; ++r) {
@@ -675,6 +709,10 @@ __device__ __forceinline__ void fused_split_body(const T *__restrict__ D, const 
 #pragma unroll
         for (int q = 0; q < NP; ++q) asm volatile("" : "+v"(ua[u][q]));
     if (!o_shared) {
+        if constexpr (!F16) {
+#pragma unroll
+            for (int n = 0; n < 2 * RP; ++n) look(y[n], &again[0]);
+        }
 #pragma unroll
         for (int n = 0; n < 2 * RP; ++n)
             fs_store_rows<M, TY>(rsrc_y, y_vo, (unsigned)(n * (FS_T / P)) * plane_bytes, (unsigned)g.Wo * (unsigned)sizeof(TY),
@@ -723,6 +761,7 @@ __device__ __forceinline__ void fused_split_body(const T *__restrict__ D, const 
                     ys[j / (M / 2)][2 * (j % (M / 2))] = y2[j][0];
                     ys[j / (M / 2)][2 * (j % (M / 2)) + 1] = y2[j][1];
                 }
+                if constexpr (!F16) look(ys, &again[1]);
                 fs_store_rows<M, TY>(rsrc_y, y_vo, (unsigned)(f * (FS_T / P)) * plane_bytes, (unsigned)g.Wo * (unsigned)sizeof(TY),
                                  out_ok && o_k0 + f * (FS_T / P) + irow < g.K, rows, ys);
             }
@@ -731,17 +770,156 @@ __device__ __forceinline__ void fused_split_body(const T *__restrict__ D, const 
     }   // items
 }
 
+template <typename T, typename TY>
+struct FsArgs {
+    const T *D;
+    const char *Us;
+    TY *Y;
+    Geo g;
+    int n_kb, n_tb, groups;
+    float *part;
+};
+
+// Outputs that came out infinite or NaN, once more with fp32 instructions and for themselves alone (bf16x3.h): the whole
+// items of this workgroup (`whole`), the shared one that it added up (`last`).  One phase after the other and one buffer:
+// it is here to be right.
+template <int M>
+__device__ __forceinline__ void fused_split_again(const FsArgs<float, float> &args, float *smem, int wave, bool whole, bool last)
+{
+    const float *const D = args.D;
+    const char *const Us = args.Us;
+    float *const Y = args.Y;
+    const Geo &g = args.g;
+    const int n_kb = args.n_kb, n_tb = args.n_tb, groups = args.groups;
+    constexpr int A = M + 2, NE = A * A, P = fs_tiles(M), TB = P / 32, NU = NE / 4;
+    const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8, slots = gridDim.x / 8;
+    const int group = xcd % groups, kb_per_group = n_kb / groups, kb32 = g.Kp / 32, nsteps = (g.C + FS_C - 1) / FS_C;
+    int first, count;
+    fs_list(xcd, groups, n_kb, n_tb, &first, &count);
+    const FsRounds rounds = fs_rounds(count, slots, nsteps, args.part != nullptr);
+    const int lane = fs_lane(), tid = wave * 64 + lane, li = lane & 31, lh = lane >> 5, simd = wave & 3, role = wave >> 2;
+    for (int it = slot; it < rounds.full + rounds.tail * rounds.shares; it += slots) {
+        if (it < rounds.full ? !whole : !last) continue;
+        const int item = first + (it < rounds.full ? it : rounds.full + (it - rounds.full) % rounds.tail);
+        const int tb = item / kb_per_group, k0 = (group * kb_per_group + item - tb * kb_per_group) * FS_K, b0 = tb * P;
+        floatx16_s acc[NU][TB];
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+#pragma unroll
+            for (int j = 0; j < TB; ++j)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[u][j][i] = 0.0f;
+        for (int step = 0; step < nsteps; ++step) {
+            // transformed tiles, unscaled: [e][tile][channel]
+            for (int id = tid; id < P * FS_C; id += FS_T) {
+                const int b = b0 + id / FS_C, c = step * FS_C + id % FS_C;
+                const int ty = b % g.Tw, tx = b / g.Tw % g.Th, n = b / g.Tw / g.Th;
+                float t[A][A];
+#pragma unroll
+                for (int p = 0; p < A; ++p) {
+                    float d[A];
+#pragma unroll
+                    for (int q = 0; q < A; ++q) {
+                        const int x = M * tx - 1 + p, y = M * ty - 1 + q;
+                        const bool ok = b < g.P && c < g.C && x >= 0 && x < g.H && y >= 0 && y < g.W;
+                        d[q] = ok ? D[(((size_t)n * g.C + c) * g.H + x) * g.W + y] : 0.0f;
+                    }
+                    bt_mul<M>(d, t[p]);
+                }
+#pragma unroll
+                for (int q = 0; q < A; ++q) {
+                    float col[A], o[A];
+#pragma unroll
+                    for (int p = 0; p < A; ++p) col[p] = t[p][q];
+                    bt_mul<M>(col, o);
+#pragma unroll
+                    for (int p = 0; p < A; ++p) smem[(p * A + q) * (FS_C * P) + id] = o[p];
+                }
+            }
+            __syncthreads();
+            // units as in the multiply above; a lane has channels 8 lh .. + 7 of its filter and of its tile
+#pragma unroll
+            for (int u = 0; u < NU; ++u) {
+                const int n = role * NU + u, e = simd * NU + n / 2, kb = min(k0 / 32 + n % 2, kb32 - 1);
+                const char *src = Us + (((size_t)e * nsteps + step) * kb32 + kb) * FS_BLOCK_BYTES + lane * 16;
+                uintx4_b w[3];
+#pragma unroll
+                for (int q = 0; q < 3; ++q) w[q] = *reinterpret_cast<const uintx4_b *>(src + q * 1024);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const unsigned h = w[0][i / 2] >> 16 * (i % 2) & 0xffffu, m = w[1][i / 2] >> 16 * (i % 2) & 0xffffu,
+                                   l = w[2][i / 2] >> 16 * (i % 2) & 0xffffu;
+                    const float sum = __builtin_bit_cast(float, h << 16) + (__builtin_bit_cast(float, m << 16) + __builtin_bit_cast(float, l << 16));
+                    const float f = (h & 0x7fffu) > 0x7f80u ? __builtin_bit_cast(float, m << 16 | l) : sum * (1.0f / BF16_SCALE);
+#pragma unroll
+                    for (int j = 0; j < TB; ++j)
+                        acc[u][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(f, smem[e * (FS_C * P) + (j * 32 + li) * FS_C + 8 * lh + i], acc[u][j], 0, 0, 0);
+                }
+            }
+            __syncthreads();
+        }
+        const int b = b0 + tid % P, ty = b % g.Tw, tx = b / g.Tw % g.Th, n = b / g.Tw / g.Th;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int u = 0; u < NU; ++u) {
+                if ((role * NU + u) % 2 != h) continue;
+#pragma unroll
+                for (int j = 0; j < TB; ++j)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i)
+                        smem[((simd * NU + (role * NU + u) / 2) * 32 + 8 * (i / 4) + 4 * lh + i % 4) * P + j * 32 + li] = acc[u][j][i];
+            }
+            __syncthreads();
+            for (int row = tid / P; row < 32; row += FS_T / P) {
+                const int k = k0 + h * 32 + row;
+                if (b >= g.P || k >= g.K) continue;
+                float tt[M][A], y[M];
+#pragma unroll
+                for (int nu = 0; nu < A; ++nu) {
+                    float col[A], o[M];
+#pragma unroll
+                    for (int xi = 0; xi < A; ++xi) col[xi] = smem[((xi * A + nu) * 32 + row) * P + tid % P];
+                    at_mul<M>(col, o);
+#pragma unroll
+                    for (int p = 0; p < M; ++p) tt[p][nu] = o[p];
+                }
+#pragma unroll
+                for (int p = 0; p < M; ++p) {
+                    at_mul<M>(tt[p], y);
+                    if (M * tx + p >= g.Ho) continue;
+                    float *at = Y + (((size_t)n * g.K + k) * g.Ho + M * tx + p) * g.Wo + M * ty;
+#pragma unroll
+                    for (int q = 0; q < M; ++q)
+                        if (!bf16_finite(at[q])) at[q] = y[q];
+                }
+            }
+            __syncthreads();
+        }
+    }
+}
+
 template <int M, bool CPAD, typename T, typename TY>
-__global__ __launch_bounds__(FS_T, 2) void fused_split_kernel(const T *__restrict__ D, const char *__restrict__ Us,
-                                                              TY *__restrict__ Y, Geo g, int n_kb, int n_tb, int groups,
-                                                              float *__restrict__ part)
+__global__ __launch_bounds__(FS_T, 2) void fused_split_kernel(FsArgs<T, TY> a)
 {
     __shared__ __attribute__((aligned(16))) float smem[2 * fs_v_floats(M)];
+    __shared__ int again[2];                   // some output is not finite: of a whole item, of the shared one
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (threadIdx.x < 2) again[threadIdx.x] = 0;
     if (wave < 4)
-        fused_split_body<M, CPAD, T, TY, 0>(D, Us, Y, g, n_kb, n_tb, groups, part, smem, wave);
+        fused_split_body<M, CPAD, T, TY, 0>(a.D, a.Us, a.Y, a.g, a.n_kb, a.n_tb, a.groups, a.part, smem, again, wave);
     else
-        fused_split_body<M, CPAD, T, TY, 1>(D, Us, Y, g, n_kb, n_tb, groups, part, smem, wave);
+        fused_split_body<M, CPAD, T, TY, 1>(a.D, a.Us, a.Y, a.g, a.n_kb, a.n_tb, a.groups, a.part, smem, again, wave);
+    if constexpr (sizeof(T) == 4) {
+        __syncthreads();
+        const bool whole = again[0] != 0, last = again[1] != 0;
+        if (whole || last) {
+            // (the arguments read anew, or their registers would be taken from the loops above)
+            auto *args = (const __attribute__((address_space(4))) FsArgs<T, TY> *)__builtin_amdgcn_kernarg_segment_ptr();
+            asm volatile("" : "+s"(args));
+            fused_split_again<M>(*(const FsArgs<T, TY> *)args, smem, wave, whole, last);
+        }
+    }
 }
 
 static int fs_n_kb(const Geo &g) { return (g.Kp + FS_K - 1) / FS_K; }
@@ -824,19 +1002,20 @@ static hipError_t fs_launch(const Geo &g, const T *D, const char *Us, TY *Y, int
     const int items = n_kb * n_tb;
     const dim3 grid((unsigned)(items >= FS_GRID ? FS_GRID : (items + 7) / 8 * 8)), block(FS_T);
     const bool cpad = g.C % FS_C != 0;
+    const FsArgs<T, TY> args = {D, Us, Y, g, n_kb, n_tb, groups, part};
     if constexpr (sizeof(T) == 4) {
         if (g.m == 2) {
             if (cpad)
-                fused_split_kernel<2, true, T, TY><<<grid, block, 0, s>>>(D, Us, Y, g, n_kb, n_tb, groups, part);
+                fused_split_kernel<2, true, T, TY><<<grid, block, 0, s>>>(args);
             else
-                fused_split_kernel<2, false, T, TY><<<grid, block, 0, s>>>(D, Us, Y, g, n_kb, n_tb, groups, part);
+                fused_split_kernel<2, false, T, TY><<<grid, block, 0, s>>>(args);
             return hipGetLastError();
         }
     }
     if (cpad)
-        fused_split_kernel<4, true, T, TY><<<grid, block, 0, s>>>(D, Us, Y, g, n_kb, n_tb, groups, part);
+        fused_split_kernel<4, true, T, TY><<<grid, block, 0, s>>>(args);
     else
-        fused_split_kernel<4, false, T, TY><<<grid, block, 0, s>>>(D, Us, Y, g, n_kb, n_tb, groups, part);
+        fused_split_kernel<4, false, T, TY><<<grid, block, 0, s>>>(args);
     return hipGetLastError();
 }
 

@@ -32,6 +32,29 @@ template <> __device__ __forceinline__ void bt_mul<4>(const float *d, float *o)
     o[5] = fmaf(4.0f, d[1], fmaf(-5.0f, d[3], d[5]));
 }
 
+// out = s B^T in, s a power of two: one multiplication per input that no fused multiply-add can take it from
+template <int M> __device__ __forceinline__ void bt_mul_scaled(const float *in, float *out, float s);
+template <> __device__ __forceinline__ void bt_mul_scaled<2>(const float *d, float *o, float s)
+{
+    const float s1 = s * d[1], s2 = s * d[2];
+    o[0] = fmaf(s, d[0], -s2);
+    o[1] = s1 + s2;
+    o[2] = s2 - s1;
+    o[3] = fmaf(-s, d[3], s1);
+}
+template <> __device__ __forceinline__ void bt_mul_scaled<4>(const float *d, float *o, float s)
+{
+    const float s3 = s * d[3], s4 = s * d[4], s5 = s * d[5];
+    const float s42 = fmaf(-4.0f * s, d[2], s4), s31 = fmaf(-4.0f * s, d[1], s3);
+    const float t42 = fmaf(-s, d[2], s4), t31 = 2.0f * fmaf(-s, d[1], s3);
+    o[0] = fmaf(4.0f * s, d[0], fmaf(-5.0f * s, d[2], s4));
+    o[1] = s42 + s31;
+    o[2] = s42 - s31;
+    o[3] = t42 + t31;
+    o[4] = t42 - t31;
+    o[5] = fmaf(4.0f * s, d[1], fmaf(-5.0f * s, d[3], s5));
+}
+
 template <> __device__ __forceinline__ void bt_mul<6>(const float *d, float *o)
 {
     // rows of B^T: (1,0,-21/4,0,21/4,0,-1,0) (0,1,1,-17/4,-17/4,1,1,0) (0,-1,1,17/4,-17/4,-1,1,0)

@@ -125,6 +125,90 @@ def test_multiply_single_values(K, C, P, value):
     assert (got[rest] == plain[rest]).all()
 
 
+# ---- one-kernel layers --------------------------------------------------------------------------
+
+# 132 items; a full round and 15 items per XCD in two shares; F(2x2,3x3): whole items; a shared last round
+LAYERS = [(4, (20, 17, 28, 60, 70)), (4, (17, 128, 28, 44, 513)), (2, (13, 17, 30, 46, 70)), (2, (6, 256, 48, 60, 400))]
+
+
+def points_check(w, torch, D, G, Y, m, tol, what):
+    pts = synth.sample_points(Y.shape, 2000, seed=5, edge=m)
+    check(Y[tuple(pts.T)], direct.conv2d_points(D, G, pts, pad=1), tol, what)
+
+
+@pytest.mark.parametrize("m,shape", LAYERS)
+@pytest.mark.parametrize("given", ["G", "U"])
+@pytest.mark.parametrize("scale", ["tiny data", "tiny filters", "huge data", "huge filters"])
+def test_layer_scaled(m, shape, given, scale):
+    torch, w = require_gpu()
+    N, C, H, W, K = shape
+    D, G = synth.make_layer(N, C, H, W, K, seed=sum(shape) + m)
+    D, G = scaled(D, SCALES[scale][0]), scaled(G, SCALES[scale][1])
+    g = to_gpu(G)
+    kw = dict(G=g) if given == "G" else dict(U=w.wino_filter_transform(g, m), K=K)
+    Y = w.wino_conv2d_fwd_ex(to_gpu(D), pad=1, m=m, flags=w.FLAG_FUSED, **kw)
+    Y2 = w.wino_conv2d_fwd_ex(to_gpu(D), pad=1, m=m, flags=w.FLAG_FUSED, **kw)
+    assert torch.equal(Y, Y2)
+    points_check(w, torch, D, G, Y.cpu().numpy(), m, TOL[("f32", m)], "F(%d) %s %s %s" % (m, shape, given, scale))
+
+
+def wino_layer(D, G, m, image):
+    """One image by the definition of the algorithm, on terms as the kernels form them."""
+    Bt, Gm, At = (np.array(x, dtype=np.float64) for x in wg.matrices(m))
+    C, H, W = D.shape[1:]
+    Th, Tw = -(-H // m), -(-W // m)
+    d = np.zeros((C, Th * m + 2, Tw * m + 2))
+    d[:, 1:H + 1, 1:W + 1] = D[image]
+    tiles = np.stack([np.stack([d[:, m * x:m * x + m + 2, m * y:m * y + m + 2] for y in range(Tw)]) for x in range(Th)])
+    v = terms(Bt, terms(Bt, tiles, 3), 4)                         # [Th][Tw][C][a][a]
+    u = terms(Gm, terms(Gm, G.astype(np.float64), 2), 3)          # [K][C][a][a]
+    M = np.zeros((G.shape[0], Th, Tw, m + 2, m + 2))
+    for c in range(C):
+        M += u[:, c, None, None] * v[None, :, :, c]
+    y = terms(At, terms(At, M, 3), 4)                             # [K][Th][Tw][m][m]
+    return y.transpose(0, 1, 3, 2, 4).reshape(G.shape[0], Th * m, Tw * m)[:, :H, :W]
+
+
+@pytest.mark.parametrize("m,shape", [(4, (20, 17, 28, 60, 70)), (2, (13, 17, 30, 46, 70))])
+@pytest.mark.parametrize("value", [np.inf, -np.inf, FLT_MAX, np.nan])
+def test_layer_single_values(m, shape, value):
+    torch, w = require_gpu()
+    N, C, H, W, K = shape
+    if m == 4 and value == FLT_MAX:
+        value = np.float32(2.0 ** 120)                            # (16 times FLT_MAX, which the transform forms, is infinite)
+    D, G = synth.make_layer(N, C, H, W, K, seed=sum(shape) + m)
+    G *= np.float32(2.0 ** -6)
+    g = to_gpu(G)
+    plain = w.wino_conv2d_fwd_ex(to_gpu(D), G=g, pad=1, m=m, flags=w.FLAG_FUSED).cpu().numpy()
+    for at in ((0, 0, 0, 0), (N - 1, C - 1, H - 1, W - 1), (4, 3, 13, 31)):
+        X = D.copy()
+        X[at] = value
+        Y = w.wino_conv2d_fwd_ex(to_gpu(X), G=g, pad=1, m=m, flags=w.FLAG_FUSED).cpu().numpy()
+        with np.errstate(invalid="ignore"):
+            check(Y[at[0]], wino_layer(X, G, m, at[0]), TOL[("f32", m)], "F(%d) %s, %g at %s" % (m, shape, value, at))
+        X[at] = np.nan
+        out = np.ones(Y.shape, dtype=bool)
+        out[at[0]] = ~np.isnan(wino_layer(X, G, m, at[0]))
+        assert (Y[out] == plain[out]).all()
+
+
+def test_layer_single_value_in_a_shared_item():
+    """The last round's items of this layer are summed from shares of their channels: an infinite value in the last tile."""
+    torch, w = require_gpu()
+    m, (N, C, H, W, K) = 2, (6, 256, 48, 60, 400)
+    D, G = synth.make_layer(N, C, H, W, K, seed=11)
+    g = to_gpu(G)
+    plain = w.wino_conv2d_fwd_ex(to_gpu(D), G=g, pad=1, m=m, flags=w.FLAG_FUSED).cpu().numpy()
+    D[N - 1, 200, H - 1, W - 1] = np.inf
+    Y = w.wino_conv2d_fwd_ex(to_gpu(D), G=g, pad=1, m=m, flags=w.FLAG_FUSED).cpu().numpy()
+    near = np.zeros(Y.shape, dtype=bool)
+    near[N - 1, :, H - 2:, W - 2:] = True
+    assert (Y[~near] == plain[~near]).all()
+    with np.errstate(invalid="ignore"):
+        ref = wino_layer(D[:, :, H - 8:, W - 8:], G, m, N - 1)[:, -2:, -2:]
+    check(Y[N - 1, :, -2:, -2:], ref, TOL[("f32", m)], "shared item")
+
+
 # ---- filter gradient ----------------------------------------------------------------------------
 
 WGRAD = [(5, 70, 9, 20, 130), (3, 320, 28, 28, 288)]
