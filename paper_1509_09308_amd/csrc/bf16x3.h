@@ -20,6 +20,12 @@
 // not finite again with fp32 instructions, from the operands as they are: they become what a chain of fp32 multiply-adds
 // gives (finite, infinite or NaN), and no other sum is touched.  A layer whose data is all NaN takes three to five times as
 // long for it (256 -> 256 channels at 56 x 56, F(4x4,3x3), N = 16: 158 us, all NaN 776).
+//
+// Long sums.  A product of low parts below half a unit in the last place of the sum it is added to is lost.  As a rule
+// such losses cancel, but where all of these products have one sign (operands between 1 and 1 + 2^-7: m m) sums of many
+// thousand terms fall short: relative error at 2048 terms 4.2e-7 (a chain of fp32 multiply-adds 6.0e-7), at 8192 6.1e-6
+// (1.2e-6), at 65000 1.5e-5 (3.3e-6).  So sums of more than BF16_LONG terms in a row are set aside every BF16_RUN terms
+// and added up as fp32 values.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -47,6 +53,7 @@ __device__ __forceinline__ void bf16_split2(float x, float y, unsigned &h, unsig
 }
 
 constexpr float BF16_SCALE = 0x1p24f, BF16_UNSCALE = 0x1p-48f;       // of operands and of sums
+constexpr int BF16_LONG = 2048, BF16_RUN = 1024;       // terms of a sum that has to be set aside, and how often
 
 // the three operand words (eight reduction steps each) of eight values
 __device__ __forceinline__ void bf16_split8(const float (&x)[8], uintx4_b (&p)[3], float scale)

@@ -59,17 +59,19 @@ __device__ __forceinline__ unsigned gemm_offset(unsigned long long floats)
 // ONE: the share is one slab.  Then there is nothing to overlap within a workgroup and what bounds the launch is writing
 // M: no second slab, half the LDS, twice the workgroups per CU, and no matrix instructions for the empty half of a
 // slab (64 products of 32 x 16 by 16 x 3600: layer 32.8 -> 30.3 us).
-template <int BM, int BN, int BK, bool ONE>
-__global__ __launch_bounds__(256, ONE && BM * BN < 128 * 128 ? 4 : 2) void gemm_f32_kernel(const float *__restrict__ U, const float *__restrict__ V,
-                                                          float *__restrict__ Mo, int Kp, int Cp, int Pp, int tiles_m,
-                                                          int tiles_n, int a2, int c_share)
+// LONG: the share is longer than BF16_LONG channels, so its sums are set aside now and then (bf16x3.h), where M will be.
+enum { ONE, USUAL, LONG };
+template <int BM, int BN, int BK, int DEPTH>
+__global__ __launch_bounds__(256, DEPTH == ONE && BM * BN < 128 * 128 ? 4 : 2) void gemm_f32_kernel(
+    const float *__restrict__ U, const float *__restrict__ V, float *__restrict__ Mo, int Kp, int Cp, int Pp, int tiles_m,
+    int tiles_n, int a2, int c_share)
 {
     constexpr int TM = BM / 64, TN = BN / 64;
     constexpr int G8 = BK / 8;                                   // groups of eight channels per slab
     constexpr int AG = G8 * BM / 256, BG = G8 * BN / 256;        // groups a thread fetches
     static_assert(G8 * BM % 256 == 0 && G8 * BN % 256 == 0 && BK % 16 == 0, "a slab divides evenly among the threads");
-    __shared__ uintx4_b As[ONE ? 1 : 2][G8 * 3 * BM];
-    __shared__ uintx4_b Bs[ONE ? 1 : 2][G8 * 3 * BN];
+    __shared__ uintx4_b As[DEPTH == ONE ? 1 : 2][G8 * 3 * BM];
+    __shared__ uintx4_b Bs[DEPTH == ONE ? 1 : 2][G8 * 3 * BN];
 
     int bid = xcd_remap(blockIdx.x, gridDim.x);
     const int tm_i = bid % tiles_m;
@@ -178,7 +180,22 @@ __global__ __launch_bounds__(256, ONE && BM * BN < 128 * 128 ? 4 : 2) void gemm_
         }
     };
 
-    if constexpr (ONE) {
+    // Accumulator register r of lane (li, lh) is row 8*(r/4) + 4*lh + r%4, column li of its tile; Kp and Pp are multiples of
+    // 32, so a 32 x 32 tile is entirely inside or entirely outside.
+    auto each = [&](auto f) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int ct = p0 + wn * (TN * 32) + j * 32, rt = k0 + wm * (TM * 32) + i * 32;
+                if (ct < Pp && rt < Kp) {
+                    float *dst = Me + (size_t)(rt + 4 * lh) * Pp + ct + li;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[i][j][r] = f(acc[i][j][r], dst[(size_t)(8 * (r / 4) + (r % 4)) * Pp]);
+                }
+            }
+    };
+    if constexpr (DEPTH == ONE) {
         request(0, 0);
         store(0, 0);
         gemm_lds_barrier();
@@ -214,6 +231,12 @@ __global__ __launch_bounds__(256, ONE && BM * BN < 128 * 128 ? 4 : 2) void gemm_
     for (; kt + 2 < nk; kt += 2) {
         slab(kt, 0);
         slab(kt + 1, 1);
+        if (DEPTH == LONG && (kt + 2) % (BF16_RUN / BK) == 0) {
+            if (kt + 2 == BF16_RUN / BK)
+                each([](float sum, float &m) { m = sum; return 0.0f; });
+            else
+                each([](float sum, float &m) { m += sum; return 0.0f; });
+        }
     }
     // the last slab is multiplied only, and only as deep as it is filled (384 filters, 48 channels, 216 tiles, F(6x6,3x3):
     // layer 33.5 -> 32.1 us; 12 channels of 20 images at 40 x 40, F(2x2,3x3): 31.7 -> 30.0)
@@ -226,6 +249,7 @@ __global__ __launch_bounds__(256, ONE && BM * BN < 128 * 128 ? 4 : 2) void gemm_
     }
     }
 
+    if (DEPTH == LONG) each([](float sum, float &m) { return m + sum; });
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -251,19 +275,7 @@ __global__ __launch_bounds__(256, ONE && BM * BN < 128 * 128 ? 4 : 2) void gemm_
                 if (!bf16_finite(acc[i][j][r])) acc[i][j][r] = exact[r];
         }
 
-    // accumulator register r of lane (li, lh) is row 8*(r/4) + 4*lh + r%4, column li of its tile;
-    // Kp and Pp are multiples of 32, so a 32 x 32 tile is entirely inside or entirely outside
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int ct = p0 + wn * (TN * 32) + j * 32, rt = k0 + wm * (TM * 32) + i * 32;
-            if (ct < Pp && rt < Kp) {
-                float *dst = Me + (size_t)(rt + 4 * lh) * Pp + ct + li;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) dst[(size_t)(8 * (r / 4) + (r % 4)) * Pp] = acc[i][j][r];
-            }
-        }
+    each([](float sum, float &m) { return m = sum; });
 }
 
 template <int BM, int BN, int BK>
@@ -277,12 +289,13 @@ static hipError_t launch_f32(const Geo &g, const float *U, const float *V, float
     // 32-bit byte offsets inside one component of U and of V
     if ((unsigned long long)g.Cp * g.Pp * 4ull >= (1ull << 32) || (unsigned long long)g.Cp * g.Kp * 4ull >= (1ull << 32))
         return hipErrorNotSupported;
+    const dim3 grid((unsigned)blocks), block(256);
     if (c_share <= BK)
-        gemm_f32_kernel<BM, BN, BK, true><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(U, V, M, g.Kp, g.Cp, g.Pp, tiles_m,
-                                                                                       tiles_n, g.a2, c_share);
+        gemm_f32_kernel<BM, BN, BK, ONE><<<grid, block, 0, s>>>(U, V, M, g.Kp, g.Cp, g.Pp, tiles_m, tiles_n, g.a2, c_share);
+    else if (c_share <= BF16_LONG)
+        gemm_f32_kernel<BM, BN, BK, USUAL><<<grid, block, 0, s>>>(U, V, M, g.Kp, g.Cp, g.Pp, tiles_m, tiles_n, g.a2, c_share);
     else
-        gemm_f32_kernel<BM, BN, BK, false><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(U, V, M, g.Kp, g.Cp, g.Pp, tiles_m,
-                                                                                        tiles_n, g.a2, c_share);
+        gemm_f32_kernel<BM, BN, BK, LONG><<<grid, block, 0, s>>>(U, V, M, g.Kp, g.Cp, g.Pp, tiles_m, tiles_n, g.a2, c_share);
     return hipGetLastError();
 }
 

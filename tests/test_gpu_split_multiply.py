@@ -65,3 +65,29 @@ def test_multiply_of_many_tiles(C):
     for e in range(16):
         for p in range(0, P, 3000000):      # whole numbers below 2^24: exact in any order
             assert torch.equal(M[e, :, p:min(p + 3000000, P)], U[e].t().contiguous() @ V[e, :, p:min(p + 3000000, P)])
+
+
+def near_one(rng, *shape):
+    """Values between 1 and 1 + 2^-7: the products of their low parts have one sign."""
+    return (1.0 + rng.random(shape) * 2.0 ** -7).astype(np.float32)
+
+
+@pytest.mark.parametrize("data", ["positive", "near one"])
+@pytest.mark.parametrize("K,C,P", [(40, 2048, 40), (40, 2100, 40), (130, 3100, 1000), (40, 20000, 40)])
+def test_long_sums_are_as_precise_as_fp32(K, C, P, data):
+    """Small products must not be lost against a large sum."""
+    torch, w = require_gpu()
+    m, a = 2, 4
+    rng = np.random.default_rng(K + C + P)
+    make = near_one if data == "near one" else (lambda r, *shape: r.random(shape).astype(np.float32))
+    u, v = make(rng, 1, 1, K, C), make(rng, 1, 1, C, P)
+    full = lambda x: np.broadcast_to(x, (a, a) + x.shape[2:])
+    M = w.unpack_m(w.wino_batched_gemm(w.pack_u(full(u), m), w.pack_v(full(v), m), K, C, P, m), K, P, m)
+    assert (M == M[:1, :1]).all()
+    ref = u[0, 0].astype(np.float64) @ v[0, 0].astype(np.float64)
+    chain = np.zeros((K, P), dtype=np.float32)                  # fp32 multiply-adds in channel order (rounded twice)
+    for c in range(C):
+        chain += u[0, 0, :, c, None] * v[0, 0, None, c, :]
+    e, ec = rel_err(M[0, 0], ref), rel_err(chain, ref)
+    print("K=%d C=%d P=%d %s: rel err %.2e, fp32 chain %.2e" % (K, C, P, data, e, ec))
+    assert e <= ec
