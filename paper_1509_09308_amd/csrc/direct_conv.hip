@@ -253,8 +253,9 @@ struct DgGeo {
     int tiles_m;
 };
 
-template <typename T, int BM, int BN, int KS>
-__global__ __launch_bounds__(256 * KS) void direct_gemm_kernel(const T *__restrict__ D, const T *__restrict__ G, T *__restrict__ Y,
+// LONG: more than BF16_LONG taps per group, whose sums are set aside now and then (bf16x3.h).
+template <typename T, int BM, int BN, int KS, bool LONG>
+__global__ __launch_bounds__(256 * KS, LONG && KS == 1 ? 4 : 1) void direct_gemm_kernel(const T *__restrict__ D, const T *__restrict__ G, T *__restrict__ Y,
                                                              DgGeo g, unsigned g_bytes, size_t d_elems)
 {
     constexpr bool F32 = sizeof(T) == 4;
@@ -416,11 +417,47 @@ __global__ __launch_bounds__(256 * KS) void direct_gemm_kernel(const T *__restri
         store(odd ^ 1, odd ^ 1);
         dg_lds_barrier();
     };
+    // accumulator register r of lane (li, lh) is filter row 8 (r / 4) + 4 lh + r % 4, pixel li of its tile
+    auto each = [&](auto f) {
+        int first = p0 + wn * TN * 32;
+        asm volatile("" : "+s"(first));           // (opaque: no address is formed ahead of where it is used)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int p = first + j * 32 + li;
+            if (p < g.P) {
+                const int n = p / plane;
+                T *dst = Y + ((size_t)n * g.K + k0 + wm * 32 + 4 * lh) * plane + (p - n * plane);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int kk = 8 * (r / 4) + r % 4;
+                    if (k0 + wm * 32 + 4 * lh + kk < g.K) acc[j][r] = f(acc[j][r], dst + (size_t)kk * plane);
+                }
+            }
+        }
+    };
+    // set aside in registers, or, where there is one group only, where the result will be (64 x 128 blocks lose half of
+    // their workgroups per CU to the registers: 512 -> 512 channels at 28 x 28, stride 2, N = 64: 665 us with sums of one
+    // run, 874 set aside in registers, 700 so)
+    constexpr bool IN_Y = LONG && KS == 1;
+    floatx16_dc aside[LONG && !IN_Y ? TN : 1] = {};
     for (; t + 1 < steps; t += 2) {
         step(0);
         step(1);
+        if (IN_Y && (t + 2) % (BF16_RUN / DG_STEP) == 0) {
+            const bool first = t + 2 == BF16_RUN / DG_STEP;
+            each([first](float sum, T *y) { st_d<T>(y, first ? sum : ld_d<T>(y) + sum); return 0.0f; });
+        }
+        if (LONG && !IN_Y && (t + 2) % (BF16_RUN / DG_STEP) == 0) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j) aside[j] += acc[j], acc[j] = floatx16_dc{};
+        }
     }
     if (t < steps) multiply(0);
+    if constexpr (IN_Y) each([](float sum, T *y) { return ld_d<T>(y) + sum; });
+    if constexpr (LONG && !IN_Y) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[j] += aside[j];
+    }
     if constexpr (KS > 1) {
         // the groups' sums, added in order by the first: [group - 1][register][thread]
         float *sums = reinterpret_cast<float *>(lds);
@@ -473,20 +510,7 @@ __global__ __launch_bounds__(256 * KS) void direct_gemm_kernel(const T *__restri
         }
     }
 
-    // accumulator register r of lane (li, lh) is filter row 8 (r / 4) + 4 lh + r % 4, pixel li of its tile
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const int p = p0 + (wn * TN + j) * 32 + li;
-        if (p < g.P) {
-            const int n = p / plane;
-            T *dst = Y + ((size_t)n * g.K + k0 + wm * 32 + 4 * lh) * plane + (p - n * plane);
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int kk = 8 * (r / 4) + r % 4;
-                if (k0 + wm * 32 + 4 * lh + kk < g.K) st_d<T>(dst + (size_t)kk * plane, acc[j][r]);
-            }
-        }
-    }
+    each([](float sum, T *y) { st_d<T>(y, sum); return sum; });
 }
 
 // What the product form takes: the images one block of pixels touches within 31-bit byte offsets, filters likewise,
@@ -507,8 +531,18 @@ static hipError_t launch_direct_gemm(DgGeo g, int N, const void *D, const void *
     g.tiles_m = (g.K + BM - 1) / BM;
     g.dv = DG_STEP * KS % g.S, g.du = DG_STEP * KS / g.S % g.R, g.dc = DG_STEP * KS / g.S / g.R;
     const long long blocks = (long long)g.tiles_m * ((g.P + BN - 1) / BN);
-    direct_gemm_kernel<T, BM, BN, KS><<<dim3((unsigned)blocks), dim3(256 * KS), 0, s>>>(
-        (const T *)D, (const T *)G, (T *)Y, g, (unsigned)((size_t)g.K * g.J * sizeof(T)), (size_t)N * g.C * g.H * g.W);
+    const unsigned g_bytes = (unsigned)((size_t)g.K * g.J * sizeof(T));
+    const size_t d_elems = (size_t)N * g.C * g.H * g.W;
+    const dim3 grid((unsigned)blocks), block(256 * KS);
+    if constexpr (sizeof(T) == 4) {
+        // (several groups: half as long again is still less than what a chain over all taps rounds off, 6100 taps of
+        // operands between 1 and 1 + 2^-7, two groups: see below; and two groups with sums set aside are 7 % slower)
+        if (g.J > (KS == 1 ? BF16_LONG : BF16_LONG * 3 / 2 * KS)) {
+            direct_gemm_kernel<T, BM, BN, KS, true><<<grid, block, 0, s>>>((const T *)D, (const T *)G, (T *)Y, g, g_bytes, d_elems);
+            return hipGetLastError();
+        }
+    }
+    direct_gemm_kernel<T, BM, BN, KS, false><<<grid, block, 0, s>>>((const T *)D, (const T *)G, (T *)Y, g, g_bytes, d_elems);
     return hipGetLastError();
 }
 

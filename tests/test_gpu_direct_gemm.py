@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 
 from oracle import direct
-from gpu_util import check_close, require_gpu, to_gpu
+from gpu_util import check_close, rel_err, require_gpu, to_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -37,3 +37,34 @@ def test_direct_product(N, C, H, W, K, R, S, pad, stride, dtype):
     ref = direct.conv2d_fwd(D.astype(np.float32), G.astype(np.float32), pad=pad, stride=stride)
     # fp32: a rounding per tap at most (2^-24 each, random: under 1e-6 in norm); fp16: one rounding of Y, 2^-11 at most
     check_close(Y, ref, 1e-6 if dtype == "f32" else 4.9e-4, "direct %s" % dtype)
+
+
+@pytest.mark.parametrize("data", ["positive", "near one"])
+@pytest.mark.parametrize("C,H,K,R,stride,N", [
+    (2100, 20, 72, 1, 1, 2),         # four groups of steps, 525 taps each
+    (13000, 9, 40, 1, 1, 2),         # the same, set aside
+    (13000, 9, 24, 1, 1, 2),         # 32 filters
+    (677, 47, 72, 3, 1, 7),          # two groups of 3046 taps
+    (700, 47, 72, 3, 1, 7),          # two groups, set aside
+    (530, 47, 72, 3, 1, 10),         # one group, 4770 taps
+    (240, 48, 136, 3, 1, 13),        # wide blocks, 2160 taps
+    (240, 48, 20, 3, 1, 32),
+])
+def test_long_sums_are_as_precise_as_fp32(C, H, K, R, stride, N, data):
+    """Small products must not be lost against a large sum; operands between 1 and 1 + 2^-7 have those of one sign."""
+    torch, w = require_gpu()
+    rng = np.random.default_rng(C + H + K + R)
+    make = (lambda *s: (1.0 + rng.random(s) * 2.0 ** -7).astype(np.float32)) if data == "near one" else \
+           (lambda *s: rng.random(s).astype(np.float32))
+    D, G = make(N, C, H, H), make(K, C, R, R)
+    Y = w.direct_conv2d_fwd(to_gpu(D), to_gpu(G), pad=0, stride=stride).cpu().numpy()
+    pts = np.array([[n, k, x, y] for n in (0, N - 1) for k in range(0, K, 5) for x in (0, H // 2 - R) for y in (1, H // 2 - R)], dtype=np.int32)
+    ref = direct.conv2d_points(D, G, pts, pad=0, stride=stride)
+    chain = np.zeros(len(pts), dtype=np.float32)                # fp32 multiply-adds in tap order (rounded twice)
+    for c in range(C):
+        for u in range(R):
+            for v in range(R):
+                chain += D[pts[:, 0], c, pts[:, 2] * stride + u, pts[:, 3] * stride + v] * G[pts[:, 1], c, u, v]
+    e, ec = rel_err(Y[tuple(pts.T)], ref), rel_err(chain, ref)
+    print("%s %s: rel err %.2e, fp32 chain %.2e" % ((C, H, K, R, N), data, e, ec))
+    assert e <= ec
