@@ -275,8 +275,9 @@ __device__ __forceinline__ void wf_lds_barrier()             // orders LDS traff
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// ERR: wavefronts 0 - 3 (error blocks, transform first), else 4 - 7 (input tiles, multiply first)
-template <bool ERR>
+// ERR: wavefronts 0 - 3 (error blocks, transform first), else 4 - 7 (input tiles, multiply first).
+// LONG: shares of more than BF16_LONG blocks, whose sums are set aside now and then (bf16x3.h), where the partial M will be.
+template <bool ERR, bool LONG>
 __device__ __forceinline__ void wgrad_fused_body(const float *__restrict__ X, float *__restrict__ Mo, const WgradGeo &g, int kt,
                                                  int ct, int z, int slabs_per_share, float *smem, int wave)
 {
@@ -462,6 +463,31 @@ __device__ __forceinline__ void wgrad_fused_body(const float *__restrict__ X, fl
     const float scale = ERR ? sign * BF16_SCALE : BF16_SCALE;
     place();
     clear();
+    float t = 0.0f;
+    bool add = false;
+    auto write = [&](bool again, float factor) {
+        int first = 2 * wave;
+        asm volatile("" : "+s"(first));        // (opaque: no address is formed ahead of where it is used)
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const int rt = kt * 64 + i * 32, ctile = ct * 64 + j * 32;
+                    if (rt < g.Kp && ctile < g.Cq) {
+                        float *dst = Mo + (((size_t)z * 16 + first + e) * g.Kp + rt + 4 * lh) * g.Cq + ctile + li;
+#pragma unroll
+                        for (int q = 0; q < 16; ++q) {
+                            float *at = dst + (size_t)(8 * (q / 4) + (q % 4)) * g.Cq;
+                            float m = factor * acc[e][i][j][q];
+                            if (LONG && add) m += *at;
+                            if (!again) t = bf16_look(m, m, t);
+                            if (!again || !bf16_finite(*at)) *at = m;
+                        }
+                    }
+                }
+    };
     if (slab_lo < slab_hi) {
         load_raw();
         transform(0, scale);
@@ -483,32 +509,16 @@ __device__ __forceinline__ void wgrad_fused_body(const float *__restrict__ X, fl
                 multiply(buf);
                 __builtin_amdgcn_s_setprio(0);
             }
+            if (LONG && more && (slab + 1 - slab_lo) % (BF16_LONG / WF_BK) == 0) {
+                write(false, sign * BF16_UNSCALE);
+                clear();
+                add = true;
+            }
             wf_lds_barrier();
         } while (++slab < slab_hi);
     }
 
     // a share past the end of the blocks still writes its (zero) partial M
-    float t = 0.0f;
-    auto write = [&](bool again, float factor) {
-#pragma unroll
-        for (int e = 0; e < 2; ++e)
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    const int rt = kt * 64 + i * 32, ctile = ct * 64 + j * 32;
-                    if (rt < g.Kp && ctile < g.Cq) {
-                        float *dst = Mo + (((size_t)z * 16 + 2 * wave + e) * g.Kp + rt + 4 * lh) * g.Cq + ctile + li;
-#pragma unroll
-                        for (int q = 0; q < 16; ++q) {
-                            float *at = dst + (size_t)(8 * (q / 4) + (q % 4)) * g.Cq;
-                            const float m = factor * acc[e][i][j][q];
-                            if (!again) t = bf16_look(m, m, t);
-                            if (!again || !bf16_finite(*at)) *at = m;
-                        }
-                    }
-                }
-    };
     write(false, sign * BF16_UNSCALE);
 
     // Sums that are not finite: the share once more with fp32 instructions (bf16x3.h), one phase after the other, keeping
@@ -523,6 +533,7 @@ __device__ __forceinline__ void wgrad_fused_body(const float *__restrict__ X, fl
     if (again) {
         place();
         clear();
+        add = false;
         for (int slab = slab_lo; slab < slab_hi; ++slab) {
             load_raw();
             transform(0, 1.0f);
@@ -544,6 +555,7 @@ __device__ __forceinline__ void wgrad_fused_body(const float *__restrict__ X, fl
     }
 }
 
+template <bool LONG>
 __global__ __launch_bounds__(WF_T, 2) void wgrad_fused_kernel(const float *__restrict__ D, const float *__restrict__ E,
                                                               float *__restrict__ Mo, WgradGeo g, int tiles_k, int tiles_c,
                                                               int slabs_per_share)
@@ -558,9 +570,9 @@ __global__ __launch_bounds__(WF_T, 2) void wgrad_fused_kernel(const float *__res
     const int z = bid / tiles_c;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (wave < 4)
-        wgrad_fused_body<true>(E, Mo, g, kt, ct, z, slabs_per_share, smem, wave);
+        wgrad_fused_body<true, LONG>(E, Mo, g, kt, ct, z, slabs_per_share, smem, wave);
     else
-        wgrad_fused_body<false>(D, Mo, g, kt, ct, z, slabs_per_share, smem, wave);
+        wgrad_fused_body<false, LONG>(D, Mo, g, kt, ct, z, slabs_per_share, smem, wave);
 }
 
 // First level of the sum over shares when there are many of them: out[zg][i] = sum of in[z][i] over
@@ -757,13 +769,16 @@ static bool wgrad_fused_ok(const WgradGeo &g)
     return (long long)g.N * (g.K > g.C ? g.K : g.C) * g.H * g.W < (1LL << 31);
 }
 
-// `workgroups`: 512, two rounds of one per CU (or 256 where the workspace holds no more partial M)
-static void wgrad_fused_shape(const WgradGeo &g, int workgroups, int *tiles_k, int *tiles_c, int *shares, int *slabs_per_share)
+// `workgroups`: 512, two rounds of one per CU (or 256 where the workspace holds no more partial M); `long_shares` false:
+// more of them where shares would be longer than BF16_LONG blocks
+static void wgrad_fused_shape(const WgradGeo &g, int workgroups, bool long_shares, int *tiles_k, int *tiles_c, int *shares, int *slabs_per_share)
 {
     *tiles_k = (g.Kp + 63) / 64;
     *tiles_c = (g.Cq + 63) / 64;
     const int slabs = (g.Pb + 15) / 16;       // (shares are whole numbers of 16 blocks)
     int want = workgroups / (*tiles_k * *tiles_c);
+    const int tiles = *tiles_k * *tiles_c, need = (slabs + BF16_LONG / 16 - 1) / (BF16_LONG / 16);
+    if (!long_shares && want < need) want = (need * tiles + 255) / 256 * 256 / tiles;      // (whole rounds of one per CU)
     if (want > slabs / 4) want = slabs / 4;   // at least 64 blocks per share
     if (want < 1) want = 1;
     const int per_share = (slabs + want - 1) / want;
@@ -795,7 +810,7 @@ size_t wgrad_workspace_bytes(int N, int C, int H, int W, int K)
     int bm, bn, shares, nk_split;
     if (wgrad_fused_ok(g) && g.K <= 256 && g.C <= 256) {
         int tk, tc, sps;
-        wgrad_fused_shape(g, 512, &tk, &tc, &shares, &sps);
+        wgrad_fused_shape(g, 512, true, &tk, &tc, &shares, &sps);
         return wgrad_fused_bytes(g, shares);
     }
     wgrad_shape(g, &bm, &bn, &shares, &nk_split);
@@ -821,14 +836,20 @@ hipError_t launch_wgrad(int N, int C, int H, int W, int K, const float *D, const
     const WgradGeo g = make_wgeo(N, C, H, W, K);
     int bm, bn, shares = 0, nk_split, tk = 0, tc = 0, sps = 0;
     const size_t room = wgrad_workspace_bytes(N, C, H, W, K);
-    for (int workgroups = 512; workgroups >= 256 && shares == 0 && wgrad_fused_ok(g); workgroups /= 2) {
-        wgrad_fused_shape(g, workgroups, &tk, &tc, &shares, &sps);
+    // short shares, where the workspace has room for them (beyond 256 filters or channels: 1088 -> 1088 at 28 x 28, N = 32,
+    // four instead of one: 3.0 -> 1.9 ms); else two rounds, else one
+    for (int n = 0; n < 3 && shares == 0 && wgrad_fused_ok(g); ++n) {
+        wgrad_fused_shape(g, n < 2 ? 512 : 256, n > 0, &tk, &tc, &shares, &sps);
         if (wgrad_fused_bytes(g, shares) > room) shares = 0;
     }
     if (shares > 0) {
         float *Mw = (float *)workspace;
         float *tmp = (float *)((char *)workspace + (((size_t)shares * 16 * g.Kp * g.Cq * 4 + 255) & ~(size_t)255));
-        wgrad_fused_kernel<<<dim3((unsigned)(tk * tc * shares)), dim3(WF_T), 0, s>>>(D, E, Mw, g, tk, tc, sps);
+        const dim3 grid((unsigned)(tk * tc * shares)), block(WF_T);
+        if (sps * WF_BK > BF16_LONG)
+            wgrad_fused_kernel<true><<<grid, block, 0, s>>>(D, E, Mw, g, tk, tc, sps);
+        else
+            wgrad_fused_kernel<false><<<grid, block, 0, s>>>(D, E, Mw, g, tk, tc, sps);
         const float *Ms = wgrad_pre_reduce(Mw, tmp, (size_t)16 * g.Kp * g.Cq, &shares, s);
         wgrad_output_kernel<<<dim3((C + 255) / 256, K), dim3(256), 0, s>>>(Ms, dG, g, shares);
         return hipGetLastError();

@@ -4,8 +4,9 @@ import numpy as np
 import pytest
 
 from oracle import direct
+from oracle import winograd as wg
 from paper_1509_09308_amd import synth
-from gpu_util import check_close, require_gpu, to_gpu
+from gpu_util import check_close, rel_err, require_gpu, to_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -44,3 +45,37 @@ def test_rounding_does_not_add_up_over_shares():
     e = np.linalg.norm(dG[tuple(pts.T)] - ref) / np.linalg.norm(ref)
     print("rel err %.2e" % e)
     assert e <= 1e-6
+
+
+@pytest.mark.parametrize("data", ["positive", "near one", "normal"])
+@pytest.mark.parametrize("N,C,H,K", [(10, 1030, 28, 1030),      # one share of 1960 blocks
+                                     (32, 1030, 28, 1030),      # 6272 blocks in four shares
+                                     (32, 640, 28, 640),        # five shares of 1264
+                                     (66, 256, 112, 256)])      # 32 shares of 6480 blocks, set aside on the way
+def test_long_shares_are_as_precise_as_fp32(N, C, H, K, data):
+    """Few, long shares: nothing may add up along them.  Operands between 1 and 1 + 2^-7 have products of low parts that
+    are all of one sign; the sums of such and of positive data hold one large component, in which those could get lost."""
+    torch, w = require_gpu()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(N + C)
+    def make(*shape):
+        if data == "normal":
+            return torch.randn(shape, generator=gen, device="cuda")
+        x = torch.rand(shape, generator=gen, device="cuda")
+        return x if data == "positive" else 1.0 + x * 2.0 ** -7
+    D, E = make(N, C, H, H), make(N, K, H, H)
+    dG = w.wino_conv2d_bwd_filter(D, E, pad=1)
+    ks, cs = [0, 70, K - 1], [0, 65, C - 2]
+    d, e = D[:, cs].cpu().numpy(), E[:, ks].cpu().numpy()
+    ref = direct.conv2d_bwd_filter(d, e, pad=1)
+    got = dG[ks][:, cs].cpu().numpy()
+    # the same blocks, one after the other, in fp32: every component is a chain of multiply-adds (rounded twice)
+    Wt, V = (x.astype(np.float32) for x in (wg.wgrad_error_transform(e), wg.wgrad_data_transform(d)))
+    assert Wt.shape[3] == N * (H // 2) ** 2
+    M = np.zeros((4, 4, len(ks), len(cs)), dtype=np.float32)
+    for b in range(Wt.shape[3]):
+        M += Wt[..., b][:, :, :, None] * V[..., b][:, :, None, :]
+    chain = wg.wgrad_inverse_transform(M)
+    err, ec = rel_err(got, ref), rel_err(chain, ref)
+    print("%s %s: rel err %.2e, fp32 chain %.2e" % ((N, C, K), data, err, ec))
+    assert err <= 1.2 * ec
