@@ -942,6 +942,9 @@ static size_t fs_part_bytes(const Geo &g) { return FS_TICKET_BYTES + (size_t)FS_
 bool fused_split_eligible(const Geo &g)
 {
     if (!fused_wide_eligible(g)) return false;
+    // longer sums than this would have to be set aside (bf16x3.h; data between 1 and 1 + 2^-7, F(4x4,3x3): error against
+    // float64 6.1e-7 with 3072 channels, 1.6e-6 with 4096; fused_wide.hip 8.4e-7 and 1.0e-6)
+    if (g.C > BF16_LONG * 3 / 2) return false;
     // the tiles of one item span at most `span` images; their byte offsets from the first must stay below 2^30
     const unsigned long long tiles = (unsigned long long)g.Th * g.Tw;
     const unsigned long long span = (fs_tiles(g.m) + tiles - 2) / tiles + 1;

@@ -5,7 +5,7 @@ import pytest
 
 from oracle import direct
 from paper_1509_09308_amd import synth
-from gpu_util import TOL, check_close, require_gpu, to_gpu
+from gpu_util import TOL, check_close, rel_err, require_gpu, to_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -72,3 +72,31 @@ def test_split_layer_f16(shape, given, y):
     assert np.isfinite(got).all()
     ref = direct.conv2d_points(D.astype(np.float32), G.astype(np.float32), pts, pad=1)
     check_close(got[tuple(pts.T)], ref, TOL[("f16", 4)], "%s %s" % (shape, given), 4)
+
+
+@pytest.mark.parametrize("C", [3072, 4096])
+@pytest.mark.parametrize("m", [2, 4])
+@pytest.mark.parametrize("data", ["positive", "near one"])
+def test_long_channel_sums(m, C, data):
+    """One-signed data: one component of a tile holds one large sum, in which small products could get lost (those of
+    operands between 1 and 1 + 2^-7 all have one sign)."""
+    torch, w = require_gpu()
+    N, H, K = 24, 28, 256
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(C + m)
+    def make(*shape):
+        x = torch.rand(shape, generator=gen, device="cuda")
+        return x if data == "positive" else 1.0 + x * 2.0 ** -7
+    D, G = make(N, C, H, H), make(K, C, 3, 3)
+    Y = w.wino_conv2d_fwd_ex(D, G=G, pad=1, m=m, flags=w.FLAG_FUSED)[-1, ::37].cpu().numpy()
+    d, g = D[-1:].cpu().numpy(), G[::37].cpu().numpy()
+    ref = direct.conv2d_fwd(d, g, pad=1)[0]
+    chain = np.zeros((len(g), H - 2, H - 2), dtype=np.float32)    # the centre taps alone, fp32 multiply-adds (rounded twice)
+    centre = np.zeros((len(g), H - 2, H - 2))
+    for c in range(C):
+        x, y = d[0, c, 1:-1, 1:-1], g[:, c, 1, 1]
+        chain += x * y[:, None, None]
+        centre += x.astype(np.float64) * y[:, None, None]
+    e, ec = rel_err(Y, ref), rel_err(chain, centre)
+    print("F(%d) C=%d %s: rel err %.2e, fp32 chain %.2e" % (m, C, data, e, ec))
+    assert e <= 1.3 * ec            # (the transforms round a few times more)
