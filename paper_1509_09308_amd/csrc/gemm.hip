@@ -64,7 +64,7 @@ enum { ONE, USUAL, LONG };
 template <int BM, int BN, int BK, int DEPTH>
 __global__ __launch_bounds__(256, DEPTH == ONE && BM * BN < 128 * 128 ? 4 : 2) void gemm_f32_kernel(
     const float *__restrict__ U, const float *__restrict__ V, float *__restrict__ Mo, int Kp, int Cp, int Pp, int tiles_m,
-    int tiles_n, int a2, int c_share)
+    int tiles_n, int a2, int c_share, int c_real)
 {
     constexpr int TM = BM / 64, TN = BN / 64;
     constexpr int G8 = BK / 8;                                   // groups of eight channels per slab
@@ -195,6 +195,29 @@ __global__ __launch_bounds__(256, DEPTH == ONE && BM * BN < 128 * 128 ? 4 : 2) v
                 }
             }
     };
+    // a tile's sums over the first `rows` channels with fp32 instructions
+    auto fp32_tile = [&](int i, int j, int rows) {
+        const float *a = Ue + min(k0 + wm * (TM * 32) + i * 32 + li, Kp - 1) + (size_t)lh * Kp;
+        const float *b = Ve + min(p0 + wn * (TN * 32) + j * 32 + li, Pp - 1) + (size_t)lh * Pp;
+        floatx16 sums;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sums[r] = 0.0f;
+#pragma unroll 8
+        for (int c = 0; c < rows; c += 2)
+            sums = __builtin_amdgcn_mfma_f32_32x32x2f32(a[(size_t)c * Kp], b[(size_t)c * Pp], sums, 0, 0, 0);
+        return sums;
+    };
+
+    if (DEPTH == ONE && c_real <= 2) {
+        // (one or two products are rounded once that way; their six parts are not always rounded to nearest: 2.5e-8 and
+        // 3.1e-8 of the product against 3.5e-8 and 3.3e-8.  From three on the parts are the more precise)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = fp32_tile(i, j, 2);
+        each([](float sum, float &m) { return m = sum; });
+        return;
+    }
     if constexpr (DEPTH == ONE) {
         request(0, 0);
         store(0, 0);
@@ -262,14 +285,7 @@ __global__ __launch_bounds__(256, DEPTH == ONE && BM * BN < 128 * 128 ? 4 : 2) v
             }
             if (!__any(!bf16_finite(t))) continue;
             // the sums that are not finite, with fp32 instructions (bf16x3.h)
-            const float *a = Ue + min(k0 + wm * (TM * 32) + i * 32 + li, Kp - 1) + (size_t)lh * Kp;
-            const float *b = Ve + min(p0 + wn * (TN * 32) + j * 32 + li, Pp - 1) + (size_t)lh * Pp;
-            floatx16 exact;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) exact[r] = 0.0f;
-#pragma unroll 8
-            for (int c = 0; c < c_rows; c += 2)
-                exact = __builtin_amdgcn_mfma_f32_32x32x2f32(a[(size_t)c * Kp], b[(size_t)c * Pp], exact, 0, 0, 0);
+            const floatx16 exact = fp32_tile(i, j, c_rows);
 #pragma unroll
             for (int r = 0; r < 16; ++r)
                 if (!bf16_finite(acc[i][j][r])) acc[i][j][r] = exact[r];
@@ -291,11 +307,11 @@ static hipError_t launch_f32(const Geo &g, const float *U, const float *V, float
         return hipErrorNotSupported;
     const dim3 grid((unsigned)blocks), block(256);
     if (c_share <= BK)
-        gemm_f32_kernel<BM, BN, BK, ONE><<<grid, block, 0, s>>>(U, V, M, g.Kp, g.Cp, g.Pp, tiles_m, tiles_n, g.a2, c_share);
+        gemm_f32_kernel<BM, BN, BK, ONE><<<grid, block, 0, s>>>(U, V, M, g.Kp, g.Cp, g.Pp, tiles_m, tiles_n, g.a2, c_share, g.C);
     else if (c_share <= BF16_LONG)
-        gemm_f32_kernel<BM, BN, BK, USUAL><<<grid, block, 0, s>>>(U, V, M, g.Kp, g.Cp, g.Pp, tiles_m, tiles_n, g.a2, c_share);
+        gemm_f32_kernel<BM, BN, BK, USUAL><<<grid, block, 0, s>>>(U, V, M, g.Kp, g.Cp, g.Pp, tiles_m, tiles_n, g.a2, c_share, g.C);
     else
-        gemm_f32_kernel<BM, BN, BK, LONG><<<grid, block, 0, s>>>(U, V, M, g.Kp, g.Cp, g.Pp, tiles_m, tiles_n, g.a2, c_share);
+        gemm_f32_kernel<BM, BN, BK, LONG><<<grid, block, 0, s>>>(U, V, M, g.Kp, g.Cp, g.Pp, tiles_m, tiles_n, g.a2, c_share, g.C);
     return hipGetLastError();
 }
 

@@ -91,3 +91,21 @@ def test_long_sums_are_as_precise_as_fp32(K, C, P, data):
     e, ec = rel_err(M[0, 0], ref), rel_err(chain, ref)
     print("K=%d C=%d P=%d %s: rel err %.2e, fp32 chain %.2e" % (K, C, P, data, e, ec))
     assert e <= ec
+
+
+@pytest.mark.parametrize("K,P", [(40, 100), (200, 3300)])
+@pytest.mark.parametrize("C", [1, 2, 3])
+def test_few_channels(K, P, C):
+    torch, w = require_gpu()
+    rng = np.random.default_rng(K + C)
+    u, v = rng.standard_normal((4, 4, K, C)).astype(np.float32), rng.standard_normal((4, 4, C, P)).astype(np.float32)
+    M = w.unpack_m(w.wino_batched_gemm(w.pack_u(u, 2), w.pack_v(v, 2), K, C, P, 2), K, P, 2)
+    if C == 1:
+        assert np.array_equal(M, u * v)          # a single product, rounded to nearest
+    ref = wg.multiply(u.astype(np.float64), v.astype(np.float64))
+    chain = u[..., :1] * v[:, :, :1]                            # fp32 multiply-adds, every sum rounded once
+    for c in range(1, C):
+        chain = (chain.astype(np.float64) + u[..., c, None].astype(np.float64) * v[:, :, None, c]).astype(np.float32)
+    e, ec = rel_err(M, ref), rel_err(chain, ref)
+    print("C=%d: rel err %.2e, fp32 chain %.2e" % (C, e, ec))
+    assert e <= 1.01 * ec
