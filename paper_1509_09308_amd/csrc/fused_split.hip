@@ -998,12 +998,28 @@ static bool fs_shares(const Geo &g, int groups)
     return false;
 }
 
+static int fs_grid(const Geo &g)      // as many workgroups as stay resident, in multiples of the 8 XCDs
+{
+    const long long items = fused_split_items(g);
+    return (int)(items >= FS_GRID ? FS_GRID : (items + 7) / 8 * 8);
+}
+
+int fused_split_plan(const Geo &g, int out[32])
+{
+    const int n_kb = fs_n_kb(g), groups = fs_groups(g, n_kb), grid = fs_grid(g);
+    for (int xcd = 0; xcd < 8; ++xcd) {
+        int first, count;
+        fs_list(xcd, groups, n_kb, (int)fs_n_tb(g), &first, &count);
+        const FsRounds r = fs_rounds(count, grid / 8, (g.C + FS_C - 1) / FS_C, fs_shares(g, groups));
+        out[4 * xcd] = count, out[4 * xcd + 1] = r.full, out[4 * xcd + 2] = r.tail, out[4 * xcd + 3] = r.shares;
+    }
+    return grid;
+}
+
 template <typename T, typename TY>
 static hipError_t fs_launch(const Geo &g, const T *D, const char *Us, TY *Y, int n_kb, int n_tb, int groups, float *part, hipStream_t s)
 {
-    // as many workgroups as stay resident, in multiples of the 8 XCDs
-    const int items = n_kb * n_tb;
-    const dim3 grid((unsigned)(items >= FS_GRID ? FS_GRID : (items + 7) / 8 * 8)), block(FS_T);
+    const dim3 grid((unsigned)fs_grid(g)), block(FS_T);
     const bool cpad = g.C % FS_C != 0;
     const FsArgs<T, TY> args = {D, Us, Y, g, n_kb, n_tb, groups, part};
     if constexpr (sizeof(T) == 4) {

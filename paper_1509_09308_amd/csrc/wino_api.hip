@@ -283,7 +283,7 @@ int wino_one_kernel_plan(int N, int C, int H, int W, int K, int pad, int m, int 
     if (st != WINO_OK) return -st;
     if (out == nullptr) return -WINO_EINVAL;
     if (!fused_eligible(g) || !fused_wide_eligible(g)) return -WINO_EUNSUPPORTED;
-    const int grid = fused_wide_plan(g, out);
+    const int grid = fused_split_eligible(g) ? fused_split_plan(g, out) : fused_wide_plan(g, out);
     return grid < 0 ? -WINO_EINVAL : grid;
 }
 

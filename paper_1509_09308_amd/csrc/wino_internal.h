@@ -57,6 +57,7 @@ size_t fused_wide_part_bytes(const Geo &g);
 bool fused_split_eligible(const Geo &g);
 long long fused_split_items(const Geo &g);
 double fused_split_us(const Geo &g);
+int fused_split_plan(const Geo &g, int out[32]);     // as fused_wide_plan
 hipError_t launch_fused_split(const Geo &g, const float *D, const float *G, const float *U, float *Y, void *workspace,
                               size_t workspace_bytes, bool bwd, hipStream_t s);
 bool fused_split_f16_eligible(const Geo &g);

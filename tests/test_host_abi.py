@@ -247,21 +247,25 @@ def test_bench_refuses_more_than_one_gpu():
 
 
 def test_one_kernel_plan_covers_every_item_once_and_shares_fit():
-    """The deal of (tile block, filter block) items to XCDs and rounds that the one-kernel fp32 layer's workgroups
-    follow (the kernel evaluates the same functions): every item belongs to exactly one XCD's list, a shared last
-    round fits the XCD's 64 workgroups, the shares divide the channel steps, and only long items are shared."""
-    import math
+    """The deal of (tile block, filter block) items to XCDs and rounds that the one-kernel fp32 layers' workgroups
+    follow (the kernels evaluate the same functions): every item belongs to exactly one XCD's list, a shared last
+    round fits the XCD's resident workgroups, the shares divide the channel steps, and only long items are shared.
+    Two kernels: 32-tile items (64 for F(2x2)), one workgroup per CU, from 128 items on; 16-tile items, two (three)
+    workgroups per CU, below that and beyond 3072 channels."""
     w = binding
     rng = __import__("numpy").random.default_rng(5)
-    seen_shared = 0
+    shared = {True: 0, False: 0}
     cases = [(64, 256, 56, 56, 256), (64, 512, 28, 28, 512), (64, 256, 28, 28, 512), (64, 64, 224, 224, 64),
              (64, 128, 112, 112, 128), (2, 256, 96, 96, 512), (6, 256, 72, 72, 320), (2, 344, 96, 96, 512),
-             (1, 64, 224, 224, 64), (8, 512, 28, 28, 512), (3, 40, 12, 20, 96)]
+             (1, 64, 224, 224, 64), (8, 512, 28, 28, 512), (3, 40, 12, 20, 96), (2, 3200, 64, 72, 512), (8, 3200, 64, 72, 512)]
     for _ in range(300):
         cases.append((int(rng.integers(1, 200)), int(rng.integers(1, 700)), int(rng.integers(3, 80)),
                       4 * int(rng.integers(1, 24)), int(rng.integers(33, 700))))
+    for _ in range(100):
+        cases.append((int(rng.integers(1, 20)), 16 * int(rng.integers(193, 240)), int(rng.integers(3, 80)),
+                      4 * int(rng.integers(1, 24)), int(rng.integers(33, 700))))
     planned = 0
-    for m, slots in ((4, 64), (2, 96)):            # resident workgroups per XCD: two resp. three per CU
+    for m in (4, 2):
       for N, C, H, W, K in cases:
         try:
             grid, plan = w.wino_one_kernel_plan(N, C, H, W, K, 1, m)
@@ -271,29 +275,35 @@ def test_one_kernel_plan_covers_every_item_once_and_shares_fit():
         planned += 1
         P = w.wino_num_tiles(N, H, W, 1, m)
         Kp = w.wino_padded_dims(K, C, P, m)[0]
-        items = ((P + 15) // 16) * ((Kp + 63) // 64)
+        tiles = 32 if m == 4 else 64
+        split = ((P + tiles - 1) // tiles) * ((Kp + 63) // 64) >= 128 and C <= 3072
+        if not split:
+            tiles = 16
+        slots = 32 if split else 64 if m == 4 else 96       # resident workgroups per XCD
+        items = ((P + tiles - 1) // tiles) * ((Kp + 63) // 64)
         nsteps = (C + 15) // 16
         assert grid == (8 * slots if items >= 8 * slots else (items + 7) // 8 * 8), (N, C, H, W, K)
         assert sum(p[0] for p in plan) == items, (N, C, H, W, K, plan)
         for count, full, tail, shares in plan:
             assert full + tail == count and full >= 0 and tail >= 0 and shares >= 1
             if shares > 1:
-                seen_shared += 1
+                shared[split] += 1
                 assert grid == 8 * slots and full % slots == 0 and 0 < tail and tail * shares <= slots
-                assert shares in (2, 4, 8) and nsteps % shares == 0 and nsteps >= 16
-                assert shares >= 4 or full == 0
+                assert shares in (2, 4, 8) and nsteps % shares == 0 and nsteps >= (8 if split else 16)
+                assert split or shares >= 4 or full == 0
             else:
                 assert tail == 0
-    assert seen_shared > 40 and planned > 400
-    # the VGG layers this is made for: conv3.2 (8 items of the last round in 8 shares on every XCD), conv4.2 (4 in 8)
-    assert w.wino_one_kernel_plan(64, 256, 56, 56, 256)[1] == [(392, 384, 8, 8)] * 8
-    assert w.wino_one_kernel_plan(64, 512, 28, 28, 512)[1] == [(196, 192, 4, 8)] * 8
+    assert shared[True] > 40 and shared[False] > 20 and planned > 400, (shared, planned)
+    # VGG layers: conv3.2 (4 items of the last round in 8 shares on every XCD), conv4.2 (2 in 8), conv1.2
+    assert w.wino_one_kernel_plan(64, 256, 56, 56, 256) == (256, [(196, 192, 4, 8)] * 8)
+    assert w.wino_one_kernel_plan(64, 512, 28, 28, 512) == (256, [(98, 96, 2, 8)] * 8)
     assert all(p[3] == 1 for p in w.wino_one_kernel_plan(64, 64, 224, 224, 64)[1])
+    assert w.wino_one_kernel_plan(64, 512, 14, 14, 512, 1, 2) == (256, [(49, 49, 0, 1)] * 8)  # F(2x2): conv5.x
+    assert w.wino_one_kernel_plan(4, 3200, 64, 72, 512) == (512, [(72, 64, 8, 8)] * 8)        # beyond 3072 channels
     L = binding.lib()
     out = (ctypes.c_int * 32)()
     assert L.wino_one_kernel_plan(2, 8, 8, 8, 8, 1, 4, 0, out) == -w.WINO_EUNSUPPORTED      # fewer than 33 filters
     assert L.wino_one_kernel_plan(2, 8, 8, 8, 40, 0, 4, 0, out) == -w.WINO_EUNSUPPORTED     # pad 0
-    assert w.wino_one_kernel_plan(64, 512, 14, 14, 512, 1, 2)[1] == [(196, 192, 4, 8)] * 8  # F(2x2): conv5.x
     assert L.wino_one_kernel_plan(2, 8, 8, 10, 8, 1, 4, 0, out) == -w.WINO_EUNSUPPORTED     # W % 4 != 0
     assert L.wino_one_kernel_plan(2, 8, 8, 8, 8, 1, 4, 1, out) == -w.WINO_EUNSUPPORTED      # fp16 storage
     assert L.wino_one_kernel_plan(0, 8, 8, 8, 8, 1, 4, 0, out) == -w.WINO_EINVAL
