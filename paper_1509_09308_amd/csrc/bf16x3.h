@@ -3,12 +3,13 @@
 // An fp32 value is the exact sum of three bf16 values (Henry, Tang and Heinecke, "Leveraging the bfloat16 Artificial
 // Intelligence Datatype For Higher-Precision Computations", ARITH 2019): x = h + m + l, h = bf16(x), m = bf16(x - h),
 // l = x - h - m (8 + 8 + 8 significant bits; both differences are exact in fp32).  Of the nine products of two such
-// values the six with an order of magnitude above 2^-26 are formed, each exact (8 x 8 bits) and accumulated in fp32 by
-// v_mfma_f32_32x32x16_bf16: h h, h m, m h, m m, h l, l h.  What is left out, m l + l m + l l, is at most 2^-25.9 of the
-// product -- a quarter of the 2^-24 that ONE fp32 multiply-add of a chain may round off -- and a chain of fp32
-// multiply-adds rounds at every term, these instructions once per eight or sixteen.  Measured against float64 on
-// N(0,1) vectors, relative error of the dot product, v_mfma_f32_32x32x2_f32 / this: 1.42e-7 / 1.14e-7 (length 64),
-// 4.13e-7 / 3.57e-7 (512), 1.11e-6 / 0.97e-6 (4096); all nine products give the same as six.
+// values six are formed, each exact (8 x 8 bits) and accumulated in fp32 by v_mfma_f32_32x32x16_bf16: h h, h m, m h, m m,
+// h l, l h.  What is left out, m l + l m + l l, is at most 2^-24 of the product, half a unit in its last place (reached by
+// two operands 1 + 2^-8 - 2^-17), and 2^-27.4 in the mean square of N(0,1) or uniform operands.  The instructions add to a
+// sum six times per sixteen terms, where a chain of fp32 multiply-adds does so sixteen times; they cut off rather than
+// round to nearest what lies far below the sum.  Measured against float64, relative error of the sums of a chain of
+// v_mfma_f32_32x32x2_f32 / of these: N(0,1) operands 7.4e-8 / 3.4e-8 (16 terms), 1.44e-7 / 1.10e-7 (64), 4.05e-7 / 3.41e-7
+// (512), 8.1e-7 / 7.0e-7 (2048); uniform in [0,1] 6.2e-8 / 3.2e-8, 1.15e-7 / 8.4e-8, 3.06e-7 / 2.38e-7, 6.0e-7 / 3.8e-7.
 // Rate on the MI355X: the bf16 instruction takes 16.3 ns per SIMD for 16 channels of a 32 x 32 block, the fp32 one
 // 30.4 ns for two: six products cost 98 ns against 243.  And where fp32 matrix and vector instructions of one SIMD
 // take turns, up to six vector instructions per bf16 matrix instruction run beside it.

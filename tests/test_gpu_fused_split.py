@@ -11,13 +11,13 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("m,shape", [
-    (4, (9, 17, 28, 60, 70)),        # 142 items, two channel steps (the second one channel deep), 38 padded filters read twice
+    (4, (20, 17, 28, 60, 70)),       # 132 items, two channel steps (the second one channel deep), 38 padded filters read twice
     (4, (33, 16, 28, 20, 256)),      # one step; items over several images, last tile block ragged
     (4, (5, 40, 66, 128, 96)),       # last tile row half outside; 96 filters: the second block half empty
     (4, (17, 128, 28, 44, 513)),     # 369 items: a full round, then 15 items per XCD in two shares; nine filter blocks
     (4, (4, 144, 48, 96, 500)),      # 288 items of nine steps, which no number of shares divides
     (4, (4, 256, 48, 96, 520)),      # 324 items: XCDs with 9 items and one with 5 in their last round
-    (2, (11, 17, 30, 46, 70)),
+    (2, (13, 17, 30, 46, 70)),
     (2, (3, 130, 65, 64, 200)),      # odd height
     (2, (6, 256, 48, 60, 400)),
 ])
@@ -25,6 +25,8 @@ pytestmark = pytest.mark.gpu
 def test_split_layer(m, shape, given):
     torch, w = require_gpu()
     N, C, H, W, K = shape
+    items = -(-w.wino_num_tiles(N, H, W, 1, m) // (32 if m == 4 else 64)) * -(-K // 64)
+    assert items >= 128 and sum(p[0] for p in w.wino_one_kernel_plan(N, C, H, W, K, 1, m)[1]) == items       # this kernel's
     D, G = synth.make_layer(N, C, H, W, K, seed=sum(shape) + m)
     d, g = to_gpu(D), to_gpu(G)
     ws = w.alloc_workspace(N, C, H, W, K, 1, m)
@@ -44,7 +46,7 @@ def test_split_layer(m, shape, given):
 
 def test_split_layer_input_gradient():
     torch, w = require_gpu()
-    N, C, H, W, K = 9, 72, 28, 60, 40
+    N, C, H, W, K = 20, 72, 28, 60, 40          # 132 items, F(2x2,3x3) 264
     _, G = synth.make_layer(1, C, 4, 4, K, seed=3)
     E = np.random.default_rng(4).standard_normal((N, K, H, W)).astype(np.float32)
     for m in (2, 4):
@@ -52,7 +54,7 @@ def test_split_layer_input_gradient():
         check_close(dD, direct.conv2d_bwd_data(E, G, H, W, pad=1), TOL[("f32", m)], "input gradient F(%d)" % m, m)
 
 
-@pytest.mark.parametrize("shape", [(9, 17, 28, 60, 70), (33, 16, 28, 20, 256), (5, 40, 66, 128, 96), (17, 128, 28, 44, 513),
+@pytest.mark.parametrize("shape", [(20, 17, 28, 60, 70), (33, 16, 28, 20, 256), (5, 40, 66, 128, 96), (17, 128, 28, 44, 513),
                                    (4, 256, 48, 96, 520)])
 @pytest.mark.parametrize("given", ["G", "U"])
 @pytest.mark.parametrize("y", ["f32", "f16"])

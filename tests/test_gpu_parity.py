@@ -298,25 +298,32 @@ def test_fused_path_matches_oracle(shape):
     print("fused %s rel err %.3e max abs err %.3e" % (shape, e, worst))
 
 
-@pytest.mark.parametrize("shape", [(2, 256, 96, 96, 512),    # 72 items per XCD: a last round of 8 items in 8 shares
-                                   (2, 344, 96, 96, 512),    # channels not a multiple of 16: 22 steps, 2 shares
-                                   (6, 256, 72, 72, 320)])   # lists of 77 and 71 items (4 and 8 shares), ragged last tile block
-def test_fused_path_shares_the_items_of_a_partly_filled_last_round(shape):
-    """Layers with at least 512 (tile block, filter block) items whose last round fills only part of the resident
+@pytest.mark.parametrize("shape,last", [
+    ((2, 256, 96, 96, 512), (4, 8)),        # 36 items per XCD: a last round of 4 items in 8 shares
+    ((2, 344, 96, 96, 512), (4, 2)),        # channels not a multiple of 16: 22 steps, 2 shares
+    ((6, 256, 72, 72, 320), (7, 4)),        # lists of 39 and 32 items, ragged last tile block
+    ((2, 3136, 64, 144, 512), (8, 4)),      # more than 3072 channels: items of 16 tiles, 72 per XCD on 64 workgroups
+])
+def test_fused_path_shares_the_items_of_a_partly_filled_last_round(shape, last):
+    """Layers with at least a round of (tile block, filter block) items whose last round fills only part of the resident
     workgroups: the channel steps of those items are shared between workgroups that hand partial outputs over
-    through the workspace.  Whole output against the oracle; a second call must reproduce the first bit for bit
+    through the workspace.  Against the oracle; a second call must reproduce the first bit for bit
     (the partial outputs are added in share order, whichever share arrives last)."""
     torch, w = require_gpu()
     N, C, H, W, K = shape
+    assert w.wino_one_kernel_plan(N, C, H, W, K)[1][0][2:] == last
     D, G = synth.make_layer(N, C, H, W, K, seed=sum(shape) + 41)
-    ref = direct.conv2d_fwd(D, G, pad=1)
     d, g = to_gpu(D), to_gpu(G)
     ws = w.alloc_workspace(N, C, H, W, K, 1, 4)
     ws.view(torch.float32).fill_(float("nan"))            # nothing may depend on what the workspace held
     Y1 = w.wino_conv2d_fwd_ex(d, G=g, pad=1, m=4, flags=w.FLAG_FUSED, workspace=ws)
     Y2 = w.wino_conv2d_fwd_ex(d, G=g, pad=1, m=4, flags=w.FLAG_FUSED, workspace=ws)
     torch.cuda.synchronize()
-    e, worst = check_close(Y1.cpu().numpy(), ref, TOL[("f32", 4)], "fused with shares %s" % (shape,), 4)
+    pts = synth.sample_points((N, K, H, W), 4000, seed=41, edge=4)
+    if C > 3000:
+        e, worst = check_close(Y1.cpu().numpy()[tuple(pts.T)], direct.conv2d_points(D, G, pts, pad=1), TOL[("f32", 4)], "%s" % (shape,), 4)
+    else:
+        e, worst = check_close(Y1.cpu().numpy(), direct.conv2d_fwd(D, G, pad=1), TOL[("f32", 4)], "fused with shares %s" % (shape,), 4)
     assert torch.equal(Y1, Y2)
     print("fused with shares %s rel err %.3e max abs err %.3e" % (shape, e, worst))
 
@@ -324,7 +331,7 @@ def test_fused_path_shares_the_items_of_a_partly_filled_last_round(shape):
 @pytest.mark.parametrize("shape", [(3, 40, 12, 20, 96), (2, 24, 8, 8, 200), (1, 130, 20, 36, 70), (5, 16, 4, 4, 64),
                                    (2, 272, 16, 16, 256),
                                    (2, 16, 10, 14, 64), (1, 20, 7, 6, 40), (1, 3, 5, 2, 33),     # widths that 4 does not divide
-                                   (3, 256, 40, 40, 512), (2, 256, 66, 66, 512)])              # a shared last round (4 shares)
+                                   (3, 256, 40, 40, 512), (2, 256, 66, 66, 512)])              # 64-tile items; a shared last round (8 shares)
 def test_fused_f2x2_path_matches_oracle(shape):
     """F(2x2,3x3) in one kernel (the 64-filter design with 4 x 4 tiles: 16 components, 8-byte rows): whole output
     against the oracle; the call repeated must give the same bits."""
@@ -347,8 +354,8 @@ def test_fused_f2x2_path_matches_oracle(shape):
 
 def test_fused_f2x2_delta_filter_bitwise_and_full_size_sampled():
     """With a centre-one filter every intermediate of F(2x2) is exact in fp32: the one-kernel path must return D bit
-    for bit (every tile, row and column in its place).  And conv5.x of the N=64 stack through this path (the shape it
-    is chosen for: 3 full rounds and a shared one), sampled against the oracle."""
+    for bit (every tile, row and column in its place).  And conv5.x of the N=64 stack through this path (392 items of
+    64 tiles), sampled against the oracle."""
     torch, w = require_gpu()
     N, C, H, W, K = 3, 72, 14, 22, 72
     D = (np.arange(N * C * H * W, dtype=np.float32) % 65521).reshape(N, C, H, W)
@@ -381,25 +388,28 @@ def test_fused_path_exact_on_integers_and_equals_unfused_bookkeeping():
 
 @pytest.mark.parametrize("C", [8, 24, 3, 16])
 @pytest.mark.parametrize("given", ["G", "U"])
-def test_fused_path_never_uses_memory_behind_the_input(C, given):
+@pytest.mark.parametrize("m,N,dtype", [(4, 2, "f32"), (4, 350, "f32"), (2, 2, "f32"), (2, 350, "f32"), (4, 350, "f16")])
+def test_fused_path_never_uses_memory_around_the_input(C, given, m, N, dtype):
     """The channel loop of the one-kernel path runs over the padded channel count: channels past C must come
     in as zeros, not from whatever follows the input in memory.  D ends where a block of NaNs begins (0 * NaN
-    would poison the sums of the last image); both one-kernel designs (untransformed filters / U given)."""
+    would poison the sums of the last image) and begins where one ends; all one-kernel designs (a few items and more than
+    128 of them, untransformed filters / U given)."""
     torch, w = require_gpu()
-    N, H, W, K = 2, 12, 16, 40
-    D, G = synth.make_layer(N, C, H, W, K, seed=77 + C)
-    ref = direct.conv2d_fwd(D, G, pad=1)
-    n = D.size
-    buf = torch.full((n + 64 * H * W,), float("nan"), dtype=torch.float32, device="cuda")
-    buf[:n] = to_gpu(D).reshape(-1)
-    d = buf[:n].view(N, C, H, W)
+    H, W, K = 12, 16, 40
+    np_dt = np.float32 if dtype == "f32" else np.float16
+    D, G = synth.make_layer(N, C, H, W, K, seed=77 + C, dtype=np_dt)
+    ref = direct.conv2d_fwd(D.astype(np.float32), G.astype(np.float32), pad=1)
+    n, edge = D.size, 64 * H * W
+    buf = torch.full((n + 2 * edge,), float("nan"), dtype=torch.float32 if dtype == "f32" else torch.float16, device="cuda")
+    buf[edge:edge + n] = to_gpu(D).reshape(-1)
+    d = buf[edge:edge + n].view(N, C, H, W)
     g = to_gpu(G)
     if given == "G":
-        Y = w.wino_conv2d_fwd_ex(d, G=g, pad=1, m=4, flags=w.FLAG_FUSED)
+        Y = w.wino_conv2d_fwd_ex(d, G=g, pad=1, m=m, flags=w.FLAG_FUSED)
     else:
-        Y = w.wino_conv2d_fwd_ex(d, U=w.wino_filter_transform(g, 4), K=K, pad=1, m=4, flags=w.FLAG_FUSED)
+        Y = w.wino_conv2d_fwd_ex(d, U=w.wino_filter_transform(g, m), K=K, pad=1, m=m, flags=w.FLAG_FUSED)
     assert bool(torch.isfinite(Y).all())
-    check_close(Y.cpu().numpy(), ref, TOL[("f32", 4)], "C=%d, %s given" % (C, given), 4)
+    check_close(Y.cpu().numpy(), ref, TOL[(dtype, m)] * (1.2 if dtype == "f16" else 1), "C=%d, %s given" % (C, given), m)
 
 
 def test_fused_flag_rejected_where_unsupported():
@@ -420,31 +430,33 @@ def test_fused_flag_rejected_where_unsupported():
     assert ei.value.status == w.WINO_EUNSUPPORTED
 
 
-@pytest.mark.parametrize("dtype", ["f32", "f16"])
+@pytest.mark.parametrize("dtype,m,N", [("f32", 4, 2), ("f16", 4, 2), ("f32", 2, 2),
+                                       ("f32", 4, 74), ("f16", 4, 74), ("f32", 2, 37)])      # 130 items: fused_split.hip
 @pytest.mark.parametrize("pos", [(0, 0), (3, 27), (4, 0), (7, 28), (11, 55), (12, 31), (15, 32)])
-def test_one_kernel_path_keeps_a_nan_inside_the_tiles_that_read_it(dtype, pos):
+def test_one_kernel_path_keeps_a_nan_inside_the_tiles_that_read_it(dtype, m, N, pos):
     """The one-kernel kernels take a tile's outer columns from the registers of the neighbouring lanes, which hold
     the neighbouring tiles -- or, at the image border, the last tile of the tile row above resp. the first of the
     one below, whose values must not be used.  One NaN in the input must reach exactly the outputs of the tiles
     whose 6 x 6 window (rows 4 tx - 1 .. 4 tx + 4, columns 4 ty - 1 .. 4 ty + 4) holds it, in the image that has
     it: a value leaking over from a neighbouring lane would poison a tile outside that set.  Within such a tile
     the first window row (column) enters only the first transformed component (B^T of Eq. (15) has (4, 0, ...) as
-    its first column), which feeds only the first output row (column); the last one likewise only the last."""
+    its first column), which feeds only the first output row (column); the last one likewise only the last.  F(2x2,3x3)
+    alike, with 4 x 4 windows."""
     torch, w = require_gpu()
-    N, C, H, W, K = 2, 16, 16, 56, 64          # 14 tiles per row: blocks of 16 (or 32) lanes straddle tile rows
+    C, H, W, K = 16, 16, 56, 64                # 14 (28) tiles per row: blocks of 16, 32 or 64 tiles straddle tile rows
     np_dt = np.float32 if dtype == "f32" else np.float16
     D, G = synth.make_layer(N, C, H, W, K, seed=4242, dtype=np_dt)
     x, y = pos
-    D[1, 5, x, y] = np.nan
-    Y = w.wino_conv2d_fwd_ex(to_gpu(D), G=to_gpu(G), pad=1, m=4, flags=w.FLAG_FUSED).float().cpu().numpy()
+    D[N - 1, 5, x, y] = np.nan
+    Y = w.wino_conv2d_fwd_ex(to_gpu(D), G=to_gpu(G), pad=1, m=m, flags=w.FLAG_FUSED).float().cpu().numpy()
     want = np.zeros((N, H, W), dtype=bool)
     def reached(t, z):          # outputs of tile t along one axis that a NaN at coordinate z of that axis reaches
-        q = z - (4 * t - 1)
-        return [] if q < 0 or q > 5 else [4 * t] if q == 0 else [4 * t + 3] if q == 5 else list(range(4 * t, 4 * t + 4))
-    for tx in range(H // 4):
-        for ty in range(W // 4):
+        q = z - (m * t - 1)
+        return [] if q < 0 or q > m + 1 else [m * t] if q == 0 else [m * t + m - 1] if q == m + 1 else list(range(m * t, m * t + m))
+    for tx in range(H // m):
+        for ty in range(W // m):
             for ox in reached(tx, x):
                 for oy in reached(ty, y):
-                    want[1, ox, oy] = True
+                    want[N - 1, ox, oy] = True
     got = np.isnan(Y)
     assert (got == want[:, None, :, :]).all(), "NaN outputs %d, expected %d" % (got.sum(), want.sum() * K)

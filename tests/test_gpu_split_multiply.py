@@ -13,19 +13,26 @@ pytestmark = pytest.mark.gpu
 # 32-channel slabs whose last one is half empty
 @pytest.mark.parametrize("K,C,P", [(256, 16, 3600), (256, 48, 3600), (200, 64, 3300), (128, 48, 130), (70, 80, 300),
                                    (40, 112, 100)])
-@pytest.mark.parametrize("spread", [0, 6])
+@pytest.mark.parametrize("spread", [0, 6, "low parts"])
 def test_multiply_is_as_precise_as_fp32(K, C, P, spread):
     torch, w = require_gpu()
     m, a = 2, 4
+    worst = spread == "low parts"
+    spread = 0 if worst else spread
     rng = np.random.default_rng(K + C + P + spread)
     # `spread`: magnitudes over 2^+-spread, so that the parts of the values meet in every combination of orders
     u = (rng.standard_normal((a, a, K, C)) * 2.0 ** rng.integers(-spread, spread + 1, (a, a, K, C))).astype(np.float32)
     v = (rng.standard_normal((a, a, C, P)) * 2.0 ** rng.integers(-spread, spread + 1, (a, a, C, P))).astype(np.float32)
+    if worst:       # operands whose products of parts that are left out are as large as they can be, 2^-24 of the product
+        u, v = np.sign(u) * np.float32(1 + 2.0 ** -8 - 2.0 ** -17), np.sign(v) * np.float32(1 + 2.0 ** -8 - 2.0 ** -17)
     M = w.unpack_m(w.wino_batched_gemm(w.pack_u(u, m), w.pack_v(v, m), K, C, P, m), K, P, m)
     ref = wg.multiply(u.astype(np.float64), v.astype(np.float64))
-    # every term may be off by the products left out (2^-25.9) and by one fp32 rounding per accumulation (2^-24 each)
-    bound = (C + 1) * 2.0 ** -24 * wg.multiply(np.abs(u).astype(np.float64), np.abs(v).astype(np.float64))
+    # every term may be off by the products left out (2^-24 of it), every sum by six accumulations per 16 channels, each
+    # off by a unit in the last place of what it holds (2^-23) at most
+    bound = (1 + 12 * -(-C // 16)) * 2.0 ** -24 * wg.multiply(np.abs(u).astype(np.float64), np.abs(v).astype(np.float64))
     assert (np.abs(M - ref) <= bound).all()
+    if worst:
+        return
     chain = np.zeros((a, a, K, P), dtype=np.float32)            # fp32 multiply-adds in channel order (rounded twice)
     for c in range(C):
         chain += u[:, :, :, c, None] * v[:, :, None, c, :]

@@ -64,7 +64,7 @@ def test_shared_last_round_on_overlapping_streams():
     workspace: calls on different streams with workspaces of their own may overlap, and each must give the result
     the same call gives alone, bit for bit."""
     torch, w = require_gpu()
-    N, C, H, W, K = 2, 256, 96, 96, 512                     # a last round of 8 items per XCD, 8 shares each
+    N, C, H, W, K = 2, 256, 96, 96, 512                     # a last round of 4 items per XCD, 8 shares each
     D, G = synth.make_layer(N, C, H, W, K, seed=78)
     d, g = to_gpu(D), to_gpu(G)
     U = w.wino_filter_transform(g, 4)
