@@ -966,12 +966,13 @@ bool fused_split_eligible(const Geo &g)
 long long fused_split_items(const Geo &g) { return fs_n_tb(g) * fs_n_kb(g); }
 
 // Estimate of the launch's time in microseconds, for the choice between it and the four stages: rounds of the slowest
-// XCD, each a fixed part (opening an item, inverse transform, stores) and its channel steps, and the two launches.  Fitted to 64 -> 64 channels
-// at 112 x 112 (169 us), 256 -> 256 at 56 x 56 (479) and 512 -> 512 at 28 x 28 (485) for F(4x4,3x3), 512 -> 512 at
-// 14 x 14 (207, N = 32: 109) for F(2x2,3x3), all others N = 64; 256 -> 512 at 28 x 28, N = 16: 87, estimate 85.
+// XCD, each a fixed part (opening an item, inverse transform, stores) and its channel steps, and the two launches.  Fitted
+// for F(4x4,3x3), N = 64, to 64 -> 64 channels at 112 x 112 (169 us), 256 -> 256 at 56 x 56 (479) and 512 -> 512 at 28 x 28
+// (485); for F(2x2,3x3) to 512 -> 512 at 14 x 14 (N = 64: 206 us, estimate 202; N = 32: 105, 105; four stages 227 and 120),
+// 512 -> 512 at 28 x 28, N = 8 (105, 105; four stages 120) and 256 -> 256 at 56 x 56, N = 4 (63, 64; 78).
 double fused_split_us(const Geo &g)
 {
-    const double item_us = g.m == 4 ? 6.4 : 8.0, step_us = g.m == 4 ? 4.4 : 3.0;
+    const double item_us = g.m == 4 ? 6.4 : 14.0, step_us = g.m == 4 ? 4.4 : 2.6;
     const int n_kb = fs_n_kb(g), groups = fs_groups(g, n_kb), n_s = g.Cp / FS_C;
     double worst = 0.0;
     for (int xcd = 0; xcd < 8; ++xcd) {

@@ -4,9 +4,10 @@
 // images of w . v,  dG = A^T M A.  The sum over blocks is 16 matrix products
 // M^(e)[K x C] = W^(e)[K x Pb] V^(e)[C x Pb]^T whose reduction index is the block index b.
 //
-// Stages, each its own kernel: error transform (E -> W[e][k][b]), data transform (D -> V[e][c][b]),
-// the 16 products on fp32 MFMAs with the reduction split over workgroups, and the inverse
-// transform that also adds the partial products.  fp32, stride 1, pad 1.
+// With W % 4 == 0 one kernel transforms both tensors and multiplies on the bf16 matrix units (wgrad_fused_kernel);
+// otherwise error transform (E -> W[e][k][b]), data transform (D -> V[e][c][b]) and the 16 products on fp32 matrix
+// instructions are kernels of their own.  Either way the reduction is split over workgroups and the inverse transform
+// adds the partial products.  fp32, stride 1, pad 1.
 #include <stdlib.h>
 
 #include "wino_internal.h"
