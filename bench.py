@@ -217,8 +217,9 @@ def stage_plan(torch, w, L, ws, sets):
                   "gemm": nU + nV + nM}          # U and V read, M (fp32) written
         bm, bn, _ = w.wino_gemm_launch_shape(L.K, L.C, L.P, L.m, L.dt)
         tile = "%d, %d" % (bm, bn)
-        bk = 16 if (bm, bn) == (128, 128) or L.C % 32 != 0 else 32      # slab depth the library picks for this block shape
-        kernel = ("gemm_f32_kernel<%s, 2, 2, %d>" % (tile, bk)) if L.dt == w.WINO_F32 else ("gemm_f16_kernel<%s>" % tile)
+        bk = 16 if (bm, bn) == (128, 128) else 32          # slab depth and number of slabs (0: one, 1: more, 2: over 2048 channels)
+        depth = 0 if L.C <= bk else 1 if L.C <= 2048 else 2
+        kernel = ("gemm_f32_kernel<%s, %d, %d>" % (tile, bk, depth)) if L.dt == w.WINO_F32 else ("gemm_f16_kernel<%s>" % tile)
     return plans, nbytes, kernel, 2 * a2 * L.K * L.C * L.P
 
 
@@ -720,6 +721,29 @@ def probe(torch, w, layers, ws):
                                   "bytes": x["bytes"]} for L, x in zip(layers, st) if x]}))
 
 
+def compact(x):
+    """A record as one readable line: five digits, one number per layer, without notes and the tables of separate kernels."""
+    if isinstance(x, float):
+        return float("%.5g" % x)
+    if isinstance(x, list):
+        return [compact(v) for v in x]
+    if not isinstance(x, dict):
+        return x
+    out = {}
+    for k, v in x.items():
+        if k in ("note", "stages", "vgg_e_weighted", "f6x6", "layers_changed_ms") or (k in ("per_layer", "algorithm") and isinstance(v, dict)):
+            continue
+        if k == "kernels" and not isinstance(v, str):
+            out[k] = {n: compact(r.get("avg_launch_ms")) for n, r in v.items()} if isinstance(v, dict) else None
+            continue
+        if isinstance(v, list) and v and isinstance(v[0], dict):
+            if "layer" in v[0] and "ms" in v[0]:
+                out[k + "_ms"] = {r["layer"]: compact(r["ms"]) for r in v}
+                continue
+        out[k] = compact(v)
+    return out
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -744,6 +768,7 @@ def main():
     ap.add_argument("--probe", action="store_true",
                     help="for rocprofv3 --pmc runs: one 1 GiB device copy (counter calibration), then every "
                          "kernel of one step of the chosen leg twice; prints the algorithmic bytes per kernel and exits")
+    ap.add_argument("--full", action="store_true", help="print every figure (40 KB) instead of the summary")
     args = ap.parse_args()
     if args.gpus != 1:
         print("bench.py: this build runs on one GPU only (batch sharding across GPUs is a design note, "
@@ -841,7 +866,7 @@ def main():
         if not args.no_single:
             out["cfg2"] = single_layer_leg(torch, w, args, 8, 512, 28, 512, (2, 4), 2, "vgg_layer_512_512_28x28_N8_f32")
             out["cfg1"] = single_layer_leg(torch, w, args, 1, 32, 56, 32, (2,), 1, "layer_32_32_56x56_N1_f32")
-    print(json.dumps(out))
+    print(json.dumps(out if args.full else compact(out)))
 
 
 if __name__ == "__main__":

@@ -21,7 +21,9 @@
  *   - Return value: a wino_status_t.  No exceptions, no abort.  Arguments are checked before
  *     any GPU call, so bad arguments are reported even on a machine with no GPU.
  *   - Storage type `dt` is that of D, G, U and V; products are always accumulated in fp32 and
- *     M is always fp32.
+ *     M is always fp32.  fp32 products run on the bf16 matrix units where those are faster, every value in
+ *     three exact parts: sums are as precise as chains of fp32 multiply-adds, over the whole range of fp32,
+ *     and what is infinite or NaN is so where the fp32 operations make it so.
  *
  * Transform-domain layouts (alpha = m + 2; component index e = xi*alpha + nu; all row-major):
  *     fp32:  U[e][c][k]          extents [alpha^2][Cp][Kp]
