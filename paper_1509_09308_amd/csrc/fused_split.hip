@@ -62,28 +62,32 @@ constexpr int FS_TICKETS = 1024, FS_TICKET_BYTES = FS_TICKETS * 4;   // arrival 
 constexpr int FS_BLOCK_BYTES = 3 * 1024;
 static size_t fs_filter_bytes(const Geo &g) { return (size_t)g.a2 * (g.Cp / 16) * (g.Kp / 32) * FS_BLOCK_BYTES; }
 
-// Filters that the scaling takes out of bounds (and infinite ones) are kept whole for fused_split_again: NaN as first
-// part, the value's bits as the other two.
-constexpr float FS_WHOLE = 0x1p103f;
 __device__ __forceinline__ void fs_store_parts(char *dst, int lane, const float (&x)[8])
 {
     uintx4_b p[3];
     bf16_split8(x, p, BF16_SCALE);
-    float t = 0.0f;
-#pragma unroll
-    for (int j = 0; j < 8; j += 2) t = bf16_look(x[j], x[j + 1], t);
-    if (__any(!(t < FS_WHOLE))) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-            if (!(__builtin_fabsf(x[j]) < FS_WHOLE)) {
-                const unsigned bits = __builtin_bit_cast(unsigned, x[j]), low = 16 * (j % 2), keep = 0xffff0000u >> low;
-                p[0][j / 2] = (p[0][j / 2] & keep) | 0x7fc0u << low;
-                p[1][j / 2] = (p[1][j / 2] & keep) | (bits >> 16) << low;
-                p[2][j / 2] = (p[2][j / 2] & keep) | (bits & 0xffffu) << low;
-            }
-    }
 #pragma unroll
     for (int q = 0; q < 3; ++q) *reinterpret_cast<uintx4_b *>(dst + q * 1024 + lane * 16) = p[q];
+}
+
+// Filters that the scaling takes out of bounds (and infinite ones) are kept whole for fused_split_again: NaN as first
+// part, the value's bits as the other two.  (Stored over the parts, behind everything else, where it is in nobody's way.)
+constexpr float FS_WHOLE = 0x1p103f;
+__device__ __forceinline__ float fs_largest(const float (&x)[8], float t)
+{
+#pragma unroll
+    for (int j = 0; j < 8; j += 2) t = bf16_look(x[j], x[j + 1], t);
+    return t;
+}
+__device__ __forceinline__ void fs_store_whole(char *dst, int lane, const float (&x)[8])
+{
+    unsigned short *at = reinterpret_cast<unsigned short *>(dst + lane * 16);
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        if (!(__builtin_fabsf(x[j]) < FS_WHOLE)) {
+            const unsigned bits = __builtin_bit_cast(unsigned, x[j]);
+            at[j] = 0x7fc0, at[512 + j] = (unsigned short)(bits >> 16), at[1024 + j] = (unsigned short)bits;
+        }
 }
 
 __device__ __forceinline__ void fs_clear(unsigned *tickets)
@@ -137,9 +141,18 @@ __global__ __launch_bounds__(64 * (M + 2)) void filter_split_kernel(const float 
 #pragma unroll
             for (int nu = 0; nu < A; ++nu) u[nu][j] = o[nu];
         }
+        char *dst = Us + (((size_t)(xi * A) * n_s + s) * n_kb + kb) * FS_BLOCK_BYTES;
+        const size_t next = (size_t)n_s * n_kb * FS_BLOCK_BYTES;
+        float t = 0.0f;
 #pragma unroll
-        for (int nu = 0; nu < A; ++nu)
-            fs_store_parts(Us + (((size_t)(xi * A + nu) * n_s + s) * n_kb + kb) * FS_BLOCK_BYTES, lane, u[nu]);
+        for (int nu = 0; nu < A; ++nu) {
+            t = fs_largest(u[nu], t);
+            fs_store_parts(dst + nu * next, lane, u[nu]);
+        }
+        if (__any(!(t < FS_WHOLE))) {
+#pragma unroll
+            for (int nu = 0; nu < A; ++nu) fs_store_whole(dst + nu * next, lane, u[nu]);
+        }
     };
     switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
     case 0: row(std::integral_constant<int, 0>()); break;
@@ -161,7 +174,9 @@ __global__ __launch_bounds__(64) void filter_resplit_kernel(const float *__restr
     float x[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) x[j] = src[(size_t)j * Kp];
-    fs_store_parts(Us + (((size_t)e * n_s + s) * n_kb + kb) * FS_BLOCK_BYTES, lane, x);
+    char *dst = Us + (((size_t)e * n_s + s) * n_kb + kb) * FS_BLOCK_BYTES;
+    fs_store_parts(dst, lane, x);
+    if (__any(!(fs_largest(x, 0.0f) < FS_WHOLE))) fs_store_whole(dst, lane, x);
 }
 
 // ---- items -----------------------------------------------------------------------------------------
