@@ -42,7 +42,8 @@ __device__ __forceinline__ int xcd_remap(int bid, int nblocks)
 // 118 TFLOP/s with v_mfma_f32_32x32x2_f32 (501 us), 184 so (320 us); 512 -> 512 channels at 28 x 28, batch 8: multiply
 // 83 -> 53 us.  Single-buffered slabs of 32 channels on v_mfma_f32_16x16x32_bf16, which takes an eighth less energy,
 // but with two barriers and no split between the matrix instructions: 355 us (matrix pipes 46 % busy).  (Operands were
-// split as they are then; the multiplication by 2^24, for the whole range of fp32, costs 5 %: that layer 84.1 -> 86.7 us.)
+// split as they are then.  The multiplication by 2^24, for the whole range of fp32, costs 4 %: the same 36 products on
+// another box 364 -> 377 us, 479 with fp32 instructions; that layer 84.1 -> 86.7 us.)
 __device__ __forceinline__ void gemm_lds_barrier()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
