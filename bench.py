@@ -731,7 +731,7 @@ def compact(x):
         return x
     out = {}
     for k, v in x.items():
-        if k in ("note", "stages", "vgg_e_weighted", "f6x6", "layers_changed_ms") or (k in ("per_layer", "algorithm") and isinstance(v, dict)):
+        if k in ("note", "stages", "sample", "vgg_e_weighted", "f6x6", "layers_changed_ms", "direct_gflop_per_step") or (k in ("per_layer", "algorithm") and isinstance(v, dict)):
             continue
         if k == "kernels" and not isinstance(v, str):
             out[k] = {n: compact(r.get("avg_launch_ms")) for n, r in v.items()} if isinstance(v, dict) else None
