@@ -21,14 +21,21 @@
 // tiles 800 vector instructions per SIMD (transform and split, 3200 cycles).  128 x 16 would double the first, 32 x 64
 // the second.
 //
-// What bounds it: 6 500 cycles per step (multiply and transform of either wavefront 2 500 - 2 700 each), 27 000 per item
-// around them (first taps, inverse transform, the stores of all CUs at once), at a clock that falls to 1.7 GHz under the
-// power of it (scaling the data for the whole range of fp32, bf16x3.h, costs 1 - 3 %).  256 -> 256 channels at 56 x 56, N = 64: 590 us in fused_wide.hip, 480 here.
+// What bounds it: 6 500 cycles per step (multiply and transform of either wavefront 2 500 - 2 700 each, of which the vector
+// instructions' issue slots are 1 840), 22 500 per item around them (inverse transform and opening of the next item), at a
+// clock that falls to 1.7 GHz under the power of it (scaling the data for the whole range of fp32, bf16x3.h, costs 1 - 3 %).
+// 256 -> 256 channels at 56 x 56, N = 64: 590 us in fused_wide.hip, 458 here.
+//
+// Between items: the inverse transform in four pieces of 16 filters, each written to one half of LDS while the one before is
+// read from the other, and the next item opened inside it, against 32 filters at a time, both phases of a piece one after the
+// other and the next item after everything (27 000 cycles): 64 -> 64 channels at 224 x 224, N = 64: 704 -> 651 us, 64 -> 128 at
+// 112 x 112: 320 -> 293, 512 -> 512 at 28 x 28: 469 -> 456; fp16 storage, N = 32: 195 -> 185, 116 -> 105, 128 -> 128 at 112 x
+// 112: 168 -> 155.
 //
 // fp16 storage (F(4x4,3x3)): the same with one part per value -- U as the filter transform lays it down is in operand
 // order already, a tile's 16 channels are 32 bytes of LDS, a unit is one matrix instruction, and the filters of a whole
 // step are in flight.  The transform and the per-item part bound it: 64 -> 64 channels at 224 x 224, N = 32: 244 us in
-// fused_f16.hip, 195 here; 128 -> 128 at 112 x 112: 228, 168.
+// fused_f16.hip, 185 here; 128 -> 128 at 112 x 112: 228, 155.
 //
 // Items and the shared last round as in fused_wide.hip.
 #include <type_traits>
@@ -49,7 +56,7 @@ constexpr int FS_K = 64, FS_C = 16, FS_T = 512;                      // filters,
 constexpr int fs_tiles(int m) { return m == 4 ? 32 : 64; }           // tiles per item
 constexpr int fs_v_floats(int m) { return (m + 2) * (m + 2) * FS_C * fs_tiles(m); }
 static_assert((4 + 2) * (4 + 2) * 32 * fs_tiles(4) <= 2 * fs_v_floats(4) && 16 * 32 * fs_tiles(2) <= 2 * fs_v_floats(2),
-              "the epilogue (32 filters of all components at a time) reuses the two tile buffers");
+              "the inverse transform (two pieces of 16 filters of all components) reuses the two tile buffers");
 constexpr unsigned FS_MAX_BYTES = 0x40000000u;                       // longest stretch of D one workgroup's buffer covers
 constexpr unsigned FS_ROW_OOB = 0x80000000u, FS_COL_OOB = 0x40000000u;   // offset markers of taps outside the image
 constexpr int FS_GRID = 256;                                         // resident workgroups: one per CU
@@ -323,15 +330,17 @@ __device__ __forceinline__ void fused_split_body(const T *__restrict__ D, const 
     bool left_in[NPR], right_in[NPR];
     auto place = [&]() {
     const int l = fs_lane(), tl = l & 15, cl = (wave >> 1) * 4 + (l >> 4);
+    int Tw = g.Tw, Th = g.Th;
+    asm volatile("" : "+s"(Tw), "+s"(Th));     // (opaque: no reciprocals are kept in registers across the steps)
 #pragma unroll
     for (int r = 0; r < NPR; ++r) {
         const int b = b0 + (wave & 1) * 16 + 32 * r + tl;
         const bool tile_ok = b < g.P;
         const int bb = tile_ok ? b : b0;
-        const int ty = bb % g.Tw;
-        const int t2 = bb / g.Tw;
-        const int tx = t2 % g.Th;
-        const int i = t2 / g.Th;
+        const int ty = bb % Tw;
+        const int t2 = bb / Tw;
+        const int tx = t2 % Th;
+        const int i = t2 / Th;
         const int x0 = M * tx - 1, y0 = M * ty - 1;
         left_in[r] = y0 >= 0;
         right_in[r] = y0 + A - 1 < g.W;
@@ -480,6 +489,19 @@ __device__ __forceinline__ void fused_split_body(const T *__restrict__ D, const 
         __builtin_amdgcn_sched_barrier(0x38f);
     };
 
+    // An item's first tiles, from taps that have been requested, and the requests of its second step.
+    auto open_item = [&]() {
+        transform(0);
+        __builtin_amdgcn_sched_barrier(0x38f);
+        load_taps(step0 + 1, nsteps > 1);
+        if constexpr (R == 0) {
+            // (the filter operands once more, behind the taps: the compiler's waits in the loop take the worst of both ways
+            // into it)
+            __builtin_amdgcn_sched_barrier(0x38f);
+            first_units(true);
+        }
+    };
+
     auto run = [&]() {
         constexpr int N0 = R * NU, C0 = N0 / 2, NC = (N0 + NU - 1) / 2 - C0 + 1;
         // part q of the operands of unit u
@@ -576,25 +598,6 @@ __device__ __forceinline__ void fused_split_body(const T *__restrict__ D, const 
             su += step_u;
             }
         };
-#pragma unroll
-        for (int u = 0; u < NU; ++u)
-#pragma unroll
-            for (int j = 0; j < TB; ++j)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) acc[u][j][i] = 0.0f;
-        transform(0);
-        __builtin_amdgcn_sched_barrier(0x38f);
-        load_taps(step0 + 1, nsteps > 1);
-        if constexpr (R == 0) {
-            // (once more, behind the taps: the compiler's waits in the loop take the worst of both ways into it)
-            __builtin_amdgcn_sched_barrier(0x38f);
-#pragma unroll
-            for (int u = 0; u < NR; ++u)
-#pragma unroll
-                for (int q = 0; q < NP; ++q) request(u, q, uvo, su);
-            __builtin_amdgcn_sched_barrier(0x38f);
-        }
-        fs_lds_barrier();
         int step = 0;
         do {
             const int buf = step & 1;
@@ -619,22 +622,19 @@ __device__ __forceinline__ void fused_split_body(const T *__restrict__ D, const 
             fs_lds_barrier();
         } while (++step < nsteps);
     };
-    if (!find()) return;
-    place();
-    load_taps(step0, true);
-    first_units(true);
-    for (bool more_items = true; more_items;) {
-    run();
+    // The inverse transform of an item: four pieces of 16 filters through the two tile buffers, one written while the one
+    // before is transformed and stored.  NEXT: the next item is opened in between -- its first requests go out as soon as
+    // half of the accumulators' registers are free, its first tiles are transformed before the last piece.  (Two copies:
+    // the requests and stores in flight at the head of the loop over steps do not depend on the path taken.)
+    auto finish = [&](auto next) {
+    constexpr bool NEXT = decltype(next)::value;
+    const int o_k0 = k0, o_b0 = b0, o_img0 = img0;                // what is needed of this item
+    const bool o_shared = !NEXT && shared;
 
-    const int o_k0 = k0, o_b0 = b0, o_img0 = img0, o_it = it;  // what the epilogue needs of this item
-    const bool o_shared = shared;
-
-    // ---- inverse transform, 32 filters at a time --------------------------------------------------------
     constexpr int NJ = M * M / 2;              // pairs of outputs per (filter, tile)
-    constexpr int RP = 32 * P / FS_T;          // (filter, tile) pairs of a thread per 32 filters
-    float *Ms = smem;                          // [e][filter][tile]
-    const int el = fs_lane(), et = wave * 64 + el, eli = el & 31, elh = el >> 5;
-    const int ot = et % P, irow = et / P;
+    constexpr int ROWS = FS_T / P;             // filters that the threads cover at a time
+    constexpr int RP = 16 / ROWS;              // (filter, tile) pairs of a thread per piece
+    const int et = wave * 64 + fs_lane(), ot = et % P, irow = et / P;
     const int ob = o_b0 + ot;
     const bool out_ok = ob < g.P;
     // Y from the item's first image and filter on; filter and row of the tile go into the scalar offset
@@ -642,67 +642,19 @@ __device__ __forceinline__ void fused_split_body(const T *__restrict__ D, const 
     unsigned y_vo;
     {
         const int bb = out_ok ? ob : o_b0;
-        const int ty = bb % g.Tw;
-        const int t2 = bb / g.Tw;
-        const int tx = t2 % g.Th;
+        int Tw = g.Tw, Th = g.Th;
+        asm volatile("" : "+s"(Tw), "+s"(Th));
+        const int ty = bb % Tw;
+        const int t2 = bb / Tw;
+        const int tx = t2 % Th;
         rows = g.Ho - M * tx;
-        y_vo = (unsigned)((((t2 / g.Th - o_img0) * g.K + irow) * g.Ho + M * tx) * g.Wo + M * ty) * (unsigned)sizeof(TY);
+        y_vo = (unsigned)((((t2 / Th - o_img0) * g.K + irow) * g.Ho + M * tx) * g.Wo + M * ty) * (unsigned)sizeof(TY);
     }
     const unsigned plane_bytes = (unsigned)(g.Ho * g.Wo) * (unsigned)sizeof(TY);
     const size_t y_first = ((size_t)o_img0 * g.K + o_k0) * g.Ho * g.Wo;
     const size_t y_left = ((size_t)g.N * g.K * g.Ho * g.Wo - y_first) * sizeof(TY);
     const __amdgpu_buffer_rsrc_t rsrc_y =
         __builtin_amdgcn_make_buffer_rsrc((void *)(Y + y_first), 0, (unsigned)(y_left < 0x7fffffffu ? y_left : 0x7fffffffu), 0x00020000);
-    float y[2 * RP][M][M];                     // piece n: filter rows n FS_T / P + irow
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        // accumulator register i of lane (li, lh) is filter row 8 (i / 4) + 4 lh + i % 4, tile li
-#pragma unroll
-        for (int u = 0; u < NU; ++u) {
-            const int n = R * NU + u;
-            if (n % 2 == h) {
-#pragma unroll
-                for (int j = 0; j < TB; ++j)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i)
-                        Ms[((simd * NU + n / 2) * 32 + 8 * (i / 4) + 4 * elh + i % 4) * P + j * 32 + eli] = acc[u][j][i];
-            }
-        }
-        fs_lds_barrier();
-        if (h == 1) {
-            // The next item's first requests: the accumulators' registers are free, and no store of this item has been
-            // issued, behind which they would wait (loads and stores of a wavefront complete in order for its counter).
-            it += slots;
-            more_items = find();
-            if (more_items) place();
-            load_taps(step0, more_items);
-            first_units(more_items);
-        }
-#pragma unroll
-        for (int rp = 0; rp < RP; ++rp) {
-            __builtin_amdgcn_sched_barrier(0);
-            const int row = rp * (FS_T / P) + irow;
-            float tt[M][A];
-#pragma unroll
-            for (int nu = 0; nu < A; ++nu) {
-                float col[A], o[M];
-#pragma unroll
-                for (int xi = 0; xi < A; ++xi) col[xi] = Ms[((xi * A + nu) * 32 + row) * P + ot];
-                at_mul<M>(col, o);
-#pragma unroll
-                for (int p = 0; p < M; ++p) tt[p][nu] = o[p];
-            }
-#pragma unroll
-            for (int p = 0; p < M; ++p) {
-                at_mul<M>(tt[p], y[h * RP + rp][p]);
-                if constexpr (!F16) {
-#pragma unroll
-                    for (int q = 0; q < M; ++q) y[h * RP + rp][p][q] *= BF16_UNSCALE;
-                }
-            }
-        }
-        fs_lds_barrier();
-    }
     // outputs that are not finite are formed again at the end (fused_split_again)
     auto look = [&](const float (&o)[M][M], int *flag) {
         float t = 0.0f;
@@ -712,36 +664,92 @@ __device__ __forceinline__ void fused_split_body(const T *__restrict__ D, const 
             for (int q = 0; q < M; q += 2) t = bf16_look(o[p][q], o[p][q + 1], t);
         if (!bf16_finite(t)) *flag = 1;
     };
-    // (the requests have arrived before the first store is issued)
+    // partial outputs of a share: [piece][pair j of outputs][thread] pairs of floats
+    float *const dst = partial + (size_t)(xcd * slots + (it - full)) * fs_share_floats(M) + et * 2;
+    // A piece lies in LDS as [e][filter][tile].  Accumulator register i of lane (li, lh) is filter row 8 (i / 4) + 4 lh + i % 4,
+    // tile li.  (Opaque: one address per piece, everything else is in the instructions.)
+    auto piece_at = [&](int offset) {
+        asm volatile("" : "+v"(offset));
+        return smem + offset;
+    };
+    auto write = [&](auto qc) {
+        constexpr int q = decltype(qc)::value;
+        __builtin_amdgcn_sched_barrier(0);
+        const int l = fs_lane();
+        float *const to = piece_at(q % 2 * V_FLOATS + (simd * NU * 16 + 4 * (l >> 5)) * P + (l & 31));
 #pragma unroll
-    for (int r = 0; r < NPR; ++r) {
+        for (int u = 0; u < NU; ++u) {
+            const int n = R * NU + u;
+            if (n % 2 == q / 2) {
 #pragma unroll
-        for (int p = 0; p < A; ++p) asm volatile("" : "+v"(mid[r][p]));
-        asm volatile("" : "+v"(ed[r]));
-    }
+                for (int j = 0; j < TB; ++j)
 #pragma unroll
-    for (int u = 0; u < NR; ++u)
-#pragma unroll
-        for (int q = 0; q < NP; ++q) asm volatile("" : "+v"(ua[u][q]));
-    if (!o_shared) {
-        if constexpr (!F16) {
-#pragma unroll
-            for (int n = 0; n < 2 * RP; ++n) look(y[n], &again[0]);
+                    for (int i = 0; i < 8; ++i)
+                        to[(n / 2 * 16 + 8 * (i / 4) + i % 4) * P + j * 32] = acc[u][j][q % 2 * 8 + i];
+            }
         }
+    };
+    auto outputs = [&](auto qc) {
+        constexpr int q = decltype(qc)::value;
 #pragma unroll
-        for (int n = 0; n < 2 * RP; ++n)
-            fs_store_rows<M, TY>(rsrc_y, y_vo, (unsigned)(n * (FS_T / P)) * plane_bytes, (unsigned)g.Wo * (unsigned)sizeof(TY),
-                             out_ok && o_k0 + n * (FS_T / P) + irow < g.K, rows, y[n]);
-    } else {
-        // partial outputs of this share: [piece][pair j of outputs][thread] pairs of floats
-        float *dst = partial + (size_t)(xcd * slots + (o_it - full)) * fs_share_floats(M) + et * 2;
+        for (int rp = 0; rp < RP; ++rp) {
+            __builtin_amdgcn_sched_barrier(0);
+            const int n = q * RP + rp;
+            const float *const from = piece_at(q % 2 * V_FLOATS + rp * FS_T + wave * 64 + fs_lane());
+            float tt[M][A], y[M][M];
 #pragma unroll
-        for (int n = 0; n < 2 * RP; ++n)
+            for (int nu = 0; nu < A; ++nu) {
+                float col[A], o[M];
 #pragma unroll
-            for (int j = 0; j < NJ; ++j)
-                fs_st_agent(dst + (n * NJ + j) * FS_T * 2, y[n][j / (M / 2)][2 * (j % (M / 2))], y[n][j / (M / 2)][2 * (j % (M / 2)) + 1]);
+                for (int xi = 0; xi < A; ++xi) col[xi] = from[(xi * A + nu) * 16 * P];
+                at_mul<M>(col, o);
+#pragma unroll
+                for (int p = 0; p < M; ++p) tt[p][nu] = o[p];
+            }
+#pragma unroll
+            for (int p = 0; p < M; ++p) {
+                at_mul<M>(tt[p], y[p]);
+                if constexpr (!F16) {
+#pragma unroll
+                    for (int r = 0; r < M; ++r) y[p][r] *= BF16_UNSCALE;
+                }
+            }
+            if (!o_shared) {
+                if constexpr (!F16) look(y, &again[0]);
+                fs_store_rows<M, TY>(rsrc_y, y_vo, (unsigned)(n * ROWS) * plane_bytes, (unsigned)g.Wo * (unsigned)sizeof(TY),
+                                     out_ok && o_k0 + n * ROWS + irow < g.K, rows, y);
+            } else {
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+                    fs_st_agent(dst + (n * NJ + j) * FS_T * 2, y[j / (M / 2)][2 * (j % (M / 2))], y[j / (M / 2)][2 * (j % (M / 2)) + 1]);
+            }
+        }
+    };
+    write(std::integral_constant<int, 0>());
+    fs_lds_barrier();
+    write(std::integral_constant<int, 1>());
+    outputs(std::integral_constant<int, 0>());
+    if constexpr (NEXT) {
+        __builtin_amdgcn_sched_barrier(0);
+        it += slots;
+        find();
+        place();
+        load_taps(step0, true);
+        first_units(true);
+    }
+    fs_lds_barrier();
+    write(std::integral_constant<int, 2>());
+    outputs(std::integral_constant<int, 1>());
+    fs_lds_barrier();
+    write(std::integral_constant<int, 3>());
+    outputs(std::integral_constant<int, 2>());
+    fs_lds_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (NEXT) open_item();           // (into the first tile buffer; the last piece is in the second)
+    outputs(std::integral_constant<int, 3>());
+    if (o_shared) {
         // ---- the share that arrives last adds the partial outputs of all shares, in share order ----
-        const int j_item = (o_it - full) % tail;
+        const int j_item = (it - full) % tail;
         unsigned int *const ticket = &tickets[xcd * slots + j_item];
         __builtin_amdgcn_s_waitcnt(0x0f70);       // vmcnt(0): this wavefront's partial outputs have been acknowledged ...
         __syncthreads();                          // ... and so have those of the others
@@ -750,11 +758,10 @@ __device__ __forceinline__ void fused_split_body(const T *__restrict__ D, const 
             *s_last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)(shares - 1);
         __syncthreads();
         const bool last = *s_last != 0;
-        __syncthreads();                          // (smem is written again by the next item)
         if (last) {
             const float *src0 = partial + (size_t)(xcd * slots + j_item) * fs_share_floats(M) + et * 2;
 #pragma unroll
-            for (int f = 0; f < 2 * RP; ++f) {
+            for (int f = 0; f < 4 * RP; ++f) {
                 floatx2_s y2[NJ];
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) y2[j] = floatx2_s{0.0f, 0.0f};
@@ -777,12 +784,31 @@ __device__ __forceinline__ void fused_split_body(const T *__restrict__ D, const 
                     ys[j / (M / 2)][2 * (j % (M / 2)) + 1] = y2[j][1];
                 }
                 if constexpr (!F16) look(ys, &again[1]);
-                fs_store_rows<M, TY>(rsrc_y, y_vo, (unsigned)(f * (FS_T / P)) * plane_bytes, (unsigned)g.Wo * (unsigned)sizeof(TY),
-                                 out_ok && o_k0 + f * (FS_T / P) + irow < g.K, rows, ys);
+                fs_store_rows<M, TY>(rsrc_y, y_vo, (unsigned)(f * ROWS) * plane_bytes, (unsigned)g.Wo * (unsigned)sizeof(TY),
+                                     out_ok && o_k0 + f * ROWS + irow < g.K, rows, ys);
             }
         }
     }
-    }   // items
+    };
+
+    if (!find()) return;
+    place();
+    load_taps(step0, true);
+    first_units(true);
+    open_item();
+    for (;;) {
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+#pragma unroll
+            for (int j = 0; j < TB; ++j)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[u][j][i] = 0.0f;
+        fs_lds_barrier();
+        run();
+        if (it + slots >= full + tail * shares) break;
+        finish(std::true_type());
+    }
+    finish(std::false_type());                 // (a shared item is the last of its workgroup)
 }
 
 template <typename T, typename TY>
