@@ -4,10 +4,10 @@
 // images of w . v,  dG = A^T M A.  The sum over blocks is 16 matrix products
 // M^(e)[K x C] = W^(e)[K x Pb] V^(e)[C x Pb]^T whose reduction index is the block index b.
 //
-// With W % 4 == 0 one kernel transforms both tensors and multiplies on the bf16 matrix units (wgrad_fused_kernel);
-// otherwise error transform (E -> W[e][k][b]), data transform (D -> V[e][c][b]) and the 16 products on fp32 matrix
-// instructions are kernels of their own.  Either way the reduction is split over workgroups and the inverse transform
-// adds the partial products.  fp32, stride 1, pad 1.
+// One kernel transforms both tensors and multiplies on the bf16 matrix units (wgrad_fused_kernel), except in small layers
+// with W % 4 != 0 (and where its partial products do not fit the workspace); there error transform (E -> W[e][k][b]), data
+// transform (D -> V[e][c][b]) and the 16 products on fp32 matrix instructions are kernels of their own.  Either way the
+// reduction is split over workgroups and the inverse transform adds the partial products.  fp32, stride 1, pad 1.
 #include <stdlib.h>
 
 #include "wino_internal.h"
@@ -263,10 +263,11 @@ __global__ __launch_bounds__(256) void wgrad_gemm_kernel(const float *__restrict
 // issue slots, where those need 1 536.  256 -> 256 channels at 56 x 56, N = 64: 1 264 us with fp32 matrix instructions,
 // 835 so (700 of them without the loads); 512 -> 512 at 28 x 28: 1 073 in separate stages, 804 so.
 // Loads are unconditional from clamped (valid) addresses; what falls outside the image, past the last block or past K / C
-// is zeroed afterwards, so the loop has no branches and no divisions.  Needs W % 4 == 0 (block pairs never straddle a
-// row; 16-byte loads) and tensors of fewer than 2^31 elements (32-bit offsets).  Partial M per share as above.
+// is zeroed afterwards, so the loop has no branches and no divisions.  Needs W >= 4 (16-byte loads) and tensors
+// of fewer than 2^31 elements (32-bit offsets).  Partial M per share as above.
 constexpr int WF_BK = 8, WF_T = 512;
 constexpr int WF_OP = 16 * 64 * WF_BK;                       // floats of one operand of a step
+typedef float floatx4_any __attribute__((ext_vector_type(4), aligned(4)));
 typedef unsigned uintx8_w __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ void wf_lds_barrier()             // orders LDS traffic only: loads stay in flight across it
@@ -277,8 +278,11 @@ __device__ __forceinline__ void wf_lds_barrier()             // orders LDS traff
 }
 
 // ERR: wavefronts 0 - 3 (error blocks, transform first), else 4 - 7 (input tiles, multiply first).
+// OVER: columns by which the rows of block pairs reach past the image's right edge (0 where W % 4 == 0; pairs never straddle
+// a row, so with an odd number of blocks per row the last pair has only one).  The last pair's loads start OVER columns to
+// the left and its values are moved up.
 // LONG: shares of more than BF16_LONG blocks, whose sums are set aside now and then (bf16x3.h), where the partial M will be.
-template <bool ERR, bool LONG>
+template <bool ERR, bool LONG, int OVER>
 __device__ __forceinline__ void wgrad_fused_body(const float *__restrict__ X, float *__restrict__ Mo, const WgradGeo &g, int kt,
                                                  int ct, int z, int slabs_per_share, float *smem, int wave)
 {
@@ -309,21 +313,22 @@ __device__ __forceinline__ void wgrad_fused_body(const float *__restrict__ X, fl
     // lacks its left and the last its right neighbour and fetch those (the others something harmless).
     float xe[NR];
     unsigned okx;              // row p is inside the image, and so is the block
-    bool okl, okr;
+    bool okl, okr, cut;        // cut: the last pair of a row that reaches past the edge
     auto load_raw = [&]() {
         const bool okb = b_cur < g.Pb && row < rows;
         okx = 0;
         okl = by > 0;
         okr = by + 2 < g.Bw;
+        cut = OVER > 0 && !okr;
         const unsigned base = ((unsigned)im * rows + rowc) * g.H * g.W + 2 * by;
 #pragma unroll
         for (int p = 0; p < NR; ++p) {
             const int x = 2 * bx + p - (ERR ? 0 : 1);
             okx |= okb && x >= 0 && x < g.H ? 1u << p : 0u;
             const float *src = X + base + (unsigned)min(max(x, 0), g.H - 1) * g.W;
-            xm[p] = *reinterpret_cast<const floatx4_w *>(src);
+            xm[p] = *reinterpret_cast<const floatx4_any *>(src - (cut ? OVER : 0));
             if constexpr (!ERR) {
-                xe[p] = *(src + (pl == 0 ? (okl ? -1 : 0) : (okr ? 4 : 3)));
+                xe[p] = *(src + (pl == 0 ? (okl ? -1 : 0) : (okr ? 4 : 0)));
             }
         }
         // the pair of the next step
@@ -346,6 +351,9 @@ __device__ __forceinline__ void wgrad_fused_body(const float *__restrict__ X, fl
         for (int p = 0; p < NR; ++p) {
             xm[p] *= scale;
             if constexpr (!ERR) xe[p] *= scale;
+            if constexpr (OVER > 0)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) xm[p][q] = cut ? (q + OVER < 4 ? xm[p][(q + OVER) % 4] : 0.0f) : xm[p][q];
         }
         if constexpr (ERR) {
             // w = G e G^T of the two error blocks
@@ -390,6 +398,9 @@ __device__ __forceinline__ void wgrad_fused_body(const float *__restrict__ X, fl
                 bt32_mul(ta, wa + 4 * p);
                 bt32_mul(tb, wb + 4 * p);
             }
+            if constexpr (OVER >= 2)           // the last pair has one block; nothing of the other one's tile may come in
+#pragma unroll
+                for (int e = 0; e < 16; ++e) wb[e] = cut ? 0.0f : wb[e];
         }
 #pragma unroll
         for (int e = 0; e < 16; ++e)
@@ -556,7 +567,7 @@ __device__ __forceinline__ void wgrad_fused_body(const float *__restrict__ X, fl
     }
 }
 
-template <bool LONG>
+template <bool LONG, int OVER>
 __global__ __launch_bounds__(WF_T, 2) void wgrad_fused_kernel(const float *__restrict__ D, const float *__restrict__ E,
                                                               float *__restrict__ Mo, WgradGeo g, int tiles_k, int tiles_c,
                                                               int slabs_per_share)
@@ -571,9 +582,9 @@ __global__ __launch_bounds__(WF_T, 2) void wgrad_fused_kernel(const float *__res
     const int z = bid / tiles_c;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (wave < 4)
-        wgrad_fused_body<true, LONG>(E, Mo, g, kt, ct, z, slabs_per_share, smem, wave);
+        wgrad_fused_body<true, LONG, OVER>(E, Mo, g, kt, ct, z, slabs_per_share, smem, wave);
     else
-        wgrad_fused_body<false, LONG>(D, Mo, g, kt, ct, z, slabs_per_share, smem, wave);
+        wgrad_fused_body<false, LONG, OVER>(D, Mo, g, kt, ct, z, slabs_per_share, smem, wave);
 }
 
 // First level of the sum over shares when there are many of them: out[zg][i] = sum of in[z][i] over
@@ -763,10 +774,15 @@ static void wgrad_shape(const WgradGeo &g, int *bm, int *bn, int *shares, int *n
     *shares = (nk + *nk_split - 1) / *nk_split;
 }
 
-// Where the one-kernel form applies: block pairs in 16-byte loads, 32-bit offsets.
+// Where the one-kernel form applies: block pairs in 16-byte loads, 32-bit offsets.  With W % 4 != 0 also from 64 MB of W and
+// V on (32 MB with 2^17 products per block), below which the separate stages' many small workgroups win: 64 -> 64 channels
+// at 30 x 30, N = 30: 39 against 46 us; 112 -> 390 at 11 x 11, N = 47: 60 against 62; 16 -> 144 at 65 x 65, N = 5: 58 against 39;
+// 512 -> 512 at 14 x 14, N = 16: 86 against 79; 512 -> 32 at 91 x 91, N = 23: 1 146 against 407.
 static bool wgrad_fused_ok(const WgradGeo &g)
 {
-    if (g.W % 4 != 0) return false;
+    if (g.W < 4) return false;
+    const size_t transformed = (size_t)16 * (g.Kp + g.Cq) * g.Pbp * 4;
+    if (g.W % 4 != 0 && transformed < ((size_t)g.Kp * g.Cq < (1u << 17) ? 1u << 26 : 1u << 25)) return false;
     return (long long)g.N * (g.K > g.C ? g.K : g.C) * g.H * g.W < (1LL << 31);
 }
 
@@ -780,7 +796,12 @@ static void wgrad_fused_shape(const WgradGeo &g, int workgroups, bool long_share
     int want = workgroups / (*tiles_k * *tiles_c);
     const int tiles = *tiles_k * *tiles_c, need = (slabs + BF16_LONG / 16 - 1) / (BF16_LONG / 16);
     if (!long_shares && want < need) want = (need * tiles + 255) / 256 * 256 / tiles;      // (whole rounds of one per CU)
-    if (want > slabs / 4) want = slabs / 4;   // at least 64 blocks per share
+    if (want > slabs / 4) {
+        // at least 64 blocks per share; 32 where the shares are still few enough to be added in one pass (W % 4 != 0 only: the
+        // workspace of the others is sized for 64)
+        const int most = g.W % 4 != 0 && slabs / 4 < WR_MIN_SHARES - 1 ? (slabs / 2 < WR_MIN_SHARES - 1 ? slabs / 2 : WR_MIN_SHARES - 1) : slabs / 4;
+        if (want > most) want = most;
+    }
     if (want < 1) want = 1;
     const int per_share = (slabs + want - 1) / want;
     *shares = (slabs + per_share - 1) / per_share;
@@ -801,21 +822,31 @@ static size_t wgrad_fused_bytes(const WgradGeo &g, int shares)
     return wgrad_align((size_t)shares * 16 * g.Kp * g.Cq * 4) + wgrad_pre_reduce_bytes((size_t)16 * g.Kp * g.Cq, shares);
 }
 
-// Room for the one-kernel form up to 256 filters and channels, beyond that for W, V and M of the separate stages, which
-// is more than the one-kernel form takes unless there are few blocks.
+// Room for the one-kernel form up to 256 filters and channels with W % 4 == 0, otherwise for W, V and M of the separate
+// stages, which is more than the one-kernel form takes unless there are few blocks.
 size_t wgrad_workspace_bytes(int N, int C, int H, int W, int K)
 {
     if (wgrad_direct_ok(C, W))
         return wgrad_align((size_t)N * WD_RS * K * C * 9 * 4) + wgrad_pre_reduce_bytes((size_t)K * C * 9, N * WD_RS);
     const WgradGeo g = make_wgeo(N, C, H, W, K);
     int bm, bn, shares, nk_split;
-    if (wgrad_fused_ok(g) && g.K <= 256 && g.C <= 256) {
+    if (g.W % 4 == 0 && wgrad_fused_ok(g) && g.K <= 256 && g.C <= 256) {
         int tk, tc, sps;
         wgrad_fused_shape(g, 512, true, &tk, &tc, &shares, &sps);
         return wgrad_fused_bytes(g, shares);
     }
     wgrad_shape(g, &bm, &bn, &shares, &nk_split);
     return wgrad_align((size_t)16 * g.Kp * g.Pbp * 4) + wgrad_align((size_t)16 * g.Cq * g.Pbp * 4) + wgrad_fused_bytes(g, shares);
+}
+
+template <int OVER>
+static void wgrad_fused_launch(int slabs_per_share, dim3 grid, const float *D, const float *E, float *Mw, const WgradGeo &g,
+                               int tiles_k, int tiles_c, hipStream_t s)
+{
+    if (slabs_per_share * WF_BK > BF16_LONG)
+        wgrad_fused_kernel<true, OVER><<<grid, dim3(WF_T), 0, s>>>(D, E, Mw, g, tiles_k, tiles_c, slabs_per_share);
+    else
+        wgrad_fused_kernel<false, OVER><<<grid, dim3(WF_T), 0, s>>>(D, E, Mw, g, tiles_k, tiles_c, slabs_per_share);
 }
 
 hipError_t launch_wgrad(int N, int C, int H, int W, int K, const float *D, const float *E, float *dG, void *workspace,
@@ -839,18 +870,25 @@ hipError_t launch_wgrad(int N, int C, int H, int W, int K, const float *D, const
     const size_t room = wgrad_workspace_bytes(N, C, H, W, K);
     // short shares, where the workspace has room for them (beyond 256 filters or channels: 1088 -> 1088 at 28 x 28, N = 32,
     // four instead of one: 3.0 -> 1.9 ms); else two rounds, else one
+    WgradGeo gf = g;                           // whole pairs of blocks in every row
+    gf.Bw = round_up(g.Bw, 2), gf.Pb = N * gf.Bh * gf.Bw;
     for (int n = 0; n < 3 && shares == 0 && wgrad_fused_ok(g); ++n) {
-        wgrad_fused_shape(g, n < 2 ? 512 : 256, n > 0, &tk, &tc, &shares, &sps);
+        wgrad_fused_shape(gf, n < 2 ? 512 : 256, n > 0, &tk, &tc, &shares, &sps);
         if (wgrad_fused_bytes(g, shares) > room) shares = 0;
     }
     if (shares > 0) {
         float *Mw = (float *)workspace;
         float *tmp = (float *)((char *)workspace + (((size_t)shares * 16 * g.Kp * g.Cq * 4 + 255) & ~(size_t)255));
-        const dim3 grid((unsigned)(tk * tc * shares)), block(WF_T);
-        if (sps * WF_BK > BF16_LONG)
-            wgrad_fused_kernel<true><<<grid, block, 0, s>>>(D, E, Mw, g, tk, tc, sps);
+        const dim3 grid((unsigned)(tk * tc * shares));
+        const int over = 2 * gf.Bw - W;
+        if (over == 0)
+            wgrad_fused_launch<0>(sps, grid, D, E, Mw, gf, tk, tc, s);
+        else if (over == 1)
+            wgrad_fused_launch<1>(sps, grid, D, E, Mw, gf, tk, tc, s);
+        else if (over == 2)
+            wgrad_fused_launch<2>(sps, grid, D, E, Mw, gf, tk, tc, s);
         else
-            wgrad_fused_kernel<false><<<grid, block, 0, s>>>(D, E, Mw, g, tk, tc, sps);
+            wgrad_fused_launch<3>(sps, grid, D, E, Mw, gf, tk, tc, s);
         const float *Ms = wgrad_pre_reduce(Mw, tmp, (size_t)16 * g.Kp * g.Cq, &shares, s);
         wgrad_output_kernel<<<dim3((C + 255) / 256, K), dim3(256), 0, s>>>(Ms, dG, g, shares);
         return hipGetLastError();

@@ -31,6 +31,30 @@ def test_wgrad_in_one_kernel(N, C, H, W, K):
     check_close(dG, direct.conv2d_bwd_filter(D, E, pad=1), 1e-5, "%s" % ((N, C, H, W, K),))
 
 
+@pytest.mark.parametrize("N,C,H,W,K", [
+    (600, 33, 7, 5, 70),         # rows of three blocks: the last pair has one, of one column
+    (700, 64, 8, 6, 64),         # of two columns
+    (260, 40, 9, 7, 130),        # rows of four blocks, the last of one column
+    (120, 70, 9, 13, 130),
+    (6, 16, 75, 101, 65),        # pairs of one step in two rows, the last step of a share ragged
+    (30, 256, 94, 94, 256),      # shares of more than 2048 blocks
+])
+def test_wgrad_in_one_kernel_any_width(N, C, H, W, K):
+    """Widths that 4 does not divide, from 64 MB of transformed operands on (smaller layers take the separate stages).
+    What lies behind D and E must not matter: rows end where the next one, the next image or nothing begins."""
+    torch, w = require_gpu()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(N + C + H + W + K)
+    D, E = (torch.randn((N, x, H, W), generator=gen, device="cuda") for x in (C, K))
+    need = w.wino_bwd_filter_workspace_bytes(N, C, H, W, K)
+    ws = torch.full((need // 4 + 1,), float("nan"), device="cuda").view(torch.uint8)[:need]
+    dG = w.wino_conv2d_bwd_filter(D, E, pad=1, workspace=ws)
+    assert bool(torch.isfinite(dG).all())
+    ks, cs = sorted({0, K // 2, K - 1}), sorted({0, C // 2, C - 1})
+    ref = direct.conv2d_bwd_filter(D[:, cs].cpu().numpy(), E[:, ks].cpu().numpy(), pad=1)
+    check_close(dG[ks][:, cs].cpu().numpy(), ref, 1e-5, "%s" % ((N, C, H, W, K),))
+
+
 def test_rounding_does_not_add_up_over_shares():
     """Positive data: every product of the first component grows the sums, the case in which a rounding that always goes
     one way shows most.  fp32 sums of n terms rounded to nearest stay within sqrt(n) 2^-24 of a share's sum."""
