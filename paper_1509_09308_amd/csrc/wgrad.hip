@@ -9,6 +9,7 @@
 // transform (D -> V[e][c][b]) and the 16 products on fp32 matrix instructions are kernels of their own.  Either way the
 // reduction is split over workgroups and the inverse transform adds the partial products.  fp32, stride 1, pad 1.
 #include <stdlib.h>
+#include <type_traits>
 
 #include "wino_internal.h"
 #include "bf16x3.h"
@@ -251,17 +252,18 @@ __global__ __launch_bounds__(256) void wgrad_gemm_kernel(const float *__restrict
 // memory.  A workgroup of 8 wavefronts, one per CU, owns a 64 x 64 block of all 16 M^(e) -- two components per wavefront,
 // 128 accumulators per lane -- and walks its share of the error blocks 8 at a time.  Per step
 //   transform: wavefronts 0 - 3 take two horizontally adjacent 2 x 2 error blocks of one filter per lane, wavefronts 4 - 7
-//     the two 4 x 4 input tiles around them of one channel, from registers requested a step ahead -- per row one aligned
-//     16-byte load plus, for tiles, one of four bytes -- and write the results to LDS as fp32 [e][row][b];
+//     the two 4 x 4 input tiles around them of one channel, from registers requested a step ahead -- one 16-byte load per
+//     row, and one of four bytes for tiles -- and write the results to LDS as fp32 [e][row][b];
 //   multiply: a lane reads four blocks of a row (16 bytes), splits them into three parts once and uses them for 64 rows of
 //     the other operand.  A 32x32x16 instruction has two places per block for them: (l, h) with (h, l), (h, m) with
 //     (m, h), (h, m) with (h, m) are the six products, three instructions per tile and step.
 // Both phases use different LDS buffers (one barrier per step), and the two wavefronts of a SIMD take them in opposite
 // order (fused_split.hip).  The halves of a row of 8 blocks change places every four rows: reads of 16 bytes and writes of
 // 8 are free of bank conflicts.
-// Bound by vector instructions: split 350, transform 190 per SIMD and step, 2 400 cycles with the matrix instructions'
-// issue slots, where those need 1 536.  256 -> 256 channels at 56 x 56, N = 64: 1 264 us with fp32 matrix instructions,
-// 835 so (700 of them without the loads); 512 -> 512 at 28 x 28: 1 073 in separate stages, 804 so.
+// Bound by vector instructions -- split 350, transform and requests 270 per SIMD and step -- and by energy: 4 100 cycles a
+// step at 2 GHz (5 000 at 2.4 with four more requests per step, for the outer columns, and with products and loops in the
+// addresses: 256 -> 256 channels at 56 x 56, N = 64: 1 264 us with fp32 matrix instructions, 796 so, 758 now; 512 -> 512 at 28 x
+// 28, N = 16: 223 -> 213).  Raw data of two steps in flight took another 8 % of the cycles and no time.
 // Loads are unconditional from clamped (valid) addresses; what falls outside the image, past the last block or past K / C
 // is zeroed afterwards, so the loop has no branches and no divisions.  Needs W >= 4 (16-byte loads) and tensors
 // of fewer than 2^31 elements (32-bit offsets).  Partial M per share as above.
@@ -292,68 +294,90 @@ __device__ __forceinline__ void wgrad_fused_body(const float *__restrict__ X, fl
     const int slab_lo = z * slabs_per_share;
     const int slab_hi = min(slab_lo + slabs_per_share, (g.Pb + WF_BK - 1) / WF_BK);
 
-    // position of this thread's pair of blocks (b, b + 1; b even, so is by)
-    int b_cur, by, bx, im;
-    auto place = [&]() {
-        b_cur = slab_lo * WF_BK + 2 * pl;
+    // Position of this thread's pair of blocks (b, b + 1; b even, so is by) of the step requested next, and where its second
+    // (first) row begins in D (E).  A step goes 8 = (qi Bh + qr) Bw + qb blocks ahead: no loops, no products.
+    const unsigned row_elems = (unsigned)g.W, image_elems = (unsigned)rows * (unsigned)g.H * row_elems;
+    const int blocks = g.Bh * g.Bw, qi = WF_BK / blocks, qr = WF_BK % blocks / g.Bw, qb = WF_BK % blocks % g.Bw;
+    const unsigned ahead = 2u * qb + 2u * qr * row_elems + qi * image_elems;
+    const unsigned next_row = 2u * row_elems - 2u * g.Bw, next_image = image_elems - 2u * g.Bh * row_elems;
+    int b_cur, by, bx;
+    unsigned at;
+    auto place = [&](int slab) {
+        b_cur = slab * WF_BK + 2 * pl;
         const int b = min(b_cur, g.Pb - 2);
         by = b % g.Bw;
         const int t2 = b / g.Bw;
         bx = t2 % g.Bh;
-        im = t2 / g.Bh;
+        at = (((unsigned)(t2 / g.Bh) * rows + rowc) * g.H + 2 * bx) * row_elems + 2 * by;
     };
     // Every other share sums the products of the negated error and stores the negative of what it gets.  Adding a small
     // product to a large sum, the instruction rounds down rather than to nearest: on average 3e-8 of a sum over 1 568
     // blocks, little by itself, but the same way in every share and component (64 -> 64 channels at 224 x 224, N = 64, 512
     // shares: error against float64 5.6e-6 without this, with it 1.0e-6; fp32 matrix instructions 1.2e-6).
     const float sign = z % 2 ? -1.0f : 1.0f;
+    // Raw data: error rows 2bx, 2bx+1 or input rows 2bx-1 .. 2bx+2, columns 2by .. 2by+3.  The outer input columns 2by-1 and
+    // 2by+4 are the neighbouring pairs': those of the four lanes that share a row (DPP) and, to the left, of the step before;
+    // to the right of the step's last pair each of the four lanes fetches one row.
     constexpr int NR = ERR ? 2 : 4;
-    floatx4_w xm[NR];          // error rows 2bx, 2bx+1 or input rows 2bx-1 .. 2bx+2, columns 2by .. 2by+3
-    // The outer input columns 2by-1 and 2by+4 are the neighbouring pairs' (DPP); of the four lanes that share a row the first
-    // lacks its left and the last its right neighbour and fetch those (the others something harmless).
-    float xe[NR];
-    unsigned okx;              // row p is inside the image, and so is the block
-    bool okl, okr, cut;        // cut: the last pair of a row that reaches past the edge
+    floatx4_w xm[NR];
+    bool okx[NR];              // the row is inside the image, and so is the block
+    bool okl, okr;             // there is a column to the left, to the right
+    bool cut;                  // the last pair of a row that reaches past the edge
+    float before[4];           // column 2by-1 of the step's first pair, in the lane of the last
+    float edge;                // row pl of column 2by+4 of the step's last pair
     auto load_raw = [&]() {
         const bool okb = b_cur < g.Pb && row < rows;
-        okx = 0;
-        okl = by > 0;
-        okr = by + 2 < g.Bw;
-        cut = OVER > 0 && !okr;
-        const unsigned base = ((unsigned)im * rows + rowc) * g.H * g.W + 2 * by;
-#pragma unroll
-        for (int p = 0; p < NR; ++p) {
-            const int x = 2 * bx + p - (ERR ? 0 : 1);
-            okx |= okb && x >= 0 && x < g.H ? 1u << p : 0u;
-            const float *src = X + base + (unsigned)min(max(x, 0), g.H - 1) * g.W;
-            xm[p] = *reinterpret_cast<const floatx4_any *>(src - (cut ? OVER : 0));
-            if constexpr (!ERR) {
-                xe[p] = *(src + (pl == 0 ? (okl ? -1 : 0) : (okr ? 4 : 0)));
-            }
+        okl = okb && by > 0;
+        okr = okb && by + 2 < g.Bw;
+        cut = OVER > 0 && by + 2 >= g.Bw;
+        // (a row outside the image is read as the one it borders on, and zeroed afterwards)
+        const bool up = bx > 0, down = 2 * bx + 1 < g.H, down2 = 2 * bx + 2 < g.H;
+        const unsigned first = at - (cut ? OVER : 0);
+        auto load = [&](int p, bool ok, unsigned from) {
+            okx[p] = okb && ok;
+            xm[p] = *reinterpret_cast<const floatx4_any *>(X + from);
+        };
+        if constexpr (ERR) {
+            load(0, true, first);
+            load(1, down, first + (down ? row_elems : 0u));
+        } else {
+            load(0, up, first - (up ? row_elems : 0u));
+            load(1, true, first);
+            load(2 % NR, down, first + (down ? row_elems : 0u));
+            load(3 % NR, down2, first + (down2 ? 2u * row_elems : 0u));
         }
-        // the pair of the next step
+        if constexpr (!ERR) {
+            const int bx3 = __builtin_amdgcn_mov_dpp(bx, 0xff, 0xf, 0xf, true);               // (of the last of the four lanes)
+            const int at3 = __builtin_amdgcn_mov_dpp((int)at, 0xff, 0xf, 0xf, true);
+            const int is_ok = __builtin_amdgcn_mov_dpp((int)okr, 0xff, 0xf, 0xf, true);
+            const int down_by = min(max(pl - 1, -2 * bx3), g.H - 1 - 2 * bx3);
+            edge = X[is_ok ? (unsigned)(at3 + 4 + down_by * (int)row_elems) : (unsigned)at3];
+        }
         b_cur += WF_BK;
         if (b_cur < g.Pb) {          // past the end the position stays on the last valid pair
-            by += WF_BK;
-            while (by >= g.Bw) {
-                by -= g.Bw;
-                if (++bx == g.Bh) {
-                    bx = 0;
-                    ++im;
-                }
-            }
+            by += qb, bx += qr, at += ahead;
+            if (by >= g.Bw) by -= g.Bw, bx += 1, at += next_row;
+            if (bx >= g.Bh) bx -= g.Bh, at += next_image;
         }
     };
     float *const t_dst = smem + (ERR ? 0 : WF_OP) + r * WF_BK + (((pl >> 1) ^ ((r >> 2) & 1)) << 2) + 2 * (pl & 1);
     auto transform = [&](int buf, float scale) {
         float t[4][4], o[4], wa[16], wb[16];
+        bool inside = true;
 #pragma unroll
-        for (int p = 0; p < NR; ++p) {
-            xm[p] *= scale;
-            if constexpr (!ERR) xe[p] *= scale;
-            if constexpr (OVER > 0)
+        for (int p = 0; p < NR; ++p) inside = inside && okx[p];
+        if constexpr (OVER > 0)
+            if (__any(cut)) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) xm[p][q] = cut ? (q + OVER < 4 ? xm[p][(q + OVER) % 4] : 0.0f) : xm[p][q];
+                for (int p = 0; p < NR; ++p)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) xm[p][q] = cut ? (q + OVER < 4 ? xm[p][(q + OVER) % 4] : 0.0f) : xm[p][q];
+            }
+        if (__any(!inside)) {
+#pragma unroll
+            for (int p = 0; p < NR; ++p)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) xm[p][q] = okx[p] ? xm[p][q] : 0.0f;
         }
         if constexpr (ERR) {
             // w = G e G^T of the two error blocks
@@ -362,7 +386,7 @@ __device__ __forceinline__ void wgrad_fused_body(const float *__restrict__ X, fl
                 float *dst = blk ? wb : wa;
 #pragma unroll
                 for (int q = 0; q < 2; ++q) {
-                    const float col[2] = {okx & 1u ? xm[0][2 * blk + q] : 0.0f, okx & 2u ? xm[1][2 * blk + q] : 0.0f};
+                    const float col[2] = {scale * xm[0][2 * blk + q], scale * xm[1][2 * blk + q]};
                     g32_mul(col, o);
 #pragma unroll
                     for (int p = 0; p < 4; ++p) t[p][q] = o[p];
@@ -375,22 +399,26 @@ __device__ __forceinline__ void wgrad_fused_body(const float *__restrict__ X, fl
             float d[4][6];
 #pragma unroll
             for (int p = 0; p < 4; ++p) {
-                const bool v = okx & (1u << p);
-                const int pp = p < NR ? p : 0;
-                const float x0 = xm[pp][0], x3 = xm[pp][3];
-                const float from_l = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x3), 0x111, 0xf, 0xf, true));
-                const float from_r = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x0), 0x101, 0xf, 0xf, true));
-                d[p][0] = v && okl ? (pl == 0 ? xe[pp] : from_l) : 0.0f;
+                // (lane l of four gets the last column of lane l - 1, lane 0 what lane 3 had a step before)
+                const float for_right = pl == 3 ? before[p] : xm[p][3];
+                const float from_l = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, for_right), 0x93, 0xf, 0xf, true));
+                const int x0 = __builtin_bit_cast(int, xm[p][0]), e = __builtin_bit_cast(int, edge);
+                const int of_edge = p == 0 ? __builtin_amdgcn_mov_dpp(e, 0x00, 0xf, 0xf, true) : p == 1 ? __builtin_amdgcn_mov_dpp(e, 0x55, 0xf, 0xf, true)
+                                  : p == 2 ? __builtin_amdgcn_mov_dpp(e, 0xaa, 0xf, 0xf, true) : __builtin_amdgcn_mov_dpp(e, 0xff, 0xf, 0xf, true);
+                const int next = __builtin_amdgcn_mov_dpp(x0, 0x39, 0xf, 0xf, true);
+                const float from_r = __builtin_bit_cast(float, pl == 3 ? of_edge : next);
+                d[p][0] = okl ? from_l : 0.0f;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) d[p][1 + q] = v ? xm[pp][q] : 0.0f;
-                d[p][5] = v && okr ? (pl == 3 ? xe[pp] : from_r) : 0.0f;
+                for (int q = 0; q < 4; ++q) d[p][1 + q] = xm[p][q];
+                d[p][5] = okr && (okx[p] || pl != 3) ? from_r : 0.0f;
+                before[p] = xm[p][3];
             }
             // (the first pass serves both tiles: they share two columns)
             float c6[6][4];
 #pragma unroll
             for (int q = 0; q < 6; ++q) {
-                const float col[4] = {d[0][q], d[1][q], d[2][q], d[3][q]};
-                bt32_mul(col, c6[q]);
+                const float d1 = scale * d[1][q], d2 = scale * d[2][q];
+                c6[q][0] = fmaf(scale, d[0][q], -d2), c6[q][1] = d1 + d2, c6[q][2] = d2 - d1, c6[q][3] = fmaf(scale, d[3][q], -d1);
             }
 #pragma unroll
             for (int p = 0; p < 4; ++p) {
@@ -405,6 +433,17 @@ __device__ __forceinline__ void wgrad_fused_body(const float *__restrict__ X, fl
 #pragma unroll
         for (int e = 0; e < 16; ++e)
             *reinterpret_cast<floatx2_w *>(t_dst + buf * (2 * WF_OP) + e * (64 * WF_BK)) = floatx2_w{wa[e], wb[e]};
+    };
+    // the first step's raw data, and the column before it
+    auto begin = [&]() {
+        if constexpr (!ERR) {
+            place(max(slab_lo - 1, 0));
+            load_raw();
+#pragma unroll
+            for (int p = 0; p < 4; ++p) before[p] = okx[p % NR] ? xm[p % NR][3] : 0.0f;
+        }
+        if (ERR || slab_lo == 0) place(slab_lo);
+        load_raw();
     };
 
     const int lane = tid & 63, li = lane & 31, lh = lane >> 5;
@@ -473,7 +512,6 @@ __device__ __forceinline__ void wgrad_fused_body(const float *__restrict__ X, fl
     };
 
     const float scale = ERR ? sign * BF16_SCALE : BF16_SCALE;
-    place();
     clear();
     float t = 0.0f;
     bool add = false;
@@ -501,24 +539,20 @@ __device__ __forceinline__ void wgrad_fused_body(const float *__restrict__ X, fl
                 }
     };
     if (slab_lo < slab_hi) {
-        load_raw();
-        transform(0, scale);
-        load_raw();
-        wf_lds_barrier();
-        int slab = slab_lo;
-        do {
-            const int buf = (slab - slab_lo) & 1;
+        // step `slab` is multiplied from buffer B, the next one transformed into the other, the one after that requested
+        auto step = [&](auto bc, int slab) {
+            constexpr int B = decltype(bc)::value;
             const bool more = slab + 1 < slab_hi;
             if constexpr (!ERR) {
                 __builtin_amdgcn_s_setprio(2);
-                multiply(buf);
+                multiply(B);
                 __builtin_amdgcn_s_setprio(0);
             }
-            if (more) transform(buf ^ 1, scale);
+            if (more) transform(B ^ 1, scale);
             load_raw();                    // (past the share's end: a valid position, read and discarded)
             if constexpr (ERR) {
                 __builtin_amdgcn_s_setprio(2);
-                multiply(buf);
+                multiply(B);
                 __builtin_amdgcn_s_setprio(0);
             }
             if (LONG && more && (slab + 1 - slab_lo) % (BF16_LONG / WF_BK) == 0) {
@@ -527,7 +561,17 @@ __device__ __forceinline__ void wgrad_fused_body(const float *__restrict__ X, fl
                 add = true;
             }
             wf_lds_barrier();
-        } while (++slab < slab_hi);
+        };
+        begin();
+        transform(0, scale);
+        load_raw();
+        wf_lds_barrier();
+        int slab = slab_lo;
+        for (; slab + 1 < slab_hi; slab += 2) {
+            step(std::integral_constant<int, 0>(), slab);
+            step(std::integral_constant<int, 1>(), slab + 1);
+        }
+        if (slab < slab_hi) step(std::integral_constant<int, 0>(), slab);
     }
 
     // a share past the end of the blocks still writes its (zero) partial M
@@ -543,12 +587,12 @@ __device__ __forceinline__ void wgrad_fused_body(const float *__restrict__ X, fl
     for (int w = 0; w < 8; ++w) again |= votes[w];
     __syncthreads();
     if (again) {
-        place();
         clear();
         add = false;
+        begin();
         for (int slab = slab_lo; slab < slab_hi; ++slab) {
-            load_raw();
             transform(0, 1.0f);
+            load_raw();
             __syncthreads();
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
