@@ -183,7 +183,8 @@ int wino_conv2d_bwd_filter(int N, int C, int H, int W, int K, int pad, int dt, c
 /* Host-side query: the variant wino_conv2d_fwd_ex runs for these arguments -- WINO_FLAG_UNFUSED,
  * WINO_FLAG_FUSED or WINO_FLAG_ONE_LAUNCH -- when called with `flags` (WINO_FLAG_AUTO resolves to one of
  * the first two; WINO_FLAG_ONE_LAUNCH is answered for untransformed filters, G given); a negative
- * wino_status_t (e.g. -WINO_EUNSUPPORTED) if the call would be rejected. */
+ * wino_status_t (e.g. -WINO_EUNSUPPORTED) if the call would be rejected.  (Small fp32 layers answered
+ * WINO_FLAG_UNFUSED for WINO_FLAG_AUTO: the call runs all four loops in one launch, without the workspace.) */
 int wino_conv2d_variant(int N, int C, int H, int W, int K, int pad, int m, int dt, int y_dt, unsigned flags);
 /* Host-side query: how the one-kernel fp32 layer of more than 32 filters (m = 4 or 2; Section 6's fusion of the
  * transforms into the multiply) deals its items to the GPU's 8 XCDs when the workspace has room for partial outputs.

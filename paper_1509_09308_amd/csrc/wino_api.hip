@@ -311,6 +311,10 @@ static int run_layer(const Geo &g, int y_dt, const void *D, const void *G, const
         return e == hipSuccess ? WINO_OK : hip_fail(e);
     }
     if (flags == WINO_FLAG_AUTO && fused_y_ok(g, y_dt) && fused_preferred(g)) flags = WINO_FLAG_FUSED;
+    if (flags == WINO_FLAG_AUTO && y_dt == WINO_F32 && fused_small_preferred(g)) {
+        e = launch_fused_small(g, (const float *)D, (const float *)G, (const float *)U, (float *)Y, bwd, s);
+        return e == hipSuccess ? WINO_OK : hip_fail(e);
+    }
     if (flags == WINO_FLAG_FUSED && fused_split_eligible(g)) {
         e = launch_fused_split(g, (const float *)D, (const float *)G, (const float *)U, (float *)Y, workspace, ub + vb + mb,
                                bwd, s);
