@@ -97,8 +97,9 @@ def _ptr(t):
 
 def _stream(stream):
     import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    # (the current stream's handle as it is: building the Stream object around it took 3.4 us of a call's 9)
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) if stream is None
+                           else stream.cuda_stream)
 
 
 def _dt(t):
