@@ -100,7 +100,7 @@ hipError_t launch_filter_transform_bwd(const Geo &g, const void *G, void *U, hip
 hipError_t launch_filter_transform(const Geo &g, const void *G, void *U, hipStream_t s, unsigned int *zero1024)
 {
     if (g.dt != WINO_F32 && zero1024 != nullptr) return hipErrorInvalidValue;
-    dim3 grid((g.Kp + 63) / 64, (g.Cp + 3) / 4), block(256);
+    dim3 grid((g.Kp + FT_KT - 1) / FT_KT, (g.Cp + FT_CT - 1) / FT_CT), block(256);
     if (g.dt == WINO_F32) {
         if (g.m == 2)
             filter_transform_kernel<2, float><<<grid, block, 0, s>>>((const float *)G, (float *)U, g.K, g.C, g.Kp, g.Cp, zero1024);

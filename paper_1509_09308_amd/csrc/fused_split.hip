@@ -118,10 +118,22 @@ __global__ __launch_bounds__(64 * (M + 2)) void filter_split_kernel(const float 
     __shared__ float gs[ROWS * STRIDE];
     fs_clear(tickets);
     const int lane = threadIdx.x & 63, kb = blockIdx.x % n_kb, s = blockIdx.x / n_kb;
-    for (int idx = threadIdx.x; idx < ROWS * LEN; idx += 64 * A) {
-        const int r = idx / LEN, j = idx % LEN;
+    // (all requests of a thread go out before the first value is used; what is past the last filter or channel comes from
+    // the last one and is zeroed)
+    constexpr int FETCH = ROWS * LEN / (64 * A);
+    static_assert(FETCH * 64 * A == ROWS * LEN, "every thread fetches as many values");
+    float v[FETCH];
+#pragma unroll
+    for (int i = 0; i < FETCH; ++i) {
+        const int idx = threadIdx.x + i * 64 * A, r = idx / LEN, j = idx % LEN;
+        const int first = (BWD ? s * 16 : kb * 32) + r, last = (BWD ? C : K) - 1, left = BWD ? K - kb * 32 : C - s * 16;
+        v[i] = G[((size_t)min(first, last) * (BWD ? K : C) + (BWD ? kb * 32 : s * 16)) * 9 + min(j, left * 9 - 1)];
+    }
+#pragma unroll
+    for (int i = 0; i < FETCH; ++i) {
+        const int idx = threadIdx.x + i * 64 * A, r = idx / LEN, j = idx % LEN;
         const int k = kb * 32 + (BWD ? j / 9 : r), c = s * 16 + (BWD ? r : j / 9);
-        gs[r * STRIDE + j] = k < K && c < C ? G[(BWD ? (size_t)c * K + kb * 32 : (size_t)k * C + s * 16) * 9 + j] : 0.0f;
+        gs[r * STRIDE + j] = k < K && c < C ? v[i] : 0.0f;
     }
     __syncthreads();
     float g[8][3][3];

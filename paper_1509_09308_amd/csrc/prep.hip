@@ -1,7 +1,8 @@
 // Loops 1 and 2 of Algorithm 1 (Lavin & Gray) in one launch.  The filter transform and the input
 // transform do not depend on each other, and for small batches each is far too small to fill the
 // GPU, so a layer that has to do both pays one kernel's start-up and drain instead of two: the
-// first blocks of the grid transform filters, the rest transform input tiles.
+// first blocks of the grid transform input tiles, the rest filters (fp16: the other way round).  Filters last are 1 % of a
+// layer with 512 x 512 of them.
 #include <stdlib.h>
 
 #include "stage_bodies.h"
@@ -15,12 +16,11 @@ __global__ __launch_bounds__(256) void prep_kernel(const float *__restrict__ G, 
                                                    int ft_gx, int ft_blocks, int it_gx)
 {
     __shared__ float gs[FT_LDS];
-    const int id = blockIdx.x;
-    if (id < ft_blocks) {
-        filter_transform_block<M, float>(G, U, g.K, g.C, g.Kp, g.Cp, id % ft_gx, id / ft_gx, gs);
+    const int j = blockIdx.x, it_blocks = gridDim.x - ft_blocks;
+    if (j >= it_blocks) {
+        filter_transform_block<M, float>(G, U, g.K, g.C, g.Kp, g.Cp, (j - it_blocks) % ft_gx, (j - it_blocks) / ft_gx, gs);
         return;
     }
-    const int j = id - ft_blocks;
     if constexpr (IT == 2)
         input_transform_pair_block<M>(D, V, g, j % it_gx, j / it_gx);
     else

@@ -15,11 +15,31 @@ template <typename T> __device__ __forceinline__ float ld_in(const T *p);
 template <> __device__ __forceinline__ float ld_in<float>(const float *p) { return *p; }
 template <> __device__ __forceinline__ float ld_in<__half>(const __half *p) { return __half2float(*p); }
 
-// One thread per (k, c) of the padded Kp x Cp grid, k fastest: a wavefront is 64 consecutive
-// filters of one channel, so each of its alpha^2 stores is 256 contiguous bytes.  A workgroup
-// covers KT filters x CT channels; the 9*CT source values of one filter are contiguous in G and
-// are staged through LDS with coalesced loads.
-constexpr int FT_KT = 64, FT_CT = 4, FT_ROW = FT_CT * 9 + 1, FT_LDS = FT_KT * FT_ROW;   // floats of LDS per block
+// The 9 CT source values of KT filters to LDS, `row` floats apart; zeros for filters past K and channels past C.  All of a
+// thread's requests go out before the first value is used (one after the other, each waited for, they were most of a
+// small layer's first launch: stack of one image 373 -> 349 us).
+template <int KT, int CT, int ROW, int NT, typename T>
+__device__ __forceinline__ void fetch_filters(const T *__restrict__ G, float *gs, int K, int C, int k0, int c0)
+{
+    constexpr int N = KT * CT * 9 / NT;
+    static_assert(N * NT == KT * CT * 9, "every thread fetches as many values");
+    T v[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int idx = threadIdx.x + i * NT, k = k0 + idx / (CT * 9), j = idx % (CT * 9);
+        v[i] = G[((size_t)min(k, K - 1) * C + c0) * 9 + min(j, (C - c0) * 9 - 1)];
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int idx = threadIdx.x + i * NT, kl = idx / (CT * 9), j = idx % (CT * 9);
+        gs[kl * ROW + j] = k0 + kl < K && c0 + j / 9 < C ? ld_f<T>(&v[i]) : 0.0f;
+    }
+}
+
+// One thread per (k, c) of the padded Kp x Cp grid, k fastest: half a wavefront is 32 consecutive filters of one channel, so
+// each of its alpha^2 stores is two whole lines.  A workgroup covers KT filters x CT channels; the 9*CT source values of one
+// filter are contiguous in G (288 bytes; 144 with 64 x 4, 1 % of a layer of 512 x 512 filters) and are staged through LDS.
+constexpr int FT_KT = 32, FT_CT = 8, FT_ROW = FT_CT * 9 + 1, FT_LDS = FT_KT * FT_ROW;   // floats of LDS per block
 
 template <int M, typename T>
 __device__ __forceinline__ void filter_transform_block(const T *__restrict__ G, T *__restrict__ U, int K, int C,
@@ -27,13 +47,7 @@ __device__ __forceinline__ void filter_transform_block(const T *__restrict__ G, 
 {
     constexpr int A = M + 2, KT = FT_KT, CT = FT_CT, ROW = FT_ROW;
     const int k0 = bx * KT, c0 = by * CT;
-    for (int idx = threadIdx.x; idx < KT * CT * 9; idx += 256) {
-        const int kl = idx / (CT * 9), j = idx % (CT * 9);
-        const int k = k0 + kl, c = c0 + j / 9;
-        float v = 0.0f;
-        if (k < K && c < C) v = ld_f<T>(G + ((size_t)k * C + c0) * 9 + j);
-        gs[kl * ROW + j] = v;
-    }
+    fetch_filters<KT, CT, ROW, 256>(G, gs, K, C, k0, c0);
     __syncthreads();
     const int kl = threadIdx.x % KT, cl = threadIdx.x / KT;
     const int k = k0 + kl, c = c0 + cl;
@@ -231,11 +245,7 @@ __device__ __forceinline__ void filter_transform_f16_block(const __half *__restr
     __half *us = reinterpret_cast<__half *>(smem);     // ... and, once every thread holds its taps, the results
     const int tid = threadIdx.x;
     const int k0 = bx * KT, c0 = by * CT;
-    for (int idx = tid; idx < KT * CT * 9; idx += NT) {
-        const int kl = idx / (CT * 9), j = idx % (CT * 9);
-        const int k = k0 + kl, c = c0 + j / 9;
-        gs[kl * ROW + j] = (k < K && c < C) ? __half2float(G[((size_t)k * C + c0) * 9 + j]) : 0.0f;
-    }
+    fetch_filters<KT, CT, ROW, NT>(G, gs, K, C, k0, c0);
     __syncthreads();
     const int kl = tid % KT;
     float g[PAIRS][3][3];
@@ -275,6 +285,25 @@ __device__ __forceinline__ void filter_transform_f16_block(const __half *__restr
     }
 }
 
+// The tile at (x0, y0) of an image plane, zeros outside the image: taps are requested from the nearest place inside, so that
+// all of them are in flight at once (loads of 2 bytes in branches are converted, and waited for, one after the other).
+template <int A>
+__device__ __forceinline__ void fetch_tile(const __half *__restrict__ plane, int H, int W, int x0, int y0, float (&d)[A][A])
+{
+    __half v[A][A];
+#pragma unroll
+    for (int p = 0; p < A; ++p) {
+        const __half *row = plane + (size_t)min(max(x0 + p, 0), H - 1) * W;
+#pragma unroll
+        for (int q = 0; q < A; ++q) v[p][q] = row[min(max(y0 + q, 0), W - 1)];
+    }
+#pragma unroll
+    for (int p = 0; p < A; ++p)
+#pragma unroll
+        for (int q = 0; q < A; ++q)
+            d[p][q] = (unsigned)(x0 + p) < (unsigned)H && (unsigned)(y0 + q) < (unsigned)W ? __half2float(v[p][q]) : 0.0f;
+}
+
 // Input transform.  V is laid out [e][c/8][b][c%8]; a block takes 8 channels x 64 tiles (512 threads) and writes V as
 // 1 KB contiguous per component and wavefront.  VEC: pad 1, W a multiple of 4, M = 4 (columns 1..4 of a tile row are
 // one aligned 8-byte load).
@@ -299,28 +328,30 @@ __device__ __forceinline__ void input_transform_f16_block(const __half *__restri
         const int i = t2 / g.Th;
         const int x0 = M * tx - g.pad, y0 = M * ty - g.pad;
         const __half *src = D + ((size_t)i * g.C + c) * g.H * g.W;
+        if constexpr (!VEC) {
+            fetch_tile<A>(src, g.H, g.W, x0, y0, d);
+        } else {
+            // (requested from the nearest place inside, as in fetch_tile)
+            uint2 mid[A];
+            __half first[A], last[A];
 #pragma unroll
-        for (int p = 0; p < A; ++p) {
-            const int x = x0 + p;
-            if (x >= 0 && x < g.H) {
-                const __half *row = src + (size_t)x * g.W + y0;
-                if constexpr (VEC) {
-                    const uint2 mid = *reinterpret_cast<const uint2 *>(row + 1);
-                    const __half2 h01 = *reinterpret_cast<const __half2 *>(&mid.x);
-                    const __half2 h23 = *reinterpret_cast<const __half2 *>(&mid.y);
-                    d[p][1] = __low2float(h01);
-                    d[p][2] = __high2float(h01);
-                    d[p][3] = __low2float(h23);
-                    d[p][4] = __high2float(h23);
-                    if (y0 >= 0) d[p][0] = __half2float(row[0]);
-                    if (y0 + 5 < g.W) d[p][5] = __half2float(row[5]);
-                } else {
+            for (int p = 0; p < A; ++p) {
+                const __half *row = src + (size_t)min(max(x0 + p, 0), g.H - 1) * g.W;
+                mid[p] = *reinterpret_cast<const uint2 *>(row + y0 + 1);
+                first[p] = row[max(y0, 0)];
+                last[p] = row[min(y0 + 5, g.W - 1)];
+            }
 #pragma unroll
-                    for (int q = 0; q < A; ++q) {
-                        const int y = y0 + q;
-                        if (y >= 0 && y < g.W) d[p][q] = __half2float(row[q]);
-                    }
-                }
+            for (int p = 0; p < A; ++p) {
+                const bool ok = (unsigned)(x0 + p) < (unsigned)g.H;
+                const __half2 h01 = *reinterpret_cast<const __half2 *>(&mid[p].x);
+                const __half2 h23 = *reinterpret_cast<const __half2 *>(&mid[p].y);
+                d[p][0] = ok && y0 >= 0 ? __half2float(first[p]) : 0.0f;
+                d[p][1] = ok ? __low2float(h01) : 0.0f;
+                d[p][2] = ok ? __high2float(h01) : 0.0f;
+                d[p][3] = ok ? __low2float(h23) : 0.0f;
+                d[p][4] = ok ? __high2float(h23) : 0.0f;
+                d[p][A - 1] = ok && y0 + 5 < g.W ? __half2float(last[p]) : 0.0f;
             }
         }
     }
