@@ -221,22 +221,30 @@ static bool direct_mfma_ok(int C, int H, int W, int K, int R, int S, int pad, in
 
 // Any filter, stride and padding as a matrix product on the matrix units: Y[k][pixel] = sum over taps j = (c, u, v) of
 // G[k][j] D[pixel's window][j], the K x CRS matrix of filters as it lies in memory times the CRS x N Ho Wo matrix of
-// windows, which is never built: a thread fetches its elements from D with one bounds check each (the tap is the same for
-// a whole wavefront, so its row, column and offset are scalars).  fp32 goes through the bf16 units in three exact parts
-// (bf16x3.h), fp16 directly; sums are fp32.
+// windows, which is never built: a thread fetches its elements from D with one bounds check each.  fp32 goes through the
+// bf16 units in three exact parts (bf16x3.h), fp16 directly; sums are fp32.
 // A workgroup of four wavefronts owns BM filters x BN pixels.  Per step of 16 taps every thread fetches quads of four
 // taps of one filter or pixel, splits them and stores the parts to LDS as 8-byte halves of the 16-byte words (eight taps
 // of one row) that the matrix instruction takes; two steps are in flight in registers, two in LDS, one barrier per step.
 // A step is a chain of fetch, split, barrier, LDS reads and six dependent matrix instructions, about 1 500 cycles for a
-// workgroup alone on its CU, so KS groups of four wavefronts take every KS-th step of the same block and add their sums in
-// LDS at the end: four groups where there are no more blocks than CUs, two up to twice as many.  64 x 128 blocks spare a
-// third of the fetches per product where there are 512 of them.  (Fetching a filter's taps with lanes along the filters:
-// 64 cache lines per request, 50 us for the first of these.)  Against one thread per pixel and 16 filters on the vector
-// ALUs: 64 -> 128 channels at 56 x 56, stride 2, N = 16: 151 -> 34 us in fp32, 127 -> 28 in fp16 (N = 1: 115 -> 17); 512 ->
-// 512 at 14 x 14, stride 2, N = 1: 807 -> 98; 1 x 1, 256 -> 512 at 28 x 28, stride 2, N = 8: 120 -> 15; 7 x 7, 3 -> 64 at
-// 224 x 224, stride 2, N = 8: 84 -> 36; 5 x 5, 48 -> 128 at 27 x 27, N = 4: 210 -> 31.  Error against float64: 25-60 % less.
+// workgroup alone on its CU, so KS groups of four wavefronts share the steps of the same block, each taking a run of them,
+// and add their sums in LDS at the end: four groups where there are no more blocks than CUs, two up to twice as many.
+// 64 x 128 blocks spare a third of the fetches per product where there are 512 of them.  (Fetching a filter's taps with
+// lanes along the filters: 64 cache lines per request, 50 us for the first layer below.)
+// Where a tap lies is looked up in LDS: (u, v) and offset repeat every 16 R S taps, 16 channels on.  Counting (c, u, v) up in
+// scalars took 85 scalar instructions per step and wavefront, which the SIMDs of a CU take turns at: that, and not the
+// chain, set the pace of CUs with two workgroups.  The check is three instructions: the part of a window inside the image
+// is a rectangle of (u, v), its corners packed in 16-bit halves.
+// One thread per pixel and 16 filters on the vector ALUs / scalars counted up / this: 64 -> 128 channels at 56 x 56, stride
+// 2, N = 16: 151 / 34 / 29 us in fp32, 127 / 28 / 21 in fp16 (N = 1, fp32: 115 / 18 / 15); 512 -> 512 at 14 x 14, stride 2,
+// N = 1: 807 / 99 / 72; 1 x 1, 256 -> 512 at 28 x 28, stride 2, N = 8: 120 / 15.4 / 14.8; 7 x 7, 3 -> 64 at 224 x 224, stride
+// 2, N = 8: 84 / 36 / 28; 5 x 5, 48 -> 128 at 27 x 27, N = 4: 210 / 31 / 23; 512 -> 512 at 28 x 28, stride 2, N = 64: - / 659
+// / 532.  Error against float64: 25-60 % less than the first form's.
 constexpr int DG_STEP = 16;
+
 typedef _Float16 halfx8_dc __attribute__((ext_vector_type(8)));
+typedef unsigned uintx2_d __attribute__((ext_vector_type(2)));
+typedef unsigned short ushortx2_dc __attribute__((ext_vector_type(2)));
 
 // Barrier that orders LDS traffic only: global loads requested earlier stay in flight across it.
 __device__ __forceinline__ void dg_lds_barrier()
@@ -249,8 +257,10 @@ __device__ __forceinline__ void dg_lds_barrier()
 struct DgGeo {
     int C, H, W, K, R, S, pad, stride, Ho, Wo;
     int J, P;                    // taps, pixels of all images
-    int dv, du, dc;              // KS steps ahead in (c, u, v)
     int tiles_m;
+    int share;                   // taps of a group
+    int period;                  // taps after which (u, v) repeat at the same place of a step, or all
+    unsigned ahead;              // bytes of D from one period to the next
 };
 
 // LONG: more than BF16_LONG taps per group, whose sums are set aside now and then (bf16x3.h).
@@ -265,6 +275,7 @@ __global__ __launch_bounds__(256 * KS, LONG && KS == 1 ? 4 : 1) void direct_gemm
     static_assert(WM == 1 || WM == 2, "32 or 64 filters");
     constexpr int GROUP_WORDS = 2 * 2 * NP * (BM + BN);        // LDS of a group: two slabs of both operands
     constexpr int SUM_WORDS = (KS - 1) * BM * BN / 4;          // or the sums of all groups but one
+    extern __shared__ uintx4_b dg_taps[];                      // of a period: offset in D, u | v << 16
     __shared__ uintx4_b lds[KS * GROUP_WORDS > SUM_WORDS ? KS * GROUP_WORDS : SUM_WORDS];
     const int tid = threadIdx.x & 255, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -285,18 +296,25 @@ __global__ __launch_bounds__(256 * KS, LONG && KS == 1 ? 4 : 1) void direct_gemm
     constexpr unsigned OOB = 0x80000000u;
 
     // quad j of this thread: taps 4 qb[j] .. + 3 of a step, pixel (filter) column; the quad is the wavefront's
-    int x0[BQ], y0[BQ], cb[BQ], ub[BQ], vb[BQ];
     unsigned vo[BQ];
+    ushortx2_dc first_tap[BQ], last_tap[BQ];                   // (u, v) of the window's part inside the image; last from first on
 #pragma unroll
     for (int j = 0; j < BQ; ++j) {
-        const int col = (tid + j * 256) % BN, q = (wave * 64 + j * 256) / BN;
+        const int col = (tid + j * 256) % BN;
         const int p = min(p0 + col, g.P - 1);                  // (pixels past the last are never stored)
         const int n = p / plane, r = p - n * plane;
         const int ox = r / g.Wo, oy = r - ox * g.Wo;
-        x0[j] = ox * g.stride - g.pad, y0[j] = oy * g.stride - g.pad;
+        const int x = ox * g.stride - g.pad, y = oy * g.stride - g.pad;
+        const int u0 = max(-x, 0), u1 = min(g.H - x, g.R), v0 = max(-y, 0), v1 = min(g.W - y, g.S);
+        const bool some = u0 < u1 && v0 < v1;                  // (none: tap 0x8000, which no window has)
+        first_tap[j] = some ? ushortx2_dc{(unsigned short)u0, (unsigned short)v0} : ushortx2_dc{0x8000, 0x8000};
+        last_tap[j] = some ? ushortx2_dc{(unsigned short)(u1 - u0 - 1), (unsigned short)(v1 - v0 - 1)} : ushortx2_dc{0, 0};
         vo[j] = (unsigned)((n - n0) * image + ox * g.stride * g.W + oy * g.stride) * (unsigned)sizeof(T);
-        const int first = DG_STEP * ks + 4 * q;
-        vb[j] = first % g.S, ub[j] = first / g.S % g.R, cb[j] = first / g.S / g.R;
+    }
+    for (int t = threadIdx.x; t < g.period; t += 256 * KS) {
+        const int c = t / (g.R * g.S), r = t - c * (g.R * g.S), u = r / g.S, v = r - u * g.S;
+        const unsigned at = (((unsigned)c * g.H + u) * g.W + v) * (unsigned)sizeof(T);
+        reinterpret_cast<uintx2_d *>(dg_taps)[t] = uintx2_d{at, (unsigned)u | (unsigned)v << 16};
     }
     // filters: four threads fetch the 16 taps of a step of one filter, which lie side by side
     const int arow = tid >> 2, a_quad = tid & 3;
@@ -306,32 +324,30 @@ __global__ __launch_bounds__(256 * KS, LONG && KS == 1 ? 4 : 1) void direct_gemm
     const bool a_wide = F32 || g.J % 2 == 0;
 
     T rb[2][BQ][4], ra[2][4];
-    int j_next = DG_STEP * ks;                                 // first tap of the step requested next
+    int j_next = g.share * ks;                                 // first tap of the step requested next
+    int entry = j_next % g.period;                             // its place in the period
+    unsigned base = (unsigned)(j_next / g.period) * g.ahead;   // the period's offset in D
     auto request = [&](int slot) {
+        const unsigned so = base & (unsigned)((j_next - g.J) >> 31);       // (masks from signs: choices between scalars become branches)
 #pragma unroll
         for (int j = 0; j < BQ; ++j) {
             const int q = (wave * 64 + j * 256) / BN;
-            int c = cb[j], u = ub[j], v = vb[j];
-            // (scalars throughout; masks from signs, because choices between scalars become branches or vector code)
+            const uintx4_b e[2] = {dg_taps[(entry + 4 * q) / 2], dg_taps[(entry + 4 * q) / 2 + 1]};
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int tap = (j_next + 4 * q + i - g.J) >> 31;          // all ones up to the last tap
-                const bool ok = (unsigned)(x0[j] + u) < (unsigned)(g.H & tap) && (unsigned)(y0[j] + v) < (unsigned)g.W;
-                const unsigned so = (unsigned)((((c * g.H + u) * g.W + v) & tap) * (int)sizeof(T));
+                const unsigned past = (unsigned)((g.J - 1 - j_next - 4 * q - i) >> 31);    // all ones behind the last tap
+                const ushortx2_dc uv = __builtin_bit_cast(ushortx2_dc, e[i / 2][2 * (i % 2) + 1] | past) - first_tap[j];
+                const bool ok = __builtin_bit_cast(unsigned, __builtin_elementwise_min(uv, last_tap[j])) == __builtin_bit_cast(unsigned, uv);
+                const unsigned o = ok ? vo[j] + e[i / 2][2 * (i % 2)] : OOB;
                 if constexpr (F32)
-                    rb[slot][j][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc_d, ok ? vo[j] : OOB, so, 0));
+                    rb[slot][j][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc_d, o, so, 0));
                 else
-                    rb[slot][j][i] = __builtin_bit_cast(__half, __builtin_amdgcn_raw_buffer_load_b16(rsrc_d, ok ? vo[j] : OOB, so, 0));
-                const int in_v = (v + 1 - g.S) >> 31;                      // all ones while the next tap is in the same row
-                v = (v + 1) & in_v;
-                const int u1 = u + 1 + in_v, in_u = (u1 - g.R) >> 31;
-                u = u1 & in_u, c += 1 + in_u;
+                    rb[slot][j][i] = __builtin_bit_cast(__half, __builtin_amdgcn_raw_buffer_load_b16(rsrc_d, o, so, 0));
             }
-            const int v2 = vb[j] + g.dv - g.S, v_low = v2 >> 31;           // ... a step ahead
-            vb[j] = v2 + (g.S & v_low);
-            const int u2 = ub[j] + g.du + 1 + v_low - g.R, u_low = u2 >> 31;
-            ub[j] = u2 + (g.R & u_low), cb[j] += g.dc + 1 + u_low;
         }
+        entry += DG_STEP;
+        const unsigned wrap = ~(unsigned)((entry - g.period) >> 31);       // all ones where the next period begins
+        entry -= g.period & (int)wrap, base += g.ahead & wrap;
         const unsigned o = ao + (unsigned)j_next * (unsigned)sizeof(T);
         if (a_wide && j_next + DG_STEP <= g.J) {
             if constexpr (F32) {
@@ -354,9 +370,8 @@ __global__ __launch_bounds__(256 * KS, LONG && KS == 1 ? 4 : 1) void direct_gemm
                     ra[slot][i] = __builtin_bit_cast(__half, __builtin_amdgcn_raw_buffer_load_b16(rsrc_g, oi, 0, 0));
             }
         }
-        j_next += DG_STEP * KS;
+        j_next += DG_STEP;
     };
-    typedef unsigned uintx2_d __attribute__((ext_vector_type(2)));
     // quad q of column col: half q % 2 of words [q / 2][part][col]
     auto put = [&](uintx4_b *dst, int cols, int col, int q, const T (&x)[4]) {
         uintx2_d *w = reinterpret_cast<uintx2_d *>(dst + (q / 2) * NP * cols + col) + q % 2;
@@ -406,6 +421,7 @@ __global__ __launch_bounds__(256 * KS, LONG && KS == 1 ? 4 : 1) void direct_gemm
     };
     const int steps = (g.J + DG_STEP * KS - 1) / (DG_STEP * KS);     // (the same for every group: a step past the last tap is zeros)
     // (requests past the last step fetch nothing; the number of loads in flight does not depend on the path taken)
+    __syncthreads();
     request(0);
     request(1);
     store(0, 0);
@@ -436,8 +452,8 @@ __global__ __launch_bounds__(256 * KS, LONG && KS == 1 ? 4 : 1) void direct_gemm
         }
     };
     // set aside in registers, or, where there is one group only, where the result will be (64 x 128 blocks lose half of
-    // their workgroups per CU to the registers: 512 -> 512 channels at 28 x 28, stride 2, N = 64: 665 us with sums of one
-    // run, 874 set aside in registers, 700 so)
+    // their workgroups per CU to the registers: 512 -> 512 channels at 28 x 28, stride 2, N = 64, with taps counted up in
+    // scalars: 665 us with sums of one run, 874 set aside in registers, 700 so)
     constexpr bool IN_Y = LONG && KS == 1;
     floatx16_dc aside[LONG && !IN_Y ? TN : 1] = {};
     for (; t + 1 < steps; t += 2) {
@@ -525,11 +541,21 @@ static bool direct_gemm_ok(int N, int C, int H, int W, int K, int R, int S, int 
            (unsigned long long)K * C * R * S * size < limit && (P / 64 + 1) * ((K + 31) / 32) < limit;
 }
 
+// entries of the table: 16 channels, or every tap the groups request
+static int dg_table(const DgGeo &g, int KS)
+{
+    const int period = DG_STEP * g.R * g.S, all = (g.J + DG_STEP * KS - 1) / (DG_STEP * KS) * (DG_STEP * KS);
+    return period < all ? period : all;
+}
+
 template <typename T, int BM, int BN, int KS>
 static hipError_t launch_direct_gemm(DgGeo g, int N, const void *D, const void *G, void *Y, hipStream_t s)
 {
     g.tiles_m = (g.K + BM - 1) / BM;
-    g.dv = DG_STEP * KS % g.S, g.du = DG_STEP * KS / g.S % g.R, g.dc = DG_STEP * KS / g.S / g.R;
+    g.share = (g.J + DG_STEP * KS - 1) / (DG_STEP * KS) * DG_STEP;
+    g.period = dg_table(g, KS);
+    g.ahead = (unsigned)DG_STEP * g.H * g.W * (unsigned)sizeof(T);
+    const size_t table = (size_t)g.period * 8;
     const long long blocks = (long long)g.tiles_m * ((g.P + BN - 1) / BN);
     const unsigned g_bytes = (unsigned)((size_t)g.K * g.J * sizeof(T));
     const size_t d_elems = (size_t)N * g.C * g.H * g.W;
@@ -538,11 +564,11 @@ static hipError_t launch_direct_gemm(DgGeo g, int N, const void *D, const void *
         // (several groups: half as long again is still less than what a chain over all taps rounds off, 6100 taps of
         // operands between 1 and 1 + 2^-7, two groups: see below; and two groups with sums set aside are 7 % slower)
         if (g.J > (KS == 1 ? BF16_LONG : BF16_LONG * 3 / 2 * KS)) {
-            direct_gemm_kernel<T, BM, BN, KS, true><<<grid, block, 0, s>>>((const T *)D, (const T *)G, (T *)Y, g, g_bytes, d_elems);
+            direct_gemm_kernel<T, BM, BN, KS, true><<<grid, block, table, s>>>((const T *)D, (const T *)G, (T *)Y, g, g_bytes, d_elems);
             return hipGetLastError();
         }
     }
-    direct_gemm_kernel<T, BM, BN, KS, false><<<grid, block, 0, s>>>((const T *)D, (const T *)G, (T *)Y, g, g_bytes, d_elems);
+    direct_gemm_kernel<T, BM, BN, KS, false><<<grid, block, table, s>>>((const T *)D, (const T *)G, (T *)Y, g, g_bytes, d_elems);
     return hipGetLastError();
 }
 
@@ -550,16 +576,23 @@ template <typename T>
 static hipError_t launch_direct_gemm(const DgGeo &g, int N, const void *D, const void *G, void *Y, hipStream_t s)
 {
     const int steps = (g.J + DG_STEP - 1) / DG_STEP;
+    // (a table of 40 KB fits beside 32 x 128 blocks of four groups: filters of up to 320 taps per channel.  Beside all others
+    // 64 KB do, what the 512 taps take that a filter may have.)
+    auto groups = [&](long long blocks, int entries) {
+        return blocks <= 256 && steps >= 8 && dg_table(g, 4) <= entries ? 4 : blocks <= 512 && steps >= 4 ? 2 : 1;
+    };
     if (g.K <= 32) {
         const long long blocks = (g.P + 127) / 128;
-        if (blocks <= 256 && steps >= 8) return launch_direct_gemm<T, 32, 128, 4>(g, N, D, G, Y, s);
-        if (blocks <= 512 && steps >= 4) return launch_direct_gemm<T, 32, 128, 2>(g, N, D, G, Y, s);
+        const int KS = groups(blocks, 5120);
+        if (KS == 4) return launch_direct_gemm<T, 32, 128, 4>(g, N, D, G, Y, s);
+        if (KS == 2) return launch_direct_gemm<T, 32, 128, 2>(g, N, D, G, Y, s);
         return launch_direct_gemm<T, 32, 128, 1>(g, N, D, G, Y, s);
     }
     if ((long long)((g.K + 63) / 64) * ((g.P + 127) / 128) >= 512) return launch_direct_gemm<T, 64, 128, 1>(g, N, D, G, Y, s);
     const long long blocks = (long long)((g.K + 63) / 64) * ((g.P + 63) / 64);
-    if (blocks <= 256 && steps >= 8) return launch_direct_gemm<T, 64, 64, 4>(g, N, D, G, Y, s);
-    if (blocks <= 512 && steps >= 4) return launch_direct_gemm<T, 64, 64, 2>(g, N, D, G, Y, s);
+    const int KS = groups(blocks, 8192);
+    if (KS == 4) return launch_direct_gemm<T, 64, 64, 4>(g, N, D, G, Y, s);
+    if (KS == 2) return launch_direct_gemm<T, 64, 64, 2>(g, N, D, G, Y, s);
     return launch_direct_gemm<T, 64, 64, 1>(g, N, D, G, Y, s);
 }
 
@@ -592,7 +625,7 @@ hipError_t launch_direct_conv(int N, int C, int H, int W, int K, int R, int S, i
         DgGeo g;
         g.C = C, g.H = H, g.W = W, g.K = K, g.R = R, g.S = S, g.pad = pad, g.stride = stride, g.Ho = Ho, g.Wo = Wo;
         g.J = C * R * S, g.P = N * Ho * Wo, g.tiles_m = 0;
-        g.dv = g.du = g.dc = 0;
+        g.share = g.period = 0, g.ahead = 0;
         return dt == WINO_F32 ? launch_direct_gemm<float>(g, N, D, G, Y, s) : launch_direct_gemm<__half>(g, N, D, G, Y, s);
     }
     if (dt == WINO_F32)

@@ -20,6 +20,13 @@ pytestmark = pytest.mark.gpu
     (4, 24, 56, 52, 96, 3, 3, 0, 2),        # two groups
     (6, 12, 112, 100, 72, 3, 3, 1, 1),      # wide blocks
     (1, 1, 40, 520, 16, 1, 512, 4, 1),      # the longest row of taps
+    (1, 150, 14, 14, 64, 3, 3, 1, 1),       # the table of taps starts again every 16 channels, groups in the middle of it
+    (4, 70, 56, 52, 96, 3, 3, 0, 2),        # ... two groups
+    (6, 35, 112, 100, 72, 3, 3, 1, 1),      # ... one group
+    (1, 17, 30, 26, 16, 19, 17, 5, 2),      # two groups, because the table would be too large beside four
+    (1, 17, 22, 40, 16, 16, 20, 5, 1),      # the largest table beside four groups
+    (1, 18, 8, 518, 40, 1, 512, 2, 1),      # the largest table of all
+    (2, 20, 8, 9, 40, 1, 1, 2, 1),          # windows without any part inside the image
 ])
 def test_direct_product(N, C, H, W, K, R, S, pad, stride, dtype):
     torch, w = require_gpu()
