@@ -706,77 +706,119 @@ __global__ __launch_bounds__(256) void wgrad_output_kernel(const float *__restri
 
 // Layers with very few channels (the 3-channel first layer): the transforms above would spend
 // almost all their time on the error tensor (16 values written and read back per 4 read) for a
-// handful of products, so the gradient is evaluated directly from its definition instead.  One
-// wavefront takes KB = 4 filters of one image and one of RS row bands; lanes run along 4-pixel
-// segments of the error rows (16-byte loads); the 3 x 6 input window of a segment is loaded once
-// per channel and used for all 4 filters; 4 * 9 * CH running sums per lane are reduced across the
-// wavefront at the end.  The per-(image, band) partial sums are added by
-// wgrad_direct_reduce_kernel in a fixed order.  Needs W % 4 == 0.
-constexpr int WD_KB = 4, WD_RS = 4;
+// handful of products, so the gradient is evaluated directly from its definition instead, as a product on the fp32 matrix
+// units: dG[k][tap] = sum over pixels of E[k][pixel] D[pixel's window][tap].  A workgroup of 16 wavefronts takes 16 filters and
+// one of WD_RS row bands of one image; its wavefronts take turns at runs of 16 pixels of a row.  Per run
+// lane (i, q) fetches pixels 4 q .. 4 q + 3 of filter i and, per 16 taps, the same pixels' inputs of tap i, 16 bytes each from
+// wherever they start; they are the operands of four v_mfma_f32_16x16x4_f32 as they are.  WD_AHEAD runs are in flight.
+// Every run's products are added up eight at a time from zero, then four runs, then all of a wavefront, and the wavefronts' sums by
+// halves in LDS (in one chain: relative error 1.72e-7 instead of 1.20e-7 for 3 -> 64 channels at 224 x 224, N = 1); the
+// per-(image, band) partial sums are added by wgrad_direct_reduce_kernel, in a fixed order.  Needs W % 4 == 0.
+// Bound by reading E and by matrix instructions: 3 -> 64 channels at 224 x 224, N = 16: 40 and 25 us of 66 (fp32 vector
+// instructions, a wavefront per four filters, one per SIMD, waiting for each row of the window: 196; the same with 16
+// wavefronts per CU and three filters each: 145); N = 64: 570 -> 273; N = 1 (16 workgroups, as the workspace has room for four
+// bands): 140 -> 51; 4 -> 128 at 112 x 112, N = 8: 105 -> 36; 1 -> 64 at 224 x 224, N = 16: 88 -> 47.
+constexpr int WD_RS = 4, WD_K = 16, WD_WAVES = 16, WD_AHEAD = 4;
 
 template <int CH>
-__global__ __launch_bounds__(256) void wgrad_direct_kernel(const float *__restrict__ D, const float *__restrict__ E,
-                                                           float *__restrict__ part, int N, int H, int W, int K)
+__global__ __launch_bounds__(64 * WD_WAVES) void wgrad_direct_kernel(const float *__restrict__ D, const float *__restrict__ E,
+                                                                     float *__restrict__ part, int H, int W, int K)
 {
-    const int KG = (K + WD_KB - 1) / WD_KB;
-    int task = blockIdx.x * 4 + (threadIdx.x >> 6);   // ((i * RS + band) * KG + kg)
-    const int lane = threadIdx.x & 63;
-    if (task >= N * WD_RS * KG) return;
-    const int kg = task % KG;
-    task /= KG;
-    const int band = task % WD_RS, i = task / WD_RS;
+    constexpr int J = 9 * CH, NT = (J + 15) / 16;                // taps, tiles of them
+    __shared__ floatx4_w red[WD_WAVES][NT][64];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int li = lane & 15, lq = lane >> 4;
+    const int wgs_k = (K + WD_K - 1) / WD_K;
+    const int k0 = blockIdx.x % wgs_k * WD_K;
+    const int band = blockIdx.x / wgs_k % WD_RS, i = blockIdx.x / wgs_k / WD_RS;
     const int rows = (H + WD_RS - 1) / WD_RS;
     const int x_lo = band * rows, x_hi = min(H, x_lo + rows);
-    const float *Di = D + (size_t)i * CH * H * W;
-    const int W4 = W >> 2, nq = max(0, x_hi - x_lo) * W4;
-    float acc[WD_KB][CH][3][3];
+    // (filters past K and taps past 9 CH are computed and dropped)
+    const float *Ek = E + ((size_t)i * K + min(k0 + li, K - 1)) * H * W;
+    const float *Dc[NT];
+    int up[NT], right[NT];                                       // where the tap lies from the pixel
 #pragma unroll
-    for (int f = 0; f < WD_KB; ++f)
-#pragma unroll
-        for (int c = 0; c < CH; ++c)
-#pragma unroll
-            for (int u = 0; u < 3; ++u)
-#pragma unroll
-                for (int v = 0; v < 3; ++v) acc[f][c][u][v] = 0.0f;
-    for (int q = lane; q < nq; q += 64) {
-        const int xr = q / W4, x = x_lo + xr, y = (q - xr * W4) * 4;
-        floatx4_w e[WD_KB];
-#pragma unroll
-        for (int f = 0; f < WD_KB; ++f) {
-            const int k = min(kg * WD_KB + f, K - 1);   // filters past K are computed and dropped
-            e[f] = *reinterpret_cast<const floatx4_w *>(E + (((size_t)i * K + k) * H + x) * W + y);
-        }
-#pragma unroll
-        for (int c = 0; c < CH; ++c)
-#pragma unroll
-            for (int u = 0; u < 3; ++u) {
-                const int xx = x + u - 1;
-                if (xx < 0 || xx >= H) continue;
-                const float *row = Di + ((size_t)c * H + xx) * W + y;
-                const floatx4_w mid = *reinterpret_cast<const floatx4_w *>(row);
-                const float d[6] = {y > 0 ? row[-1] : 0.0f, mid[0], mid[1], mid[2], mid[3], y + 4 < W ? row[4] : 0.0f};
-#pragma unroll
-                for (int f = 0; f < WD_KB; ++f)
-#pragma unroll
-                    for (int v = 0; v < 3; ++v)
-                        acc[f][c][u][v] += e[f][0] * d[v] + e[f][1] * d[v + 1] + e[f][2] * d[v + 2] + e[f][3] * d[v + 3];
-            }
+    for (int n = 0; n < NT; ++n) {
+        const int j = min(16 * n + li, J - 1);
+        Dc[n] = D + ((size_t)i * CH + j / 9) * H * W;
+        up[n] = j % 9 / 3 - 1, right[n] = j % 3 - 1;
     }
-    float *dst = part + (size_t)(i * WD_RS + band) * K * CH * 9;
+    const int runs = (W + 15) / 16, dx = WD_WAVES / runs, dr = WD_WAVES % runs;
+    floatx4_w e[WD_AHEAD], d[WD_AHEAD][NT], some[NT], sum[NT];   // sums of the last runs, of all
 #pragma unroll
-    for (int f = 0; f < WD_KB; ++f)
+    for (int n = 0; n < NT; ++n) some[n] = sum[n] = floatx4_w{0.f, 0.f, 0.f, 0.f};
+    int x_req = x_lo + wave / runs, r_req = wave % runs;         // row and run requested next
+    int x = x_req, r = r_req;                                    // ... and multiplied next
+    auto next = [&](int &xx, int &rr) {
+        xx += dx, rr += dr;
+        if (rr >= runs) rr -= runs, ++xx;
+    };
+    // all addresses are inside the image: what lies outside is taken from the nearest place inside and left out below
+    auto request = [&](int slot) {
+        const int xc = min(x_req, x_hi - 1), y = min(16 * r_req + 4 * lq, W - 4);
+        e[slot] = *reinterpret_cast<const floatx4_w *>(Ek + ((size_t)xc * W + y));
 #pragma unroll
-        for (int c = 0; c < CH; ++c)
+        for (int n = 0; n < NT; ++n) {
+            const int row = min(max(xc + up[n], 0), H - 1), col = min(max(y + right[n], 0), W - 4);
+            const float *p = Dc[n] + ((size_t)row * W + col);
+            __builtin_memcpy(&d[slot][n], p, 16);                // (aligned to four bytes)
+        }
+        next(x_req, r_req);
+    };
+    auto multiply = [&](int slot) {
+        const int y = 16 * r + 4 * lq;
+        if (r == 0 || r == runs - 1) {                           // columns outside are zeros, pixels past the row not there
 #pragma unroll
-            for (int u = 0; u < 3; ++u)
+            for (int n = 0; n < NT; ++n) {
+                const floatx4_w v = d[slot][n];
+                if (y + right[n] < 0) d[slot][n] = floatx4_w{0.f, v[0], v[1], v[2]};
+                if (y + right[n] > W - 4) d[slot][n] = floatx4_w{v[1], v[2], v[3], 0.f};
+                if (y >= W) d[slot][n] = floatx4_w{0.f, 0.f, 0.f, 0.f};
+            }
+            if (y >= W) e[slot] = floatx4_w{0.f, 0.f, 0.f, 0.f};
+        }
+        floatx4_w t[2][NT];
 #pragma unroll
-                for (int v = 0; v < 3; ++v) {
-                    float a = acc[f][c][u][v];
+        for (int n = 0; n < NT; ++n) t[0][n] = t[1][n] = floatx4_w{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int off = 32; off >= 1; off >>= 1) a += __shfl_xor(a, off, 64);
-                    const int k = kg * WD_KB + f;
-                    if (lane == 0 && k < K) dst[((size_t)k * CH + c) * 9 + u * 3 + v] = a;
-                }
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int n = 0; n < NT; ++n)
+                t[j % 2][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(e[slot][j], d[slot][n][j], t[j % 2][n], 0, 0, 0);
+        // rows outside have no products (an error there need not be finite); column li of a result is tap li
+#pragma unroll
+        for (int n = 0; n < NT; ++n)
+            if ((unsigned)(x + up[n]) < (unsigned)H) some[n] += t[0][n] + t[1][n];
+        next(x, r);
+    };
+    if (x_lo < x_hi) {
+#pragma unroll
+        for (int slot = 0; slot < WD_AHEAD; ++slot) request(slot);
+        while (x < x_hi) {
+#pragma unroll
+            for (int slot = 0; slot < WD_AHEAD; ++slot) {
+                if (x < x_hi) multiply(slot);
+                request(slot);
+            }
+#pragma unroll
+            for (int n = 0; n < NT; ++n) sum[n] += some[n], some[n] = floatx4_w{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+#pragma unroll
+    for (int n = 0; n < NT; ++n) red[wave][n][lane] = sum[n];
+    __syncthreads();
+    // register r of lane (i, q) is filter 4 q + r, tap i
+    for (int t = threadIdx.x; t < NT * 256; t += 64 * WD_WAVES) {
+        const int n = t / 256, tap = 16 * n + t % 16, k = k0 + t / 16 % 16;
+        float a[WD_WAVES];
+#pragma unroll
+        for (int w = 0; w < WD_WAVES; ++w) a[w] = red[w][n][t % 16 + 16 * (t / 64 % 4)][t / 16 % 4];
+#pragma unroll
+        for (int half = WD_WAVES / 2; half >= 1; half /= 2)
+#pragma unroll
+            for (int w = 0; w < half; ++w) a[w] += a[w + half];
+        if (tap < J && k < K) part[((size_t)(i * WD_RS + band) * K + k) * J + tap] = a[0];
+    }
 }
 
 // dG[k][c][uv] = sum over images and row bands of part[.][k][c][uv]; one thread per output.
@@ -898,11 +940,11 @@ hipError_t launch_wgrad(int N, int C, int H, int W, int K, const float *D, const
 {
     if (wgrad_direct_ok(C, W)) {
         float *part = (float *)workspace;
-        const dim3 grid((N * WD_RS * ((K + WD_KB - 1) / WD_KB) + 3) / 4), blk(256);
-        if (C == 1) wgrad_direct_kernel<1><<<grid, blk, 0, s>>>(D, E, part, N, H, W, K);
-        else if (C == 2) wgrad_direct_kernel<2><<<grid, blk, 0, s>>>(D, E, part, N, H, W, K);
-        else if (C == 3) wgrad_direct_kernel<3><<<grid, blk, 0, s>>>(D, E, part, N, H, W, K);
-        else wgrad_direct_kernel<4><<<grid, blk, 0, s>>>(D, E, part, N, H, W, K);
+        const dim3 grid(N * WD_RS * ((K + WD_K - 1) / WD_K)), blk(256), threads(64 * WD_WAVES);
+        if (C == 1) wgrad_direct_kernel<1><<<grid, threads, 0, s>>>(D, E, part, H, W, K);
+        else if (C == 2) wgrad_direct_kernel<2><<<grid, threads, 0, s>>>(D, E, part, H, W, K);
+        else if (C == 3) wgrad_direct_kernel<3><<<grid, threads, 0, s>>>(D, E, part, H, W, K);
+        else wgrad_direct_kernel<4><<<grid, threads, 0, s>>>(D, E, part, H, W, K);
         int nparts = N * WD_RS;
         float *tmp = (float *)((char *)workspace + (((size_t)nparts * K * C * 9 * 4 + 255) & ~(size_t)255));
         const float *ps = wgrad_pre_reduce(part, tmp, (size_t)K * C * 9, &nparts, s);

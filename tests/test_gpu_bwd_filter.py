@@ -26,7 +26,9 @@ TOL_SMALL, TOL_FULL = 2e-6, 2e-5
                                    (2, 19, 12, 16, 70), (1, 130, 8, 8, 140), (2, 5, 7, 8, 6), (1, 8, 2, 4, 8),
                                    (3, 64, 9, 20, 33), (1, 256, 6, 12, 200),
                                    # at most 4 channels and W % 4 == 0: the direct kernel
-                                   (2, 3, 12, 16, 10), (3, 1, 8, 4, 5), (2, 4, 6, 8, 7), (1, 2, 5, 12, 3), (3, 3, 31, 36, 70)])
+                                   (2, 3, 12, 16, 10), (3, 1, 8, 4, 5), (2, 4, 6, 8, 7), (1, 2, 5, 12, 3), (3, 3, 31, 36, 70),
+                                   # ... runs of 16 pixels: one and a part, more than wavefronts, bands without rows
+                                   (2, 4, 9, 20, 16), (1, 3, 5, 300, 17), (2, 2, 1, 4, 33), (1, 1, 3, 272, 16), (1, 4, 40, 48, 15)])
 def test_bwd_filter_matches_oracle(shape):
     torch, w = require_gpu()
     N, C, H, W, K = shape
@@ -113,3 +115,29 @@ def test_bwd_filter_full_size_sampled(layer):
     print("%s N=64 bwd-filter sampled rel err %.3e" % (name, err))
     assert err <= TOL_FULL
     assert bool(torch.isfinite(dG).all())
+
+
+@pytest.mark.parametrize("C", [1, 2, 3, 4])
+def test_bwd_filter_few_channels_errors_that_are_not_finite(C):
+    """Rows outside the image have no products: an infinite error in the first or last row leaves the taps that would reach
+    there as they are, and a filter's errors leave other filters alone."""
+    torch, w = require_gpu()
+    N, H, W, K = 2, 9, 20, 18
+    rng = np.random.default_rng(C)
+    D, E = rng.random((N, C, H, W), dtype=np.float32), rng.standard_normal((N, K, H, W), dtype=np.float32)
+    ref = direct.conv2d_bwd_filter(D, E, pad=1)
+    want = np.isfinite(ref)
+    for k, x, u in ((3, 0, 0), (17, H - 1, 2)):
+        E[0, k, x, 7] = np.inf
+        want[k] = False
+        want[k, :, u] = True
+    # inputs outside the tensors are NaN
+    def inside(a):
+        room = torch.full((a.size + 8,), float("nan"), device="cuda")
+        room[4:4 + a.size] = to_gpu(a).reshape(-1)
+        return room[4:4 + a.size].view(a.shape)
+    dG = w.wino_conv2d_bwd_filter(inside(D), inside(E), pad=1).cpu().numpy()
+    assert np.array_equal(np.isfinite(dG), want)
+    E[~np.isfinite(E)] = 0.0
+    ref = direct.conv2d_bwd_filter(D, E, pad=1)
+    assert rel_err(dG[want], ref[want]) <= TOL_SMALL
