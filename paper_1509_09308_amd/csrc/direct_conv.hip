@@ -258,7 +258,6 @@ struct DgGeo {
     int C, H, W, K, R, S, pad, stride, Ho, Wo;
     int J, P;                    // taps, pixels of all images
     int tiles_m;
-    int share;                   // taps of a group
     int period;                  // taps after which (u, v) repeat at the same place of a step, or all
     unsigned ahead;              // bytes of D from one period to the next
 };
@@ -324,18 +323,22 @@ __global__ __launch_bounds__(256 * KS, LONG && KS == 1 ? 4 : 1) void direct_gemm
     const bool a_wide = F32 || g.J % 2 == 0;
 
     T rb[2][BQ][4], ra[2][4];
-    int j_next = g.share * ks;                                 // first tap of the step requested next
+    // a group's run of steps; runs differ by one step at most, as the error grows with the longest (of ten steps 2, 3, 2 and 3:
+    // 3, 3, 3 and 1 were 1.10 times as far from float64 with 3 -> 34 channels, 7 x 7)
+    const int all_steps = (g.J + DG_STEP - 1) / DG_STEP;
+    const int j_end = min(all_steps * (ks + 1) / KS * DG_STEP, g.J);       // its taps end here
+    int j_next = all_steps * ks / KS * DG_STEP;                // first tap of the step requested next
     int entry = j_next % g.period;                             // its place in the period
     unsigned base = (unsigned)(j_next / g.period) * g.ahead;   // the period's offset in D
     auto request = [&](int slot) {
-        const unsigned so = base & (unsigned)((j_next - g.J) >> 31);       // (masks from signs: choices between scalars become branches)
+        const unsigned so = base & (unsigned)((j_next - j_end) >> 31);       // (masks from signs: choices between scalars become branches)
 #pragma unroll
         for (int j = 0; j < BQ; ++j) {
             const int q = (wave * 64 + j * 256) / BN;
             const uintx4_b e[2] = {dg_taps[(entry + 4 * q) / 2], dg_taps[(entry + 4 * q) / 2 + 1]};
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const unsigned past = (unsigned)((g.J - 1 - j_next - 4 * q - i) >> 31);    // all ones behind the last tap
+                const unsigned past = (unsigned)((j_end - 1 - j_next - 4 * q - i) >> 31);   // all ones behind the last tap
                 const ushortx2_dc uv = __builtin_bit_cast(ushortx2_dc, e[i / 2][2 * (i % 2) + 1] | past) - first_tap[j];
                 const bool ok = __builtin_bit_cast(unsigned, __builtin_elementwise_min(uv, last_tap[j])) == __builtin_bit_cast(unsigned, uv);
                 const unsigned o = ok ? vo[j] + e[i / 2][2 * (i % 2)] : OOB;
@@ -349,7 +352,7 @@ __global__ __launch_bounds__(256 * KS, LONG && KS == 1 ? 4 : 1) void direct_gemm
         const unsigned wrap = ~(unsigned)((entry - g.period) >> 31);       // all ones where the next period begins
         entry -= g.period & (int)wrap, base += g.ahead & wrap;
         const unsigned o = ao + (unsigned)j_next * (unsigned)sizeof(T);
-        if (a_wide && j_next + DG_STEP <= g.J) {
+        if (a_wide && j_next + DG_STEP <= j_end) {
             if constexpr (F32) {
                 const floatx4_dc w = __builtin_bit_cast(floatx4_dc, __builtin_amdgcn_raw_buffer_load_b128(rsrc_g, o, 0, 0));
 #pragma unroll
@@ -363,7 +366,7 @@ __global__ __launch_bounds__(256 * KS, LONG && KS == 1 ? 4 : 1) void direct_gemm
         } else {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const unsigned oi = a_role && j_next + 4 * a_quad + i < g.J ? o + i * (unsigned)sizeof(T) : OOB;
+                const unsigned oi = a_role && j_next + 4 * a_quad + i < j_end ? o + i * (unsigned)sizeof(T) : OOB;
                 if constexpr (F32)
                     ra[slot][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc_g, oi, 0, 0));
                 else
@@ -419,7 +422,7 @@ __global__ __launch_bounds__(256 * KS, LONG && KS == 1 ? 4 : 1) void direct_gemm
                                                                 __builtin_bit_cast(halfx8_dc, b[0][j]), acc[j], 0, 0, 0);
         }
     };
-    const int steps = (g.J + DG_STEP * KS - 1) / (DG_STEP * KS);     // (the same for every group: a step past the last tap is zeros)
+    const int steps = (all_steps + KS - 1) / KS;                     // (the same for every group: a step past the last tap is zeros)
     // (requests past the last step fetch nothing; the number of loads in flight does not depend on the path taken)
     __syncthreads();
     request(0);
@@ -552,7 +555,6 @@ template <typename T, int BM, int BN, int KS>
 static hipError_t launch_direct_gemm(DgGeo g, int N, const void *D, const void *G, void *Y, hipStream_t s)
 {
     g.tiles_m = (g.K + BM - 1) / BM;
-    g.share = (g.J + DG_STEP * KS - 1) / (DG_STEP * KS) * DG_STEP;
     g.period = dg_table(g, KS);
     g.ahead = (unsigned)DG_STEP * g.H * g.W * (unsigned)sizeof(T);
     const size_t table = (size_t)g.period * 8;
@@ -625,7 +627,7 @@ hipError_t launch_direct_conv(int N, int C, int H, int W, int K, int R, int S, i
         DgGeo g;
         g.C = C, g.H = H, g.W = W, g.K = K, g.R = R, g.S = S, g.pad = pad, g.stride = stride, g.Ho = Ho, g.Wo = Wo;
         g.J = C * R * S, g.P = N * Ho * Wo, g.tiles_m = 0;
-        g.share = g.period = 0, g.ahead = 0;
+        g.period = 0, g.ahead = 0;
         return dt == WINO_F32 ? launch_direct_gemm<float>(g, N, D, G, Y, s) : launch_direct_gemm<__half>(g, N, D, G, Y, s);
     }
     if (dt == WINO_F32)
