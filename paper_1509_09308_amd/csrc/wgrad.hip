@@ -821,15 +821,16 @@ __global__ __launch_bounds__(64 * WD_WAVES) void wgrad_direct_kernel(const float
     }
 }
 
-// dG[k][c][uv] = sum over images and row bands of part[.][k][c][uv]; one thread per output.
+// dG[k][c][uv] = sum over images and row bands of part[.][k][c][uv] (up to 32 of them, or of their sums), in 64 bits; one
+// thread per output.
 __global__ __launch_bounds__(256) void wgrad_direct_reduce_kernel(const float *__restrict__ part, float *__restrict__ dG,
                                                                   int nparts, int KC9)
 {
     const int o = blockIdx.x * 256 + threadIdx.x;
     if (o >= KC9) return;
-    float a = 0.0f;
-    for (int i = 0; i < nparts; ++i) a += part[(size_t)i * KC9 + o];
-    dG[o] = a;
+    double a = 0.0;
+    for (int i = 0; i < nparts; ++i) a += (double)part[(size_t)i * KC9 + o];
+    dG[o] = (float)a;
 }
 
 static bool wgrad_direct_ok(int C, int W) { return C <= 4 && W % 4 == 0; }

@@ -141,3 +141,18 @@ def test_bwd_filter_few_channels_errors_that_are_not_finite(C):
     E[~np.isfinite(E)] = 0.0
     ref = direct.conv2d_bwd_filter(D, E, pad=1)
     assert rel_err(dG[want], ref[want]) <= TOL_SMALL
+
+
+@pytest.mark.parametrize("N,C,H,W,K,bound", [(15, 3, 62, 16, 19, 1.2e-7), (8, 4, 56, 56, 128, 1.15e-7)])
+def test_bwd_filter_few_channels_partial_sums(N, C, H, W, K, bound):
+    """Up to 32 partial sums of images and row bands, as large as the result, are added in 64 bits: 8.3e-8 and 9.2e-8 from float64
+    (in fp32 1.64e-7 and 1.38e-7; N(0,1) data, over seeds)."""
+    torch, w = require_gpu()
+    err = []
+    for seed in range(3):
+        rng = np.random.default_rng(seed)
+        D, E = rng.standard_normal((N, C, H, W)).astype(np.float32), rng.standard_normal((N, K, H, W)).astype(np.float32)
+        dG = w.wino_conv2d_bwd_filter(to_gpu(D), to_gpu(E), pad=1).cpu().numpy()
+        err.append(rel_err(dG, direct.conv2d_bwd_filter(D, E, pad=1)))
+    print("rel err %s" % err)
+    assert np.sqrt(np.mean(np.square(err))) <= bound
