@@ -708,17 +708,19 @@ __global__ __launch_bounds__(256) void wgrad_output_kernel(const float *__restri
 // almost all their time on the error tensor (16 values written and read back per 4 read) for a
 // handful of products, so the gradient is evaluated directly from its definition instead, as a product on the fp32 matrix
 // units: dG[k][tap] = sum over pixels of E[k][pixel] D[pixel's window][tap].  A workgroup of 16 wavefronts takes 16 filters and
-// one of WD_RS row bands of one image; its wavefronts take turns at runs of 16 pixels of a row.  Per run
+// one of WD_RS row bands of one image; its wavefronts take turns at pairs of runs of 16 pixels of a row.  Per run
 // lane (i, q) fetches pixels 4 q .. 4 q + 3 of filter i and, per 16 taps, the same pixels' inputs of tap i, 16 bytes each from
-// wherever they start; they are the operands of four v_mfma_f32_16x16x4_f32 as they are.  WD_AHEAD runs are in flight.
-// Every run's products are added up eight at a time from zero, then four runs, then all of a wavefront, and the wavefronts' sums by
+// wherever they start; they are the operands of four v_mfma_f32_16x16x4_f32 as they are.  The next pair is in flight, requested
+// together: a filter's two runs are a whole line.
+// Every run's products are added up eight at a time from zero, then two runs, then all of a wavefront, and the wavefronts' sums by
 // halves in LDS (in one chain: relative error 1.72e-7 instead of 1.20e-7 for 3 -> 64 channels at 224 x 224, N = 1); the
 // per-(image, band) partial sums are added by wgrad_direct_reduce_kernel, in a fixed order.  Needs W % 4 == 0.
-// Bound by reading E and by matrix instructions: 3 -> 64 channels at 224 x 224, N = 16: 40 and 25 us of 66 (fp32 vector
-// instructions, a wavefront per four filters, one per SIMD, waiting for each row of the window: 196; the same with 16
-// wavefronts per CU and three filters each: 145); N = 64: 570 -> 273; N = 1 (16 workgroups, as the workspace has room for four
-// bands): 140 -> 51; 4 -> 128 at 112 x 112, N = 8: 105 -> 36; 1 -> 64 at 224 x 224, N = 16: 88 -> 47.
-constexpr int WD_RS = 4, WD_K = 16, WD_WAVES = 16, WD_AHEAD = 4;
+// Bound by reading E and by matrix instructions: 3 -> 64 channels at 224 x 224, N = 16: 40 and 25 us of 59.  Fp32 vector
+// instructions, a wavefront per four filters (one per SIMD, waiting for each row of the window) / four single runs in flight,
+// requested one by one and behind the band too / this: N = 16 196 / 61 / 59; N = 64 569 / 274 / 255; N = 1 (16 workgroups, as
+// the workspace has room for four bands) 140 / 51 / 47; 4 -> 128 at 112 x 112, N = 8 104 / 36 / 30; 1 -> 64 at 224 x 224, N = 16
+// 87 / 47 / 44, N = 64 175 / 207 / 163; 1 -> 459 at 204 x 204, N = 6 124 / 139 / 110; 1 -> 96 at 8 x 160, N = 25 20.5 / 23.0 / 13.7.
+constexpr int WD_RS = 4, WD_K = 16, WD_WAVES = 16, WD_PAIR = 2;
 
 template <int CH>
 __global__ __launch_bounds__(64 * WD_WAVES) void wgrad_direct_kernel(const float *__restrict__ D, const float *__restrict__ E,
@@ -743,14 +745,17 @@ __global__ __launch_bounds__(64 * WD_WAVES) void wgrad_direct_kernel(const float
         Dc[n] = D + ((size_t)i * CH + j / 9) * H * W;
         up[n] = j % 9 / 3 - 1, right[n] = j % 3 - 1;
     }
-    const int runs = (W + 15) / 16, dx = WD_WAVES / runs, dr = WD_WAVES % runs;
-    floatx4_w e[WD_AHEAD], d[WD_AHEAD][NT], some[NT], sum[NT];   // sums of the last runs, of all
+    const int runs = (W + 15) / 16, far = WD_PAIR * WD_WAVES - 1, dx = far / runs, dr = far % runs;
+    floatx4_w e[WD_PAIR], d[WD_PAIR][NT], some[NT], sum[NT];     // sums of the last runs, of all
 #pragma unroll
     for (int n = 0; n < NT; ++n) some[n] = sum[n] = floatx4_w{0.f, 0.f, 0.f, 0.f};
-    int x_req = x_lo + wave / runs, r_req = wave % runs;         // row and run requested next
+    int x_req = x_lo + WD_PAIR * wave / runs, r_req = WD_PAIR * wave % runs;       // row and run requested next
     int x = x_req, r = r_req;                                    // ... and multiplied next
-    auto next = [&](int &xx, int &rr) {
-        xx += dx, rr += dr;
+    auto next = [&](int &xx, int &rr, int slot) {
+        if (slot == 0)
+            ++rr;
+        else
+            xx += dx, rr += dr;
         if (rr >= runs) rr -= runs, ++xx;
     };
     // all addresses are inside the image: what lies outside is taken from the nearest place inside and left out below
@@ -763,7 +768,7 @@ __global__ __launch_bounds__(64 * WD_WAVES) void wgrad_direct_kernel(const float
             const float *p = Dc[n] + ((size_t)row * W + col);
             __builtin_memcpy(&d[slot][n], p, 16);                // (aligned to four bytes)
         }
-        next(x_req, r_req);
+        next(x_req, r_req, slot);
     };
     auto multiply = [&](int slot) {
         const int y = 16 * r + 4 * lq;
@@ -789,20 +794,22 @@ __global__ __launch_bounds__(64 * WD_WAVES) void wgrad_direct_kernel(const float
 #pragma unroll
         for (int n = 0; n < NT; ++n)
             if ((unsigned)(x + up[n]) < (unsigned)H) some[n] += t[0][n] + t[1][n];
-        next(x, r);
+        next(x, r, slot);
     };
-    if (x_lo < x_hi) {
+    auto set_aside = [&]() {
 #pragma unroll
-        for (int slot = 0; slot < WD_AHEAD; ++slot) request(slot);
-        while (x < x_hi) {
-#pragma unroll
-            for (int slot = 0; slot < WD_AHEAD; ++slot) {
-                if (x < x_hi) multiply(slot);
-                request(slot);
-            }
-#pragma unroll
-            for (int n = 0; n < NT; ++n) sum[n] += some[n], some[n] = floatx4_w{0.f, 0.f, 0.f, 0.f};
+        for (int n = 0; n < NT; ++n) sum[n] += some[n], some[n] = floatx4_w{0.f, 0.f, 0.f, 0.f};
+    };
+    if (x < x_hi) {
+        request(0), request(1);
+        while (x_req < x_hi) {                                   // (there is another pair, so all of this one is in the band)
+            multiply(0), multiply(1);
+            request(0), request(1);
+            set_aside();
         }
+        multiply(0);
+        if (x < x_hi) multiply(1);
+        set_aside();
     }
 #pragma unroll
     for (int n = 0; n < NT; ++n) red[wave][n][lane] = sum[n];

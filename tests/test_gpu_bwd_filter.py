@@ -28,7 +28,9 @@ TOL_SMALL, TOL_FULL = 2e-6, 2e-5
                                    # at most 4 channels and W % 4 == 0: the direct kernel
                                    (2, 3, 12, 16, 10), (3, 1, 8, 4, 5), (2, 4, 6, 8, 7), (1, 2, 5, 12, 3), (3, 3, 31, 36, 70),
                                    # ... runs of 16 pixels: one and a part, more than wavefronts, bands without rows
-                                   (2, 4, 9, 20, 16), (1, 3, 5, 300, 17), (2, 2, 1, 4, 33), (1, 1, 3, 272, 16), (1, 4, 40, 48, 15)])
+                                   (2, 4, 9, 20, 16), (1, 3, 5, 300, 17), (2, 2, 1, 4, 33), (1, 1, 3, 272, 16), (1, 4, 40, 48, 15),
+                                   # ... 33 runs in a band (16 pairs and half of one), 64, 68 and 35
+                                   (1, 3, 44, 48, 20), (2, 1, 64, 64, 16), (1, 2, 66, 64, 18), (1, 4, 28, 80, 16)])
 def test_bwd_filter_matches_oracle(shape):
     torch, w = require_gpu()
     N, C, H, W, K = shape
