@@ -215,6 +215,27 @@ def test_input_transform_f16_bit_exact(m, N, C, H, W, pad):
 
 
 @pytest.mark.parametrize("m", [2, 4])
+@pytest.mark.parametrize("N,C,H,W,pad", [
+    (40, 3, 5, 4, 1),        # rows of one tile
+    (20, 9, 7, 8, 1),        # ... of two
+    (9, 2, 13, 12, 1),       # of three: blocks of 64 tiles begin and end inside a row
+    (2, 3, 4, 252, 1), (1, 2, 5, 256, 1), (1, 2, 9, 260, 1),        # ... of 63, 64 and 65
+])
+def test_input_transform_f16_small_images(m, N, C, H, W, pad):
+    """Tiles that lie mostly outside the image, and edges of a block of 64 tiles, with NaNs right before and behind D."""
+    torch, w = require_gpu()
+    rng = np.random.default_rng(H + W + m + N)
+    D = rng.integers(-3, 4, (N, C, H, W)).astype(np.float16)
+    room = torch.full((D.size + 16,), float("nan"), dtype=torch.float16, device="cuda")
+    d = room[8:8 + D.size].view(D.shape)
+    d.copy_(to_gpu(D))
+    V = w.wino_input_transform(d, pad, m)
+    P = wg.num_tiles(N, H, W, pad, m)
+    ref = wg.data_transform(D.astype(np.float64), pad, m)
+    assert np.array_equal(w.unpack_v(V, C, P, m, w.WINO_F16).astype(np.float64), ref)
+
+
+@pytest.mark.parametrize("m", [2, 4])
 @pytest.mark.parametrize("K,C,P", [(32, 32, 784), (70, 19, 100), (128, 48, 300), (256, 256, 130), (5, 3, 17)])
 def test_batched_gemm_f16_exact_on_integers(m, K, C, P):
     torch, w = require_gpu()
