@@ -285,23 +285,50 @@ __device__ __forceinline__ void filter_transform_f16_block(const __half *__restr
     }
 }
 
-// The tile at (x0, y0) of an image plane, zeros outside the image: taps are requested from the nearest place inside, so that
-// all of them are in flight at once (loads of 2 bytes in branches are converted, and waited for, one after the other).
+// The tile at (x0, y0) of channel c (the wavefront's) of image i, zeros outside the image, for the 64 tiles from b0 on.  All
+// taps are requested at once, from a buffer behind whose end those outside lie: nothing is fetched for them.  (Loads of 2 bytes
+// in branches are converted, and waited for, one after the other; from the nearest place inside instead, tiles that lie
+// mostly outside cost as much as any.  256 channels, N = 64, F(4x4,3x3), branches / nearest / this: 3 x 3 5.4 / 10.4 / 5.5 us, 7 x 7
+// 9.1 / 11.4 / 8.9, 21 x 21 29.4 / 21.0 / 19.5.)
 template <int A>
-__device__ __forceinline__ void fetch_tile(const __half *__restrict__ plane, int H, int W, int x0, int y0, float (&d)[A][A])
+__device__ __forceinline__ void fetch_tile(const __half *__restrict__ D, const Geo &g, int b0, int i, int c, int x0, int y0, float (&d)[A][A])
 {
+    constexpr unsigned OUTSIDE = 0x80000000u;
+    const int tiles = g.Th * g.Tw, i0 = b0 / tiles, images = min(b0 + 63, g.P - 1) / tiles - i0 + 1;
+    const size_t plane = (size_t)g.H * g.W, image = g.C * plane;
     __half v[A][A];
+    if (images * image * 2 < OUTSIDE) {
+        const size_t first = i0 * image + __builtin_amdgcn_readfirstlane(c) * plane, left = (g.N * image - first) * 2;
+        const __amdgpu_buffer_rsrc_t rsrc =
+            __builtin_amdgcn_make_buffer_rsrc((void *)(D + first), 0, (unsigned)(left < OUTSIDE ? left : OUTSIDE - 1), 0x00020000);
+        const unsigned at = (unsigned)(i - i0) * (unsigned)image * 2u;
+        unsigned col[A];
 #pragma unroll
-    for (int p = 0; p < A; ++p) {
-        const __half *row = plane + (size_t)min(max(x0 + p, 0), H - 1) * W;
+        for (int q = 0; q < A; ++q) col[q] = (unsigned)(y0 + q) < (unsigned)g.W ? at + (unsigned)(y0 + q) * 2u : OUTSIDE;
 #pragma unroll
-        for (int q = 0; q < A; ++q) v[p][q] = row[min(max(y0 + q, 0), W - 1)];
+        for (int p = 0; p < A; ++p) {
+            const bool inside = (unsigned)(x0 + p) < (unsigned)g.H;
+            const unsigned row = (unsigned)((x0 + p) * g.W) * 2u;
+#pragma unroll
+            for (int q = 0; q < A; ++q)
+                v[p][q] = __builtin_bit_cast(__half, __builtin_amdgcn_raw_buffer_load_b16(rsrc, inside ? col[q] + row : OUTSIDE, 0, 0));
+        }
+#pragma unroll
+        for (int p = 0; p < A; ++p)
+#pragma unroll
+            for (int q = 0; q < A; ++q) d[p][q] = __half2float(v[p][q]);
+    } else {                   // images beyond a buffer's reach: from the nearest place inside
+        const __half *const src = D + ((size_t)i * g.C + c) * plane;
+#pragma unroll
+        for (int p = 0; p < A; ++p)
+#pragma unroll
+            for (int q = 0; q < A; ++q) v[p][q] = src[(size_t)min(max(x0 + p, 0), g.H - 1) * g.W + min(max(y0 + q, 0), g.W - 1)];
+#pragma unroll
+        for (int p = 0; p < A; ++p)
+#pragma unroll
+            for (int q = 0; q < A; ++q)
+                d[p][q] = (unsigned)(x0 + p) < (unsigned)g.H && (unsigned)(y0 + q) < (unsigned)g.W ? __half2float(v[p][q]) : 0.0f;
     }
-#pragma unroll
-    for (int p = 0; p < A; ++p)
-#pragma unroll
-        for (int q = 0; q < A; ++q)
-            d[p][q] = (unsigned)(x0 + p) < (unsigned)H && (unsigned)(y0 + q) < (unsigned)W ? __half2float(v[p][q]) : 0.0f;
 }
 
 // Input transform.  V is laid out [e][c/8][b][c%8]; a block takes 8 channels x 64 tiles (512 threads) and writes V as
@@ -327,15 +354,15 @@ __device__ __forceinline__ void input_transform_f16_block(const __half *__restri
         const int tx = t2 % g.Th;
         const int i = t2 / g.Th;
         const int x0 = M * tx - g.pad, y0 = M * ty - g.pad;
-        const __half *src = D + ((size_t)i * g.C + c) * g.H * g.W;
         if constexpr (!VEC) {
-            fetch_tile<A>(src, g.H, g.W, x0, y0, d);
+            fetch_tile<A>(D, g, bx * TB, i, c, x0, y0, d);
         } else {
             // A wavefront's 64 tiles lie side by side, so the outer columns are the neighbouring lanes' (DPP); the first and the
             // last lane fetch theirs, the others of that request what they have already.  Rows outside are taken from the
             // nearest place inside.  (Both outer columns fetched by every lane, in branches / without: 256 channels, N = 64, 8 x 4
             // 4.4 / 6.0 us, this 4.1; 8 x 8 5.7 / 6.5 / 5.1; 64 channels at 112 x 112, N = 16: 22.0 / 18.0 / 16.5.)
             static_assert(TB == 64, "a wavefront per channel");
+            const __half *src = D + ((size_t)i * g.C + c) * g.H * g.W;
             uint2 mid[A];
             unsigned short edge[A] = {};
             const int outer = bl == 0 ? max(y0, 0) : bl == TB - 1 ? min(y0 + 5, g.W - 1) : y0 + 1;

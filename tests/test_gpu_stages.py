@@ -220,6 +220,8 @@ def test_input_transform_f16_bit_exact(m, N, C, H, W, pad):
     (20, 9, 7, 8, 1),        # ... of two
     (9, 2, 13, 12, 1),       # of three: blocks of 64 tiles begin and end inside a row
     (2, 3, 4, 252, 1), (1, 2, 5, 256, 1), (1, 2, 9, 260, 1),        # ... of 63, 64 and 65
+    (70, 3, 3, 3, 1),        # one tile per image (m = 4): a block of 64 images
+    (30, 10, 7, 7, 1), (13, 8, 8, 8, 0), (5, 3, 11, 30, 1), (3, 2, 30, 7, 0),
 ])
 def test_input_transform_f16_small_images(m, N, C, H, W, pad):
     """Tiles that lie mostly outside the image, and edges of a block of 64 tiles, with NaNs right before and behind D."""
@@ -233,6 +235,30 @@ def test_input_transform_f16_small_images(m, N, C, H, W, pad):
     P = wg.num_tiles(N, H, W, pad, m)
     ref = wg.data_transform(D.astype(np.float64), pad, m)
     assert np.array_equal(w.unpack_v(V, C, P, m, w.WINO_F16).astype(np.float64), ref)
+
+
+def test_input_transform_f16_beyond_a_buffers_reach():
+    """An image of more than 2 GiB, whose taps are not fetched through a buffer: tiles at its corners, edges and inside."""
+    torch, w = require_gpu()
+    m, C, H, W = 4, 9, 11003, 11001
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    D = torch.randint(-3, 4, (1, C, H, W), generator=gen, device="cuda", dtype=torch.int8).half()
+    assert D.numel() * 2 > 2 ** 31
+    V = w.wino_input_transform(D, 1, m)
+    Th, Tw = -(-H // m), -(-W // m)
+    _, Cp, Pp = w.wino_padded_dims(1, C, Th * Tw, m, w.WINO_F16)
+    V = V.view(36, Cp // 8, Pp, 8)
+    rng = np.random.default_rng(4)
+    for tx, ty in [(0, 0), (0, Tw - 1), (Th - 1, 0), (Th - 1, Tw - 1)] + [(int(rng.integers(Th)), int(rng.integers(Tw))) for _ in range(30)]:
+        d = np.zeros((1, C, 6, 6))
+        x0, y0 = max(m * tx - 1, 0), max(m * ty - 1, 0)
+        part = D[0, :, x0:m * tx + 5, y0:m * ty + 5].cpu().numpy()
+        ox, oy = x0 - (m * tx - 1), y0 - (m * ty - 1)
+        d[0, :, ox:ox + part.shape[1], oy:oy + part.shape[2]] = part
+        ref = wg.data_transform(d, 0, m)[..., 0]                       # [6][6][C]
+        got = V[:, :, tx * Tw + ty].reshape(36, Cp)[:, :C].float().cpu().numpy().reshape(6, 6, C)
+        assert np.array_equal(got, ref), (tx, ty)
 
 
 @pytest.mark.parametrize("m", [2, 4])
