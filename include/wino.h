@@ -20,8 +20,8 @@
  *     enqueue work on it; they never synchronise the device.
  *   - Return value: a wino_status_t.  No exceptions, no abort.  Arguments are checked before
  *     any GPU call, so bad arguments are reported even on a machine with no GPU.
- *   - Storage type `dt` is that of D, G, U and V; products are always accumulated in fp32 and
- *     M is always fp32.  fp32 products run on the bf16 matrix units where those are faster, every value in
+ *   - Storage type `dt` is that of D, G, U and V; products are accumulated in fp32 (small fp32 layers: in
+ *     64 bits, see wino_small_layer) and M is always fp32.  fp32 products run on the bf16 matrix units where those are faster, every value in
  *     three exact parts: sums are as precise as chains of fp32 multiply-adds, over the whole range of fp32,
  *     and what is infinite or NaN is so where the fp32 operations make it so.
  *
@@ -180,12 +180,20 @@ size_t wino_bwd_filter_workspace_bytes(int N, int C, int H, int W, int K);   /* 
 int wino_conv2d_bwd_filter(int N, int C, int H, int W, int K, int pad, int dt, const void *D, const void *E, void *dG,
                            void *workspace, size_t workspace_bytes, void *stream);
 
-/* Host-side query: the variant wino_conv2d_fwd_ex runs for these arguments -- WINO_FLAG_UNFUSED,
- * WINO_FLAG_FUSED or WINO_FLAG_ONE_LAUNCH -- when called with `flags` (WINO_FLAG_AUTO resolves to one of
- * the first two; WINO_FLAG_ONE_LAUNCH is answered for untransformed filters, G given); a negative
- * wino_status_t (e.g. -WINO_EUNSUPPORTED) if the call would be rejected.  (Small fp32 layers answered
- * WINO_FLAG_UNFUSED for WINO_FLAG_AUTO: the call runs all four loops in one launch, without the workspace.) */
+/* Host-side query: what wino_conv2d_fwd_ex takes when called with `flags`: WINO_FLAG_FUSED or WINO_FLAG_ONE_LAUNCH
+ * for the variant of that name (the latter for untransformed filters, G given), WINO_FLAG_UNFUSED for everything else --
+ * the four stages or, with WINO_FLAG_AUTO, the small-layer kernel where wino_small_layer() answers 1, which has no flag of
+ * its own.  WINO_FLAG_AUTO never resolves to WINO_FLAG_ONE_LAUNCH.  A negative wino_status_t (e.g. -WINO_EUNSUPPORTED) if
+ * the call would be rejected. */
 int wino_conv2d_variant(int N, int C, int H, int W, int K, int pad, int m, int dt, int y_dt, unsigned flags);
+/* Host-side query: 1 if WINO_FLAG_AUTO runs this layer's four loops in one launch made for small layers (fp32; sums in 64
+ * bits; the workspace is checked as always, and neither read nor written), 0 if it runs the variant that
+ * wino_conv2d_variant() answers, a negative wino_status_t if the call would be rejected.  `filters`: what the call is given.
+ * For wino_conv2d_bwd_data with K and C exchanged; wino_conv2d_fwd and wino_conv2d_fwd_noalloc choose as WINO_FILTERS_G. */
+#define WINO_FILTERS_G 0       /* G of a forward layer */
+#define WINO_FILTERS_U 1       /* U, of either */
+#define WINO_FILTERS_G_BWD 2   /* G of an input gradient */
+int wino_small_layer(int N, int C, int H, int W, int K, int pad, int m, int dt, int y_dt, int filters);
 /* Host-side query: how the one-kernel fp32 layer of more than 32 filters (m = 4 or 2; Section 6's fusion of the
  * transforms into the multiply) deals its items to the GPU's 8 XCDs when the workspace has room for partial outputs.
  * An item is 64 filters x 32 tiles (64 tiles for m = 2) and 32 workgroups per XCD are resident; layers of fewer than

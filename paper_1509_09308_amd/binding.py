@@ -15,6 +15,7 @@ from . import build as _build
 WINO_OK, WINO_EINVAL, WINO_EUNSUPPORTED, WINO_EWORKSPACE, WINO_EHIP = range(5)
 WINO_F32, WINO_F16 = 0, 1
 FLAG_AUTO, FLAG_UNFUSED, FLAG_FUSED, FLAG_ONE_LAUNCH = 0, 1, 2, 3
+FILTERS_G, FILTERS_U, FILTERS_G_BWD = 0, 1, 2
 
 _lib = None
 
@@ -61,6 +62,7 @@ def lib():
             "wino_conv2d_fwd_noalloc": (i, [i] * 7 + [p, p, p, p]),
             "wino_conv2d_fwd_ex": (i, [i] * 9 + [p, p, p, p, p, sz, u, p]),
             "wino_conv2d_variant": (i, [i] * 9 + [u]),
+            "wino_small_layer": (i, [i] * 10),
             "wino_one_kernel_plan": (i, [i] * 8 + [ip]),
             "wino_filter_transform_bwd": (i, [i, i, i, i, p, p, p]),
             "wino_bwd_filter_workspace_bytes": (sz, [i] * 5),
@@ -80,7 +82,7 @@ EXPORTS = ["wino_status_string", "wino_last_hip_error", "wino_num_tiles", "wino_
            "wino_padded_dims", "wino_u_offset", "wino_v_offset", "wino_m_offset", "wino_filter_bytes",
            "wino_v_bytes", "wino_m_bytes", "wino_workspace_bytes", "wino_filter_transform",
            "wino_filter_transform_ex", "wino_input_transform", "wino_batched_gemm", "wino_gemm_launch_shape",
-           "wino_output_transform", "wino_conv2d_fwd", "wino_conv2d_fwd_noalloc", "wino_conv2d_fwd_ex", "wino_conv2d_variant", "wino_one_kernel_plan", "wino_filter_transform_bwd", "wino_conv2d_bwd_data",
+           "wino_output_transform", "wino_conv2d_fwd", "wino_conv2d_fwd_noalloc", "wino_conv2d_fwd_ex", "wino_conv2d_variant", "wino_small_layer", "wino_one_kernel_plan", "wino_filter_transform_bwd", "wino_conv2d_bwd_data",
            "wino_bwd_filter_workspace_bytes", "wino_conv2d_bwd_filter",
            "direct_conv2d_fwd",
            "wino_shutdown"]
@@ -378,11 +380,20 @@ def wino_gemm_launch_shape(K, C, P, m, dt=WINO_F32):
 
 
 def wino_conv2d_variant(N, C, H, W, K, pad, m, dt=WINO_F32, y_dt=WINO_F32, flags=FLAG_AUTO):
-    """FLAG_UNFUSED, FLAG_FUSED or FLAG_ONE_LAUNCH: the path wino_conv2d_fwd_ex takes; raises if it would be rejected."""
+    """FLAG_FUSED, FLAG_ONE_LAUNCH or (the four stages, or what wino_small_layer tells) FLAG_UNFUSED: the path
+    wino_conv2d_fwd_ex takes; raises if it would be rejected."""
     v = int(lib().wino_conv2d_variant(N, C, H, W, K, pad, m, dt, y_dt, flags))
     if v < 0:
         raise WinoError(-v, "wino_conv2d_variant")
     return v
+
+
+def wino_small_layer(N, C, H, W, K, pad, m, dt=WINO_F32, y_dt=WINO_F32, filters=FILTERS_G):
+    """Whether FLAG_AUTO runs the layer in the one launch made for small layers; raises if the call would be rejected."""
+    v = int(lib().wino_small_layer(N, C, H, W, K, pad, m, dt, y_dt, filters))
+    if v < 0:
+        raise WinoError(-v, "wino_small_layer")
+    return bool(v)
 
 
 def wino_filter_transform_bwd(G, m, U=None, stream=None):

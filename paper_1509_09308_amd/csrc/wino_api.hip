@@ -263,6 +263,10 @@ int wino_output_transform(int N, int K, int H, int W, int pad, int m, int y_dt, 
 // The one-kernel paths write fp32 outputs; the fp16-storage one also writes fp16.
 static bool fused_y_ok(const Geo &g, int y_dt) { return y_dt == WINO_F32 || g.dt == WINO_F16; }
 
+// What WINO_FLAG_AUTO runs: the one-kernel path, else the small-layer kernel, else the four stages.
+static bool auto_fused(const Geo &g, int y_dt) { return fused_y_ok(g, y_dt) && fused_preferred(g); }
+static bool auto_small(const Geo &g, int y_dt) { return y_dt == WINO_F32 && fused_small_preferred(g); }   // (not auto_fused)
+
 int wino_conv2d_variant(int N, int C, int H, int W, int K, int pad, int m, int dt, int y_dt, unsigned flags)
 {
     Geo g;
@@ -272,8 +276,17 @@ int wino_conv2d_variant(int N, int C, int H, int W, int K, int pad, int m, int d
     if (flags == WINO_FLAG_ONE_LAUNCH)
         return (fused_f2_eligible(g) && y_dt == WINO_F32) ? (int)WINO_FLAG_ONE_LAUNCH : -WINO_EUNSUPPORTED;
     if (flags == WINO_FLAG_FUSED) return (fused_eligible(g) && fused_y_ok(g, y_dt)) ? (int)WINO_FLAG_FUSED : -WINO_EUNSUPPORTED;
-    if (flags == WINO_FLAG_AUTO && fused_y_ok(g, y_dt) && fused_preferred(g)) return WINO_FLAG_FUSED;
+    if (flags == WINO_FLAG_AUTO && auto_fused(g, y_dt)) return WINO_FLAG_FUSED;
     return WINO_FLAG_UNFUSED;
+}
+
+int wino_small_layer(int N, int C, int H, int W, int K, int pad, int m, int dt, int y_dt, int filters)
+{
+    Geo g;
+    const int st = make_geo(N, C, H, W, K, pad, m, dt, &g);
+    if (st != WINO_OK) return -st;
+    if (bad_dtype(y_dt) || filters < WINO_FILTERS_G || filters > WINO_FILTERS_G_BWD) return -WINO_EINVAL;
+    return !auto_fused(g, y_dt) && auto_small(g, y_dt);
 }
 
 int wino_one_kernel_plan(int N, int C, int H, int W, int K, int pad, int m, int dt, int out[32])
@@ -310,8 +323,8 @@ static int run_layer(const Geo &g, int y_dt, const void *D, const void *G, const
         e = launch_fused_f2(g, (const float *)D, (const float *)G, (float *)Y, workspace, workspace_bytes, bwd, s);
         return e == hipSuccess ? WINO_OK : hip_fail(e);
     }
-    if (flags == WINO_FLAG_AUTO && fused_y_ok(g, y_dt) && fused_preferred(g)) flags = WINO_FLAG_FUSED;
-    if (flags == WINO_FLAG_AUTO && y_dt == WINO_F32 && fused_small_preferred(g)) {
+    if (flags == WINO_FLAG_AUTO && auto_fused(g, y_dt)) flags = WINO_FLAG_FUSED;
+    if (flags == WINO_FLAG_AUTO && auto_small(g, y_dt)) {
         e = launch_fused_small(g, (const float *)D, (const float *)G, (const float *)U, (float *)Y, bwd, s);
         return e == hipSuccess ? WINO_OK : hip_fail(e);
     }

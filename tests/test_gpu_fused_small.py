@@ -50,13 +50,7 @@ def test_small_layers(N, C, H, W, K, pad, m):
         Y = torch.full(ref.shape, float("nan"), device="cuda")
         w.wino_conv2d_fwd_ex(d, pad=pad, m=m, Y=Y, workspace=ws, **kw)
         check_close(Y.cpu().numpy(), ref, TOL[m], "m=%d %s %s" % (m, (N, C, H, W, K, pad), list(kw)), m=m)
-        assert bool((ws == 0xff).all()) == takes(w, N, C, H, W, K, pad, m)
-
-
-def takes(w, N, C, H, W, K, pad, m):
-    """Whether one launch without workspace is expected: at least a tile's columns, few channels (a step of F(6x6,3x3) takes
-    3 us), and no other form preferred."""
-    return W >= m + 2 and (m != 6 or C <= 8) and w.wino_conv2d_variant(N, C, H, W, K, pad, m) == w.FLAG_UNFUSED
+        assert bool((ws == 0xff).all()) == w.wino_small_layer(N, C, H, W, K, pad, m, filters=w.FILTERS_G if "G" in kw else w.FILTERS_U)
 
 
 @pytest.mark.parametrize("m", [2, 4, 6])

@@ -223,6 +223,24 @@ def test_variant_query_host_only(L):
     assert L.wino_conv2d_variant(1, 512, 14, 14, 512, 1, 2, 0, 0, 4) == -w.WINO_EINVAL
 
 
+def test_small_layer_query_host_only(L):
+    """Whether WINO_FLAG_AUTO takes the one launch made for small layers can be asked on the host: wino_conv2d_variant answers
+    WINO_FLAG_UNFUSED for these, as for the four stages.  (That calls do as answered: test_gpu_fused_small.py.)"""
+    for m, C in ((2, 32), (4, 16)):
+        assert w.wino_small_layer(1, C, 56, 56, 32, 1, m) and w.wino_conv2d_variant(1, C, 56, 56, 32, 1, m) == w.FLAG_UNFUSED
+    assert w.wino_small_layer(1, 16, 226, 226, 32, 1, 6)
+    assert w.wino_small_layer(5, 5, 5, 10, 9, 0, 4)                              # any padding and width
+    assert not w.wino_small_layer(1, 128, 112, 112, 128, 1, 4)                   # the four stages
+    assert not w.wino_small_layer(64, 256, 56, 56, 256, 1, 4)                    # one kernel
+    assert not w.wino_small_layer(1, 8, 9, 5, 16, 1, 4)                          # narrower than a tile
+    assert L.wino_small_layer(1, 32, 56, 56, 32, 1, 2, 1, 0, 0) == 0             # fp16 storage
+    assert L.wino_small_layer(1, 32, 56, 56, 32, 1, 2, 0, 1, 0) == 0             # fp16 Y
+    assert L.wino_small_layer(1, 32, 56, 56, 32, 1, 2, 0, 2, 0) == -w.WINO_EINVAL
+    assert L.wino_small_layer(1, 32, 56, 56, 32, 1, 2, 0, 0, 3) == -w.WINO_EINVAL
+    assert L.wino_small_layer(0, 32, 56, 56, 32, 1, 2, 0, 0, 0) == -w.WINO_EINVAL
+    assert L.wino_small_layer(1, 32, 56, 56, 32, 1, 3, 0, 0, 0) == -w.WINO_EUNSUPPORTED
+
+
 def test_gemm_launch_shape_host_only(L):
     """The block shape and channel shares of the multiply inside a layer call can be asked on the host."""
     assert w.wino_gemm_launch_shape(256, 256, 64 * 196, 4) == (128, 128, 1)     # conv3.x at N = 64: 27.6 blocks per CU
