@@ -100,6 +100,7 @@ def make_layers(N, np_dtype, policy, config_idx, shapes=None):
             L.P = w.wino_num_tiles(N, HW, HW, 1, L.m)
             L.ws_bytes = w.wino_workspace_bytes(N, C, HW, HW, K, 1, L.m, L.dt)
             L.variant = w.wino_conv2d_variant(N, C, HW, HW, K, 1, L.m, L.dt)
+            L.small = w.wino_small_layer(N, C, HW, HW, K, 1, L.m, L.dt)
         layers.append(L)
     return layers
 
@@ -188,7 +189,12 @@ def stage_plan(torch, w, L, ws, sets):
     Ds = [L.D] + [L.D.clone() for _ in range(sets - 1)]
     Ys = [L.Y] + [torch.empty_like(L.Y) for _ in range(sets - 1)]
     plans = []
-    if L.variant == w.FLAG_FUSED:
+    if L.small:                  # all four loops in one launch, from G
+        for d, y in zip(Ds, Ys):
+            plans.append([("fused", lambda d=d, y=y: w.wino_conv2d_fwd_ex(d, G=L.G, pad=1, m=L.m, Y=y, workspace=ws))])
+        nbytes = {"fused": nD + 9 * L.K * L.C * s + nY}
+        kernel = "fused_small_kernel<%d, 0>" % L.m
+    elif L.variant == w.FLAG_FUSED:
         for d, y in zip(Ds, Ys):
             plans.append([("filter", lambda: w.wino_filter_transform(L.G, L.m, U=U)),
                           ("fused", (lambda d=d, y=y: w.wino_conv2d_fwd_ex(d, U=U, K=L.K, pad=1, m=L.m, Y=y, workspace=ws,
@@ -288,8 +294,9 @@ def summarize_stages(w, layers, stages, dtype, workload):
     for L, st in zip(layers, stages):
         if st is None:
             continue
-        main = "fused" if st["variant"] == w.FLAG_FUSED else "gemm"
-        row = {"layer": L.name, "m": L.m, "variant": "fused" if main == "fused" else "unfused", "kernel": st["kernel"],
+        main = "fused" if "fused" in st else "gemm"
+        row = {"layer": L.name, "m": L.m, "variant": "small" if "fused_small" in st["kernel"] else "fused" if main == "fused" else "unfused",
+               "kernel": st["kernel"],
                "kernel_ms": st[main]["mean"], "kernel_ms_min": st[main]["min"],
                "kernel_tflops": st["gemm_flops"] / st[main]["mean"] / 1e9, "buffer_sets_cold": st["sets"]}
         if main + "_cold" in st:
@@ -648,7 +655,7 @@ def stack_leg(torch, w, args, N, dtype, policy, cfg_idx, steps, warmup, cold=Tru
             ref_layers = []
             for m in sorted({L.m for L in layers if not L.direct}):
                 L = copy.copy([x for x in layers if not x.direct and x.m == m][-1])
-                L.variant = w.FLAG_UNFUSED
+                L.variant, L.small = w.FLAG_UNFUSED, False
                 ref_layers.append(L)
             ref = summarize_stages(w, ref_layers, time_stages(torch, w, ref_layers, ws, max(5, steps), cold=cold), dtype, workload)
             out["four_stage_reference"] = {"layers": [L.name for L in ref_layers], "stages": ref["stages"], "kernels": ref["kernels"],

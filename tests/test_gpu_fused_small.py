@@ -76,3 +76,16 @@ def test_small_layers_are_at_least_as_precise(m):
     four = rel_err(w.wino_conv2d_fwd_ex(d, G=g, pad=1, m=m, flags=w.FLAG_UNFUSED).cpu().numpy(), ref)
     print("m=%d: one launch %.2e, four stages %.2e" % (m, one, four))
     assert one <= four
+
+
+def test_bench_times_the_launch_that_the_layer_makes():
+    torch, w = require_gpu()
+    import bench
+    L = bench.make_layers(1, np.float32, "2", 1, shapes=[("layer", 32, 56, 32)])[0]
+    ws = torch.empty(L.ws_bytes, dtype=torch.uint8, device="cuda").fill_(0xff)
+    plans, nbytes, kernel, _ = bench.stage_plan(torch, w, L, ws, 1)
+    assert w.wino_small_layer(1, 32, 56, 56, 32, 1, 2) and kernel.startswith("fused_small_kernel<2")
+    assert [name for name, _ in plans[0]] == list(nbytes) == ["fused"]
+    plans[0][0][1]()
+    assert bool((ws == 0xff).all())
+    assert rel_err(L.Y.cpu().numpy(), direct.conv2d_fwd(L.D_host, L.G_host, pad=1)) <= TOL[2]
