@@ -16,8 +16,8 @@
 // bf16 parts would be split once per 16 filters or tiles.
 //
 // Bound by its chain: a step of F(4x4) takes 1.5 us (18 matrix instructions of a wavefront, 250 vector instructions, a
-// barrier), whether one step or two are in flight.  32 -> 32 channels at 56 x 56, N = 1, F(2x2): three launches 15.2 us, 10.3 so;
-// 64 -> 64, 14 and 8.7 (as much as a call takes on the host); 32 -> 16 at 84 x 84, N = 6, F(4x4): 21.6 and 10.9.  32 filters
+// barrier), whether one step or two are in flight.  32 -> 32 channels at 56 x 56, N = 1, F(2x2): three launches 11.9 us, 6.6 so;
+// 64 -> 64, 13.9 and 8.8; 32 -> 16 at 84 x 84, N = 6, F(4x4): 22.1 and 10.8.  32 filters
 // per workgroup: 10-50 % slower.
 #include <type_traits>
 
@@ -329,27 +329,38 @@ bool fused_small_eligible(const Geo &g)
     return ((long long)g.P + 15) / 16 * ((g.K + 15) / 16) <= 0x7fffffffLL;
 }
 
-// Small enough: estimates of both forms' time in microseconds.  The one-launch form runs rounds of two workgroups per CU
-// (F(6x6): one), each a fixed part and its steps; up to one workgroup per CU the steps go faster.  Measured: 16 -> 208
-// channels, 432 tiles of F(4x4): 9.9 us (estimate 9.9), 32 -> 86, 1290: 15.3 (17.7), 39 -> 48, 16 224: 98 (94), 100 -> 150, 594: 35
-// (38); F(2x2): 64 -> 64, 784: 8.7 (8.8), 256 -> 256, 49: 23 (23); F(6x6): 16 -> 9, 3 600: 13.6 (14), 76 -> 48, 12: 36 (38).  The
-// four stages pass U, V and M through memory and fill and drain the chip three times: 22 us (estimate 18), 27 (23), 131
-// (114), 29 (29); 14 (14), 15 (14); 32 (27), 16 (14).
-bool fused_small_preferred(const Geo &g)
+// Small enough: estimates of both forms' time in microseconds, fitted to 2400 layers of up to 50 000 items: for the stages so that
+// 85-95 % of the layers take longer, for this form so that 90 % take less.  The four stages: a fixed part and what V, M (padded, and
+// once more the filters that exist) and D take through the caches (MB); the input gradient's filter transform is a launch of its
+// own.  This form: up to one workgroup per CU a fixed part and its steps; beyond, rounds of two workgroups per CU (F(6x6): one),
+// between as many as they fill and as many as they begin, each a fixed part and its steps; and Y.  Transformed filters are fetched
+// value by value.  Of 1500 other layers that the rule sends here none took longer than the four stages.
+// Measured, stages / this form: F(2x2), 64 -> 64 channels at 56 x 56: 13.9 / 8.8 us (from U 13.0 / 9.6); 5 -> 98 at 53 x 53, N = 19, 6062
+// items: 46 / 51 (45 / 54); 2 -> 129 at 197 x 11, N = 24, 6615 items: 47 / 57 (45 / 61); 31 -> 22 at 120 x 120, N = 13: 63 / 70 (63 /
+// 78); 109 -> 44 at 17 x 17: 12.1 / 12.1 (11.6 / 13.0); F(4x4), 32 -> 16 at 84 x 84, N = 6: 22.1 / 10.8; F(6x6), 39 -> 16 at 150 x 147,
+// N = 4: 34 / 23; 5 -> 20 at 64 x 97, N = 49: 49 / 59.
+bool fused_small_preferred(const Geo &g, int filters)
 {
     if (!fused_small_eligible(g)) return false;
     const double items = (double)((g.P + 15) / 16) * ((g.K + 15) / 16), steps = (g.C + sm_cs(g.m) - 1) / sm_cs(g.m);
-    const double bytes = 8.0 * g.a2 * ((double)g.Cp + g.Kp) * g.Pp;
-    const double stages = bytes / 5e6 + 9.0 > 14.0 ? bytes / 5e6 + 9.0 : 14.0;
-    const auto rounds = [&](int resident) { return (double)(long long)((items + resident - 1) / resident); };
-    double us;
-    if (g.m == 6)
-        us = 3.0 + rounds(256) * (5.0 + 3.0 * steps);
-    else if (items <= 256)
-        us = g.m == 4 ? 5.5 + 1.55 * steps : 4.0 + 1.2 * steps;
-    else
-        us = g.m == 4 ? 5.5 + rounds(512) * (3.0 + 2.35 * steps) : 4.0 + rounds(512) * (2.0 + 1.75 * steps);
-    return us < 0.9 * stages;
+    const double row = 4e-6 * g.a2 * g.Pp, D = 4e-6 * g.N * g.C * g.H * g.W, Y = 4e-6 * g.N * g.K * g.Ho * g.Wo;
+    const bool u = filters == WINO_FILTERS_U;
+    const double resident = g.m == 6 ? 256.0 : 512.0;
+    const double rounds = 0.5 * (items / resident + (double)(long long)((items + resident - 1.0) / resident));
+    const double past = row * ((double)g.Cp + g.Kp) > 256.0 ? row * ((double)g.Cp + g.Kp) - 256.0 : 0.0;     // MB that the last-level cache does not hold
+    double stages, us;
+    if (g.m == 2) {
+        stages = 8.8 + row * (0.09 * g.Cp + 0.1 * g.Kp + 0.22 * g.K) + 1.15 * D + 0.1 * past;
+        us = items <= 256 ? 4.8 + (u ? 1.2 : 1.0) * steps + 0.7 * Y : 3.5 + rounds * (1.8 + (u ? 2.1 : 1.78) * steps) + 0.26 * Y;
+    } else if (g.m == 4) {
+        stages = 10.2 + row * (0.08 * g.Cp + 0.13 * g.Kp + 0.27 * g.K) + 0.88 * D + 0.1 * past;
+        us = items <= 256 ? 5.5 + 1.5 * steps + 0.35 * Y : 4.1 + rounds * ((u ? 3.4 : 2.7) + 2.5 * steps) + 0.24 * Y;
+    } else {
+        stages = 13.2 + row * (0.16 * g.Cp + 0.055 * g.Kp + 0.43 * g.K) + 0.58 * D + 0.1 * past;
+        us = items <= 256 ? 7.1 + 3.2 * steps + 0.65 * Y : 6.6 + rounds * (3.5 + 3.4 * steps) + 0.54 * Y;
+    }
+    if (filters == WINO_FILTERS_G_BWD) stages += 2.5;
+    return us < stages;
 }
 
 template <int M>

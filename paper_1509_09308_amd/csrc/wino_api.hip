@@ -265,7 +265,7 @@ static bool fused_y_ok(const Geo &g, int y_dt) { return y_dt == WINO_F32 || g.dt
 
 // What WINO_FLAG_AUTO runs: the one-kernel path, else the small-layer kernel, else the four stages.
 static bool auto_fused(const Geo &g, int y_dt) { return fused_y_ok(g, y_dt) && fused_preferred(g); }
-static bool auto_small(const Geo &g, int y_dt) { return y_dt == WINO_F32 && fused_small_preferred(g); }   // (not auto_fused)
+static bool auto_small(const Geo &g, int y_dt, int filters) { return y_dt == WINO_F32 && fused_small_preferred(g, filters); }   // (not auto_fused)
 
 int wino_conv2d_variant(int N, int C, int H, int W, int K, int pad, int m, int dt, int y_dt, unsigned flags)
 {
@@ -286,7 +286,7 @@ int wino_small_layer(int N, int C, int H, int W, int K, int pad, int m, int dt, 
     const int st = make_geo(N, C, H, W, K, pad, m, dt, &g);
     if (st != WINO_OK) return -st;
     if (bad_dtype(y_dt) || filters < WINO_FILTERS_G || filters > WINO_FILTERS_G_BWD) return -WINO_EINVAL;
-    return !auto_fused(g, y_dt) && auto_small(g, y_dt);
+    return !auto_fused(g, y_dt) && auto_small(g, y_dt, filters);
 }
 
 int wino_one_kernel_plan(int N, int C, int H, int W, int K, int pad, int m, int dt, int out[32])
@@ -324,7 +324,7 @@ static int run_layer(const Geo &g, int y_dt, const void *D, const void *G, const
         return e == hipSuccess ? WINO_OK : hip_fail(e);
     }
     if (flags == WINO_FLAG_AUTO && auto_fused(g, y_dt)) flags = WINO_FLAG_FUSED;
-    if (flags == WINO_FLAG_AUTO && auto_small(g, y_dt)) {
+    if (flags == WINO_FLAG_AUTO && auto_small(g, y_dt, U != nullptr ? WINO_FILTERS_U : bwd ? WINO_FILTERS_G_BWD : WINO_FILTERS_G)) {
         e = launch_fused_small(g, (const float *)D, (const float *)G, (const float *)U, (float *)Y, bwd, s);
         return e == hipSuccess ? WINO_OK : hip_fail(e);
     }

@@ -69,7 +69,7 @@ hipError_t launch_fused_f2(const Geo &g, const float *D, const float *G, float *
                            size_t workspace_bytes, bool bwd, hipStream_t s);
 // fused_small.hip: all four loops in one launch for small layers (fp32; G or U given).
 bool fused_small_eligible(const Geo &g);
-bool fused_small_preferred(const Geo &g);
+bool fused_small_preferred(const Geo &g, int filters);      // WINO_FILTERS_...
 hipError_t launch_fused_small(const Geo &g, const float *D, const float *G, const float *U, float *Y, bool bwd, hipStream_t s);
 bool prep_eligible(const Geo &g);
 hipError_t launch_prep(const Geo &g, const void *G, void *U, const void *D, void *V, hipStream_t s);

@@ -233,6 +233,12 @@ def test_small_layer_query_host_only(L):
     assert not w.wino_small_layer(1, 128, 112, 112, 128, 1, 4)                   # the four stages
     assert not w.wino_small_layer(64, 256, 56, 56, 256, 1, 4)                    # one kernel
     assert not w.wino_small_layer(1, 8, 9, 5, 16, 1, 4)                          # narrower than a tile
+    # layers that the four stages run faster: many items of one step each, many steps of few items
+    for m, shape in ((2, (19, 5, 53, 53, 98)), (2, (24, 2, 197, 11, 129)), (2, (1, 109, 17, 17, 44)), (2, (13, 31, 120, 120, 22)), (6, (49, 5, 64, 97, 20))):
+        assert not any(w.wino_small_layer(*shape, 1, m, filters=f) for f in (w.FILTERS_G, w.FILTERS_U)), shape
+    # transformed filters are fetched value by value; the input gradient's stages have one launch more
+    assert w.wino_small_layer(3, 97, 57, 58, 20, 1, 2) and not w.wino_small_layer(3, 97, 57, 58, 20, 1, 2, filters=w.FILTERS_U)
+    assert w.wino_small_layer(23, 3, 172, 18, 50, 1, 6, filters=w.FILTERS_G_BWD) and not w.wino_small_layer(23, 3, 172, 18, 50, 1, 6)
     assert L.wino_small_layer(1, 32, 56, 56, 32, 1, 2, 1, 0, 0) == 0             # fp16 storage
     assert L.wino_small_layer(1, 32, 56, 56, 32, 1, 2, 0, 1, 0) == 0             # fp16 Y
     assert L.wino_small_layer(1, 32, 56, 56, 32, 1, 2, 0, 2, 0) == -w.WINO_EINVAL
