@@ -331,3 +331,17 @@ def test_one_kernel_plan_covers_every_item_once_and_shares_fit():
     assert L.wino_one_kernel_plan(2, 8, 8, 10, 8, 1, 4, 0, out) == -w.WINO_EUNSUPPORTED     # W % 4 != 0
     assert L.wino_one_kernel_plan(2, 8, 8, 8, 8, 1, 4, 1, out) == -w.WINO_EUNSUPPORTED      # fp16 storage
     assert L.wino_one_kernel_plan(0, 8, 8, 8, 8, 1, 4, 0, out) == -w.WINO_EINVAL
+
+
+def test_current_stream_without_its_raw_handle(monkeypatch):
+    """The raw handle of the current stream comes from a function that torch does not document: without it, the public one."""
+    import types
+    import torch
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x1230))
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 1)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 0x4560 + device, raising=False)
+    assert binding._stream(None).value == 0x4561
+    assert binding._stream(types.SimpleNamespace(cuda_stream=0x7890)).value == 0x7890
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    assert binding._stream(None).value == 0x1230
+    assert binding._stream(types.SimpleNamespace(cuda_stream=0x7890)).value == 0x7890
