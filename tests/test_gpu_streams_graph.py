@@ -14,9 +14,13 @@ from gpu_util import TOL, check_close, require_gpu, to_gpu
 pytestmark = pytest.mark.gpu
 
 
-def test_short_entry_point_on_overlapping_streams():
+@pytest.mark.parametrize("shapes,small", [
+    ([(2, 32, 28, 28, 48), (1, 64, 56, 56, 64), (3, 16, 14, 14, 40), (2, 24, 20, 36, 24)], 2),    # two do without a workspace
+    ([(2, 40, 28, 28, 48), (1, 64, 56, 56, 64), (3, 48, 14, 14, 40), (2, 56, 20, 36, 24)], 0),    # every stream needs its own
+])
+def test_short_entry_point_on_overlapping_streams(shapes, small):
     torch, w = require_gpu()
-    shapes = [(2, 32, 28, 28, 48), (1, 64, 56, 56, 64), (3, 16, 14, 14, 40), (2, 24, 20, 36, 24)]
+    assert sum(w.wino_small_layer(*s, 1, 4) for s in shapes) == small
     streams = [torch.cuda.Stream() for _ in shapes]
     data = [synth.make_layer(*s, seed=900 + i) for i, s in enumerate(shapes)]
     dev = [(to_gpu(D), to_gpu(G)) for D, G in data]

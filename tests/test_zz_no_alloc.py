@@ -38,6 +38,17 @@ def test_noalloc_matches_allocating_entry_point_on_two_calls_in_a_row(m):
     _one_call(torch, w, (1, 128, 112, 112, 128), 4, seed=707)      # a VGG layer at batch 1 (37 MB of workspace)
 
 
+@pytest.mark.parametrize("m", [2, 4])
+def test_noalloc_second_call_in_the_same_workspace(m):
+    """Two calls whose U, V and M lie in the shared buffer (small layers do without), the second smaller in every extent and
+    ragged: its padding lies where the first call's values were."""
+    torch, w = require_gpu()
+    for shape in ((2, 160, 28, 56, 96), (1, 115, 13, 27, 40)):
+        N, C, H, W, K = shape
+        assert not w.wino_small_layer(N, C, H, W, K, 1, m) and w.wino_conv2d_variant(N, C, H, W, K, 1, m) == w.FLAG_UNFUSED
+        _one_call(torch, w, shape, m, seed=709 + C + m)
+
+
 def test_noalloc_rejects_what_does_not_fit():
     torch, w = require_gpu()
     N, C, H, W, K = 64, 64, 224, 224, 64                            # 3.7 GB of workspace
