@@ -56,6 +56,11 @@ def test_ragged_and_degenerate_shapes(m, shape):
     assert Y.shape == ref.shape
     e, worst = check_close(Y, ref, TOL[("f32", m)], "ragged %s m=%d" % (shape, m), m)
     print("ragged %s m=%d rel err %.3e max abs err %.3e" % (shape, m, e, worst))
+    # most of these are small layers, which the library runs in one launch: the four stages as well, from G and from U
+    d, g = to_gpu(D), to_gpu(G)
+    for kw in ({"G": g}, {"U": w.wino_filter_transform(g, m), "K": K}):
+        Y = w.wino_conv2d_fwd_ex(d, pad=pad, m=m, flags=w.FLAG_UNFUSED, **kw).cpu().numpy()
+        check_close(Y, ref, TOL[("f32", m)], "ragged %s m=%d, four stages" % (shape, m), m)
 
 
 @pytest.mark.parametrize("shape", [(1, 1024, 14, 14, 1024, 1), (2, 768, 9, 23, 40, 1), (1, 48, 7, 250, 1030, 0)])

@@ -115,6 +115,9 @@ def test_f2x2_delta_filter_end_to_end_bitwise(shape):
     Y = w.wino_conv2d_fwd(to_gpu(D), to_gpu(G), pad=1, m=2)
     torch.cuda.synchronize()
     assert np.array_equal(Y.cpu().numpy(), D)
+    # (a small layer, which the library runs in one launch: the four stages as well)
+    Y = w.wino_conv2d_fwd_ex(to_gpu(D), G=to_gpu(G), pad=1, m=2, flags=w.FLAG_UNFUSED)
+    assert np.array_equal(Y.cpu().numpy(), D)
 
 
 @pytest.mark.parametrize("m", [2, 4, 6])
@@ -124,14 +127,15 @@ def test_integer_layer_end_to_end_exact(m):
     constants (amplified, for F(6x6), by the larger entries of its matrices)."""
     torch, w = require_gpu()
     D, G = synth.make_integer_layer(2, 6, 18, 22, 7, seed=3, gscale=4.0 if m == 2 else 576.0)
-    Y = w.wino_conv2d_fwd(to_gpu(D), to_gpu(G), pad=1, m=m).cpu().numpy()
     ref = direct.conv2d_fwd(D, G, pad=1)
-    if m == 2:
-        assert np.array_equal(Y.astype(np.float64), ref)
-    else:
-        e = rel_err(Y, ref)
-        print("integer layer m=%d rel err %.3e" % (m, e))
-        assert e < (1e-6 if m == 4 else 1e-5)
+    for Y in (w.wino_conv2d_fwd(to_gpu(D), to_gpu(G), pad=1, m=m).cpu().numpy(),        # (one launch)
+              w.wino_conv2d_fwd_ex(to_gpu(D), G=to_gpu(G), pad=1, m=m, flags=w.FLAG_UNFUSED).cpu().numpy()):
+        if m == 2:
+            assert np.array_equal(Y.astype(np.float64), ref)
+        else:
+            e = rel_err(Y, ref)
+            print("integer layer m=%d rel err %.3e" % (m, e))
+            assert e < (1e-6 if m == 4 else 1e-5)
 
 
 @pytest.mark.parametrize("shape", [(1, 3, 20, 20, 8, 3, 3, 1, 1), (2, 3, 17, 23, 5, 5, 5, 2, 2),
