@@ -211,7 +211,8 @@ def test_layer_single_value_in_a_shared_item():
 
 # ---- filter gradient ----------------------------------------------------------------------------
 
-WGRAD = [(5, 70, 9, 20, 130), (3, 320, 28, 28, 288)]
+WGRAD = [(5, 70, 9, 20, 130), (3, 320, 28, 28, 288),
+         (220, 40, 13, 13, 70), (220, 40, 13, 14, 70), (220, 40, 13, 15, 70)]      # W % 4 = 1, 2, 3: 110 MB and more transformed
 
 
 @pytest.mark.parametrize("N,C,H,W,K", WGRAD)
@@ -227,17 +228,23 @@ def test_filter_gradient_scaled(N, C, H, W, K, scale):
 
 @pytest.mark.parametrize("value", [np.inf, FLT_MAX, np.nan])
 @pytest.mark.parametrize("which", ["data", "error"])
-def test_filter_gradient_single_values(value, which):
+@pytest.mark.parametrize("shape,at", [((5, 70, 9, 20, 130), (4, 7)),
+                                      # W % 4 = 1, 2, 3 in one kernel (110 MB and more transformed): the last column of a row, the
+                                      # first of the next
+                                      ((220, 40, 13, 13, 70), (4, 12)), ((220, 40, 13, 13, 70), (5, 0)),
+                                      ((220, 40, 13, 14, 70), (4, 13)), ((220, 40, 13, 14, 70), (5, 0)),
+                                      ((220, 40, 13, 15, 70), (4, 14)), ((220, 40, 13, 15, 70), (12, 14))])
+def test_filter_gradient_single_values(value, which, shape, at):
     torch, w = require_gpu()
-    N, C, H, W, K = 5, 70, 9, 20, 130
+    N, C, H, W, K = shape
     rng = np.random.default_rng(7)
     D = rng.standard_normal((N, C, H, W)).astype(np.float32)
     E = (rng.standard_normal((N, K, H, W)) * 2.0 ** -6).astype(np.float32)
     if which == "error":
         D, E = (D * 2.0 ** -6).astype(np.float32), (E * 2.0 ** 6).astype(np.float32)
     plain = w.wino_conv2d_bwd_filter(to_gpu(D), to_gpu(E), pad=1).cpu().numpy()
-    line = 66
-    (D if which == "data" else E)[3, line, 4, 7] = value
+    line = min(66, C - 4) if which == "data" else 66
+    (D if which == "data" else E)[(3, line) + at] = value
     dG = w.wino_conv2d_bwd_filter(to_gpu(D), to_gpu(E), pad=1).cpu().numpy()
     rest = np.ones(dG.shape, dtype=bool)
     if which == "data":
@@ -246,15 +253,15 @@ def test_filter_gradient_single_values(value, which):
         rest[line] = False
     assert (dG[rest] == plain[rest]).all()
     Bt, Gm, At = (np.array(x, dtype=np.float64) for x in wg.matrices(3, 2))
-    d = np.zeros((N, C, H + 3, W + 2))
+    d = np.zeros((N, C, H + 3, W + 3))
     d[:, :, 1:H + 1, 1:W + 1] = D
-    e = np.zeros((N, K, H + 1, W))
-    e[:, :, :H] = E
+    e = np.zeros((N, K, H + 1, W + 1))
+    e[:, :, :H, :W] = E
     if which == "data":
         d = d[:, line:line + 1]
     else:
         e = e[:, line:line + 1]
-    bx, by = (H + 1) // 2, W // 2
+    bx, by = (H + 1) // 2, (W + 1) // 2
     tiles = np.stack([d[:, :, 2 * x:2 * x + 4, 2 * y:2 * y + 4] for x in range(bx) for y in range(by)])
     blocks = np.stack([e[:, :, 2 * x:2 * x + 2, 2 * y:2 * y + 2] for x in range(bx) for y in range(by)])
     with np.errstate(invalid="ignore"):

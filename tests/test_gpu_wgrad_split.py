@@ -31,6 +31,37 @@ def test_wgrad_in_one_kernel(N, C, H, W, K):
     check_close(dG, direct.conv2d_bwd_filter(D, E, pad=1), 1e-5, "%s" % ((N, C, H, W, K),))
 
 
+def inside(torch, x):
+    """`x` with NaNs right in front of it and right behind."""
+    room = torch.full((x.numel() + 8,), float("nan"), device="cuda")
+    t = room[4:4 + x.numel()].view(x.shape)
+    t.copy_(x)
+    return t
+
+
+def gradient(torch, w, D, E):
+    """The gradient with a workspace of NaNs, and whether one kernel formed it: the separate stages write all of the workspace
+    but what alignment leaves between their tensors."""
+    (N, C, H, W), K = D.shape, E.shape[1]
+    need = w.wino_bwd_filter_workspace_bytes(N, C, H, W, K)
+    ws = torch.full((need // 4,), float("nan"), device="cuda")
+    dG = w.wino_conv2d_bwd_filter(D, E, pad=1, workspace=ws.view(torch.uint8))
+    return dG, int(torch.isnan(ws).sum()) > 1024
+
+
+@pytest.mark.parametrize("N,C,H,W,K", [(30, 64, 30, 30, 64), (47, 112, 11, 11, 390)])
+def test_small_layers_of_any_width_in_stages(N, C, H, W, K):
+    torch, w = require_gpu()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(N + C + H + W + K)
+    D, E = (inside(torch, torch.randn((N, x, H, W), generator=gen, device="cuda")) for x in (C, K))
+    dG, one = gradient(torch, w, D, E)
+    assert not one
+    ks, cs = [0, K // 2, K - 1], [0, C // 2, C - 1]
+    ref = direct.conv2d_bwd_filter(D[:, cs].cpu().numpy(), E[:, ks].cpu().numpy(), pad=1)
+    check_close(dG[ks][:, cs].cpu().numpy(), ref, 2e-6, "%s" % ((N, C, H, W, K),))
+
+
 @pytest.mark.parametrize("N,C,H,W,K", [
     (600, 33, 7, 5, 70),         # rows of three blocks: the last pair has one, of one column
     (700, 64, 8, 6, 64),         # of two columns
@@ -41,25 +72,26 @@ def test_wgrad_in_one_kernel(N, C, H, W, K):
 ])
 def test_wgrad_in_one_kernel_any_width(N, C, H, W, K):
     """Widths that 4 does not divide, from 64 MB of transformed operands on (smaller layers take the separate stages).
-    What lies behind D and E must not matter: rows end where the next one, the next image or nothing begins."""
+    What lies before and behind D and E must not matter: rows end where the next one, the next image or nothing begins.
+    Bound: as for the small layers on the separate stages, twice the largest that is measured (9.8e-7)."""
     torch, w = require_gpu()
     gen = torch.Generator(device="cuda")
     gen.manual_seed(N + C + H + W + K)
-    D, E = (torch.randn((N, x, H, W), generator=gen, device="cuda") for x in (C, K))
-    need = w.wino_bwd_filter_workspace_bytes(N, C, H, W, K)
-    ws = torch.full((need // 4 + 1,), float("nan"), device="cuda").view(torch.uint8)[:need]
-    dG = w.wino_conv2d_bwd_filter(D, E, pad=1, workspace=ws)
+    D, E = (inside(torch, torch.randn((N, x, H, W), generator=gen, device="cuda")) for x in (C, K))
+    dG, one = gradient(torch, w, D, E)
+    assert one
     assert bool(torch.isfinite(dG).all())
     ks, cs = sorted({0, K // 2, K - 1}), sorted({0, C // 2, C - 1})
     ref = direct.conv2d_bwd_filter(D[:, cs].cpu().numpy(), E[:, ks].cpu().numpy(), pad=1)
-    check_close(dG[ks][:, cs].cpu().numpy(), ref, 1e-5, "%s" % ((N, C, H, W, K),))
+    check_close(dG[ks][:, cs].cpu().numpy(), ref, 2e-6, "%s" % ((N, C, H, W, K),))
 
 
-def test_rounding_does_not_add_up_over_shares():
+@pytest.mark.parametrize("H,W", [(112, 112), (111, 113), (112, 110), (112, 111)])
+def test_rounding_does_not_add_up_over_shares(H, W):
     """Positive data: every product of the first component grows the sums, the case in which a rounding that always goes
     one way shows most.  fp32 sums of n terms rounded to nearest stay within sqrt(n) 2^-24 of a share's sum."""
     torch, w = require_gpu()
-    N, C, H, W, K = 4, 64, 112, 112, 64
+    N, C, K = 4, 64, 64
     rng = np.random.default_rng(1)
     D = rng.uniform(0.0, 1.0, (N, C, H, W)).astype(np.float32)
     E = rng.uniform(0.0, 1.0, (N, K, H, W)).astype(np.float32)
@@ -72,7 +104,11 @@ def test_rounding_does_not_add_up_over_shares():
 
 
 @pytest.mark.parametrize("data", ["positive", "near one", "normal"])
-@pytest.mark.parametrize("N,C,H,K", [(10, 1030, 28, 1030),      # one share of 1960 blocks
+@pytest.mark.parametrize("N,C,H,K", [(64, 512, 14, 512),        # widths that 4 does not divide: eight shares of 448 blocks
+                                     (30, 256, 93, 250),        # ... 32 shares of 2128, set aside on the way
+                                     (30, 256, 94, 250),
+                                     (32, 256, 91, 250),
+                                     (10, 1030, 28, 1030),      # one share of 1960 blocks
                                      (32, 1030, 28, 1030),      # 6272 blocks in four shares
                                      (32, 640, 28, 640),        # five shares of 1264
                                      (66, 256, 112, 256)])      # 32 shares of 6480 blocks, set aside on the way
@@ -95,7 +131,7 @@ def test_long_shares_are_as_precise_as_fp32(N, C, H, K, data):
     got = dG[ks][:, cs].cpu().numpy()
     # the same blocks, one after the other, in fp32: every component is a chain of multiply-adds (rounded twice)
     Wt, V = (x.astype(np.float32) for x in (wg.wgrad_error_transform(e), wg.wgrad_data_transform(d)))
-    assert Wt.shape[3] == N * (H // 2) ** 2
+    assert Wt.shape[3] == N * ((H + 1) // 2) ** 2
     M = np.zeros((4, 4, len(ks), len(cs)), dtype=np.float32)
     for b in range(Wt.shape[3]):
         M += Wt[..., b][:, :, :, None] * V[..., b][:, :, None, :]
