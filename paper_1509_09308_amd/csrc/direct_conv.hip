@@ -236,10 +236,10 @@ static bool direct_mfma_ok(int C, int H, int W, int K, int R, int S, int pad, in
 // chain, set the pace of CUs with two workgroups.  The check is three instructions: the part of a window inside the image
 // is a rectangle of (u, v), its corners packed in 16-bit halves.
 // One thread per pixel and 16 filters on the vector ALUs / scalars counted up / this: 64 -> 128 channels at 56 x 56, stride
-// 2, N = 16: 151 / 34 / 29 us in fp32, 127 / 28 / 21 in fp16 (N = 1, fp32: 115 / 18 / 15); 512 -> 512 at 14 x 14, stride 2,
-// N = 1: 807 / 99 / 72; 1 x 1, 256 -> 512 at 28 x 28, stride 2, N = 8: 120 / 15.4 / 14.8; 7 x 7, 3 -> 64 at 224 x 224, stride
-// 2, N = 8: 84 / 36 / 28; 5 x 5, 48 -> 128 at 27 x 27, N = 4: 210 / 31 / 23; 512 -> 512 at 28 x 28, stride 2, N = 64: - / 659
-// / 532.  Error against float64: 25-60 % less than the first form's.
+// 2, N = 16: 151 / 34 / 29 us in fp32 (call after call into one output 26), 127 / 28 / 22 in fp16 (N = 1, fp32: 115 / 18 / 16);
+// 512 -> 512 at 14 x 14, stride 2, N = 1: 807 / 99 / 72; 1 x 1, 256 -> 512 at 28 x 28, stride 2, N = 8: 120 / 15.4 / 14.9; 7 x 7,
+// 3 -> 64 at 224 x 224, stride 2, N = 8: 84 / 36 / 28; 5 x 5, 48 -> 128 at 27 x 27, N = 4: 210 / 31 / 24; 512 -> 512 at 28 x 28,
+// stride 2, N = 64: - / 659 / 541.  Error against float64: 25-60 % less than the first form's.
 constexpr int DG_STEP = 16;
 
 typedef _Float16 halfx8_dc __attribute__((ext_vector_type(8)));

@@ -405,8 +405,9 @@ bool fused_preferred(const Geo &g)
     if (!fused_eligible(g)) return false;
     const long long blocks = (long long)((g.P + FP - 1) / FP) * ((g.K + FK - 1) / FK);
     if (g.dt == WINO_F16) {
-        // 256 -> 256 channels at 56 x 56: N = 32 (784 items of fused_split.hip) 158 against 195 us, N = 16 (392 items) 88
-        // against 87; 256 -> 512 at 28 x 28, N = 32: 95 against 80
+        // 256 -> 256 channels at 56 x 56: N = 32 (784 items of fused_split.hip) 139 against 179 us, N = 16 (392 items) 76
+        // against 84; 256 -> 512 at 28 x 28, N = 32: 83 against 72.  (The line at 512 items is from before the inverse transform
+        // went through in overlapping pieces, 88 against 87 then.)
         if (fused_split_f16_eligible(g) && (long long)g.K * g.C <= 130LL * (g.K + g.C) && fused_split_items(g) >= 512) return true;
         return (long long)g.K * g.C <= 100LL * (g.K + g.C) && (long long)((g.P + 31) / 32) * ((g.K + 63) / 64) >= 256;
     }
@@ -416,7 +417,7 @@ bool fused_preferred(const Geo &g)
         // of 512 -> 512 channels at 28 x 28: N = 16 124 us, estimate 129; N = 64 506, estimate 507; F(2x2,3x3), 14 x 14,
         // N = 64: 217, estimate 221).  Below 160 items three CUs of eight have nothing to do and the two are within a few
         // per cent of each other for 64 and 128 channels, the four stages ahead for more (F(2x2,3x3), 512 -> 512 at
-        // 14 x 14, N = 24, 152 items: 105 against 89 us).
+        // 14 x 14, N = 24, 152 items: 94 against 91 us, 99 when the line was drawn).
         const double flops = 2.0 * g.a2 * g.Kp * g.Cp * g.Pp;
         const double bytes = 4.0 * ((double)g.N * g.C * g.H * g.W + (double)g.N * g.K * g.Ho * g.Wo +
                                     2.0 * g.a2 * ((double)g.Cp + g.Kp) * g.Pp);

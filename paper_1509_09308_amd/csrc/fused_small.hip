@@ -329,7 +329,7 @@ bool fused_small_eligible(const Geo &g)
     return ((long long)g.P + 15) / 16 * ((g.K + 15) / 16) <= 0x7fffffffLL;
 }
 
-// Small enough: estimates of both forms' time in microseconds, fitted to 2400 layers of up to 50 000 items: for the stages so that
+// Small enough: estimates of both forms' time in microseconds, fitted to 2300 layers of up to 50 000 items: for the stages so that
 // 85-95 % of the layers take longer, for this form so that 90 % take less.  The four stages: a fixed part and what V, M (padded, and
 // once more the filters that exist) and D take through the caches (MB); the input gradient's filter transform is a launch of its
 // own.  This form: up to one workgroup per CU a fixed part and its steps; beyond, rounds of two workgroups per CU (F(6x6): one),

@@ -1009,9 +1009,9 @@ bool fused_split_eligible(const Geo &g)
         fs_part_offset(g) > (size_t)g.a2 * 4 * ((size_t)g.Cp * g.Kp + (size_t)(g.Cp + g.Kp) * g.Pp))
         return false;
     // Half of the CUs at least: with 98 to 104 items the 16-tile items of fused_wide.hip, twice as many, are 8-31 %
-    // faster (128 -> 128 channels at 112 x 112, N = 2: 37 against 42 us; 256 -> 256 at 56 x 56, N = 4: 59 against 72),
-    // with 148 they are 11-29 % slower (64 -> 128 at 112 x 112, N = 3: 34 against 30 us; 128 -> 128 at 56 x 56, N = 12:
-    // 56 against 45; 256 -> 256 at 56 x 56, N = 6: 94 against 73).
+    // faster (128 -> 128 channels at 112 x 112, N = 2: 37 against 42 us; 256 -> 256 at 56 x 56, N = 4: 59 against 72; both
+    // before the inverse transform went through in overlapping pieces), with 148 they are slower (64 -> 128 at 112 x 112, N
+    // = 3: 34 against 29 us; 128 -> 128 at 56 x 56, N = 12: 56 against 43; 256 -> 256 at 56 x 56, N = 6: 94 against 68).
     const long long items = fs_n_tb(g) * fs_n_kb(g);
     return items <= 0x7fffffffLL && items >= 128;
 }
@@ -1020,9 +1020,10 @@ long long fused_split_items(const Geo &g) { return fs_n_tb(g) * fs_n_kb(g); }
 
 // Estimate of the launch's time in microseconds, for the choice between it and the four stages: rounds of the slowest
 // XCD, each a fixed part (opening an item, inverse transform, stores) and its channel steps, and the two launches.  Fitted
-// for F(4x4,3x3), N = 64, to 64 -> 64 channels at 112 x 112 (169 us), 256 -> 256 at 56 x 56 (479) and 512 -> 512 at 28 x 28
-// (485); for F(2x2,3x3) to 512 -> 512 at 14 x 14 (N = 64: 206 us, estimate 202; N = 32: 105, 105; four stages 227 and 120),
-// 512 -> 512 at 28 x 28, N = 8 (105, 105; four stages 120) and 256 -> 256 at 56 x 56, N = 4 (63, 64; 78).
+// before the inverse transform went through in overlapping pieces; the kernel takes 0.83 - 0.96 of it since.  Time and estimate,
+// us: F(4x4,3x3), N = 64, 64 -> 64 channels at 112 x 112 169, 176; 256 -> 256 at 56 x 56 460, 484 (N = 16: 134, 162); 512 -> 512 at
+// 28 x 28 449, 474; F(2x2,3x3), 512 -> 512 at 14 x 14, N = 64 190, 202, N = 32 98, 105; 512 -> 512 at 28 x 28, N = 8 99, 105; 256 ->
+// 256 at 56 x 56, N = 4 56, 64.  (64 -> 64 at 224 x 224, bound by its stores: 651, 608.)
 double fused_split_us(const Geo &g)
 {
     const double item_us = g.m == 4 ? 6.4 : 14.0, step_us = g.m == 4 ? 4.4 : 2.6;

@@ -262,11 +262,15 @@ __global__ __launch_bounds__(256) void wgrad_gemm_kernel(const float *__restrict
 // 8 are free of bank conflicts.
 // Bound by vector instructions -- split 350, transform and requests 270 per SIMD and step -- and by energy: 4 100 cycles a
 // step at 2 GHz (5 000 at 2.4 with four more requests per step, for the outer columns, and with products and loops in the
-// addresses: 256 -> 256 channels at 56 x 56, N = 64: 1 264 us with fp32 matrix instructions, 796 so, 758 now; 512 -> 512 at 28 x
+// addresses: 256 -> 256 channels at 56 x 56, N = 64: 1 264 us with fp32 matrix instructions, 816 so, 782 now; 512 -> 512 at 28 x
 // 28, N = 16: 223 -> 213).  Raw data of two steps in flight took another 8 % of the cycles and no time.
 // Loads are unconditional from clamped (valid) addresses; what falls outside the image, past the last block or past K / C
-// is zeroed afterwards, so the loop has no branches and no divisions.  Needs W >= 4 (16-byte loads) and tensors
-// of fewer than 2^31 elements (32-bit offsets).  Partial M per share as above.
+// is zeroed afterwards, in branches that most steps do not take, like the moving up of a row's last pair.  The loop has no
+// divisions.  Needs W >= 4 (16-byte loads) and tensors of fewer than 2^31 elements (32-bit offsets).  Partial M per share as above.
+// Precision: products have six of nine parts (bf16x3.h), sums are those of fp32 instructions but shorter.  Error against
+// float64, separate stages / this, 36 layers with W % 4 != 0: N(0,1) data 5.1e-7 - 2.8e-6 / 2.8e-7 - 1.2e-6, smaller in each (0.28
+// - 0.84 of it); behind a ReLU 0.29 - 0.84; uniform in [0,1] 0.20 - 1.01; between 1 and 1 + 2^-7, where all that is left out has one
+// sign, 0.21 - 1.08 (1.08: 7.2e-8 / 7.7e-8).
 constexpr int WF_BK = 8, WF_T = 512;
 constexpr int WF_OP = 16 * 64 * WF_BK;                       // floats of one operand of a step
 typedef float floatx4_any __attribute__((ext_vector_type(4), aligned(4)));
@@ -869,9 +873,12 @@ static void wgrad_shape(const WgradGeo &g, int *bm, int *bn, int *shares, int *n
 }
 
 // Where the one-kernel form applies: block pairs in 16-byte loads, 32-bit offsets.  With W % 4 != 0 also from 64 MB of W and
-// V on (32 MB with 2^17 products per block), below which the separate stages' many small workgroups win: 64 -> 64 channels
-// at 30 x 30, N = 30: 39 against 46 us; 112 -> 390 at 11 x 11, N = 47: 60 against 62; 16 -> 144 at 65 x 65, N = 5: 58 against 39;
-// 512 -> 512 at 14 x 14, N = 16: 86 against 79; 512 -> 32 at 91 x 91, N = 23: 1 146 against 407.
+// V on (32 MB with 2^17 products per block), below which the separate stages' many small workgroups win.  Stages / one kernel,
+// above: 512 -> 512 channels at 14 x 14, N = 16 (49 MB) 86 / 78 us; 561 -> 850 at 10 x 10, N = 30 (66 MB) 161 / 151; 401 -> 436 at 54 x
+// 54, N = 2 (78 MB) 128 / 92; 512 -> 32 at 91 x 91, N = 23 1 131 / 373.  Below: 64 -> 64 at 30 x 30, N = 30 (53 MB) 39 / 44; 112 -> 390 at
+// 11 x 11, N = 47 (56 MB) 60 / 62; 45 -> 55 at 11 x 70, N = 11 (18 MB) 31 / 37; 676 -> 800 at 9 x 9, N = 6 (15 MB) 59 / 62; but also 16 ->
+// 144 at 65 x 65, N = 5 (52 MB) 58 / 40 and 113 -> 186 at 73 x 14, N = 10 (51 MB) 59 / 46: of 40 layers drawn between a fifth of the
+// limits and them one kernel was faster for half, up to 1.3 times; of 40 on both sides of the limits no layer above them is slower.
 static bool wgrad_fused_ok(const WgradGeo &g)
 {
     if (g.W < 4) return false;
