@@ -139,3 +139,57 @@ def test_long_shares_are_as_precise_as_fp32(N, C, H, K, data):
     err, ec = rel_err(got, ref), rel_err(chain, ref)
     print("%s %s: rel err %.2e, fp32 chain %.2e" % ((N, C, K), data, err, ec))
     assert err <= 1.2 * ec
+
+
+def no_less_precise(w, D, E, ks, cs):
+    """Every filter by itself over the channels `cs` (data and error on the GPU): its error against that of a chain of fp32
+    multiply-adds over the blocks.  (Some tens of sums, over which the two vary by a third; where a sum has few blocks that count, the
+    2^-24 of a product that six bf16 products leave out is as much again as the chain's half unit: 2.)"""
+    torch = require_gpu()[0]
+    dG, one = gradient(torch, w, D, E)
+    assert one or D.shape[3] % 4 == 0
+    got = dG[ks][:, cs].cpu().numpy()
+    d, e = D[:, cs].cpu().numpy(), E[:, ks].cpu().numpy()
+    ref = direct.conv2d_bwd_filter(d, e, pad=1)
+    Wt, V = (x.astype(np.float32) for x in (wg.wgrad_error_transform(e), wg.wgrad_data_transform(d)))
+    M = np.zeros((4, 4, len(ks), len(cs)), dtype=np.float32)
+    for b in range(Wt.shape[3]):
+        M += Wt[..., b][:, :, :, None] * V[..., b][:, :, None, :]
+    chain = wg.wgrad_inverse_transform(M)
+    for i, k in enumerate(ks):
+        err, ec = rel_err(got[i], ref[i]), rel_err(chain[i], ref[i])
+        assert err <= 2.0 * ec, "filter %d: %.2e, fp32 chain %.2e" % (k, err, ec)
+
+
+# two steps per row of blocks; rows of any width in one kernel (W % 4 = 1, 2, 3); shares of more than 2048 blocks
+APART = [(8, 40, 30, 32, 130), (3, 300, 20, 32, 70), (220, 40, 13, 13, 70), (220, 40, 13, 14, 70), (220, 40, 13, 15, 70),
+         (30, 256, 94, 96, 250)]
+
+
+@pytest.mark.parametrize("shape,bits", [(s, b) for s in APART for b in ([0, 12, 16, 20, 24, 36, 60] if s[0] != 30 else [16, 36])])
+@pytest.mark.parametrize("which", ["data", "error"])
+@pytest.mark.parametrize("kind", ["dark half", "zeros", "dark rows"])
+def test_filter_gradient_far_apart(shape, bits, which, kind):
+    """Rows whose magnitudes change from step to step, and others that see the small blocks alone.  dark half: every second step
+    2^-bits; zeros: a first image 2^bits above the rest, then every second step zero; dark rows: blocks by the row of the image."""
+    torch, w = require_gpu()
+    N, C, H, W, K = shape
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(sum(shape))
+    D, E = (torch.randn((N, x, H, W), generator=gen, device="cuda") for x in (C, K))
+    X, Z = (D, E) if which == "data" else (E, D)                 # X has the magnitudes, every other row of Z sees the small ones alone
+    half, rows = W // 2, torch.arange(H, device="cuda") // 2 % 3 == 1
+    if kind == "dark half":
+        X[..., half:] *= 2.0 ** -bits
+        Z[:, ::2, :, :half + 2] = 0
+    elif kind == "zeros":
+        X[0] *= 2.0 ** bits
+        X[1:, ..., :half] = 0
+        Z[0, ::2] = 0
+        Z[1:, ::2, :, :half + 2] = 0
+    else:
+        X[:, :, rows] *= 2.0 ** -bits
+        X[:, :, ~rows] *= (torch.arange(X.shape[1], device="cuda") % 4 != 3)[None, :, None, None]
+        Z[:, ::2] *= rows[None, None, :, None]
+    ks, cs = [0, 1, 8, K // 2, K - 2], [0, 1, 3, 4, 7, C // 2, C - 1]
+    no_less_precise(w, D, E, ks, cs)
