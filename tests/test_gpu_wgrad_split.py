@@ -193,3 +193,24 @@ def test_filter_gradient_far_apart(shape, bits, which, kind):
         Z[:, ::2] *= rows[None, None, :, None]
     ks, cs = [0, 1, 8, K // 2, K - 2], [0, 1, 3, 4, 7, C // 2, C - 1]
     no_less_precise(w, D, E, ks, cs)
+
+
+@pytest.mark.parametrize("N,C,H,W,K", [(1, 16, 4096, 4096, 16), (2, 256, 1280, 1280, 16), (1, 40, 2500, 2502, 24), (1, 24, 2501, 2503, 40),
+                                       (1, 20, 2502, 2501, 70)])
+def test_images_of_gigabytes(N, C, H, W, K):
+    """Images whose 64 planes, or that by themselves, are more than a share's buffer reaches."""
+    torch, w = require_gpu()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(N + C + H + W + K)
+    D, E = (inside(torch, torch.randn((N, x, H, W), generator=gen, device="cuda")) for x in (C, K))
+    dG, one = gradient(torch, w, D, E)
+    assert one or W % 4 == 0
+    ks, cs = [0, K // 2, K - 1], [0, C // 2, C - 1]
+    e = E[:, ks].double().transpose(0, 1).reshape(len(ks), -1)
+    ref = torch.zeros((len(ks), len(cs), 3, 3), dtype=torch.float64)
+    for j, c in enumerate(cs):
+        d = torch.nn.functional.pad(D[:, c].double(), (1, 1, 1, 1))
+        for u in range(3):
+            for v in range(3):
+                ref[:, j, u, v] = (e @ d[:, u:u + H, v:v + W].reshape(-1)).cpu()
+    check_close(dG[ks][:, cs].cpu().numpy(), ref.numpy(), 2e-6, "%s" % ((N, C, H, W, K),))

@@ -98,6 +98,13 @@ def test_argument_validation_without_gpu(L):
     assert L.wino_num_tiles(1, 8, 8, 3, 2) == -1
 
 
+@pytest.mark.parametrize("shape,most", [((1, 16, 4096, 4096, 16), 48 << 20), ((2, 256, 1280, 1280, 256), 256 << 20), ((2, 64, 2600, 2600, 64), 160 << 20)])
+def test_filter_gradient_of_images_of_gigabytes_is_one_kernel(shape, most):
+    """Partial products alone, no transformed tensors (some 30 GB)."""
+    import paper_1509_09308_amd as w
+    assert 0 < w.lib().wino_bwd_filter_workspace_bytes(*shape) < most
+
+
 SHAPES = [(1, 56, 56, 1, 2), (8, 28, 28, 1, 2), (8, 28, 28, 1, 4), (1, 224, 224, 1, 4), (2, 112, 112, 1, 4),
           (3, 14, 14, 1, 4), (3, 14, 14, 1, 2), (2, 7, 9, 1, 4), (2, 7, 9, 0, 2), (1, 5, 5, 0, 4), (64, 14, 14, 1, 4),
           (2, 56, 56, 1, 6), (3, 14, 14, 1, 6), (1, 9, 20, 0, 6)]
