@@ -43,8 +43,8 @@ PEAK = {"hbm_GBs": 8000.0, "mfma_f32_TFs": 2500.0 / 3, "mfma_f16_TFs": 2500.0}
 # `bench.py --probe` (summaries under profiles/); keyed by (workload, kernel).  None until measured.
 MEASURED_TRAFFIC = {
     # profiles/cases_counters.md
-    ("vgg16_3x3_conv_stack_N64_f32", "fused_split_kernel<4, false, float, float, 2>"): 714.0e6,     # 9 launches (algorithmic 544.5 MB)
-    ("vgg16_3x3_conv_stack_N64_f32", "fused_split_kernel<2, false, float, float, 2>"): 150.3e6,     # 3 launches (algorithmic 68.2 MB)
+    ("vgg16_3x3_conv_stack_N64_f32", "fused_split_kernel<4, false, float, float, 2>"): 712.8e6,     # 9 launches (algorithmic 544.5 MB)
+    ("vgg16_3x3_conv_stack_N64_f32", "fused_split_kernel<2, false, float, float, 2>"): 150.6e6,     # 3 launches (algorithmic 68.2 MB)
     ("vgg16_3x3_conv_stack_N32_f16", "fused_split_kernel<4, false, __half, float, 1>"): 289.8e6,
     ("vgg16_3x3_conv_stack_N32_f16", "gemm_f16_kernel<128, 128>"): 104.0e6,
 }

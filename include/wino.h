@@ -21,9 +21,13 @@
  *   - Return value: a wino_status_t.  No exceptions, no abort.  Arguments are checked before
  *     any GPU call, so bad arguments are reported even on a machine with no GPU.
  *   - Storage type `dt` is that of D, G, U and V; products are accumulated in fp32 (small fp32 layers: in
- *     64 bits, see wino_small_layer) and M is always fp32.  fp32 products run on the bf16 matrix units where those are faster, every value in
- *     three exact parts: sums are as precise as chains of fp32 multiply-adds, over the whole range of fp32,
- *     and what is infinite or NaN is so where the fp32 operations make it so.
+ *     64 bits, see wino_small_layer) and M is always fp32.  fp32 products run on the 16-bit matrix units where those are faster, every
+ *     value in three exact bf16 parts or, in layers and input gradients in one kernel, of 64 channels and more, in two fp16 parts, rounded
+ *     to 2^-23 of itself or of the largest of its channel's 3x3 filter (of its channel in the tile).  Sums are as precise as chains of fp32
+ *     multiply-adds over the whole range of fp32 and whatever the magnitudes of filters and channels: where they are too far apart for two
+ *     parts three are taken, or fp32 instructions.  (With two parts, sums in which only a few channels count, or all products are rounded the same way,
+ *     may be off by two to three times what such a chain is, 2^-21 of the sum of magnitudes at most beside the rounding of the sums.)
+ *     What is infinite or NaN is so where the fp32 operations make it so.
  *
  * Transform-domain layouts (alpha = m + 2; component index e = xi*alpha + nu; all row-major):
  *     fp32:  U[e][c][k]          extents [alpha^2][Cp][Kp]

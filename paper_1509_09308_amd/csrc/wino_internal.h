@@ -53,7 +53,7 @@ hipError_t launch_fused_wide(const Geo &g, const float *D, const float *U, float
 bool fused_wide_shares(const Geo &g, const void *part, size_t part_bytes);
 int fused_wide_plan(const Geo &g, int out[32]);      // per XCD: items, in full rounds, in the last round, shares; returns the grid
 size_t fused_wide_part_bytes(const Geo &g);
-// fused_split.hip: the same on the bf16 matrix units; transforms or splits the filters itself (G or U given).
+// fused_split.hip: the same on the 16-bit matrix units; transforms or splits the filters itself (G or U given).
 bool fused_split_eligible(const Geo &g);
 long long fused_split_items(const Geo &g);
 double fused_split_us(const Geo &g, bool two_parts);
